@@ -10,7 +10,8 @@ alpha and 1500 beta strings of weight 5 (2.25M determinants), in FP64.
 
 Output: one JSON line.  ``value`` = stored matrix elements (structural nonzeros of H_S)
 processed per second of SpMV.  ``roofline`` prices the SpMV kernel's algorithmic bytes
-against the 8 TB/s HBM peak.  ``cpu_baseline`` times the CPU oracle (term-by-term, binary
+against the 8 TB/s HBM peak, or, for an operator that factors over a product subspace, its
+operands against the LDS rate.  ``cpu_baseline`` times the CPU oracle (term-by-term, binary
 search) on the host cores on a row sample of the same input, lowest of 5 runs at all host
 threads and at one thread.  Extra keys report the ground-state solve time (GPU Lanczos, FP64),
 the work counters, and the same SpMV measurement on the 6x6 XXZ workload (one vector) and the
@@ -28,16 +29,20 @@ sys.path.insert(0, ROOT)
 METRIC = "matrix elements/s in matrix-free SpMV; ground-state solve s; serve p50/p99 ms"
 HBM_PEAK_GBS = 8000.0
 # the SpMV kernel, the row engine it runs and its launch
-KERNEL_SOURCES = ["paper_2603_18731_amd/csrc/engine.h", "paper_2603_18731_amd/csrc/matvec.h",
-                  "paper_2603_18731_amd/csrc/device.h", "paper_2603_18731_amd/csrc/spmv_impl.h"]
+KERNEL_SOURCES = {
+    "k_matvec": ["paper_2603_18731_amd/csrc/engine.h", "paper_2603_18731_amd/csrc/matvec.h",
+                 "paper_2603_18731_amd/csrc/device.h", "paper_2603_18731_amd/csrc/spmv_impl.h"],
+    "k_prod_matvec": ["paper_2603_18731_amd/csrc/product.h", "paper_2603_18731_amd/csrc/product.hip"],
+}
+LDS_PEAK_GBS = 256 * 128 * 2.4  # 256 CUs x 128 bytes per clock at 2.4 GHz
 
 
-def kernel_digest():
+def kernel_digest(kernel="k_matvec"):
     """Digest of the SpMV kernel's sources (ties a stored counter profile to the code)."""
     import hashlib
 
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES:
+    for f in KERNEL_SOURCES[kernel]:
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -46,13 +51,13 @@ def kernel_digest():
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4  # wave64 VALU instructions/s: 256 CUs x 4 SIMDs, 4 cycles each
 
 
-def stored_traffic(workload, dtype, nvec, capacity, key="hbm_bytes_per_launch"):
+def stored_traffic(workload, dtype, nvec, capacity, key="hbm_bytes_per_launch", kernel="k_matvec"):
     """HBM bytes per SpMV launch (or, with key="valu_insts_per_launch", VALU wave instructions)
     from the committed counter profile of this workload, or None when there is none, it was
     taken on other kernel sources or with another hash-table size.  The profile records
     FETCH_SIZE and WRITE_SIZE per dispatch (KiB) and the factors that scale them to the bytes a
     plain copy of known size moves."""
-    path = os.path.join(ROOT, "profiles", "k_matvec_%s_%s_nvec%d.md" % (workload, dtype, nvec))
+    path = os.path.join(ROOT, "profiles", "%s_%s_%s_nvec%d.md" % (kernel, workload, dtype, nvec))
     if not os.path.exists(path):
         return None
     vals = {}
@@ -62,7 +67,7 @@ def stored_traffic(workload, dtype, nvec, capacity, key="hbm_bytes_per_launch"):
                 for kv in line.split()[1:]:
                     k, v = kv.split("=")
                     vals[k] = v
-    if vals.get("source_digest") != kernel_digest() or int(vals.get("capacity", -1)) != capacity:
+    if vals.get("source_digest") != kernel_digest(kernel) or int(vals.get("capacity", -1)) != capacity:
         return None
     return float(vals[key]) if key in vals else None
 
@@ -693,7 +698,15 @@ def measure_spmv(w, nvec, dtype_name, steps, warmup, max_load, schedule, split=0
     kms = [e0.elapsed_time(e1) for e0, e1 in evs]
     k_avg = float(np.mean(kms))
     ms_per_step = wall * 1e3 / steps
-    balg = algorithmic_bytes(N, W, probes, hits, nvec, esz)
+    # an operator that factors over an alpha x beta product runs from per-part lists: no table and
+    # no row keys are read, and its bound is the LDS, with at least one value of x and one
+    # coefficient read per stored element
+    kernel = "k_prod_matvec" if product and group_order == "parts" and not sched & qsd.SCHED_HASH_LOOKUP and \
+        not H.is_complex else "k_matvec"
+    if kernel == "k_matvec":
+        bound, peak, balg = "hbm", HBM_PEAK_GBS, algorithmic_bytes(N, W, probes, hits, nvec, esz)
+    else:
+        bound, peak, balg = "lds", LDS_PEAK_GBS, hits * (nvec + 1) * esz
     achieved = balg / (k_avg / 1e3) / 1e9
     print("# SpMV: %.4f ms/step wall, kernel avg %.4f ms (min %.4f), %.1f GB/s algorithmic" %
           (ms_per_step, k_avg, min(kms), achieved), file=sys.stderr, flush=True)
@@ -701,21 +714,21 @@ def measure_spmv(w, nvec, dtype_name, steps, warmup, max_load, schedule, split=0
         "value": nnz * nvec / (ms_per_step / 1e3),
         "ms_per_step": ms_per_step,
         "config": {"workload": w.name, "n_qubits": w.ops.n_qubits, "subspace_dim": N, "nnz": nnz,
-                   "groups": op.n_groups, "terms": op.n_terms, "nvec": nvec, "kernel": "k_matvec",
+                   "groups": op.n_groups, "terms": op.n_terms, "nvec": nvec, "kernel": kernel,
                    "schedule": sched, "hash_capacity": sub.capacity, "part_filter_split": hsplit,
                    "exact_slots": exact, "product_map": product, "group_order": group_order,
                    "autotune": tune},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": stored_traffic(w.name, dtype_name, nvec, sub.capacity),
+        "roofline": {"bound": bound, "achieved": achieved, "peak": peak, "unit": "GB/s",
+                     "frac": achieved / peak,
+                     "traffic": stored_traffic(w.name, dtype_name, nvec, sub.capacity, kernel=kernel),
                      "bytes_per_launch": balg, "kernel_ms": k_avg, "kernel_ms_min": min(kms),
-                     "kernel_source_digest": kernel_digest()},
+                     "kernel_source_digest": kernel_digest(kernel)},
         "roofline_issue": None,
         "work": {"probes": probes, "hits": hits, "evaluations": N * op.n_groups,
                  "probes_per_s": probes / (k_avg / 1e3), "evaluations_per_s": N * op.n_groups / (k_avg / 1e3)},
     }
     # the instruction-issue roofline, from the profiled VALU instruction count of this kernel
-    valu = stored_traffic(w.name, dtype_name, nvec, sub.capacity, key="valu_insts_per_launch")
+    valu = stored_traffic(w.name, dtype_name, nvec, sub.capacity, key="valu_insts_per_launch", kernel=kernel)
     if valu is not None:
         res["roofline_issue"] = {"bound": "valu_issue", "achieved": valu / (k_avg / 1e3), "peak": VALU_ISSUE_PEAK,
                                  "unit": "wave instructions/s", "frac": valu / (k_avg / 1e3) / VALU_ISSUE_PEAK,

@@ -205,6 +205,8 @@ constexpr uint32_t kInfoKMask = 7u;
 constexpr uint32_t kInfoLadder = 1u << 3;
 constexpr uint32_t kInfoCare = 1u << 4;
 
+struct qsd_prod;  // factored form on a product subspace (product.h)
+
 struct qsd_ham {
     qsd_allocator alloc{nullptr, nullptr, nullptr};
     void *stream = nullptr;
@@ -235,6 +237,7 @@ struct qsd_ham {
     float *diag32_im = nullptr;
     // [ceil(N / 64)] bit r = row r has an off-diagonal element; built for the slot-order schedules
     uint64_t *rowbits = nullptr;
+    qsd_prod *prod = nullptr;  // NULL: the operator does not factor, or the subspace is no product
 };
 
 struct qsd_csr {

@@ -8,6 +8,7 @@
 #include "device.h"
 #include "engine.h"
 #include "matvec.h"
+#include "product.h"
 #include "rowsort.h"
 #include "spmv.h"
 
@@ -177,6 +178,7 @@ void free_ham(qsd_ham *h) {
     dev_free(h->diag32);
     dev_free(h->diag32_im);
     dev_free(h->rowbits);
+    prod_free(h->prod);
     delete h;
 }
 
@@ -239,7 +241,8 @@ int create_impl(qsd_ham *h, hipStream_t st) {
         }
         k_to_f32<<<1024, kBlock, 0, st>>>(h->diag, h->diag32, h->N);
         if (h->is_complex) k_to_f32<<<1024, kBlock, 0, st>>>(h->diag_im, h->diag32_im, h->N);
-        if (hipStreamSynchronize(st) != hipSuccess)
+        rc = prod_build(h, st);
+        if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
             rc = fail(QSD_ERR_HIP, "diagonal kernel failed: %s", hipGetErrorString(hipGetLastError()));
     }
     dev_free(dcws);
@@ -359,6 +362,14 @@ extern "C" int qsd_matvec(const qsd_ham *h, int32_t nvec, const void *d_x, int64
     if (ldx > INT32_MAX || ldy > INT32_MAX) return fail(QSD_ERR_INVALID_ARG, "leading dimension of 2^31 or more");
     QSD_TRY(check_dtype(h, dtype));
     hipStream_t st = (hipStream_t)stream;
+    if (prod_usable(h)) {  // real operators only
+        if (dtype == QSD_F64)
+            prod_matvec<double>(h, d_x, ldx, d_y, ldy, nvec, st);
+        else
+            prod_matvec<float>(h, d_x, ldx, d_y, ldy, nvec, st);
+        QSD_CHECK_HIP(hipGetLastError());
+        return QSD_OK;
+    }
     const int chunk = (dtype == QSD_C128 || dtype == QSD_C64) ? 4 : 16;
     const size_t esz = dtype == QSD_F64 ? 8 : dtype == QSD_F32 ? 4 : dtype == QSD_C128 ? 16 : 8;
     for (int v0 = 0; v0 < nvec; v0 += chunk) {

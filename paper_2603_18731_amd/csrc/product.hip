@@ -1,0 +1,782 @@
+// Factored SpMV on alpha x beta product subspaces: the plan (host classification of the groups,
+// lists built on the device) and the kernel.  See product.h for the form.
+#include "product.h"
+
+#include <algorithm>
+#include <cstring>
+#include <type_traits>
+#include <unordered_map>
+#include <unordered_set>
+
+#include "device.h"
+#include "matvec.h"
+
+namespace qsd {
+namespace {
+
+constexpr uint32_t kLdsBytes = 64u * 1024u;  // a workgroup's x row and tables (two or more workgroups per CU)
+constexpr uint32_t kMaxKeys = 16384;         // term keys of one part: 2 key + sign fits 15 bits
+constexpr uint32_t kMaxTail = 200;           // terms after the table, counted in 8 bits
+constexpr uint64_t kMaxTable = 1ull << 23;   // entries of a two-sided table
+
+// What the list kernels read of the operator.
+struct GroupList {
+    const uint32_t *flip;  // [n] the part's flip mask
+    const uint32_t *t0;    // [n] first term
+    const uint32_t *nt;    // [n] terms
+    uint32_t n, n1;                     // groups, and those of segment 1
+};
+struct FlipList {
+    const uint32_t *flip;  // [n]
+    const uint32_t *care;  // [n] bits that select the flip's key
+    const uint32_t *key0;  // [n + 1] keys of the flip
+    const uint32_t *want;  // [keys]
+    const uint32_t *sign;  // [keys]
+    uint32_t n;
+};
+struct BuildView {
+    const uint64_t *keys;    // [N] rows
+    const uint32_t *pfilt;
+    const uint16_t *prank;
+    const uint4 *cw;         // [T] care, want, sign
+    const double2 *coef;     // [T]
+    const float2 *coef32;    // [T]
+    const uint32_t *tinfo;   // [T] kind | key << 8
+    uint32_t na, nb;
+    int split;
+};
+
+// Term kinds within a group's part-only segment.
+constexpr uint32_t kOwn = 0;    // depends on the group's own part alone
+constexpr uint32_t kOther = 1;  // wants one qubit of the other part (class A: its key's table row)
+constexpr uint32_t kFirst = 2;  // class B: the own term that heads its key's table row
+
+__device__ __forceinline__ uint32_t below(uint64_t m, int lane) {
+    return (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+}
+
+// Position of a lane's flip in its part's list of keys: the flip's key that matches the part
+// (at most one does), or -1.
+__device__ __forceinline__ int flip_key(const FlipList &f, uint32_t i, uint32_t part, uint32_t &sgn) {
+    const uint32_t c = part & f.care[i];
+    for (uint32_t k = f.key0[i]; k < f.key0[i + 1]; ++k)
+        if (c == f.want[k]) {
+            sgn = (uint32_t)__popc(part & f.sign[k]) & 1u;
+            return (int)k;
+        }
+    return -1;
+}
+
+// The lists of one part, one wave per part: 64 groups (flips) at a time, the entries that exist
+// keep their order through a ballot.  WRITE = false only counts (lengths and their maxima).
+// (One pass over some thousand groups per part, once per operator: latency-bound.)
+template <bool HIGH, bool WRITE>
+__global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, FlipList f, qsd_prod p,
+                                                    uint32_t *__restrict__ mx) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t i = blockIdx.x * 4u + (threadIdx.x >> 6), n = HIGH ? v.nb : v.na;
+    if (i >= n) return;  // whole waves
+    const uint32_t lowmask = (1u << v.split) - 1u;
+    const uint32_t part = HIGH ? (uint32_t)(v.keys[(int64_t)i * v.na] >> v.split) : (uint32_t)v.keys[i] & lowmask;
+    const uint32_t *filt = v.pfilt + (HIGH ? kPartWords / 2 : 0);
+    uint32_t n1 = 0, n2 = 0, n3 = 0;
+    for (uint32_t g0 = 0; g0 < g.n; g0 += 64u) {
+        const uint32_t q = g0 + (uint32_t)lane;
+        bool on = false;
+        uint32_t col = 0, key = 0, sgn = 0, nt = 0;
+        double val = 0.0;
+        float val32 = 0.0f;
+        // segment 1's slot in the lists is known only after the ballot: its tail terms are
+        // written in a second walk below
+        if (q < g.n) {
+            const uint32_t to = part ^ g.flip[q];
+            if ((filt[to >> 5] >> (to & 31u)) & 1u) {
+                col = part_rank(v.pfilt, v.prank, HIGH ? 1 : 0, to);
+                key = HIGH ? 2u * (p.nWb - 1u) : 2u * (p.nUa - 1u);  // the table row of zeros
+                for (uint32_t t = g.t0[q]; t < g.t0[q] + g.nt[q]; ++t) {
+                    const uint4 m = v.cw[t];
+                    const uint32_t care = HIGH ? m.x >> v.split : m.x & lowmask;
+                    const uint32_t want = HIGH ? m.y >> v.split : m.y & lowmask;
+                    if ((part & care) != want) continue;
+                    const uint32_t s = (uint32_t)__popc(part & (HIGH ? m.z >> v.split : m.z & lowmask)) & 1u;
+                    const uint32_t info = v.tinfo[t];
+                    if ((info & 255u) == kOwn) {
+                        on = true;
+                        ++nt;
+                        val += s ? -v.coef[t].x : v.coef[t].x;
+                        val32 += s ? -v.coef32[t].x : v.coef32[t].x;
+                    } else {
+                        if ((info & 255u) == kFirst) on = true;
+                        key = 2u * (info >> 8) + s;
+                    }
+                }
+            }
+        }
+        const uint64_t b1 = __ballot(on && q < g.n1), b2 = __ballot(on && q >= g.n1);
+        if (WRITE && on) {
+            if (q < g.n1) {
+                const uint32_t k = n1 + below(b1, lane);
+                if (HIGH) {
+                    uint32_t *e = p.b1_ent + 2 * ((int64_t)i * p.nB1 + k);
+                    e[0] = col;
+                    e[1] = key | nt << 24;
+                    const int64_t o = ((int64_t)i * p.nB1 + k) * p.tail_len;
+                    uint32_t at = 0;
+                    for (uint32_t t = g.t0[q]; t < g.t0[q] + g.nt[q]; ++t) {
+                        const uint4 m = v.cw[t];
+                        if ((part & (m.x >> v.split)) != (m.y >> v.split) || (v.tinfo[t] & 255u) != kOwn) continue;
+                        const bool s = (__popc(part & (m.z >> v.split)) & 1) != 0;
+                        p.d.tail[o + at] = s ? -v.coef[t].x : v.coef[t].x;
+                        p.f.tail[o + at] = s ? -v.coef32[t].x : v.coef32[t].x;
+                        ++at;
+                    }
+                } else {
+                    const int64_t o = (int64_t)k * v.na + i;
+                    p.a1_ent[o] = col | key << 16;
+                    p.d.a1[o] = val;
+                    p.f.a1[o] = val32;
+                }
+            } else {
+                const uint32_t k = n2 + below(b2, lane);
+                const int64_t o = HIGH ? (int64_t)i * p.nB2 + k : (int64_t)k * v.na + i;
+                (HIGH ? p.b2_col : p.a2_col)[o] = col;
+                (HIGH ? p.d.b2 : p.d.a2)[o] = val;
+                (HIGH ? p.f.b2 : p.f.a2)[o] = val32;
+            }
+        }
+        n1 += (uint32_t)__popcll(b1);
+        n2 += (uint32_t)__popcll(b2);
+    }
+    for (uint32_t f0 = 0; f0 < f.n; f0 += 64u) {
+        const uint32_t q = f0 + (uint32_t)lane;
+        uint32_t col = 0, sgn = 0;
+        int key = -1;
+        if (q < f.n) {
+            const uint32_t to = part ^ f.flip[q];
+            if ((filt[to >> 5] >> (to & 31u)) & 1u) {
+                col = part_rank(v.pfilt, v.prank, HIGH ? 1 : 0, to);
+                key = flip_key(f, q, part, sgn);
+            }
+        }
+        const uint64_t b3 = __ballot(key >= 0);
+        if (WRITE && key >= 0) {
+            const uint32_t k = n3 + below(b3, lane);
+            if (HIGH) {
+                uint32_t *e = p.bab_ent + 2 * ((int64_t)i * p.nBAB + k);
+                e[0] = col;
+                e[1] = 2u * (uint32_t)key + sgn;
+            } else {
+                p.ab_ent[(int64_t)k * v.na + i] = col | (2u * (uint32_t)key + sgn) << 16;
+            }
+        }
+        n3 += (uint32_t)__popcll(b3);
+    }
+    if (!WRITE && lane == 0) {
+        uint32_t *len = HIGH ? p.blen : p.alen;
+        len[i] = n1;
+        len[n + i] = n2;
+        len[2 * (int64_t)n + i] = n3;
+        if (HIGH) len[3 * (int64_t)n + i] = part;
+        atomicMax(&mx[0], n1);
+        atomicMax(&mx[1], n2);
+        atomicMax(&mx[2], n3);
+        if (HIGH) atomicMax(&mx[3], (uint32_t)__popc(part & p.rmask));
+    }
+}
+
+// wtab[w][a] = the key's first term plus its terms that want a low qubit the part has set, in
+// increasing qubit order (dep[w][q], 0 where there is none).
+template <class ET>
+__global__ __launch_bounds__(256) void k_prod_wtab(const uint64_t *__restrict__ keys, uint32_t na, int split,
+                                                   const ET *__restrict__ head, const ET *__restrict__ dep,
+                                                   ET *__restrict__ wtab) {
+    const uint32_t a = blockIdx.x * 256u + threadIdx.x, w = blockIdx.y;
+    if (a >= na) return;
+    const uint32_t part = (uint32_t)keys[a] & ((1u << split) - 1u);
+    ET s = 0;
+    s += head[w];
+    for (int q = 0; q < split; ++q)
+        if ((part >> q) & 1u) s += dep[(int64_t)w * split + q];
+    wtab[(int64_t)w * na + a] = s;
+}
+
+// ------------------------------------------------------------------------------- SpMV
+
+// What the SpMV kernel reads, by value.
+template <class ET>
+struct ProdView {
+    uint32_t na, nb, nB1, nB2, nBAB, nUa, nU, tail_len, rmask;
+    const uint32_t *__restrict__ a1_ent, *__restrict__ a2_col, *__restrict__ ab_ent;
+    const uint32_t *__restrict__ b1_ent, *__restrict__ b2_col, *__restrict__ bab_ent;
+    const uint32_t *__restrict__ alen, *__restrict__ blen;
+    const ET *__restrict__ a1, *__restrict__ a2, *__restrict__ dep, *__restrict__ ctab, *__restrict__ wtab,
+        *__restrict__ tail, *__restrict__ b2;
+};
+
+// One workgroup: 256 low parts of one high part b, V of the interleaved vectors.  Class A and AB
+// columns lie in whole rows x[b'][:], which are staged in LDS (12 KB for 1500 strings in FP64), so
+// the random gathers run at the LDS rate and not at the 0.36 lanes per clock and CU that the texture
+// path gives gathers from L2; b's own list is uniform over the workgroup (scalar loads), and class
+// B reads x[b'][a] coalesced.  Bound by the LDS gathers (one for x, one for the coefficient of an
+// AB element).
+template <class ET, int V, bool FULL>
+__global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ diag,
+                                                     const ET *__restrict__ x, int64_t ldx, ET *__restrict__ y,
+                                                     int64_t ldy, int nvec) {
+    extern __shared__ __align__(16) char smem[];
+    ET *xs = (ET *)smem;            // [na][V]
+    ET *aux = xs + (size_t)p.na * V;  // class A table rows, then the AB coefficients of one high key
+    // workgroups of one XCD take consecutive high parts of one tile of low parts: they share the
+    // tile's lists in that XCD's L2
+    const uint32_t id = (uint32_t)tile_index(blockIdx.x, gridDim.x, true);
+    const uint32_t tile = id / p.nb, b = id - tile * p.nb;
+    const uint32_t al = tile * 256u + threadIdx.x;
+    const bool valid = al < p.na;
+    const uint32_t a = valid ? al : p.na - 1u;
+    const int v0 = blockIdx.y * V, nv = min(V, nvec - v0);
+    x += v0;
+    y += v0;
+    const int64_t row = (int64_t)b * p.na + a;
+
+    auto stage = [&](uint32_t bc) {
+        const ET *xr = x + (int64_t)bc * p.na * ldx;
+        for (uint32_t j = threadIdx.x; j < p.na; j += 256u)
+#pragma unroll
+            for (int v = 0; v < V; ++v) xs[j * V + v] = (V == 1 || v < nv) ? xr[(int64_t)j * ldx + v] : (ET)0;
+    };
+    double acc[V];
+    {
+        const double dr = (double)diag[row];
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] = (V == 1 || v < nv) ? dr * (double)x[row * ldx + v] : 0.0;
+    }
+    // class A: columns of the row's own block
+    const uint32_t nocc = (uint32_t)__popc(p.blen[3 * (int64_t)p.nb + b] & p.rmask);
+    {
+        stage(b);
+        uint32_t m = p.blen[3 * (int64_t)p.nb + b] & p.rmask;
+        for (uint32_t q = 0; m; ++q, m &= m - 1u) {
+            const ET *d = p.dep + (int64_t)__builtin_ctz(m) * p.nUa;
+            for (uint32_t u = threadIdx.x; u < p.nUa; u += 256u) aux[q * p.nUa + u] = d[u];
+        }
+    }
+    __syncthreads();
+    const uint32_t n1 = valid ? p.alen[a] : 0u, n2 = valid ? p.alen[p.na + a] : 0u;
+    const uint32_t n3 = valid ? p.alen[2 * (int64_t)p.na + a] : 0u;
+    for (uint32_t k = 0; k < n1; ++k) {
+        const uint32_t e = p.a1_ent[(int64_t)k * p.na + a];
+        ET val = p.a1[(int64_t)k * p.na + a];
+        const uint32_t u = e >> 17, col = e & 0xFFFFu;
+        const bool neg = (e >> 16) & 1u;
+        for (uint32_t q = 0; q < nocc; ++q) {
+            const ET c = aux[q * p.nUa + u];
+            val += neg ? -c : c;
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] += (double)val * (double)xs[col * V + v];
+    }
+#pragma unroll 4
+    for (uint32_t k = 0; k < n2; ++k) {
+        const uint32_t col = p.a2_col[(int64_t)k * p.na + a];
+        const ET val = p.a2[(int64_t)k * p.na + a];
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] += (double)val * (double)xs[col * V + v];
+    }
+    // class AB: for each of b's flips, its row of x and its key's coefficients (both signs: entry
+    // 2 u + s is the coefficient with the low part's sign s applied)
+    const uint32_t nab = p.blen[2 * (int64_t)p.nb + b];
+    for (uint32_t e = 0; e < nab; ++e) {
+        const uint32_t bc = p.bab_ent[2 * ((int64_t)b * p.nBAB + e)];
+        const uint32_t w = p.bab_ent[2 * ((int64_t)b * p.nBAB + e) + 1];
+        const ET *ct = p.ctab + (int64_t)(w >> 1) * p.nU;
+        __syncthreads();  // the previous row and table are no longer read
+        stage(bc);
+        for (uint32_t u = threadIdx.x; u < p.nU; u += 256u) {
+            const ET c = (w & 1u) ? -ct[u] : ct[u];
+            aux[2 * u] = c;
+            aux[2 * u + 1] = -c;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t k = 0; k < n3; ++k) {
+            const uint32_t f = p.ab_ent[(int64_t)k * p.na + a];
+            const ET c = aux[f >> 16];
+            const uint32_t col = f & 0xFFFFu;
+            if (FULL || c != (ET)0) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[v] += (double)c * (double)xs[col * V + v];
+            }
+        }
+    }
+    // class B: the same low part in other blocks
+    const ET *xa = x + (int64_t)a * ldx;
+    const int64_t bstride = (int64_t)p.na * ldx;
+    const uint32_t m1 = p.blen[b], m2 = p.blen[p.nb + b];
+    for (uint32_t i = 0; i < m1; ++i) {
+        const int64_t at = (int64_t)b * p.nB1 + i;
+        const uint32_t bc = p.b1_ent[2 * at], e = p.b1_ent[2 * at + 1];
+        const uint32_t w = (e & 0xFFFFFFu) >> 1, nt = e >> 24;
+        const ET wv = p.wtab[(int64_t)w * p.na + a];
+        ET val = (e & 1u) ? -wv : wv;
+        for (uint32_t t = 0; t < nt; ++t) val += p.tail[at * p.tail_len + t];
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (V == 1 || v < nv) acc[v] += (double)val * (double)xa[bc * bstride + v];
+    }
+#pragma unroll 8
+    for (uint32_t i = 0; i < m2; ++i) {
+        const int64_t at = (int64_t)b * p.nB2 + i;
+        const double val = (double)p.b2[at];
+        const int64_t o = p.b2_col[at] * bstride;
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (V == 1 || v < nv) acc[v] += val * (double)xa[o + v];
+    }
+    if (valid) {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (V == 1 || v < nv) y[row * ldy + v] = (ET)acc[v];
+    }
+}
+
+uint32_t aux_entries(const qsd_prod *p) { return std::max(p->max_occ * p->nUa, 2u * p->nU); }
+
+template <class ET>
+uint32_t lds_bytes(const qsd_prod *p, int V) {
+    return (uint32_t)((p->na * V + aux_entries(p)) * sizeof(ET));
+}
+
+template <class ET, int V>
+void launch_prod(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
+    const qsd_prod *p = h->prod;
+    const ProdVals<ET> *pv;
+    const ET *diag;
+    if constexpr (std::is_same<ET, double>::value) {
+        pv = &p->d;
+        diag = h->diag;
+    } else {
+        pv = &p->f;
+        diag = h->diag32;
+    }
+    const ProdView<ET> v{p->na, p->nb, p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask,
+                         p->a1_ent, p->a2_col, p->ab_ent, p->b1_ent, p->b2_col, p->bab_ent, p->alen, p->blen,
+                         pv->a1, pv->a2, pv->dep, pv->ctab, pv->wtab, pv->tail, pv->b2};
+    const dim3 grid((p->na + 255u) / 256u * p->nb, (unsigned)((nvec + V - 1) / V));
+    const uint32_t lds = lds_bytes<ET>(p, V);
+    if (p->full)
+        k_prod_matvec<ET, V, true><<<grid, 256, lds, st>>>(v, diag, (const ET *)x, ldx, (ET *)y, ldy, nvec);
+    else
+        k_prod_matvec<ET, V, false><<<grid, 256, lds, st>>>(v, diag, (const ET *)x, ldx, (ET *)y, ldy, nvec);
+}
+
+// ------------------------------------------------------------------- host classification
+
+struct HostTerm {
+    uint32_t care, want, sign;
+};
+
+// Everything the device lists need of the operator, or `ok` = false.
+struct Classified {
+    bool ok = false;
+    std::vector<uint32_t> tinfo;                    // [T]
+    std::vector<uint32_t> gflip[2], gt0[2], gnt[2]; // part-only groups (A, B)
+    uint32_t n1[2] = {0, 0};
+    std::vector<uint32_t> fflip[2], fcare[2], fkey0[2], fwant[2], fsign[2];
+    std::vector<double> ctab, dep, whead, wdep;     // dep [high][nUa], wdep [nWb][low]
+    uint32_t nUa = 0, nWb = 0, tail_len = 0, rmask = 0;
+    bool full = true;
+};
+
+Classified classify(const qsd_op *op, int split) {
+    Classified c;
+    const int nhi = op->n_qubits - split;
+    if (op->Wp != 1 || op->is_complex || split < 1 || split > 16 || nhi < 1 || nhi > 16) return c;
+    const uint32_t lm = (1u << split) - 1u;
+    const size_t G = op->g_info.size(), T = op->t_coef.size() / 2;
+    c.tinfo.assign(T, 0u);
+    auto term = [&](size_t t) {
+        return HostTerm{(uint32_t)op->t_cws[3 * t], (uint32_t)op->t_cws[3 * t + 1], (uint32_t)op->t_cws[3 * t + 2]};
+    };
+    auto half = [&](uint32_t m, int high) { return high ? m >> split : m & lm; };
+    // the classes in order: low part only, both, high part only
+    int stage = 0;
+    size_t ab0 = G, ab1 = 0;
+    for (size_t g = 0; g < G; ++g) {
+        const uint32_t m = (uint32_t)op->g_mask[g];
+        const int cls = half(m, 0) ? (half(m, 1) ? 1 : 0) : 2;
+        if (cls < stage) return c;
+        stage = cls;
+        if (cls == 1) {
+            ab0 = std::min(ab0, g);
+            ab1 = g + 1;
+        }
+    }
+    if (ab0 == G) ab1 = G;
+    // classes A and B: within the terms that one ladder pattern selects, own terms and terms
+    // that want one qubit of the other part
+    uint32_t seg_tail = 0;
+    std::vector<std::pair<uint64_t, double>> dep;  // (key << 8 | qubit, coefficient)
+    for (size_t g = 0; g < G; ++g) {
+        if (g >= ab0 && g < ab1 && ab0 < G) continue;
+        const uint32_t m = (uint32_t)op->g_mask[g];
+        const int H = half(m, 0) ? 0 : 1;
+        const size_t a = op->g_term0[g], e = a + op->g_nterm[g];
+        bool byflip = true;
+        for (size_t t = a; t < e; ++t) byflip &= (term(t).care & m) == m;
+        bool anydep = false;
+        uint32_t tails = 0;
+        // patterns: at most 2^4 with a ladder group, found in stored order
+        std::vector<uint32_t> pats;
+        for (size_t t = a; t < e; ++t) {
+            const uint32_t p = byflip ? term(t).want & m : 0u;
+            if (std::find(pats.begin(), pats.end(), p) == pats.end()) {
+                pats.push_back(p);
+                if (pats.size() > 16) return c;
+            }
+        }
+        for (const uint32_t p : pats) {
+            uint32_t own_before = 0, own_after = 0, deps = 0, last_q = 0;
+            HostTerm key{};
+            size_t head_t = 0;  // the last own term before the others
+            for (size_t t = a; t < e; ++t) {
+                const HostTerm x = term(t);
+                if (byflip && (x.want & m) != p) continue;
+                const uint32_t oc = half(x.care, !H), ow = half(x.want, !H), os = half(x.sign, !H);
+                const HostTerm k{half(x.care, H), half(x.want, H), half(x.sign, H)};
+                if (!oc && !os) {
+                    if (deps) {
+                        if (H == 0) return c;  // class A: own terms come first
+                        ++own_after;
+                    } else {
+                        ++own_before;
+                        head_t = t;
+                    }
+                    continue;
+                }
+                if (os || oc != ow || (oc & (oc - 1u))) return c;
+                const uint32_t q = (uint32_t)__builtin_ctz(oc);
+                if (deps && q <= last_q) return c;
+                last_q = q;
+                if (!deps) {
+                    // the terms' own part: one key for all of them; an own term with the key's
+                    // projector bits makes the element exist whenever one of them matches (class
+                    // B: that term alone comes before them, with the key's sign mask)
+                    if (!own_before || (H == 1 && own_before != 1)) return c;
+                    bool same = false;
+                    for (size_t u = a; u < t; ++u) {
+                        const HostTerm y = term(u);
+                        if (byflip && (y.want & m) != p) continue;
+                        same |= half(y.care, H) == k.care && half(y.want, H) == k.want &&
+                                (H == 0 || half(y.sign, H) == k.sign);
+                    }
+                    if (!same) return c;
+                    key = k;
+                    const uint32_t id = H == 0 ? c.nUa++ : c.nWb++;
+                    if (id + 1 >= kMaxKeys) return c;
+                    if (H == 1) {
+                        c.tinfo[head_t] = kFirst | id << 8;
+                        c.whead.push_back(op->t_coef[2 * head_t]);
+                    }
+                } else if (key.care != k.care || key.want != k.want || key.sign != k.sign) {
+                    return c;
+                }
+                ++deps;
+                const uint32_t id = (H == 0 ? c.nUa : c.nWb) - 1u;
+                c.tinfo[t] = kOther | id << 8;
+                if (H == 0) {
+                    dep.push_back({(uint64_t)id << 8 | q, op->t_coef[2 * t]});
+                    c.rmask |= 1u << q;
+                } else {
+                    c.wdep.resize((size_t)c.nWb * split, 0.0);
+                    c.wdep[(size_t)id * split + q] = op->t_coef[2 * t];
+                }
+            }
+            anydep |= deps != 0;
+            if (H == 1) tails = std::max(tails, deps ? own_after : own_before);
+        }
+        // (terms that follow the table in segment 1, which ends with the last group that has one)
+        if (H == 1) {
+            seg_tail = std::max(seg_tail, tails);
+            if (anydep) c.tail_len = seg_tail;
+        }
+        c.gflip[H].push_back(half(m, H));
+        c.gt0[H].push_back((uint32_t)a);
+        c.gnt[H].push_back((uint32_t)(e - a));
+        if (anydep) c.n1[H] = (uint32_t)c.gflip[H].size();
+    }
+    // (groups of segment 1 without such terms use a table row of zeros, the last one)
+    ++c.nUa;
+    ++c.nWb;
+    c.whead.push_back(0.0);
+    c.wdep.resize((size_t)c.nWb * split, 0.0);
+    c.dep.assign((size_t)nhi * c.nUa, 0.0);
+    for (auto &d : dep) c.dep[(size_t)(d.first & 255u) * c.nUa + (size_t)(d.first >> 8)] = d.second;
+    if (c.tail_len > kMaxTail) return c;
+    // class AB: per part, the flips and their keys
+    struct Flip {
+        uint32_t care;
+        std::vector<std::pair<uint32_t, uint32_t>> keys;  // want, sign
+    };
+    std::unordered_map<uint32_t, Flip> flips[2];
+    std::vector<uint32_t> order[2];
+    std::unordered_set<uint32_t> runs;
+    uint32_t cur = 0, prev = 0;
+    auto before = [](uint32_t x, uint32_t z) {
+        const int px = __builtin_popcount(x), pz = __builtin_popcount(z);
+        return px != pz ? px < pz : x < z;
+    };
+    for (size_t g = ab0; g < ab1; ++g) {
+        const uint32_t m = (uint32_t)op->g_mask[g], ml = half(m, 0), mh = half(m, 1);
+        if (g == ab0 || mh != cur) {
+            if (!runs.insert(mh).second) return c;  // the groups of one high flip are not together
+            cur = mh;
+            order[1].push_back(mh);
+        } else if (!before(prev, ml)) {
+            return c;
+        }
+        prev = ml;
+        for (size_t t = op->g_term0[g], e = t + op->g_nterm[g]; t < e; ++t) {
+            const HostTerm x = term(t);
+            if (op->t_coef[2 * t] == 0.0 || (float)op->t_coef[2 * t] == 0.0f) return c;  // 0 marks an absent pair
+            for (int H = 0; H < 2; ++H) {
+                auto it = flips[H].find(half(m, H));
+                if (it == flips[H].end()) {
+                    it = flips[H].emplace(half(m, H), Flip{half(x.care, H), {}}).first;
+                    if (H == 0) order[0].push_back(ml);
+                }
+                if (it->second.care != half(x.care, H)) return c;
+                bool have = false;
+                for (auto &k : it->second.keys)
+                    if (k.first == half(x.want, H)) {
+                        if (k.second != half(x.sign, H)) return c;
+                        have = true;
+                    }
+                if (!have) it->second.keys.push_back({half(x.want, H), half(x.sign, H)});
+                if (it->second.keys.size() > 16) return c;
+            }
+        }
+    }
+    std::sort(order[0].begin(), order[0].end(), before);
+    std::unordered_map<uint64_t, uint32_t> id[2];  // flip << 16 | want -> key
+    for (int H = 0; H < 2; ++H) {
+        for (const uint32_t m : order[H]) {
+            c.fflip[H].push_back(m);
+            c.fcare[H].push_back(flips[H][m].care);
+            c.fkey0[H].push_back((uint32_t)c.fwant[H].size());
+            for (auto &k : flips[H][m].keys) {
+                id[H][(uint64_t)m << 16 | k.first] = (uint32_t)c.fwant[H].size();
+                c.fwant[H].push_back(k.first);
+                c.fsign[H].push_back(k.second);
+            }
+        }
+        c.fkey0[H].push_back((uint32_t)c.fwant[H].size());
+        if (c.fwant[H].size() >= kMaxKeys) return c;
+    }
+    const size_t nU = c.fwant[0].size(), nW = c.fwant[1].size();
+    if ((uint64_t)nU * nW > kMaxTable) return c;
+    c.ctab.assign(nU * nW, 0.0);
+    for (size_t g = ab0; g < ab1; ++g) {
+        const uint32_t m = (uint32_t)op->g_mask[g];
+        for (size_t t = op->g_term0[g], e = t + op->g_nterm[g]; t < e; ++t) {
+            const HostTerm x = term(t);
+            const uint32_t u = id[0][(uint64_t)half(m, 0) << 16 | half(x.want, 0)];
+            const uint32_t w = id[1][(uint64_t)half(m, 1) << 16 | half(x.want, 1)];
+            double &v = c.ctab[(size_t)w * nU + u];
+            if (v != 0.0) return c;  // two terms for one pair of keys
+            v = op->t_coef[2 * t];
+        }
+    }
+    for (double v : c.ctab) c.full &= v != 0.0;
+    c.ok = true;
+    return c;
+}
+
+// Arrays laid out in one block of device memory (256-byte aligned), the first `bytes` of which
+// are copied from the host image.
+struct Block {
+    std::vector<uint8_t> image;
+    size_t size = 0;
+    uint8_t *dev = nullptr;
+    template <class T>
+    size_t put(const std::vector<T> &v) {
+        const size_t at = room(v.size() * sizeof(T));
+        image.resize(size);
+        if (!v.empty()) std::memcpy(image.data() + at, v.data(), v.size() * sizeof(T));
+        return at;
+    }
+    size_t room(size_t bytes) {
+        const size_t at = size;
+        size += (bytes + 255) / 256 * 256;
+        return at;
+    }
+    template <class T>
+    T *at(size_t off) const {
+        return (T *)(dev + off);
+    }
+    int upload(hipStream_t st) {
+        QSD_TRY(dev_alloc(&dev, size));
+        if (!image.empty())
+            QSD_CHECK_HIP(hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, st));
+        return QSD_OK;
+    }
+};
+
+std::vector<float> narrowed(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
+
+// The lists: counted, sized by one round trip to the host, then written.  `scratch` and `keep`
+// hold the host images, which the caller keeps until the stream has passed the copies.
+int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, Block &keep, hipStream_t st) {
+    const qsd_subspace *s = h->s;
+    size_t og[2][3], of[2][5];
+    for (int H = 0; H < 2; ++H) {
+        og[H][0] = scratch.put(c.gflip[H]);
+        og[H][1] = scratch.put(c.gt0[H]);
+        og[H][2] = scratch.put(c.gnt[H]);
+        of[H][0] = scratch.put(c.fflip[H]);
+        of[H][1] = scratch.put(c.fcare[H]);
+        of[H][2] = scratch.put(c.fkey0[H]);
+        of[H][3] = scratch.put(c.fwant[H]);
+        of[H][4] = scratch.put(c.fsign[H]);
+    }
+    const size_t oi = scratch.put(c.tinfo), om = scratch.put(std::vector<uint32_t>(8, 0u));
+    const size_t owh = scratch.put(c.whead), owd = scratch.put(c.wdep);
+    const size_t owh32 = scratch.put(narrowed(c.whead)), owd32 = scratch.put(narrowed(c.wdep));
+    const size_t od = keep.put(c.dep), od32 = keep.put(narrowed(c.dep));
+    const size_t oc = keep.put(c.ctab), oc32 = keep.put(narrowed(c.ctab));
+    const size_t oa = keep.room(3 * (size_t)p->na * 4), ob = keep.room(4 * (size_t)p->nb * 4);
+    QSD_TRY(scratch.upload(st));
+    QSD_TRY(keep.upload(st));
+    p->mem[0] = keep.dev;
+    p->d.dep = keep.at<double>(od);
+    p->f.dep = keep.at<float>(od32);
+    p->d.ctab = keep.at<double>(oc);
+    p->f.ctab = keep.at<float>(oc32);
+    p->alen = keep.at<uint32_t>(oa);
+    p->blen = keep.at<uint32_t>(ob);
+    const BuildView v{s->keys, s->pfilt, s->prank, (const uint4 *)h->t_cw32, (const double2 *)h->t_coef,
+                      (const float2 *)h->t_coef32, scratch.at<uint32_t>(oi), p->na, p->nb, p->split};
+    GroupList g[2];
+    FlipList f[2];
+    for (int H = 0; H < 2; ++H) {
+        g[H] = GroupList{scratch.at<uint32_t>(og[H][0]), scratch.at<uint32_t>(og[H][1]), scratch.at<uint32_t>(og[H][2]),
+                         (uint32_t)c.gflip[H].size(), c.n1[H]};
+        f[H] = FlipList{scratch.at<uint32_t>(of[H][0]), scratch.at<uint32_t>(of[H][1]), scratch.at<uint32_t>(of[H][2]),
+                        scratch.at<uint32_t>(of[H][3]), scratch.at<uint32_t>(of[H][4]), (uint32_t)c.fflip[H].size()};
+    }
+    uint32_t *mx = scratch.at<uint32_t>(om);
+    const unsigned ga = (p->na + 3u) / 4u, gb = (p->nb + 3u) / 4u;
+    k_prod_lists<false, false><<<ga, 256, 0, st>>>(v, g[0], f[0], *p, mx);
+    k_prod_lists<true, false><<<gb, 256, 0, st>>>(v, g[1], f[1], *p, mx + 4);
+    uint32_t m[8];
+    QSD_CHECK_HIP(hipMemcpyAsync(m, mx, sizeof(m), hipMemcpyDeviceToHost, st));
+    QSD_CHECK_HIP(hipStreamSynchronize(st));
+    p->nA1 = m[0];
+    p->nA2 = m[1];
+    p->nAB = m[2];
+    p->nB1 = m[4];
+    p->nB2 = m[5];
+    p->nBAB = m[6];
+    p->max_occ = m[7];
+    Block lists;
+    const size_t na = p->na, nb = p->nb;
+    const size_t o1 = lists.room(4 * p->nA1 * na), o2 = lists.room(4 * p->nA2 * na), o3 = lists.room(4 * p->nAB * na);
+    const size_t o4 = lists.room(8 * p->nB1 * nb), o5 = lists.room(4 * p->nB2 * nb), o6 = lists.room(8 * p->nBAB * nb);
+    size_t ov[2][5];
+    for (int k = 0; k < 2; ++k) {
+        const size_t e = k ? 4 : 8;
+        ov[k][0] = lists.room(e * p->nA1 * na);
+        ov[k][1] = lists.room(e * p->nA2 * na);
+        ov[k][2] = lists.room(e * p->nWb * na);
+        ov[k][3] = lists.room(e * nb * p->nB1 * p->tail_len);
+        ov[k][4] = lists.room(e * nb * p->nB2);
+    }
+    QSD_TRY(lists.upload(st));
+    p->mem[1] = lists.dev;
+    p->a1_ent = lists.at<uint32_t>(o1);
+    p->a2_col = lists.at<uint32_t>(o2);
+    p->ab_ent = lists.at<uint32_t>(o3);
+    p->b1_ent = lists.at<uint32_t>(o4);
+    p->b2_col = lists.at<uint32_t>(o5);
+    p->bab_ent = lists.at<uint32_t>(o6);
+    auto values = [&](auto &w, const size_t *o) {
+        using T = std::remove_pointer_t<decltype(w.a1)>;
+        w.a1 = lists.at<T>(o[0]);
+        w.a2 = lists.at<T>(o[1]);
+        w.wtab = lists.at<T>(o[2]);
+        w.tail = lists.at<T>(o[3]);
+        w.b2 = lists.at<T>(o[4]);
+    };
+    values(p->d, ov[0]);
+    values(p->f, ov[1]);
+    k_prod_lists<false, true><<<ga, 256, 0, st>>>(v, g[0], f[0], *p, nullptr);
+    k_prod_lists<true, true><<<gb, 256, 0, st>>>(v, g[1], f[1], *p, nullptr);
+    const dim3 gw((p->na + 255u) / 256u, p->nWb);
+    k_prod_wtab<double><<<gw, 256, 0, st>>>(s->keys, p->na, p->split, scratch.at<double>(owh), scratch.at<double>(owd),
+                                           p->d.wtab);
+    k_prod_wtab<float><<<gw, 256, 0, st>>>(s->keys, p->na, p->split, scratch.at<float>(owh32),
+                                          scratch.at<float>(owd32), p->f.wtab);
+    QSD_CHECK_HIP(hipGetLastError());
+    return QSD_OK;
+}
+
+}  // namespace
+
+void prod_free(qsd_prod *&p) {
+    if (!p) return;
+    dev_free(p->mem[0]);
+    dev_free(p->mem[1]);
+    delete p;
+    p = nullptr;
+}
+
+int prod_build(qsd_ham *h, hipStream_t st) {
+    const qsd_subspace *s = h->s;
+    if (!s->prank || h->is_complex || h->G == 0) return QSD_OK;
+    // the x row of one block and the tables have to fit a workgroup's LDS
+    if ((uint64_t)s->pna * sizeof(double) > kLdsBytes) return QSD_OK;
+    const Classified c = classify(h->op, s->split);
+    if (!c.ok || (uint64_t)c.nWb * s->pna > kMaxTable) return QSD_OK;
+    auto *p = new (std::nothrow) qsd_prod();
+    if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
+    p->split = s->split;
+    p->na = s->pna;
+    p->nb = (uint32_t)(s->N / s->pna);
+    p->nUa = c.nUa;
+    p->nU = (uint32_t)c.fwant[0].size();
+    p->nW = (uint32_t)c.fwant[1].size();
+    p->nWb = c.nWb;
+    p->tail_len = c.tail_len;
+    p->rmask = c.rmask;
+    p->full = c.full;
+    Block scratch, keep;
+    const int rc = build_device(h, p, c, scratch, keep, st);
+    if (rc != QSD_OK) (void)hipStreamSynchronize(st);  // the host images outlive their copies
+    dev_free(scratch.dev);
+    if (!p->mem[0]) p->mem[0] = keep.dev;
+    if (rc != QSD_OK || lds_bytes<double>(p, 1) > kLdsBytes) {
+        prod_free(p);
+        return rc;
+    }
+    h->prod = p;
+    return QSD_OK;
+}
+
+bool prod_usable(const qsd_ham *h) {
+    return h->prod && h->s->prank && h->s->split == h->prod->split && !(h->schedule & QSD_SCHED_HASH_LOOKUP);
+}
+
+template <class ET>
+void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
+    // as many vectors per workgroup as fit: they share the lists and the coefficients
+    if (nvec >= 3 && lds_bytes<ET>(h->prod, 4) <= kLdsBytes)
+        launch_prod<ET, 4>(h, x, ldx, y, ldy, nvec, st);
+    else if (nvec >= 2 && lds_bytes<ET>(h->prod, 2) <= kLdsBytes)
+        launch_prod<ET, 2>(h, x, ldx, y, ldy, nvec, st);
+    else
+        launch_prod<ET, 1>(h, x, ldx, y, ldy, nvec, st);
+}
+
+template void prod_matvec<double>(const qsd_ham *, const void *, int64_t, void *, int64_t, int, hipStream_t);
+template void prod_matvec<float>(const qsd_ham *, const void *, int64_t, void *, int64_t, int, hipStream_t);
+
+}  // namespace qsd
