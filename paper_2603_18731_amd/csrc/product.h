@@ -62,6 +62,31 @@ struct qsd_prod {
 
 namespace qsd {
 
+// What the SpMV kernels read of a plan, by value (or in a request table).
+template <class ET>
+struct ProdView {
+    uint32_t na, nb, nB1, nB2, nBAB, nUa, nU, tail_len, rmask, full;
+    const uint32_t *__restrict__ a1_ent, *__restrict__ a2_col, *__restrict__ ab_ent;
+    const uint32_t *__restrict__ b1_ent, *__restrict__ b2_col, *__restrict__ bab_ent;
+    const uint32_t *__restrict__ alen, *__restrict__ blen;
+    const ET *__restrict__ a1, *__restrict__ a2, *__restrict__ dep, *__restrict__ ctab, *__restrict__ wtab,
+        *__restrict__ tail, *__restrict__ b2;
+    const ET *__restrict__ diag;
+};
+
+// One request of a batched launch; its workgroups are [first, the next request's first).
+template <class ET>
+struct ProdReq {
+    ProdView<ET> p;
+    const ET *x;
+    ET *y;
+    int64_t ld;
+    int32_t nv;
+    uint32_t first;
+    const int *kdev;  // batched Lanczos: the request idles once *kdev >= m (NULL: never)
+    int32_t m;
+};
+
 // Builds h->prod when the subspace has a product map and the operator factors as above (the group
 // order keeps the classes apart); leaves it NULL otherwise.  The operator's tables must have been
 // uploaded.  Waits once for the list lengths; the lists themselves are enqueued.
@@ -71,8 +96,23 @@ void prod_free(qsd_prod *&p);
 // Whether the SpMV of `h` runs from the plan.
 bool prod_usable(const qsd_ham *h);
 
+template <class ET>
+ProdView<ET> prod_view(const qsd_ham *h);
+
+// Vectors that one workgroup takes when a launch's widest request has nvec of them, and the LDS
+// bytes and workgroups a request needs then.
+template <class ET>
+int prod_width(const qsd_ham *h, int nvec);
+template <class ET>
+uint32_t prod_lds(const qsd_ham *h, int V);
+uint32_t prod_blocks(const qsd_ham *h, int nvec, int V);
+
 // Y = H X from the plan (real operators); nvec interleaved vectors.
 template <class ET>
 void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st);
+
+// The same for n requests of a device table in one launch; every row is evaluated as above.
+template <class ET>
+void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, int V, uint32_t lds, hipStream_t st);
 
 }  // namespace qsd

@@ -202,40 +202,21 @@ __global__ __launch_bounds__(256) void k_prod_wtab(const uint64_t *__restrict__ 
 
 // ------------------------------------------------------------------------------- SpMV
 
-// What the SpMV kernel reads, by value.
-template <class ET>
-struct ProdView {
-    uint32_t na, nb, nB1, nB2, nBAB, nUa, nU, tail_len, rmask;
-    const uint32_t *__restrict__ a1_ent, *__restrict__ a2_col, *__restrict__ ab_ent;
-    const uint32_t *__restrict__ b1_ent, *__restrict__ b2_col, *__restrict__ bab_ent;
-    const uint32_t *__restrict__ alen, *__restrict__ blen;
-    const ET *__restrict__ a1, *__restrict__ a2, *__restrict__ dep, *__restrict__ ctab, *__restrict__ wtab,
-        *__restrict__ tail, *__restrict__ b2;
-};
-
 // One workgroup: 256 low parts of one high part b, V of the interleaved vectors.  Class A and AB
 // columns lie in whole rows x[b'][:], which are staged in LDS (12 KB for 1500 strings in FP64), so
 // the random gathers run at the LDS rate and not at the 0.36 lanes per clock and CU that the texture
 // path gives gathers from L2; b's own list is uniform over the workgroup (scalar loads), and class
 // B reads x[b'][a] coalesced.  Bound by the LDS gathers (one for x, one for the coefficient of an
 // AB element).
-template <class ET, int V, bool FULL>
-__global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ diag,
-                                                     const ET *__restrict__ x, int64_t ldx, ET *__restrict__ y,
-                                                     int64_t ldy, int nvec) {
-    extern __shared__ __align__(16) char smem[];
-    ET *xs = (ET *)smem;            // [na][V]
+template <class ET, int V>
+__device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__restrict__ x, int64_t ldx,
+                                           ET *__restrict__ y, int64_t ldy, int nv, uint32_t tile, uint32_t b,
+                                           char *smem) {
+    ET *xs = (ET *)smem;              // [na][V]
     ET *aux = xs + (size_t)p.na * V;  // class A table rows, then the AB coefficients of one high key
-    // workgroups of one XCD take consecutive high parts of one tile of low parts: they share the
-    // tile's lists in that XCD's L2
-    const uint32_t id = (uint32_t)tile_index(blockIdx.x, gridDim.x, true);
-    const uint32_t tile = id / p.nb, b = id - tile * p.nb;
     const uint32_t al = tile * 256u + threadIdx.x;
     const bool valid = al < p.na;
     const uint32_t a = valid ? al : p.na - 1u;
-    const int v0 = blockIdx.y * V, nv = min(V, nvec - v0);
-    x += v0;
-    y += v0;
     const int64_t row = (int64_t)b * p.na + a;
 
     auto stage = [&](uint32_t bc) {
@@ -246,7 +227,7 @@ __global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *_
     };
     double acc[V];
     {
-        const double dr = (double)diag[row];
+        const double dr = (double)p.diag[row];
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = (V == 1 || v < nv) ? dr * (double)x[row * ldx + v] : 0.0;
     }
@@ -283,31 +264,37 @@ __global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *_
         for (int v = 0; v < V; ++v) acc[v] += (double)val * (double)xs[col * V + v];
     }
     // class AB: for each of b's flips, its row of x and its key's coefficients (both signs: entry
-    // 2 u + s is the coefficient with the low part's sign s applied)
-    const uint32_t nab = p.blen[2 * (int64_t)p.nb + b];
-    for (uint32_t e = 0; e < nab; ++e) {
-        const uint32_t bc = p.bab_ent[2 * ((int64_t)b * p.nBAB + e)];
-        const uint32_t w = p.bab_ent[2 * ((int64_t)b * p.nBAB + e) + 1];
-        const ET *ct = p.ctab + (int64_t)(w >> 1) * p.nU;
-        __syncthreads();  // the previous row and table are no longer read
-        stage(bc);
-        for (uint32_t u = threadIdx.x; u < p.nU; u += 256u) {
-            const ET c = (w & 1u) ? -ct[u] : ct[u];
-            aux[2 * u] = c;
-            aux[2 * u + 1] = -c;
-        }
-        __syncthreads();
+    // 2 u + s is the coefficient with the low part's sign s applied; 0 = the pair has no term)
+    auto class_ab = [&](auto full) {
+        const uint32_t nab = p.blen[2 * (int64_t)p.nb + b];
+        for (uint32_t e = 0; e < nab; ++e) {
+            const uint32_t bc = p.bab_ent[2 * ((int64_t)b * p.nBAB + e)];
+            const uint32_t w = p.bab_ent[2 * ((int64_t)b * p.nBAB + e) + 1];
+            const ET *ct = p.ctab + (int64_t)(w >> 1) * p.nU;
+            __syncthreads();  // the previous row and table are no longer read
+            stage(bc);
+            for (uint32_t u = threadIdx.x; u < p.nU; u += 256u) {
+                const ET c = (w & 1u) ? -ct[u] : ct[u];
+                aux[2 * u] = c;
+                aux[2 * u + 1] = -c;
+            }
+            __syncthreads();
 #pragma unroll 4
-        for (uint32_t k = 0; k < n3; ++k) {
-            const uint32_t f = p.ab_ent[(int64_t)k * p.na + a];
-            const ET c = aux[f >> 16];
-            const uint32_t col = f & 0xFFFFu;
-            if (FULL || c != (ET)0) {
+            for (uint32_t k = 0; k < n3; ++k) {
+                const uint32_t f = p.ab_ent[(int64_t)k * p.na + a];
+                const ET c = aux[f >> 16];
+                const uint32_t col = f & 0xFFFFu;
+                if (decltype(full)::value || c != (ET)0) {
 #pragma unroll
-                for (int v = 0; v < V; ++v) acc[v] += (double)c * (double)xs[col * V + v];
+                    for (int v = 0; v < V; ++v) acc[v] += (double)c * (double)xs[col * V + v];
+                }
             }
         }
-    }
+    };
+    if (p.full)
+        class_ab(std::true_type{});
+    else
+        class_ab(std::false_type{});
     // class B: the same low part in other blocks
     const ET *xa = x + (int64_t)a * ldx;
     const int64_t bstride = (int64_t)p.na * ldx;
@@ -339,34 +326,46 @@ __global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *_
     }
 }
 
+template <class ET, int V>
+__global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ x, int64_t ldx,
+                                                     ET *__restrict__ y, int64_t ldy, int nvec) {
+    extern __shared__ __align__(16) char smem[];
+    // workgroups of one XCD take consecutive high parts of one tile of low parts: they share the
+    // tile's lists in that XCD's L2
+    const uint32_t id = (uint32_t)tile_index(blockIdx.x, gridDim.x, true);
+    const uint32_t tile = id / p.nb;
+    const int v0 = blockIdx.y * V;
+    prod_block<ET, V>(p, x + v0, ldx, y + v0, ldy, min(V, nvec - v0), tile, id - tile * p.nb, smem);
+}
+
+// Requests of a table: a workgroup finds its request by the requests' first workgroups.
+template <class ET, int V>
+__global__ __launch_bounds__(256) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n) {
+    extern __shared__ __align__(16) char smem[];
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (reqs[mid].first <= blockIdx.x)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    const ProdReq<ET> &R = reqs[lo];
+    if (R.kdev && *R.kdev >= R.m) return;  // at its iteration limit (uniform for the block)
+    uint32_t id = blockIdx.x - R.first;
+    const uint32_t per = (R.p.na + 255u) / 256u * R.p.nb;  // workgroups per vector chunk
+    const uint32_t vc = id / per;
+    id -= vc * per;
+    const uint32_t tile = id / R.p.nb;
+    const int v0 = (int)vc * V;
+    prod_block<ET, V>(R.p, R.x + v0, R.ld, R.y + v0, R.ld, min(V, R.nv - v0), tile, id - tile * R.p.nb, smem);
+}
+
 uint32_t aux_entries(const qsd_prod *p) { return std::max(p->max_occ * p->nUa, 2u * p->nU); }
 
 template <class ET>
 uint32_t lds_bytes(const qsd_prod *p, int V) {
     return (uint32_t)((p->na * V + aux_entries(p)) * sizeof(ET));
-}
-
-template <class ET, int V>
-void launch_prod(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
-    const qsd_prod *p = h->prod;
-    const ProdVals<ET> *pv;
-    const ET *diag;
-    if constexpr (std::is_same<ET, double>::value) {
-        pv = &p->d;
-        diag = h->diag;
-    } else {
-        pv = &p->f;
-        diag = h->diag32;
-    }
-    const ProdView<ET> v{p->na, p->nb, p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask,
-                         p->a1_ent, p->a2_col, p->ab_ent, p->b1_ent, p->b2_col, p->bab_ent, p->alen, p->blen,
-                         pv->a1, pv->a2, pv->dep, pv->ctab, pv->wtab, pv->tail, pv->b2};
-    const dim3 grid((p->na + 255u) / 256u * p->nb, (unsigned)((nvec + V - 1) / V));
-    const uint32_t lds = lds_bytes<ET>(p, V);
-    if (p->full)
-        k_prod_matvec<ET, V, true><<<grid, 256, lds, st>>>(v, diag, (const ET *)x, ldx, (ET *)y, ldy, nvec);
-    else
-        k_prod_matvec<ET, V, false><<<grid, 256, lds, st>>>(v, diag, (const ET *)x, ldx, (ET *)y, ldy, nvec);
 }
 
 // ------------------------------------------------------------------- host classification
@@ -766,17 +765,74 @@ bool prod_usable(const qsd_ham *h) {
 }
 
 template <class ET>
-void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
-    // as many vectors per workgroup as fit: they share the lists and the coefficients
-    if (nvec >= 3 && lds_bytes<ET>(h->prod, 4) <= kLdsBytes)
-        launch_prod<ET, 4>(h, x, ldx, y, ldy, nvec, st);
-    else if (nvec >= 2 && lds_bytes<ET>(h->prod, 2) <= kLdsBytes)
-        launch_prod<ET, 2>(h, x, ldx, y, ldy, nvec, st);
-    else
-        launch_prod<ET, 1>(h, x, ldx, y, ldy, nvec, st);
+ProdView<ET> prod_view(const qsd_ham *h) {
+    const qsd_prod *p = h->prod;
+    const ProdVals<ET> *v;
+    const ET *diag;
+    if constexpr (std::is_same<ET, double>::value) {
+        v = &p->d;
+        diag = h->diag;
+    } else {
+        v = &p->f;
+        diag = h->diag32;
+    }
+    return ProdView<ET>{p->na, p->nb, p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask, p->full ? 1u : 0u,
+                        p->a1_ent, p->a2_col, p->ab_ent, p->b1_ent, p->b2_col, p->bab_ent, p->alen, p->blen,
+                        v->a1, v->a2, v->dep, v->ctab, v->wtab, v->tail, v->b2, diag};
 }
 
-template void prod_matvec<double>(const qsd_ham *, const void *, int64_t, void *, int64_t, int, hipStream_t);
-template void prod_matvec<float>(const qsd_ham *, const void *, int64_t, void *, int64_t, int, hipStream_t);
+template <class ET>
+uint32_t prod_lds(const qsd_ham *h, int V) {
+    return lds_bytes<ET>(h->prod, V);
+}
+
+// As many vectors per workgroup as there are and fit its LDS: they share the lists and the
+// coefficients (one vector always fits: prod_build).
+template <class ET>
+int prod_width(const qsd_ham *h, int nvec) {
+    int V = nvec >= 3 ? 4 : nvec == 2 ? 2 : 1;
+    while (V > 1 && lds_bytes<ET>(h->prod, V) > kLdsBytes) V >>= 1;
+    return V;
+}
+
+uint32_t prod_blocks(const qsd_ham *h, int nvec, int V) {
+    return (h->prod->na + 255u) / 256u * h->prod->nb * (uint32_t)((nvec + V - 1) / V);
+}
+
+template <class ET>
+void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
+    const int V = prod_width<ET>(h, nvec);
+    const uint32_t lds = prod_lds<ET>(h, V);
+    const ProdView<ET> p = prod_view<ET>(h);
+    const dim3 grid(prod_blocks(h, 1, 1), (unsigned)((nvec + V - 1) / V));
+    const ET *xe = (const ET *)x;
+    ET *ye = (ET *)y;
+    if (V == 4)
+        k_prod_matvec<ET, 4><<<grid, 256, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
+    else if (V == 2)
+        k_prod_matvec<ET, 2><<<grid, 256, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
+    else
+        k_prod_matvec<ET, 1><<<grid, 256, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
+}
+
+template <class ET>
+void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, int V, uint32_t lds, hipStream_t st) {
+    if (V == 4)
+        k_prod_batched<ET, 4><<<blocks, 256, lds, st>>>(d_reqs, n);
+    else if (V == 2)
+        k_prod_batched<ET, 2><<<blocks, 256, lds, st>>>(d_reqs, n);
+    else
+        k_prod_batched<ET, 1><<<blocks, 256, lds, st>>>(d_reqs, n);
+}
+
+#define QSD_PROD_FOR(ET)                                                                                     \
+    template ProdView<ET> prod_view<ET>(const qsd_ham *);                                                    \
+    template uint32_t prod_lds<ET>(const qsd_ham *, int);                                                    \
+    template int prod_width<ET>(const qsd_ham *, int);                                                       \
+    template void prod_matvec<ET>(const qsd_ham *, const void *, int64_t, void *, int64_t, int, hipStream_t); \
+    template void prod_matvec_batched<ET>(const ProdReq<ET> *, int, uint32_t, int, uint32_t, hipStream_t);
+QSD_PROD_FOR(double)
+QSD_PROD_FOR(float)
+#undef QSD_PROD_FOR
 
 }  // namespace qsd

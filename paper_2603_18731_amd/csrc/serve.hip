@@ -8,11 +8,13 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
 #include "common.h"
 #include "matvec.h"
+#include "product.h"
 #include "tridiag.h"
 
 namespace qsd {
@@ -401,6 +403,7 @@ struct qsd_batch {
         void *stream = nullptr;   // stream of the request's add (an owned workspace is released on it)
         double tol = 1e-10;
         int steps = 0;
+        bool prod = false;        // runs from the operator's factored form
     };
     std::vector<Slot> slots;
     ReqDev *d_reqs = nullptr;
@@ -413,6 +416,11 @@ struct qsd_batch {
     Tile *d_pmt = nullptr;
     int n_pmt = 0;
     size_t cap_pmt = 0;
+    // requests that run from their factored form (product.h): a table of the batch's SpMV type
+    uint8_t *d_prod = nullptr;
+    int n_prod = 0;
+    size_t cap_prod = 0;
+    uint32_t prod_blocks = 0, prod_lds = 0;
     double *d_out = nullptr;  // [max_slots][4]
     int64_t *d_spike = nullptr;
     bool dirty = true;
@@ -457,9 +465,58 @@ Layout layout_of(int64_t N, int m, bool f32) {
     return L;
 }
 
+// The factored requests of the batch (one vector each), as an upload image.
+template <class ET>
+std::vector<ProdReq<ET>> prod_requests(qsd_batch *b, uint32_t &blocks, uint32_t &lds) {
+    std::vector<ProdReq<ET>> out;
+    blocks = lds = 0;
+    for (const auto &S : b->slots) {
+        if (!S.used || !S.prod) continue;
+        ProdReq<ET> R{};
+        R.p = prod_view<ET>(S.h);
+        if constexpr (std::is_same<ET, float>::value) {
+            R.x = S.d.x32;
+            R.y = S.d.w32;
+        } else {
+            R.x = S.d.x;
+            R.y = S.d.w;
+        }
+        R.ld = R.nv = 1;
+        R.first = blocks;
+        R.kdev = S.d.kdev;
+        R.m = S.d.m;
+        out.push_back(R);
+        blocks += prod_blocks(S.h, 1, 1);
+        lds = std::max(lds, prod_lds<ET>(S.h, 1));
+    }
+    return out;
+}
+
+template <class ET>
+int sync_prod(qsd_batch *b, hipStream_t st) {
+    const auto reqs = prod_requests<ET>(b, b->prod_blocks, b->prod_lds);
+    b->n_prod = (int)reqs.size();
+    const size_t bytes = reqs.size() * sizeof(ProdReq<ET>);
+    if (bytes > b->cap_prod) {
+        dev_free(b->d_prod);
+        b->cap_prod = 0;
+        QSD_TRY(dev_alloc(&b->d_prod, 2 * bytes));
+        b->cap_prod = 2 * bytes;
+    }
+    if (bytes) {
+        QSD_CHECK_HIP(hipMemcpyAsync(b->d_prod, reqs.data(), bytes, hipMemcpyHostToDevice, st));
+        QSD_CHECK_HIP(hipStreamSynchronize(st));  // `reqs` ends here
+    }
+    return QSD_OK;
+}
+
 int sync_tables(qsd_batch *b, hipStream_t st) {
     if (!b->dirty) return QSD_OK;
     AllocScope scope(&b->alloc, st);
+    if (b->f32)
+        QSD_TRY(sync_prod<float>(b, st));
+    else
+        QSD_TRY(sync_prod<double>(b, st));
     std::vector<ReqDev> host(b->max_slots);
     std::vector<Tile> mv, mvo, bl, pmt;
     for (int i = 0; i < b->max_slots; ++i) {
@@ -474,7 +531,7 @@ int sync_tables(qsd_batch *b, hipStream_t st) {
         // kernel), then the others; no kernel depends on the order of the tiles
         const bool pm = b->Wp == 1 && !S.d.cptr && S.d.s.prank && !(S.d.sched & QSD_SCHED_HASH_LOOKUP);
         for (int64_t t = 0; t < (S.d.N + kBlock - 1) / kBlock; ++t) (pm ? mv : mvo).push_back({i, (int)t});
-        if (pm) {
+        if (pm && !S.prod) {
             const int64_t n = pm_tiles(S.d.N, S.d.s.pna, S.d.sched);
             for (int64_t t = 0; t < (n ? n : (S.d.N + kBlock - 1) / kBlock); ++t) pmt.push_back({i, (int)t});
         }
@@ -512,11 +569,19 @@ int sync_tables(qsd_batch *b, hipStream_t st) {
     return QSD_OK;
 }
 
-// The batched SpMV: product-map tiles in one launch (one-word keys), the others in another.
+// The batched SpMV: factored requests, product-map tiles (one-word keys) and the others, in a
+// launch each.
 template <int Wp>
 void launch_bmv(qsd_batch *b, hipStream_t st) {
     const int np = Wp == 1 ? b->n_mv_pm : 0, no = b->n_mv - np;
-    if (np > 0) {
+    if (b->n_prod > 0) {
+        if (b->f32)
+            prod_matvec_batched<float>((const ProdReq<float> *)b->d_prod, b->n_prod, b->prod_blocks, 1, b->prod_lds, st);
+        else
+            prod_matvec_batched<double>((const ProdReq<double> *)b->d_prod, b->n_prod, b->prod_blocks, 1, b->prod_lds,
+                                        st);
+    }
+    if (b->n_pmt > 0) {
         if (b->f32)
             kb_matvec<1, float, 2><<<b->n_pmt, kBlock, 0, st>>>(b->d_reqs, b->d_pmt);
         else
@@ -618,6 +683,7 @@ int add_impl(qsd_batch *b, const qsd_ham *h, const qsd_csr *c, int32_t v0_mode, 
         d.diag = h->diag;
         d.diag32 = h->diag32;
         d.sched = h->schedule;
+        S.prod = prod_usable(h);
     } else {
         d.diag = c->diag;
         d.cptr = c->indptr;
@@ -794,6 +860,7 @@ extern "C" int qsd_batch_destroy(qsd_batch *b) {
     dev_free(b->d_mv);
     dev_free(b->d_bl);
     dev_free(b->d_pmt);
+    dev_free(b->d_prod);
     dev_free(b->d_out);
     dev_free(b->d_spike);
     delete b;
@@ -843,7 +910,52 @@ struct BatchedPlan {
     std::vector<MvReq> reqs;
     std::vector<Tile> tiles;
     std::vector<Launch> launches;
+    // requests that run from their factored form (product.h), all in one launch: a table entry
+    // each, with the vectors' element type, and no row tiles
+    std::vector<ProdReq<double>> prod64;
+    std::vector<ProdReq<float>> prod32;
+    int prod_V = 4;
+    uint32_t prod_lds = 0, prod_blocks = 0;
+    size_t row_tiles = 0;  // 256-row tiles of all requests (a limit of the allocation-free entry)
+
+    bool empty() const { return reqs.empty() && prod64.empty() && prod32.empty(); }
+    size_t chunks() const { return reqs.size() + prod64.size() + prod32.size(); }
+    // the tables lie one after the other in one upload
+    static size_t up(size_t n) { return (n + 255) / 256 * 256; }
+    size_t prod_bytes() const {
+        return prod64.size() * sizeof(ProdReq<double>) + prod32.size() * sizeof(ProdReq<float>);
+    }
+    size_t prod_at() const { return up(reqs.size() * sizeof(MvReq)); }
+    size_t tiles_at() const { return prod_at() + up(prod_bytes()); }
+    size_t bytes() const { return tiles_at() + tiles.size() * sizeof(Tile); }
 };
+
+// Adds the factored requests of a call: their common width is the narrowest that fits every one.
+template <class ET>
+int plan_prod(int32_t n, const qsd_ham *const *hams, const void *const *xs, void *const *ys, const int32_t *nvecs,
+              std::vector<ProdReq<ET>> &out, BatchedPlan &P) {
+    int nv_max = 0;
+    for (int i = 0; i < n; ++i)
+        if (prod_usable(hams[i])) nv_max = std::max(nv_max, nvecs[i]);
+    for (int i = 0; i < n; ++i)
+        if (prod_usable(hams[i])) P.prod_V = std::min(P.prod_V, prod_width<ET>(hams[i], nv_max));
+    uint64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        if (!prod_usable(hams[i])) continue;
+        ProdReq<ET> R{};
+        R.p = prod_view<ET>(hams[i]);
+        R.x = (const ET *)xs[i];
+        R.y = (ET *)ys[i];
+        R.ld = R.nv = nvecs[i];
+        R.first = (uint32_t)blocks;
+        out.push_back(R);
+        blocks += prod_blocks(hams[i], nvecs[i], P.prod_V);
+        P.prod_lds = std::max(P.prod_lds, prod_lds<ET>(hams[i], P.prod_V));
+    }
+    if (blocks > (uint64_t)INT32_MAX) return fail(QSD_ERR_CAPACITY, "too many workgroups");
+    P.prod_blocks = (uint32_t)blocks;
+    return QSD_OK;
+}
 
 int plan_batched(int32_t n, const qsd_ham *const *hams, const void *const *xs, void *const *ys, const int32_t *nvecs,
                  int32_t dtype, BatchedPlan &P) {
@@ -869,6 +981,10 @@ int plan_batched(int32_t n, const qsd_ham *const *hams, const void *const *xs, v
                 if (h->Wp != Wp || nvecs[i] <= c0 || h->N == 0) continue;
                 const bool hpm = Wp == 1 && h->s->prank && !(h->schedule & QSD_SCHED_HASH_LOOKUP);
                 if (hpm != (pm != 0)) continue;
+                const int64_t nb = L.pm ? pm_tiles(h->N, h->s->pna, h->schedule) : 0;
+                const int64_t nt = nb ? nb : (h->N + kBlock - 1) / kBlock;
+                P.row_tiles += (size_t)nt;
+                if (!cplx && prod_usable(h)) continue;
                 MvReq R{};
                 R.s = sub_view(h->s);
                 R.h = ham_view(h, f32);
@@ -883,24 +999,40 @@ int plan_batched(int32_t n, const qsd_ham *const *hams, const void *const *xs, v
                 const int slot = (int)P.reqs.size();
                 P.reqs.push_back(R);
                 // product-map requests: tiles within the product's blocks of rows (see pm_tile)
-                const int64_t nb = L.pm ? pm_tiles(h->N, h->s->pna, h->schedule) : 0;
-                for (int64_t t = 0; t < (nb ? nb : (h->N + kBlock - 1) / kBlock); ++t) P.tiles.push_back({slot, (int)t});
+                for (int64_t t = 0; t < nt; ++t) P.tiles.push_back({slot, (int)t});
             }
             L.nt = P.tiles.size() - L.t0;
             if (L.nt > 0) P.launches.push_back(L);
           }
         }
     }
-    if (P.tiles.size() > (size_t)INT32_MAX) return fail(QSD_ERR_CAPACITY, "too many row tiles");
+    if (P.row_tiles > (size_t)INT32_MAX) return fail(QSD_ERR_CAPACITY, "too many row tiles");
+    if (dtype == QSD_F64) return plan_prod<double>(n, hams, xs, ys, nvecs, P.prod64, P);
+    if (dtype == QSD_F32) return plan_prod<float>(n, hams, xs, ys, nvecs, P.prod32, P);
     return QSD_OK;
 }
 
-// Uploads the plan's tables to d_reqs / d_tiles and enqueues its launches on st.
-int run_batched(const BatchedPlan &P, int32_t dtype, MvReq *d_reqs, Tile *d_tiles, hipStream_t st) {
-    // pageable sources: the copies return once the host data is staged
-    if (hipMemcpyAsync(d_reqs, P.reqs.data(), P.reqs.size() * sizeof(MvReq), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(d_tiles, P.tiles.data(), P.tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, st) != hipSuccess)
+// Uploads the plan's tables to `mem` (P.bytes() long) and enqueues its launches on st.
+int run_batched(const BatchedPlan &P, int32_t dtype, uint8_t *mem, hipStream_t st) {
+    std::vector<uint8_t> image(P.bytes());
+    auto put = [&](size_t at, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(image.data() + at, src, bytes);
+    };
+    put(0, P.reqs.data(), P.reqs.size() * sizeof(MvReq));
+    put(P.prod_at(), P.prod64.data(), P.prod64.size() * sizeof(ProdReq<double>));
+    put(P.prod_at(), P.prod32.data(), P.prod32.size() * sizeof(ProdReq<float>));  // (one of the two is empty)
+    put(P.tiles_at(), P.tiles.data(), P.tiles.size() * sizeof(Tile));
+    // a pageable source: the copy returns once the host data is staged
+    if (hipMemcpyAsync(mem, image.data(), image.size(), hipMemcpyHostToDevice, st) != hipSuccess)
         return fail(QSD_ERR_HIP, "table upload failed");
+    const MvReq *d_reqs = (const MvReq *)mem;
+    const Tile *d_tiles = (const Tile *)(mem + P.tiles_at());
+    if (!P.prod64.empty())
+        prod_matvec_batched<double>((const ProdReq<double> *)(mem + P.prod_at()), (int)P.prod64.size(), P.prod_blocks,
+                                    P.prod_V, P.prod_lds, st);
+    if (!P.prod32.empty())
+        prod_matvec_batched<float>((const ProdReq<float> *)(mem + P.prod_at()), (int)P.prod32.size(), P.prod_blocks,
+                                   P.prod_V, P.prod_lds, st);
     for (const auto &L : P.launches) {
         const Tile *tl = d_tiles + L.t0;
         switch (dtype) {
@@ -914,13 +1046,13 @@ int run_batched(const BatchedPlan &P, int32_t dtype, MvReq *d_reqs, Tile *d_tile
     return QSD_OK;
 }
 
-// Fixed device scratch of qsd_matvec_batched_noalloc: the request table, then the tile list.
+// Fixed device scratch of qsd_matvec_batched_noalloc: the request tables, then the tile list.
 // Every GPU the library runs on holds one until the process ends.  In host code the name is only
 // a symbol: its device address comes from hipGetSymbolAddress, once per device.
 constexpr int kScratchReqs = QSD_NOALLOC_MAX_REQUESTS;
 constexpr size_t kScratchTiles = QSD_NOALLOC_MAX_TILES;
-constexpr size_t kScratchTileOff = (kScratchReqs * sizeof(MvReq) + 255) / 256 * 256;
-constexpr size_t kScratchBytes = kScratchTileOff + kScratchTiles * sizeof(Tile);
+constexpr size_t kReqBytes = std::max(sizeof(MvReq), sizeof(ProdReq<double>));
+constexpr size_t kScratchBytes = kScratchReqs * kReqBytes + 512 + kScratchTiles * sizeof(Tile);
 static_assert(kScratchBytes <= (size_t(1) << 20), "the fixed scratch stays under 1 MiB");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -952,35 +1084,22 @@ extern "C" int qsd_matvec_batched(int32_t n, const qsd_ham *const *hams, const v
     clear_error();
     BatchedPlan P;
     QSD_TRY(plan_batched(n, hams, xs, ys, nvecs, dtype, P));
-    if (P.launches.empty()) return QSD_OK;
+    if (P.empty()) return QSD_OK;
     hipStream_t st = (hipStream_t)stream;
     // Stream-ordered tables: allocated, filled, used and released in order on `stream`, by the
     // first operator's allocator (stream-ordered by contract) or hipMallocAsync.
     AllocScope scope(&hams[0]->alloc, stream);
     const bool own_alloc = custom_allocator();
-    MvReq *d_reqs = nullptr;
-    Tile *d_tiles = nullptr;
-    if (own_alloc) {
-        QSD_TRY(dev_alloc(&d_reqs, P.reqs.size()));
-        if (dev_alloc(&d_tiles, P.tiles.size()) != QSD_OK) {
-            dev_free(d_reqs);
-            return QSD_ERR_OUT_OF_MEMORY;
-        }
-    } else {
-        QSD_CHECK_HIP(hipMallocAsync((void **)&d_reqs, P.reqs.size() * sizeof(MvReq), st));
-        if (hipMallocAsync((void **)&d_tiles, P.tiles.size() * sizeof(Tile), st) != hipSuccess) {
-            (void)hipFreeAsync(d_reqs, st);
-            return fail(QSD_ERR_OUT_OF_MEMORY, "tile table allocation failed");
-        }
-    }
-    const int rc = run_batched(P, dtype, d_reqs, d_tiles, st);
-    if (own_alloc) {
-        dev_free(d_tiles);
-        dev_free(d_reqs);
-    } else {
-        (void)hipFreeAsync(d_tiles, st);
-        (void)hipFreeAsync(d_reqs, st);
-    }
+    uint8_t *mem = nullptr;
+    if (own_alloc)
+        QSD_TRY(dev_alloc(&mem, P.bytes()));
+    else
+        QSD_CHECK_HIP(hipMallocAsync((void **)&mem, P.bytes(), st));
+    const int rc = run_batched(P, dtype, mem, st);
+    if (own_alloc)
+        dev_free(mem);
+    else
+        (void)hipFreeAsync(mem, st);
     return rc;
 }
 
@@ -989,17 +1108,15 @@ extern "C" int qsd_matvec_batched_noalloc(int32_t n, const qsd_ham *const *hams,
     clear_error();
     BatchedPlan P;
     QSD_TRY(plan_batched(n, hams, xs, ys, nvecs, dtype, P));
-    if (P.launches.empty()) return QSD_OK;
-    if (P.reqs.size() > (size_t)kScratchReqs)
-        return fail(QSD_ERR_CAPACITY, "%zu request chunks exceed the %d the fixed scratch holds", P.reqs.size(),
+    if (P.empty()) return QSD_OK;
+    if (P.chunks() > (size_t)kScratchReqs)
+        return fail(QSD_ERR_CAPACITY, "%zu request chunks exceed the %d the fixed scratch holds", P.chunks(),
                     kScratchReqs);
-    if (P.tiles.size() > kScratchTiles)
-        return fail(QSD_ERR_CAPACITY, "%zu row tiles exceed the %zu the fixed scratch holds", P.tiles.size(),
+    if (P.row_tiles > kScratchTiles)
+        return fail(QSD_ERR_CAPACITY, "%zu row tiles exceed the %zu the fixed scratch holds", P.row_tiles,
                     (size_t)kScratchTiles);
     void *base = nullptr;
     QSD_TRY(scratch_address(&base));
-    MvReq *d_reqs = (MvReq *)base;
-    Tile *d_tiles = (Tile *)((unsigned char *)base + kScratchTileOff);
     // nothing in the scratch must start at zero: the call uploads its whole table first
-    return run_batched(P, dtype, d_reqs, d_tiles, (hipStream_t)stream);
+    return run_batched(P, dtype, (uint8_t *)base, (hipStream_t)stream);
 }

@@ -175,3 +175,35 @@ def test_rehash_keeps_the_results():
     G = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(ops))
     sub.rehash(0.125, 16)
     assert torch.equal(G.matvec(x), want)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_batched_mix(dtype):
+    """Factored requests beside product-map (group order by weight), table and non-product ones
+    in one batched call and in one Lanczos batch: bitwise the single calls' results."""
+    hams = []
+    for na, nb, kw in ((257, 3, {}), (40, 40, {}), (40, 40, {"order_by_parts": False}), (1, 30, {}), (1200, 2, {})):
+        ops, keys = c3_parts(na, nb) if na > 1 else (lambda w: (w.ops, w.keys))(wl.c3_molecular(na, nb))
+        hams.append(qsd.SubspaceHamiltonian(qsd.Subspace(keys, 32), qsd.operator_from_termlist(ops, **kw)))
+    hams.append(qsd.SubspaceHamiltonian(hams[1].subspace, hams[1].op))
+    hams[-1].schedule |= qsd.SCHED_HASH_LOOKUP
+    hams.append(qsd.SubspaceHamiltonian(qsd.Subspace(wl.full_space(9), 9), qsd.operator_from_termlist(wl.tfim_chain(9))))
+    nvecs = [1, 5, 2, 16, 3, 1, 1]
+    xs = [_vec(h.N, nv, dtype, k) for k, (h, nv) in enumerate(zip(hams, nvecs))]
+    say("batched mix", dtype)
+    for entry in (qsd.matvec_batched, qsd.matvec_batched_noalloc):
+        ys = entry(hams, xs, [torch.full_like(x, float("nan")) for x in xs])
+        for h, x, y in zip(hams, xs, ys):
+            assert torch.equal(y, h.matvec(x))
+    b = qsd.LanczosBatch(8, max_iter=60, spmv_dtype="f64" if dtype == torch.float64 else "f32")
+    one = qsd.LanczosBatch(8, max_iter=60, spmv_dtype="f64" if dtype == torch.float64 else "f32")
+    slots = [b.add(h, v0="random", seed=k) for k, h in enumerate(hams)]
+    b.step(12)
+    st, e, it, rr = b.poll()
+    for k, h in enumerate(hams):
+        s = one.add(h, v0="random", seed=k)
+        one.step(12)
+        _, e1, it1, rr1 = one.poll()
+        assert (e1[s], it1[s], rr1[s]) == (e[slots[k]], it[slots[k]], rr[slots[k]])
+        one.remove(s)
+    assert e[slots[1]] == e[slots[1]] and st[slots[1]] != 0
