@@ -292,7 +292,9 @@ int qsd_ham_diag_splitting(const qsd_ham *h, double *lowest, double *splitting, 
  *                         without off-diagonal elements, and the slot-order rows write only the
  *                         rows that have some (per-row bits built once per operator, N / 8
  *                         bytes, by the first qsd_ham_set_schedule or qsd_ham_autotune call that
- *                         needs them; that call synchronizes).
+ *                         needs them; that call synchronizes).  For an operator with at most N
+ *                         off-diagonal elements that call also lists each element's column and
+ *                         term range (16 bytes an element), and qsd_matvec runs from the list.
  *   QSD_SCHED_LOCKSTEP    the 64 lanes of a wave probe the same group in the same instruction
  *                         (lanes whose row does not have it live sit idle) instead of each lane
  *                         walking its own live groups; with SLOT_ORDER the wave's occupancy-bit

@@ -205,6 +205,7 @@ constexpr uint32_t kInfoKMask = 7u;
 constexpr uint32_t kInfoLadder = 1u << 3;
 constexpr uint32_t kInfoCare = 1u << 4;
 
+struct qsd_hits;  // element list of a sparse operator (hits.h)
 struct qsd_prod;  // factored form on a product subspace (product.h)
 
 struct qsd_ham {
@@ -237,6 +238,8 @@ struct qsd_ham {
     float *diag32_im = nullptr;
     // [ceil(N / 64)] bit r = row r has an off-diagonal element; built for the slot-order schedules
     uint64_t *rowbits = nullptr;
+    // list of the off-diagonal elements (sparse operators), built beside them
+    qsd_hits *hits = nullptr;
     qsd_prod *prod = nullptr;  // NULL: the operator does not factor, or the subspace is no product
 };
 
@@ -257,15 +260,20 @@ struct qsd_csr {
 
 namespace qsd {
 // The operator an eigensolver applies: matrix-free (a bound Hamiltonian) or a stored CSR matrix.
+int hits_matvec(const qsd_ham *h, const qsd_hits *p, int nvec, const void *x, int64_t ldx, void *y, int64_t ldy,
+                int32_t dtype, hipStream_t st);
+
 struct SpmvOp {
     const qsd_ham *h = nullptr;
     const qsd_csr *c = nullptr;
+    const qsd_hits *hits = nullptr;  // element list of `h` that the solve made for itself
     int64_t N() const { return c ? c->N : h->N; }
     bool is_complex() const { return c ? c->cplx : h->is_complex; }
     const double *diag() const { return c ? c->diag : h->diag; }
     const qsd_allocator *allocator() const { return c ? &c->alloc : &h->alloc; }
     bool takes(int32_t dtype) const { return !c || c->dtype == dtype; }
     int matvec(int nvec, const void *x, int64_t ldx, void *y, int64_t ldy, int32_t dtype, hipStream_t st) const {
+        if (hits) return hits_matvec(h, hits, nvec, x, ldx, y, ldy, dtype, st);
         return c ? qsd_csr_matvec(c, nvec, x, ldx, y, ldy, dtype, st) : qsd_matvec(h, nvec, x, ldx, y, ldy, dtype, st);
     }
 };

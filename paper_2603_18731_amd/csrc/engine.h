@@ -408,9 +408,11 @@ __device__ __forceinline__ uint32_t group_msob(const uint64_t *__restrict__ mask
 // uses them in increasing group order, so the load latencies overlap while every row's sum
 // keeps its fixed order.  Probes whose column is present but where no term matches the row's
 // projector bits are not stored entries and are not handed over.
-template <class ET, class Use, class Fetch>
+// A range sink's use(j, t0, len) takes the element's term range instead of its value.
+template <class ET, class Use, class Fetch, bool RANGE = false>
 struct HitSink {
     using value_type = ET;
+    static constexpr bool kRange = RANGE;
     Use use;
     Fetch fetch;
 };
@@ -424,6 +426,18 @@ __device__ __forceinline__ HitSink<ET, Use, NoFetch> sink(Use u) {
 template <class ET, class Use, class Fetch>
 __device__ __forceinline__ HitSink<ET, Use, Fetch> sink(Use u, Fetch f) {
     return HitSink<ET, Use, Fetch>{u, f};
+}
+template <class ET, class Use>
+__device__ __forceinline__ HitSink<ET, Use, NoFetch, true> range_sink(Use u) {
+    return HitSink<ET, Use, NoFetch, true>{u, NoFetch{}};
+}
+template <class Sink, class ET, class Pre>
+__device__ __forceinline__ void hand_over(Sink &s, int64_t j, uint32_t t0, uint32_t len, ET vre, ET vim,
+                                          const Pre &pre) {
+    if constexpr (Sink::kRange)
+        s.use(j, t0, len);
+    else
+        s.use(j, vre, vim, pre);
 }
 
 // Term range [t0, t0 + len) of chunk group cc for the row (its ladder integer selects it).
@@ -494,7 +508,7 @@ __device__ __forceinline__ void deliver(const HamView &h, const ChunkLds<Wp> &ld
             if (!len[b]) continue;
             ET vre, vim;
             if (range_sum<Wp, true, ET>(h, key, t0[b], len[b], first[b], vre, vim))
-                on_hit.use(j[b], vre, vim, pre[b]);
+                hand_over(on_hit, j[b], t0[b], len[b], vre, vim, pre[b]);
         }
     } else {
 #pragma unroll
@@ -503,7 +517,7 @@ __device__ __forceinline__ void deliver(const HamView &h, const ChunkLds<Wp> &ld
             uint32_t t0, len;
             hit_range<Wp>(lds, key, planes, lane, c[b], t0, len);
             ET vre, vim;
-            if (range_value<Wp, ET>(h, key, t0, len, vre, vim)) on_hit.use(j[b], vre, vim, pre[b]);
+            if (range_value<Wp, ET>(h, key, t0, len, vre, vim)) hand_over(on_hit, j[b], t0, len, vre, vim, pre[b]);
         }
     }
 }
@@ -728,7 +742,7 @@ __device__ __forceinline__ void pm_phase2(const SubView &s, const HamView &h, co
             if (!len[b]) continue;
             ET vre, vim;
             if (range_sum<Wp, true, ET>(h, key, t0[b], len[b], first[b], vre, vim))
-                on_hit.use(j[b], vre, vim, pre[b]);
+                hand_over(on_hit, j[b], t0[b], len[b], vre, vim, pre[b]);
         }
 #pragma unroll
         for (int b = 0; b < NB; ++b) {

@@ -7,6 +7,7 @@
 #include "common.h"
 #include "device.h"
 #include "engine.h"
+#include "hits.h"
 #include "matvec.h"
 #include "product.h"
 #include "rowsort.h"
@@ -178,6 +179,7 @@ void free_ham(qsd_ham *h) {
     dev_free(h->diag32);
     dev_free(h->diag32_im);
     dev_free(h->rowbits);
+    hits_free(h->hits);
     prod_free(h->prod);
     delete h;
 }
@@ -370,6 +372,8 @@ extern "C" int qsd_matvec(const qsd_ham *h, int32_t nvec, const void *d_x, int64
         QSD_CHECK_HIP(hipGetLastError());
         return QSD_OK;
     }
+    if (h->hits && (h->schedule & QSD_SCHED_SLOT_ORDER) && !(h->schedule & QSD_SCHED_HASH_LOOKUP))
+        return hits_matvec(h, h->hits, nvec, d_x, ldx, d_y, ldy, dtype, st);
     const int chunk = (dtype == QSD_C128 || dtype == QSD_C64) ? 4 : 16;
     const size_t esz = dtype == QSD_F64 ? 8 : dtype == QSD_F32 ? 4 : dtype == QSD_C128 ? 16 : 8;
     for (int v0 = 0; v0 < nvec; v0 += chunk) {
@@ -542,9 +546,12 @@ extern "C" int qsd_ham_diag_splitting(const qsd_ham *h, double *lowest, double *
 namespace qsd {
 namespace {
 
-// The per-row bits that the slot-order schedules split the SpMV by (built once per operator).
+// The per-row bits that the slot-order schedules split the SpMV by (built once per operator), and
+// the element list of a sparse operator, which runs instead of them.
 int ensure_rowbits(qsd_ham *h, hipStream_t st) {
-    if (h->rowbits || h->N == 0) return QSD_OK;
+    if (h->rowbits || h->hits || h->N == 0) return QSD_OK;
+    QSD_TRY(hits_build(h, &h->hits, st));
+    if (h->hits) return hipStreamSynchronize(st) == hipSuccess ? QSD_OK : fail(QSD_ERR_HIP, "element list failed");
     uint64_t *bits = nullptr;
     QSD_TRY(dev_alloc(&bits, (size_t)((h->N + 63) / 64)));
     const unsigned g = grid_for(h->N, kBlock);
@@ -570,7 +577,7 @@ extern "C" int qsd_ham_set_schedule(qsd_ham *h, uint32_t schedule) {
     clear_error();
     if (!h) return fail(QSD_ERR_INVALID_ARG, "NULL handle");
     if (schedule & ~kSchedBits) return fail(QSD_ERR_INVALID_ARG, "unknown schedule bits 0x%x", schedule);
-    if ((schedule & QSD_SCHED_SLOT_ORDER) && !h->rowbits) {
+    if ((schedule & QSD_SCHED_SLOT_ORDER) && !h->rowbits && !h->hits) {
         // no caller stream here: wait for all work on the device (the tables may still be
         // being written on another stream), then build on the default stream
         if (hipDeviceSynchronize() != hipSuccess) return fail(QSD_ERR_HIP, "device synchronize failed");

@@ -1,0 +1,300 @@
+// Element lists of sparse operators and the SpMV that runs from them (see hits.h).
+#include "hits.h"
+
+#include <algorithm>
+#include <type_traits>
+
+#include "matvec.h"
+
+namespace qsd {
+namespace {
+
+constexpr int kSampleTiles = 256;
+
+inline unsigned tiles_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+
+// Off-diagonal elements of the rows of tile blockIdx.x * stride: their number per row (1 << 32 |
+// count for a row that has some; NULL: not kept), the row bits, and the total.
+template <int Wp>
+__global__ __launch_bounds__(kBlock) void k_hit_count(SubView s, HamView h, int64_t stride,
+                                                      int64_t *__restrict__ cnt, uint64_t *__restrict__ bits,
+                                                      unsigned long long *__restrict__ total) {
+    __shared__ ChunkLds<Wp> lds;
+    uint64_t key[Wp], hrow;
+    uint32_t prow;
+    bool valid;
+    const int64_t row0 = (int64_t)blockIdx.x * stride * kBlock;
+    const int64_t r = load_row<Wp>(s, row0, key, hrow, prow, valid);
+    uint32_t n = 0;
+    row_engine<Wp>(s, h, key, hrow, prow, valid, lds, sink<double>([&](int64_t, double, double, int) { ++n; }), nullptr,
+                   false, true);
+    if (!valid) n = 0;
+    if (valid && cnt) cnt[r] = n ? (int64_t)((1ull << 32) | n) : 0;
+    const uint64_t w = __ballot(n != 0u);
+    const int64_t word = (row0 >> 6) + (threadIdx.x >> 6);
+    if (bits && (threadIdx.x & 63) == 0 && word * 64 < s.N) bits[word] = w;
+    unsigned long long t = n;
+    for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
+    if ((threadIdx.x & 63) == 0 && t) atomicAdd(total, t);
+}
+
+// rows[i], ptr[i] of the rows with elements, from the scanned counts (rows << 32 | elements).
+__global__ __launch_bounds__(kBlock) void k_hit_rows(const int64_t *__restrict__ scan, int64_t N,
+                                                     uint32_t *__restrict__ rows, uint32_t *__restrict__ ptr) {
+    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r > N) return;
+    const uint64_t a = (uint64_t)scan[r];
+    if (r == N) {
+        ptr[a >> 32] = (uint32_t)a;
+    } else if ((uint64_t)scan[r + 1] != a) {
+        rows[a >> 32] = (uint32_t)r;
+        ptr[a >> 32] = (uint32_t)a;
+    }
+}
+
+template <int Wp>
+__global__ __launch_bounds__(kBlock) void k_hit_fill(SubView s, HamView h, const uint32_t *__restrict__ rows, int64_t M,
+                                                     const uint32_t *__restrict__ ptr, qsd_hit *__restrict__ rec) {
+    __shared__ ChunkLds<Wp> lds;
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool valid = i < M;
+    const int64_t r = rows[valid ? i : M - 1];
+    uint64_t key[Wp];
+#pragma unroll
+    for (int w = 0; w < Wp; ++w) key[w] = s.keys[(int64_t)w * s.N + r];
+    const uint64_t hrow = s.hkey[r];
+    const uint32_t prow = s.pfilt ? s.pkey[r] : 0u;
+    uint32_t o = valid ? ptr[i] : 0u;
+    row_engine<Wp>(s, h, key, hrow, prow, valid, lds, range_sink<double>([&](int64_t j, uint32_t t0, uint32_t len) {
+        rec[o++] = qsd_hit{(uint32_t)j, t0, len, 0u};
+    }), nullptr, false, true);
+}
+
+// The first `nl` workgroups take the listed rows (a chain of dependent reads each, so they start
+// first), the others write y = d x, element by element in storage order (coalesced whatever the
+// number of vectors), for the rows without elements.  The listed rows' sums are formed as in every other path (d x first, then the elements in group
+// order), so the results are bitwise the same.  Bound by the stream of x, d and y: the list is a
+// few per cent of the rows on the workloads this serves.
+constexpr int kDiagItems = 4;
+
+template <int Wp, int NV, class ET, bool CPLX>
+__global__ __launch_bounds__(kBlock) void k_hits_matvec(SubView s, HamView h, qsd_hits p, const ET *__restrict__ dre,
+                                                        const ET *__restrict__ dim, const ET *__restrict__ x,
+                                                        int64_t ldx, ET *__restrict__ y, int64_t ldy, int nvec,
+                                                        unsigned nl) {
+    if (blockIdx.x >= nl) {
+        const int64_t n = s.N * nvec, e0 = (int64_t)(blockIdx.x - nl) * (kBlock * kDiagItems) + threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < kDiagItems; ++k) {
+            const int64_t e = e0 + k * kBlock;
+            if (e >= n) continue;
+            const int64_t r = nvec == NV ? e / NV : e / nvec;
+            const int64_t v = e - r * nvec;
+            if ((p.rowbits[r >> 6] >> (r & 63)) & 1ull) continue;
+            double re, im;
+            if (CPLX) {
+                diag_term<true>((double)dre[r], (double)dim[r], (double)x[2 * (r * ldx + v)],
+                                (double)x[2 * (r * ldx + v) + 1], re, im);
+                y[2 * (r * ldy + v)] = (ET)re;
+                y[2 * (r * ldy + v) + 1] = (ET)im;
+            } else {
+                diag_term<false>((double)dre[r], 0.0, (double)x[r * ldx + v], 0.0, re, im);
+                y[r * ldy + v] = (ET)re;
+            }
+        }
+        return;
+    }
+    // NV lanes per listed row, a vector each: x and y are read and written in whole lines
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t i = t / NV;
+    const int v = (int)(t % NV);
+    if (i >= p.M || v >= nvec) return;
+    const int64_t r = p.rows[i];
+    uint64_t key[Wp];
+#pragma unroll
+    for (int w = 0; w < Wp; ++w) key[w] = s.keys[(int64_t)w * s.N + r];
+    double are, aim = 0.0;
+    if (CPLX)
+        diag_term<true>((double)dre[r], (double)dim[r], (double)x[2 * (r * ldx + v)],
+                        (double)x[2 * (r * ldx + v) + 1], are, aim);
+    else
+        diag_term<false>((double)dre[r], 0.0, (double)x[r * ldx + v], 0.0, are, aim);
+    for (uint32_t e = p.ptr[i], end = p.ptr[i + 1]; e < end; ++e) {
+        const qsd_hit q = p.rec[e];
+        const int64_t j = q.col;
+        ET vre, vim;
+        if (CPLX) {
+            const double xr = (double)x[2 * (j * ldx + v)], xi = (double)x[2 * (j * ldx + v) + 1];
+            (void)range_value<Wp, ET>(h, key, q.t0, q.len, vre, vim);
+            are += (double)vre * xr - (double)vim * xi;
+            aim += (double)vre * xi + (double)vim * xr;
+        } else {
+            const double xj = (double)x[j * ldx + v];
+            (void)range_value<Wp, ET>(h, key, q.t0, q.len, vre, vim);
+            are += (double)vre * xj;
+        }
+    }
+    if (CPLX) {
+        y[2 * (r * ldy + v)] = (ET)are;
+        y[2 * (r * ldy + v) + 1] = (ET)aim;
+    } else {
+        y[r * ldy + v] = (ET)are;
+    }
+}
+
+__global__ void k_hit_zero(unsigned long long *p, int n) {
+    if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
+}
+
+template <int Wp>
+void count_launch(const qsd_ham *h, unsigned grid, int64_t stride, int64_t *cnt, uint64_t *bits,
+                  unsigned long long *total, hipStream_t st) {
+    k_hit_count<Wp><<<grid, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, false), stride, cnt, bits, total);
+}
+
+void count(const qsd_ham *h, unsigned grid, int64_t stride, int64_t *cnt, uint64_t *bits, unsigned long long *total,
+           hipStream_t st) {
+    switch (h->Wp) {
+        case 1: count_launch<1>(h, grid, stride, cnt, bits, total, st); break;
+        case 2: count_launch<2>(h, grid, stride, cnt, bits, total, st); break;
+        case 4: count_launch<4>(h, grid, stride, cnt, bits, total, st); break;
+        case 8: count_launch<8>(h, grid, stride, cnt, bits, total, st); break;
+        case 16: count_launch<16>(h, grid, stride, cnt, bits, total, st); break;
+    }
+}
+
+template <int Wp>
+void fill_launch(const qsd_ham *h, const qsd_hits *p, hipStream_t st) {
+    k_hit_fill<Wp><<<tiles_of(p->M), kBlock, 0, st>>>(sub_view(h->s), ham_view(h, false), p->rows, p->M, p->ptr, p->rec);
+}
+
+int build(const qsd_ham *h, qsd_hits *p, unsigned long long *total, int64_t *&cnt, hipStream_t st) {
+    const int64_t N = h->N, tiles = tiles_of(N);
+    unsigned long long t[2] = {0, 0};
+    // a sample first: operators with more elements than rows are left after a small part of a pass
+    k_hit_zero<<<1, 64, 0, st>>>(total, 2);
+    if (tiles > 2 * kSampleTiles) {
+        const int64_t stride = tiles / kSampleTiles;
+        count(h, kSampleTiles, stride, nullptr, nullptr, total + 1, st);
+        QSD_CHECK_HIP(hipMemcpyAsync(t, total, sizeof(t), hipMemcpyDeviceToHost, st));
+        QSD_CHECK_HIP(hipStreamSynchronize(st));
+        if (t[1] > (unsigned long long)kSampleTiles * kBlock) return QSD_OK;
+    }
+    QSD_TRY(dev_alloc(&cnt, N + 1));
+    QSD_TRY(dev_alloc(&p->rowbits, (size_t)((N + 63) / 64)));
+    count(h, (unsigned)tiles, 1, cnt, p->rowbits, total, st);
+    int64_t sum = 0;
+    QSD_TRY(exclusive_scan_i64(cnt, cnt, N + 1, st));  // (cnt[N] is read, and moves nothing)
+    QSD_CHECK_HIP(hipMemcpyAsync(t, total, 8, hipMemcpyDeviceToHost, st));
+    QSD_CHECK_HIP(hipMemcpyAsync(&sum, cnt + N, 8, hipMemcpyDeviceToHost, st));
+    QSD_CHECK_HIP(hipStreamSynchronize(st));
+    if (t[0] > (unsigned long long)N) return QSD_OK;
+    p->H = (int64_t)t[0];
+    p->M = sum >> 32;
+    QSD_TRY(dev_alloc(&p->rows, (size_t)p->M));
+    QSD_TRY(dev_alloc(&p->ptr, (size_t)p->M + 1));
+    QSD_TRY(dev_alloc(&p->rec, (size_t)p->H));
+    k_hit_rows<<<tiles_of(N + 1), kBlock, 0, st>>>(cnt, N, p->rows, p->ptr);
+    if (p->M > 0) {
+        switch (h->Wp) {
+            case 1: fill_launch<1>(h, p, st); break;
+            case 2: fill_launch<2>(h, p, st); break;
+            case 4: fill_launch<4>(h, p, st); break;
+            case 8: fill_launch<8>(h, p, st); break;
+            case 16: fill_launch<16>(h, p, st); break;
+        }
+    }
+    QSD_CHECK_HIP(hipGetLastError());
+    return QSD_OK;
+}
+
+template <int Wp, int NV, class ET, bool CPLX>
+void launch(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec,
+            hipStream_t st) {
+    constexpr bool f32 = std::is_same<ET, float>::value;
+    const ET *dre = f32 ? (const ET *)h->diag32 : (const ET *)h->diag;
+    const ET *dim = CPLX ? (f32 ? (const ET *)h->diag32_im : (const ET *)h->diag_im) : nullptr;
+    const unsigned nd = (unsigned)((h->N * nvec + kBlock * kDiagItems - 1) / (kBlock * kDiagItems));
+    const unsigned nl = tiles_of(p->M * NV);
+    k_hits_matvec<Wp, NV, ET, CPLX><<<nl + nd, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), *p, dre, dim,
+                                                               (const ET *)x, ldx, (ET *)y, ldy, nvec, nl);
+}
+
+template <int Wp, class ET, bool CPLX>
+void by_width(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec,
+              hipStream_t st) {
+    if (nvec <= 1)
+        launch<Wp, 1, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st);
+    else if (nvec <= 2)
+        launch<Wp, 2, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st);
+    else if (nvec <= 4 || CPLX)
+        launch<Wp, 4, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st);
+    else if (nvec <= 8)
+        launch<Wp, CPLX ? 4 : 8, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st);
+    else
+        launch<Wp, CPLX ? 4 : 16, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st);
+}
+
+template <class ET, bool CPLX>
+void by_key(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec,
+            hipStream_t st) {
+    switch (h->Wp) {
+        case 1: by_width<1, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
+        case 2: by_width<2, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
+        case 4: by_width<4, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
+        case 8: by_width<8, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
+        case 16: by_width<16, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
+    }
+}
+
+}  // namespace
+
+void hits_free(qsd_hits *&p) {
+    if (!p) return;
+    dev_free(p->rowbits);
+    dev_free(p->rows);
+    dev_free(p->ptr);
+    dev_free(p->rec);
+    delete p;
+    p = nullptr;
+}
+
+int hits_build(const qsd_ham *h, qsd_hits **out, hipStream_t st) {
+    *out = nullptr;
+    if (h->N == 0 || h->G == 0) return QSD_OK;
+    auto *p = new (std::nothrow) qsd_hits();
+    if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
+    unsigned long long *total = nullptr;
+    int64_t *cnt = nullptr;
+    int rc = dev_alloc(&total, 2);
+    if (rc == QSD_OK) rc = build(h, p, total, cnt, st);
+    dev_free(cnt);
+    dev_free(total);
+    if (rc != QSD_OK || !p->rec)
+        hits_free(p);
+    else
+        *out = p;
+    return rc;
+}
+
+int hits_matvec(const qsd_ham *h, const qsd_hits *p, int nvec, const void *x, int64_t ldx, void *y, int64_t ldy,
+                int32_t dtype, hipStream_t st) {
+    const bool cplx = dtype == QSD_C128 || dtype == QSD_C64;
+    const int chunk = cplx ? 4 : 16;
+    const size_t esz = dtype == QSD_F64 ? 8 : dtype == QSD_F32 ? 4 : dtype == QSD_C128 ? 16 : 8;
+    for (int v0 = 0; v0 < nvec; v0 += chunk) {
+        const int nv = std::min(chunk, nvec - v0);
+        const void *xv = (const char *)x + v0 * esz;
+        void *yv = (char *)y + v0 * esz;
+        switch (dtype) {
+            case QSD_F64: by_key<double, false>(h, p, xv, ldx, yv, ldy, nv, st); break;
+            case QSD_F32: by_key<float, false>(h, p, xv, ldx, yv, ldy, nv, st); break;
+            case QSD_C128: by_key<double, true>(h, p, xv, ldx, yv, ldy, nv, st); break;
+            case QSD_C64: by_key<float, true>(h, p, xv, ldx, yv, ldy, nv, st); break;
+        }
+    }
+    QSD_CHECK_HIP(hipGetLastError());
+    return QSD_OK;
+}
+
+}  // namespace qsd

@@ -15,12 +15,15 @@
 #include <vector>
 
 #include "common.h"
+#include "hits.h"
+#include "product.h"
 #include "tridiag.h"
 
 namespace qsd {
 namespace {
 
 constexpr int kRed = 256;       // threads of reduction kernels
+constexpr int kListIters = 24;  // iterations from which a solve makes its own element list
 constexpr int kDotBlocks = 512; // partial-sum blocks (fixed => deterministic sums)
 
 struct LzState {
@@ -440,7 +443,7 @@ extern "C" void qsd_lanczos_default_opts(qsd_lanczos_opts *o) {
 
 namespace {
 
-int lanczos_impl(const SpmvOp &op, const qsd_lanczos_opts *opts, double *eval_out, void *d_evec,
+int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void *d_evec,
                  qsd_lanczos_info *info, void *stream) {
     auto t_start = std::chrono::steady_clock::now();
     if (!eval_out) return fail(QSD_ERR_INVALID_ARG, "NULL argument");
@@ -487,6 +490,13 @@ int lanczos_impl(const SpmvOp &op, const qsd_lanczos_opts *opts, double *eval_ou
         return QSD_OK;
     };
     rc = alloc_all();
+    // a sparse operator is applied from the list of its elements: the operator's own, or one made
+    // for this solve (its cost is that of about three SpMVs)
+    qsd_hits *made = nullptr;
+    if (rc == QSD_OK && op.h && !prod_usable(op.h) && !(op.h->schedule & QSD_SCHED_HASH_LOOKUP)) {
+        if (!op.h->hits && S.m >= kListIters) rc = hits_build(op.h, &made, st);
+        op.hits = op.h->hits ? op.h->hits : made;
+    }
     if (rc != QSD_OK) {
         S.free_all();
         return rc;
@@ -621,6 +631,7 @@ int lanczos_impl(const SpmvOp &op, const qsd_lanczos_opts *opts, double *eval_ou
     if (graph) hipGraphDestroy(graph);
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);
+    hits_free(made);
     S.free_all();
     if (rc != QSD_OK) return rc;
     *eval_out = theta;
