@@ -12,11 +12,13 @@ struct qsd_hit {
 };
 
 struct qsd_hits {
-    int64_t M = 0, H = 0;         // rows with elements, elements
+    int64_t M = 0, H = 0, L = 0;  // rows with elements, elements, rows with many
     uint64_t *rowbits = nullptr;  // [ceil(N / 64)] bit r = row r has elements
     uint32_t *rows = nullptr;     // [M] ascending
     uint32_t *ptr = nullptr;      // [M + 1] first element of each listed row
+    uint32_t *lng = nullptr;      // [L] positions in `rows` of the rows with many elements, any order
     qsd_hit *rec = nullptr;       // [H] in group order within a row
+    uint8_t *mem = nullptr;       // rows, ptr, lng and rec lie in it
 };
 
 namespace qsd {

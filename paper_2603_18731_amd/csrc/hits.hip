@@ -10,6 +10,11 @@ namespace qsd {
 namespace {
 
 constexpr int kSampleTiles = 256;
+// Elements from which a row gets a wave of its own.  A lane walks its elements in a chain of
+// dependent reads, about a microsecond each: 156 rows of 18 to 39 elements (700 000 heavy-hex
+// strings) kept the launch going for 34 us, and 150 rows of 48 to 117 (3M strings, 8 vectors) for
+// 180; sharing such a row among the lanes of whichever wave held it took 41 and 121.
+constexpr uint32_t kLongRow = 8;
 
 inline unsigned tiles_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
@@ -35,12 +40,15 @@ __global__ __launch_bounds__(kBlock) void k_hit_count(SubView s, HamView h, int6
     if (bits && (threadIdx.x & 63) == 0 && word * 64 < s.N) bits[word] = w;
     unsigned long long t = n;
     for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
+    const uint64_t lng = __ballot(n > kLongRow);
     if ((threadIdx.x & 63) == 0 && t) atomicAdd(total, t);
+    if (cnt && (threadIdx.x & 63) == 0 && lng) atomicAdd(total + 2, (unsigned long long)__popcll(lng));
 }
 
 // rows[i], ptr[i] of the rows with elements, from the scanned counts (rows << 32 | elements).
 __global__ __launch_bounds__(kBlock) void k_hit_rows(const int64_t *__restrict__ scan, int64_t N,
-                                                     uint32_t *__restrict__ rows, uint32_t *__restrict__ ptr) {
+                                                     uint32_t *__restrict__ rows, uint32_t *__restrict__ ptr,
+                                                     uint32_t *__restrict__ lng, unsigned long long *__restrict__ nlng) {
     const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (r > N) return;
     const uint64_t a = (uint64_t)scan[r];
@@ -49,6 +57,7 @@ __global__ __launch_bounds__(kBlock) void k_hit_rows(const int64_t *__restrict__
     } else if ((uint64_t)scan[r + 1] != a) {
         rows[a >> 32] = (uint32_t)r;
         ptr[a >> 32] = (uint32_t)a;
+        if ((uint32_t)scan[r + 1] - (uint32_t)a > kLongRow) lng[atomicAdd(nlng, 1ull)] = (uint32_t)(a >> 32);
     }
 }
 
@@ -70,8 +79,8 @@ __global__ __launch_bounds__(kBlock) void k_hit_fill(SubView s, HamView h, const
     }), nullptr, false, true);
 }
 
-// The first `nl` workgroups take the listed rows (a chain of dependent reads each, so they start
-// first), the others write y = d x, element by element in storage order (coalesced whatever the
+// The first `nl` workgroups take the listed rows (chains of dependent reads, so they start first,
+// the longest rows before the rest), the others write y = d x, element by element in storage order (coalesced whatever the
 // number of vectors), for the rows without elements.  The listed rows' sums are formed as in every other path (d x first, then the elements in group
 // order), so the results are bitwise the same.  Bound by the stream of x, d and y: the list is a
 // few per cent of the rows on the workloads this serves.
@@ -104,35 +113,89 @@ __global__ __launch_bounds__(kBlock) void k_hits_matvec(SubView s, HamView h, qs
         }
         return;
     }
-    // NV lanes per listed row, a vector each: x and y are read and written in whole lines
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t i = t / NV;
-    const int v = (int)(t % NV);
-    if (i >= p.M || v >= nvec) return;
-    const int64_t r = p.rows[i];
+    const int lane = threadIdx.x & 63;
+    auto load_x = [&](int64_t j, int64_t u, double &xr, double &xi) {
+        if (CPLX) {
+            xr = (double)x[2 * (j * ldx + u)];
+            xi = (double)x[2 * (j * ldx + u) + 1];
+        } else {
+            xr = (double)x[j * ldx + u];
+            xi = 0.0;
+        }
+    };
+    // a row with many elements has a wave of its own, another NV lanes, a vector each (x and y are
+    // read and written in whole lines)
+    const unsigned nw = (unsigned)((p.L + kBlock / 64 - 1) / (kBlock / 64));
+    const bool own = blockIdx.x < nw;
+    int64_t i, ic;  // position in the list, and one that is always valid
+    if (own) {
+        i = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+        if (i >= p.L) return;  // whole waves
+        i = ic = p.lng[i];
+    } else {
+        i = ((int64_t)(blockIdx.x - nw) * kBlock + threadIdx.x) / NV;
+        ic = i < p.M ? i : p.M - 1;
+    }
+    const int v = lane % NV, vc = v < nvec ? v : 0;
+    const int64_t r = p.rows[ic];
     uint64_t key[Wp];
 #pragma unroll
     for (int w = 0; w < Wp; ++w) key[w] = s.keys[(int64_t)w * s.N + r];
-    double are, aim = 0.0;
-    if (CPLX)
-        diag_term<true>((double)dre[r], (double)dim[r], (double)x[2 * (r * ldx + v)],
-                        (double)x[2 * (r * ldx + v) + 1], are, aim);
-    else
-        diag_term<false>((double)dre[r], 0.0, (double)x[r * ldx + v], 0.0, are, aim);
-    for (uint32_t e = p.ptr[i], end = p.ptr[i + 1]; e < end; ++e) {
-        const qsd_hit q = p.rec[e];
-        const int64_t j = q.col;
-        ET vre, vim;
+    double are, aim = 0.0, x0r, x0i;
+    load_x(r, vc, x0r, x0i);
+    diag_term<CPLX>((double)dre[r], CPLX ? (double)dim[r] : 0.0, x0r, x0i, are, aim);
+    auto add = [&](ET vre, ET vim, double xr, double xi) {
         if (CPLX) {
-            const double xr = (double)x[2 * (j * ldx + v)], xi = (double)x[2 * (j * ldx + v) + 1];
-            (void)range_value<Wp, ET>(h, key, q.t0, q.len, vre, vim);
             are += (double)vre * xr - (double)vim * xi;
             aim += (double)vre * xi + (double)vim * xr;
         } else {
-            const double xj = (double)x[j * ldx + v];
-            (void)range_value<Wp, ET>(h, key, q.t0, q.len, vre, vim);
-            are += (double)vre * xj;
+            are += (double)vre * xr;
         }
+    };
+    uint32_t e = p.ptr[ic];
+    const uint32_t end = p.ptr[ic + 1];
+    if (!own) {
+        if (i >= p.M || v >= nvec || end - e > kLongRow) return;
+        // two elements at a time, their records and x before either is evaluated
+        for (; e < end; e += 2u) {
+            qsd_hit q[2];
+            double xr[2], xi[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) q[k] = p.rec[min(e + k, end - 1u)];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) load_x(q[k].col, vc, xr[k], xi[k]);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                if (e + k >= end) continue;
+                ET vre, vim;
+                (void)range_value<Wp, ET>(h, key, q[k].t0, q[k].len, vre, vim);
+                add(vre, vim, xr[k], xi[k]);
+            }
+        }
+    } else {
+        // 64 elements are evaluated, a lane each; then 64 / NV at a time have their x fetched and
+        // every group of NV lanes adds the products in order
+        for (; e < end; e += 64u) {
+            const uint32_t n = min(64u, end - e);
+            const qsd_hit q = p.rec[min(e + (uint32_t)lane, end - 1u)];
+            ET vre, vim;
+            (void)range_value<Wp, ET>(h, key, q.t0, q.len, vre, vim);
+            // (one step's x in registers: eight steps' cost the streaming workgroups their occupancy)
+#pragma unroll 1
+            for (uint32_t c = 0; c < n; c += 64u / NV) {
+                double xr, xi;
+                load_x((uint32_t)__shfl((int)q.col, (int)min(c + (uint32_t)lane / NV, n - 1u), 64), vc, xr, xi);
+                const uint32_t m = min(64u / NV, n - c);
+                for (uint32_t k = 0; k < m; ++k) {
+                    const ET a = (ET)__shfl(vre, (int)(c + k), 64);
+                    const ET ai = CPLX ? (ET)__shfl(vim, (int)(c + k), 64) : (ET)0;
+                    const double br = __shfl(xr, (int)k * NV + v, 64);
+                    const double bi = CPLX ? __shfl(xi, (int)k * NV + v, 64) : 0.0;
+                    add(a, ai, br, bi);
+                }
+            }
+        }
+        if (lane >= NV || v >= nvec) return;
     }
     if (CPLX) {
         y[2 * (r * ldy + v)] = (ET)are;
@@ -168,11 +231,15 @@ void fill_launch(const qsd_ham *h, const qsd_hits *p, hipStream_t st) {
     k_hit_fill<Wp><<<tiles_of(p->M), kBlock, 0, st>>>(sub_view(h->s), ham_view(h, false), p->rows, p->M, p->ptr, p->rec);
 }
 
-int build(const qsd_ham *h, qsd_hits *p, unsigned long long *total, int64_t *&cnt, hipStream_t st) {
+int build(const qsd_ham *h, qsd_hits *p, int64_t *&scratch, hipStream_t st) {
     const int64_t N = h->N, tiles = tiles_of(N);
-    unsigned long long t[2] = {0, 0};
+    unsigned long long t[3] = {0, 0, 0};
+    // totals, then the rows' counts
+    QSD_TRY(dev_alloc(&scratch, 4 + N + 1));
+    auto *total = (unsigned long long *)scratch;
+    int64_t *cnt = scratch + 4;
     // a sample first: operators with more elements than rows are left after a small part of a pass
-    k_hit_zero<<<1, 64, 0, st>>>(total, 2);
+    k_hit_zero<<<1, 64, 0, st>>>(total, 4);
     if (tiles > 2 * kSampleTiles) {
         const int64_t stride = tiles / kSampleTiles;
         count(h, kSampleTiles, stride, nullptr, nullptr, total + 1, st);
@@ -180,21 +247,25 @@ int build(const qsd_ham *h, qsd_hits *p, unsigned long long *total, int64_t *&cn
         QSD_CHECK_HIP(hipStreamSynchronize(st));
         if (t[1] > (unsigned long long)kSampleTiles * kBlock) return QSD_OK;
     }
-    QSD_TRY(dev_alloc(&cnt, N + 1));
     QSD_TRY(dev_alloc(&p->rowbits, (size_t)((N + 63) / 64)));
     count(h, (unsigned)tiles, 1, cnt, p->rowbits, total, st);
     int64_t sum = 0;
     QSD_TRY(exclusive_scan_i64(cnt, cnt, N + 1, st));  // (cnt[N] is read, and moves nothing)
-    QSD_CHECK_HIP(hipMemcpyAsync(t, total, 8, hipMemcpyDeviceToHost, st));
+    QSD_CHECK_HIP(hipMemcpyAsync(t, total, sizeof(t), hipMemcpyDeviceToHost, st));
     QSD_CHECK_HIP(hipMemcpyAsync(&sum, cnt + N, 8, hipMemcpyDeviceToHost, st));
     QSD_CHECK_HIP(hipStreamSynchronize(st));
     if (t[0] > (unsigned long long)N) return QSD_OK;
     p->H = (int64_t)t[0];
     p->M = sum >> 32;
-    QSD_TRY(dev_alloc(&p->rows, (size_t)p->M));
-    QSD_TRY(dev_alloc(&p->ptr, (size_t)p->M + 1));
-    QSD_TRY(dev_alloc(&p->rec, (size_t)p->H));
-    k_hit_rows<<<tiles_of(N + 1), kBlock, 0, st>>>(cnt, N, p->rows, p->ptr);
+    p->L = (int64_t)t[2];
+    auto up = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t at1 = up(p->H * sizeof(qsd_hit)), at2 = at1 + up(p->M * 4), at3 = at2 + up((p->M + 1) * 4);
+    QSD_TRY(dev_alloc(&p->mem, at3 + p->L * 4));
+    p->rec = (qsd_hit *)p->mem;
+    p->rows = (uint32_t *)(p->mem + at1);
+    p->ptr = (uint32_t *)(p->mem + at2);
+    p->lng = (uint32_t *)(p->mem + at3);
+    k_hit_rows<<<tiles_of(N + 1), kBlock, 0, st>>>(cnt, N, p->rows, p->ptr, p->lng, total + 3);
     if (p->M > 0) {
         switch (h->Wp) {
             case 1: fill_launch<1>(h, p, st); break;
@@ -215,7 +286,7 @@ void launch(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, voi
     const ET *dre = f32 ? (const ET *)h->diag32 : (const ET *)h->diag;
     const ET *dim = CPLX ? (f32 ? (const ET *)h->diag32_im : (const ET *)h->diag_im) : nullptr;
     const unsigned nd = (unsigned)((h->N * nvec + kBlock * kDiagItems - 1) / (kBlock * kDiagItems));
-    const unsigned nl = tiles_of(p->M * NV);
+    const unsigned nl = (unsigned)((p->L + kBlock / 64 - 1) / (kBlock / 64)) + tiles_of(p->M * NV);
     k_hits_matvec<Wp, NV, ET, CPLX><<<nl + nd, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), *p, dre, dim,
                                                                (const ET *)x, ldx, (ET *)y, ldy, nvec, nl);
 }
@@ -252,9 +323,7 @@ void by_key(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, voi
 void hits_free(qsd_hits *&p) {
     if (!p) return;
     dev_free(p->rowbits);
-    dev_free(p->rows);
-    dev_free(p->ptr);
-    dev_free(p->rec);
+    dev_free(p->mem);
     delete p;
     p = nullptr;
 }
@@ -264,13 +333,10 @@ int hits_build(const qsd_ham *h, qsd_hits **out, hipStream_t st) {
     if (h->N == 0 || h->G == 0) return QSD_OK;
     auto *p = new (std::nothrow) qsd_hits();
     if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
-    unsigned long long *total = nullptr;
-    int64_t *cnt = nullptr;
-    int rc = dev_alloc(&total, 2);
-    if (rc == QSD_OK) rc = build(h, p, total, cnt, st);
-    dev_free(cnt);
-    dev_free(total);
-    if (rc != QSD_OK || !p->rec)
+    int64_t *scratch = nullptr;
+    const int rc = build(h, p, scratch, st);
+    dev_free(scratch);
+    if (rc != QSD_OK || !p->mem)
         hits_free(p);
     else
         *out = p;

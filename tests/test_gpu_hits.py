@@ -37,6 +37,20 @@ def _chain_keys(n, pairs):
     return np.concatenate([a[: max(1, n - pairs)], b]).reshape(-1, 1)
 
 
+def _star_keys(n, others):
+    """A string, its ``n`` single flips, and ``others`` far from them and from each other."""
+    rng = np.random.default_rng(n)
+    ref = int(rng.integers(1, 1 << 50))
+    vals = [ref] + [ref ^ (1 << q) for q in range(n)]
+    # a parity that single flips change keeps these apart: even weight, none within one flip
+    while len(vals) < n + 1 + others:
+        v = int(rng.integers(0, 1 << 62)) | (int(rng.integers(0, 1 << 36)) << 62 if n > 62 else 0)
+        v &= (1 << n) - 1
+        if bin(v ^ ref).count("1") % 2 == 0:
+            vals.append(v)
+    return wl.ints_to_keys(sorted(set(vals)), n)
+
+
 # no element at all, one row in few, at most N elements, and more (the row engine): sizes around
 # the tile of 256 rows and past the 512 tiles from which a sample is counted first
 CASES = {
@@ -44,6 +58,9 @@ CASES = {
     "few": (lambda: (_chain_keys(511, 40), wl.xxz_terms(40, [(0, 1), (7, 31)], 1.0, 0.5))),
     "edge": (lambda: (_chain_keys(257, 120), wl.xxz_terms(40, [(0, 1)], 1.0, 0.5))),
     "sampled": (lambda: (_chain_keys(140_000, 30_000), wl.xxz_terms(40, [(0, 1)], 1.0, 0.5))),
+    # rows of up to 60 and 100 elements among rows of one (a wave of their own beyond eight)
+    "long_rows": (lambda: (_star_keys(60, 3_000), wl.tfim_chain(60))),
+    "longer_rows": (lambda: (_star_keys(100, 9_000), wl.tfim_chain(100))),
     "wide": (lambda: heavy_hex_small(4_000)[::-1]),
     "dense": (lambda: (wl.full_space(9), wl.xxz_terms(9, [(q, q + 1) for q in range(8)], 1.0, 0.5))),
     "one_row": (lambda: (c2_keys(1), wl.xxz_grid_6x6())),
