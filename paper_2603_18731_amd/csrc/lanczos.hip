@@ -1,9 +1,9 @@
 // Ground-state Lanczos on the device (FP64 basis and recurrence, full reorthogonalization).
 //
 // The paper hands its SpMV operator to external eigensolvers; this solver keeps the whole
-// iteration on the GPU.  Every buffer has a fixed address and the iteration number lives in
-// device memory, so one iteration is a fixed kernel sequence that can be captured once in a
-// HIP graph and replayed:
+// iteration on the GPU.  The iteration number comes with the launches; for graph replay it lives in
+// device memory and every buffer has a fixed address, so that one iteration, a fixed kernel
+// sequence, can be captured once and replayed:
 //   w = H x                       (SpMV, FP64 or FP32 elements with FP64 accumulation)
 //   h = V^T w; w -= V h  (twice)  (classical Gram-Schmidt applied twice against v_0..v_k)
 //   alpha_k = sum of the two h_k; beta_k = ||w||; v_{k+1} = x = w / beta_k
@@ -24,37 +24,34 @@ namespace {
 
 constexpr int kRed = 256;       // threads of reduction kernels
 constexpr int kListIters = 24;  // iterations from which a solve makes its own element list
-constexpr int kDotBlocks = 512; // partial-sum blocks (fixed => deterministic sums)
+constexpr int kPartRows = 256;  // rows per partial sum of the projections, at most kMaxParts of them
+constexpr int kMaxParts = 512;  // (fixed by N alone => deterministic sums)
+constexpr int kInlineParts = 16;   // partial sums per projection that the update kernel adds itself
+constexpr int kNextRows = 4;       // rows per thread of the normalization
+constexpr int kNormParts = 4096;   // partial squared norms that the normalization adds itself
 
 struct LzState {
     int64_t N = 0;           // rows
     int64_t NR = 0;          // doubles per vector: N (real) or 2N (complex, interleaved)
     bool cplx = false;
     int m = 0;               // max iterations
+    int parts = 0;           // partial sums per projection
+    int64_t sqn = 0;         // partial squared norms (256-row tiles)
+    uint8_t *mem = nullptr;  // every array below lies in it
     double *V = nullptr;     // [m+1][N]
-    double *x = nullptr;     // [N] current basis vector
+    double *x = nullptr;     // [N] current basis vector (graph replay, which needs a fixed address)
     double *w = nullptr;     // [N]
     float *x32 = nullptr;    // [N]
     float *w32 = nullptr;    // [N]
-    double *part = nullptr;  // [(m+1) * kDotBlocks]
+    double *part = nullptr;  // [(m+1) * parts] (two planes for complex)
+    double *sq = nullptr;    // [max(sqn, kMaxParts)]
     double *hv = nullptr;    // [m+1]
     double *alpha = nullptr; // [m]
     double *beta = nullptr;  // [m]
-    int *kdev = nullptr;     // iteration number
+    int *kdev = nullptr;     // iteration number (graph replay)
     double *tri = nullptr;   // [m + 4]: theta, resid, breakdown flag, s[0..m)
-    void free_all() {
-        dev_free(V);
-        dev_free(x);
-        dev_free(w);
-        dev_free(x32);
-        dev_free(w32);
-        dev_free(part);
-        dev_free(hv);
-        dev_free(alpha);
-        dev_free(beta);
-        dev_free(kdev);
-        dev_free(tri);
-    }
+    int64_t *spike = nullptr;
+    void free_all() { dev_free(mem); }
 };
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -63,160 +60,183 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// partial[j][b] = sum over the rows of chunk b of V[j][i] * w[i], j = 0..k (k = *kdev).
-// blockIdx.y selects kGemvJ basis vectors: each thread reads w[i] once and kGemvJ basis values,
-// so the basis streams at full occupancy; block sums by a fixed tree (deterministic).
-constexpr int kGemvJ = 8;
-
-__global__ __launch_bounds__(kRed) void k_gemv_t(const double *__restrict__ V, const double *__restrict__ w, int64_t N,
-                                                 const int *__restrict__ kdev, int extra, double *__restrict__ part) {
-    __shared__ double red[kGemvJ][kRed / 64];
-    const int cnt = *kdev + 1 + extra;
-    const int j0 = blockIdx.y * kGemvJ;
-    if (j0 >= cnt) return;
-    const int nj = min(kGemvJ, cnt - j0);
-    const int64_t chunk = (N + gridDim.x - 1) / gridDim.x;
-    const int64_t a = (int64_t)blockIdx.x * chunk;
-    const int64_t b = min(N, a + chunk);
-    double acc[kGemvJ];
-#pragma unroll
-    for (int q = 0; q < kGemvJ; ++q) acc[q] = 0.0;
-    const double *v0 = V + (int64_t)j0 * N;
-    for (int64_t i = a + threadIdx.x; i < b; i += kRed) {
-        const double wi = w[i];
-#pragma unroll
-        for (int q = 0; q < kGemvJ; ++q)
-            if (q < nj) acc[q] += v0[(int64_t)q * N + i] * wi;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int q = 0; q < kGemvJ; ++q) {
-        const double s = wave_sum(acc[q]);
-        if (lane == 0) red[q][wave] = s;
-    }
+// Sum of v over the workgroup (kRed threads), by a fixed tree, in every thread.
+__device__ __forceinline__ double block_sum(double v, double *ws) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (threadIdx.x < nj) {
-        double t = 0.0;
-        for (int q = 0; q < kRed / 64; ++q) t += red[threadIdx.x][q];
-        part[(int64_t)(j0 + threadIdx.x) * gridDim.x + blockIdx.x] = t;
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kRed / 64; ++q) t += ws[q];
+    __syncthreads();
+    return t;
+}
+
+// Sums of 16 values over a wave: on return the lane holds the sum of value (lane >> 2).  Each of
+// the first four steps halves the values a lane carries (15 exchanges and additions, then 2),
+// where 16 separate trees take 96 of each: 6.8 us of a 4096-row launch were mostly these.
+template <int Q>
+__device__ __forceinline__ double wave_sum_q(double (&a)[Q], int lane) {
+    if constexpr (Q == 1) {
+        a[0] += __shfl_xor(a[0], 2, 64);
+        a[0] += __shfl_xor(a[0], 1, 64);
+        return a[0];
+    } else {
+        const bool up = (lane & (2 * Q)) != 0;  // Q = 16 splits by lane bit 5, .., Q = 2 by bit 2
+        double b[Q / 2];
+#pragma unroll
+        for (int q = 0; q < Q / 2; ++q) {
+            const double keep = up ? a[q + Q / 2] : a[q], send = up ? a[q] : a[q + Q / 2];
+            b[q] = keep + __shfl_xor(send, 2 * Q, 64);
+        }
+        return wave_sum_q(b, lane);
     }
 }
 
-// Complex (Hermitian) variant: part[j][b] and part[P + j][b] (P = plane stride) are the real
-// and imaginary parts of sum over chunk b of conj(V[j][i]) w[i], vectors interleaved (re, im).
-__global__ __launch_bounds__(kRed) void k_gemv_t_c(const double2 *__restrict__ V, const double2 *__restrict__ w,
-                                                   int64_t N, const int *__restrict__ kdev, int64_t plane,
-                                                   double *__restrict__ part) {
-    __shared__ double red[2 * kGemvJ][kRed / 64];
-    const int cnt = *kdev + 1;
-    const int j0 = blockIdx.y * kGemvJ;
+// The iteration number: the launch's, or the device counter's under graph replay.
+__device__ __forceinline__ int iter_of(const int *kdev, int k) { return kdev ? *kdev : k; }
+
+// part[j][b] = sum over the rows of chunk b of V[j][i] * w[i], j = 0..k; complex (Hermitian)
+// vectors: the real and imaginary parts of sum conj(V[j][i]) w[i] in two planes.
+// blockIdx.x selects kGemvJ basis vectors: each thread reads w[i] once and kGemvJ basis values,
+// so the basis streams at full occupancy; block sums by a fixed tree (deterministic).  Row
+// chunks ascend with blockIdx.y; the update kernel walks the rows downwards, so each pass over the
+// basis starts with what the pass before read last (a basis of up to 256 MB is served from the
+// memory-side cache).
+constexpr int kGemvJ = 16;
+
+template <bool C>
+__global__ __launch_bounds__(kRed) void k_gemv_t(const double *__restrict__ V, const double *__restrict__ w, int64_t N,
+                                                 const int *__restrict__ kdev, int karg, int64_t plane,
+                                                 double *__restrict__ part) {
+    constexpr int P = C ? 2 : 1;
+    __shared__ double red[P * kGemvJ][kRed / 64];
+    const int cnt = iter_of(kdev, karg) + 1;
+    const int j0 = blockIdx.x * kGemvJ;
     if (j0 >= cnt) return;
     const int nj = min(kGemvJ, cnt - j0);
-    const int64_t chunk = (N + gridDim.x - 1) / gridDim.x;
-    const int64_t a = (int64_t)blockIdx.x * chunk;
+    const int64_t chunk = (N + gridDim.y - 1) / gridDim.y;
+    const int64_t a = (int64_t)blockIdx.y * chunk;
     const int64_t b = min(N, a + chunk);
-    double are[kGemvJ], aim[kGemvJ];
+    double acc[P][kGemvJ];
 #pragma unroll
-    for (int q = 0; q < kGemvJ; ++q) are[q] = aim[q] = 0.0;
-    const double2 *v0 = V + (int64_t)j0 * N;
+    for (int q = 0; q < kGemvJ; ++q) acc[0][q] = acc[P - 1][q] = 0.0;
     for (int64_t i = a + threadIdx.x; i < b; i += kRed) {
-        const double2 wi = w[i];
+        if constexpr (C) {
+            const double2 *v0 = (const double2 *)V + (int64_t)j0 * N;
+            const double2 wi = ((const double2 *)w)[i];
 #pragma unroll
-        for (int q = 0; q < kGemvJ; ++q)
-            if (q < nj) {
-                const double2 v = v0[(int64_t)q * N + i];
-                are[q] += v.x * wi.x + v.y * wi.y;
-                aim[q] += v.x * wi.y - v.y * wi.x;
-            }
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+            for (int q = 0; q < kGemvJ; ++q)
+                if (q < nj) {
+                    const double2 v = v0[(int64_t)q * N + i];
+                    acc[0][q] += v.x * wi.x + v.y * wi.y;
+                    acc[1][q] += v.x * wi.y - v.y * wi.x;
+                }
+        } else {
+            // (past the last vector the loads repeat it and the sums are dropped: no branch keeps
+            // them apart)
+            const double *v0 = V + (int64_t)j0 * N + i;
+            const double wi = w[i];
 #pragma unroll
-    for (int q = 0; q < kGemvJ; ++q) {
-        const double sr = wave_sum(are[q]), si = wave_sum(aim[q]);
-        if (lane == 0) {
-            red[2 * q][wave] = sr;
-            red[2 * q + 1][wave] = si;
+            for (int q = 0; q < kGemvJ; ++q) acc[0][q] += v0[(int64_t)min(q, nj - 1) * N] * wi;
         }
     }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(kGemvJ == 16, "wave_sum_q leaves value lane >> 2 in a lane");
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+        const double s = wave_sum_q(acc[c], lane);
+        if ((lane & 3) == 0) red[P * (lane >> 2) + c][wave] = s;
+    }
     __syncthreads();
-    if (threadIdx.x < 2 * nj) {
+    if ((int)threadIdx.x < P * nj) {
         double t = 0.0;
+#pragma unroll
         for (int q = 0; q < kRed / 64; ++q) t += red[threadIdx.x][q];
-        const int jj = threadIdx.x >> 1;
-        part[(threadIdx.x & 1) * plane + (int64_t)(j0 + jj) * gridDim.x + blockIdx.x] = t;
+        const int jj = threadIdx.x / P;
+        part[(threadIdx.x % P) * plane + (int64_t)(j0 + jj) * gridDim.y + blockIdx.y] = t;
     }
 }
 
-// w[i] -= sum_{j<=k} V[j][i] h[j] for complex vectors and coefficients (h interleaved)
-__global__ __launch_bounds__(kRed) void k_gemv_n_sub_c(const double2 *__restrict__ V, const double *__restrict__ hv,
-                                                       int64_t N, const int *__restrict__ kdev,
-                                                       double2 *__restrict__ w) {
-    __shared__ double sh[2 * 512];
-    const int cnt = *kdev + 1;
-    const int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x;
+// hv[j] = sum_b part[j][b] (one block per j and plane, fixed tree; planes interleaved in hv).
+template <bool C>
+__global__ __launch_bounds__(kRed) void k_reduce_parts(const double *__restrict__ part, int nparts,
+                                                       const int *__restrict__ kdev, int karg, int64_t plane,
+                                                       double *__restrict__ hv) {
+    __shared__ double ws[kRed / 64];
+    const int j = blockIdx.x, im = blockIdx.y;
+    if (j > iter_of(kdev, karg)) return;
+    double s = 0.0;
+    const double *pp = part + im * plane + (int64_t)j * nparts;
+    for (int p = threadIdx.x; p < nparts; p += kRed) s += pp[p];
+    s = block_sum(s, ws);
+    if (threadIdx.x == 0) hv[(C ? 2 : 1) * j + im] = s;
+}
+
+// w[i] -= sum_{j<=k} V[j][i] h[j], and alpha[k] += Re h[k] (one block).  h is hv, or with
+// nparts > 0 the sum of the few partial sums, which saves the reduction's launch.  With `sq` each
+// block also leaves its rows' squared norm there.  Rows descend with blockIdx.x.
+template <bool C>
+__global__ __launch_bounds__(kRed) void k_update(const double *__restrict__ V, const double *__restrict__ hv,
+                                                 const double *__restrict__ part, int nparts, int64_t plane, int64_t N,
+                                                 const int *__restrict__ kdev, int karg, double *__restrict__ w,
+                                                 double *__restrict__ alpha, double *__restrict__ sq) {
+    constexpr int P = C ? 2 : 1;
+    __shared__ double sh[P * 512];
+    __shared__ double ws[kRed / 64];
+    const int k = iter_of(kdev, karg), cnt = k + 1;
+    const int64_t i = (int64_t)(gridDim.x - 1 - blockIdx.x) * kRed + threadIdx.x;
     double ar = 0.0, ai = 0.0;
     for (int j0 = 0; j0 < cnt; j0 += 512) {
         const int nj = min(512, cnt - j0);
         __syncthreads();
-        for (int q = threadIdx.x; q < 2 * nj; q += kRed) sh[q] = hv[2 * j0 + q];
-        __syncthreads();
-        if (i < N)
-            for (int q = 0; q < nj; ++q) {
-                const double2 v = V[(int64_t)(j0 + q) * N + i];
-                const double hr = sh[2 * q], hi = sh[2 * q + 1];
-                ar += v.x * hr - v.y * hi;
-                ai += v.x * hi + v.y * hr;
+        for (int q = threadIdx.x; q < P * nj; q += kRed) {
+            double h;
+            if (nparts > 0) {
+                const double *pp = part + (q % P) * plane + (int64_t)(j0 + q / P) * nparts;
+                h = 0.0;
+#pragma unroll 8
+                for (int p = 0; p < nparts; ++p) h += pp[p];
+            } else {
+                h = hv[P * j0 + q];
             }
+            sh[q] = h;
+            if (blockIdx.x == 0 && P * j0 + q == P * k) alpha[k] += h;
+        }
+        __syncthreads();
+        if (i < N) {
+            if constexpr (C) {
+                for (int q = 0; q < nj; ++q) {
+                    const double2 v = ((const double2 *)V)[(int64_t)(j0 + q) * N + i];
+                    const double hr = sh[2 * q], hi = sh[2 * q + 1];
+                    ar += v.x * hr - v.y * hi;
+                    ai += v.x * hi + v.y * hr;
+                }
+            } else {
+                const double *v0 = V + (int64_t)j0 * N + i;
+#pragma unroll 8
+                for (int q = 0; q < nj; ++q) ar += v0[(int64_t)q * N] * sh[q];
+            }
+        }
     }
+    double n2 = 0.0;
     if (i < N) {
-        double2 t = w[i];
-        t.x -= ar;
-        t.y -= ai;
-        w[i] = t;
+        if constexpr (C) {
+            double2 t = ((double2 *)w)[i];
+            t.x -= ar;
+            t.y -= ai;
+            ((double2 *)w)[i] = t;
+            n2 = t.x * t.x + t.y * t.y;
+        } else {
+            const double t = w[i] - ar;
+            w[i] = t;
+            n2 = t * t;
+        }
     }
-}
-
-// hv[j] = sum_b part[j][b] (one block per j, fixed tree); optionally alpha[k] += hv[k].
-// With planes = 2 (complex), blockIdx.y selects the real / imaginary plane at offset `plane`
-// and hv holds interleaved pairs; alpha takes the real part.
-__global__ __launch_bounds__(kRed) void k_reduce_parts(const double *__restrict__ part, int nparts,
-                                                       const int *__restrict__ kdev, int extra, double *__restrict__ hv,
-                                                       double *__restrict__ alpha, int planes = 1,
-                                                       int64_t plane = 0) {
-    __shared__ double ws[kRed / 64];
-    const int cnt = *kdev + 1 + extra;
-    const int j = blockIdx.x, im = blockIdx.y;
-    if (j >= cnt) return;
-    double s = 0.0;
-    const double *pp = part + im * plane;
-    for (int p = threadIdx.x; p < nparts; p += kRed) s += pp[(int64_t)j * nparts + p];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < kRed / 64; ++q) t += ws[q];
-        hv[planes * j + im] = t;
-        if (alpha && im == 0 && j == *kdev) alpha[j] += t;
+    if (sq) {
+        n2 = block_sum(n2, ws);
+        if (threadIdx.x == 0) sq[blockIdx.x] = n2;
     }
-}
-
-// w[i] -= sum_{j<=k} V[j][i] hv[j]
-__global__ __launch_bounds__(kRed) void k_gemv_n_sub(const double *__restrict__ V, const double *__restrict__ hv,
-                                                     int64_t N, const int *__restrict__ kdev, double *__restrict__ w) {
-    __shared__ double sh[1024];
-    const int cnt = *kdev + 1;
-    const int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x;
-    double acc = 0.0;
-    for (int j0 = 0; j0 < cnt; j0 += 1024) {
-        const int nj = min(1024, cnt - j0);
-        __syncthreads();
-        for (int q = threadIdx.x; q < nj; q += kRed) sh[q] = hv[j0 + q];
-        __syncthreads();
-        if (i < N)
-            for (int q = 0; q < nj; ++q) acc += V[(int64_t)(j0 + q) * N + i] * sh[q];
-    }
-    if (i < N) w[i] -= acc;
 }
 
 // y[i] = sum_{j<cnt} V[j][i] s[j]
@@ -243,44 +263,47 @@ __global__ __launch_bounds__(kRed) void k_sq_part(const double *__restrict__ w, 
     }
 }
 
-// beta[k] = sqrt(sum part); flags breakdown in tri[2]
-__global__ __launch_bounds__(kRed) void k_beta(const double *__restrict__ part, int nparts, const int *__restrict__ kdev,
-                                               double *__restrict__ beta, double *__restrict__ tri) {
+// One value from n partial sums (more than the normalization adds itself).
+__global__ __launch_bounds__(kRed) void k_sum(double *__restrict__ part, int64_t n) {
     __shared__ double ws[kRed / 64];
     double s = 0.0;
-    for (int p = threadIdx.x; p < nparts; p += kRed) s += part[p];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < kRed / 64; ++q) t += ws[q];
-        beta[*kdev] = sqrt(t);
-    }
+    for (int64_t p = threadIdx.x; p < n; p += kRed) s += part[p];
+    s = block_sum(s, ws);
+    if (threadIdx.x == 0) part[0] = s;
 }
 
-// x = V[k+1] = w / beta[k]; k += 1 (the last block to finish bumps k)
+// beta[k] = sqrt(sum of the nsq partial squared norms), V[k+1] = w / beta[k] (also x when given).
 // Breakdown (w vanished relative to the recurrence: an invariant subspace) records the
 // number of valid iterations in tri[2] once; later iterations then carry zeros.
 __global__ __launch_bounds__(kRed) void k_next(double *__restrict__ V, double *__restrict__ x,
                                                const double *__restrict__ w, int64_t N, const int *__restrict__ kdev,
+                                               int karg, const double *__restrict__ sq, int nsq,
                                                const double *__restrict__ alpha, double *__restrict__ beta, int m,
                                                double *__restrict__ tri) {
-    const int k = *kdev;
-    const double b = beta[k];
+    __shared__ double ws[kRed / 64];
+    const int k = iter_of(kdev, karg);
+    double s = 0.0;
+    for (int p = threadIdx.x; p < nsq; p += kRed) s += sq[p];
+    const double b = sqrt(block_sum(s, ws));  // the same sum in every block
     const double scale = fabs(alpha[k]) + (k > 0 ? beta[k - 1] : 0.0);
-    const bool brk = tri[2] != 0.0 || !(b > 1e-12 * scale) || !(b > 1e-300);
+    const bool brk0 = !(b > 1e-12 * scale) || !(b > 1e-300);
+    const bool brk = tri[2] != 0.0 || brk0;  // (block 0 may set it meanwhile: then brk0 holds here too)
     const double inv = brk ? 0.0 : 1.0 / b;
-    const int64_t i = (int64_t)blockIdx.x * kRed + threadIdx.x;
-    if (i < N) {
-        const double v = w[i] * inv;
-        x[i] = v;
-        if (k + 1 <= m) V[(int64_t)(k + 1) * N + i] = v;
+    const int64_t i0 = (int64_t)blockIdx.x * (kRed * kNextRows) + threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < kNextRows; ++q) {
+        const int64_t i = i0 + q * kRed;
+        if (i < N) {
+            const double v = w[i] * inv;
+            if (x) x[i] = v;
+            if (k + 1 <= m) V[(int64_t)(k + 1) * N + i] = v;
+        }
     }
     __syncthreads();
-    if (i == 0 && brk && tri[2] == 0.0) {
-        tri[2] = (double)(k + 1);
-        beta[k] = 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const bool first = brk && tri[2] == 0.0;
+        if (first) tri[2] = (double)(k + 1);
+        beta[k] = first ? 0.0 : b;
     }
 }
 
@@ -347,22 +370,19 @@ __global__ void k_init_v0(double *__restrict__ x, int64_t N, int mode, uint64_t 
     }
 }
 
-__global__ void k_scale(double *__restrict__ x, int64_t N, const double *__restrict__ part, int nparts) {
-    // x /= sqrt(sum part) (sum recomputed per block in fixed order)
-    __shared__ double inv;
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int p = 0; p < nparts; ++p) t += part[p];
-        inv = 1.0 / sqrt(t);
+// x /= sqrt(sum part) (summed per block in fixed order; kRed threads); also stored in `copy`
+__global__ __launch_bounds__(kRed) void k_scale(double *__restrict__ x, int64_t N, const double *__restrict__ part,
+                                                int nparts, double *__restrict__ copy) {
+    __shared__ double ws[kRed / 64];
+    double s = 0.0;
+    for (int p = threadIdx.x; p < nparts; p += kRed) s += part[p];
+    const double inv = 1.0 / sqrt(block_sum(s, ws));
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
+    {
+        const double v = x[i] * inv;
+        x[i] = v;
+        if (copy) copy[i] = v;
     }
-    __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
-        x[i] *= inv;
-}
-
-__global__ void k_copy_row(const double *__restrict__ x, double *__restrict__ V0, int64_t N) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
-        V0[i] = x[i];
 }
 
 // r = Hy - theta y -> partial sums of r^2 and of y^2
@@ -386,42 +406,58 @@ __global__ __launch_bounds__(kRed) void k_resid_part(const double *__restrict__ 
 
 inline unsigned gridN(int64_t n) { return (unsigned)((n + kRed - 1) / kRed); }
 
-int enqueue_iteration(const SpmvOp &op, LzState &S, bool f32, hipStream_t st) {
-    const int64_t N = S.N, NR = S.NR;
-    const int32_t dt64 = S.cplx ? QSD_C128 : QSD_F64, dt32 = S.cplx ? QSD_C64 : QSD_F32;
-    if (f32) {
-        k_f64_to_f32<<<1024, kRed, 0, st>>>(S.x, S.x32, NR);
-        QSD_TRY(op.matvec(1, S.x32, 1, S.w32, 1, dt32, st));
-        k_f32_to_f64<<<1024, kRed, 0, st>>>(S.w32, S.w, NR);
-    } else {
-        QSD_TRY(op.matvec(1, S.x, 1, S.w, 1, dt64, st));
-    }
-    const dim3 gt(kDotBlocks, (S.m + 1 + kGemvJ - 1) / kGemvJ);
-    const int64_t plane = (int64_t)(S.m + 1) * kDotBlocks;
+// The current basis vector: under graph replay at the fixed address, else in the basis.
+const double *current(const LzState &S, int k) { return k < 0 ? S.x : S.V + (int64_t)k * S.NR; }
+
+template <bool C>
+void enqueue_blas(LzState &S, int k, hipStream_t st) {
+    const int64_t N = S.N;
+    const int *kdev = k < 0 ? S.kdev : nullptr;
+    const int cnt = k < 0 ? S.m + 1 : k + 1;  // basis vectors the launch has to cover
+    const dim3 gt((cnt + kGemvJ - 1) / kGemvJ, S.parts);
+    const int64_t plane = (int64_t)(S.m + 1) * S.parts;
+    const bool own = S.parts <= kInlineParts;
     for (int pass = 0; pass < 2; ++pass) {
-        if (S.cplx) {
-            k_gemv_t_c<<<gt, kRed, 0, st>>>((const double2 *)S.V, (const double2 *)S.w, N, S.kdev, plane, S.part);
-            k_reduce_parts<<<dim3(S.m + 1, 2), kRed, 0, st>>>(S.part, kDotBlocks, S.kdev, 0, S.hv, S.alpha, 2, plane);
-            k_gemv_n_sub_c<<<gridN(N), kRed, 0, st>>>((const double2 *)S.V, S.hv, N, S.kdev, (double2 *)S.w);
-        } else {
-            k_gemv_t<<<gt, kRed, 0, st>>>(S.V, S.w, N, S.kdev, 0, S.part);
-            k_reduce_parts<<<S.m + 1, kRed, 0, st>>>(S.part, kDotBlocks, S.kdev, 0, S.hv, S.alpha);
-            k_gemv_n_sub<<<gridN(N), kRed, 0, st>>>(S.V, S.hv, N, S.kdev, S.w);
-        }
+        k_gemv_t<C><<<gt, kRed, 0, st>>>(S.V, S.w, N, kdev, k, plane, S.part);
+        if (!own) k_reduce_parts<C><<<dim3(cnt, C ? 2 : 1), kRed, 0, st>>>(S.part, S.parts, kdev, k, plane, S.hv);
+        k_update<C><<<(unsigned)S.sqn, kRed, 0, st>>>(S.V, S.hv, S.part, own ? S.parts : 0, plane, N, kdev, k, S.w,
+                                                      S.alpha, pass ? S.sq : nullptr);
     }
-    k_sq_part<<<kDotBlocks, kRed, 0, st>>>(S.w, NR, S.part);
-    k_beta<<<1, kRed, 0, st>>>(S.part, kDotBlocks, S.kdev, S.beta, S.tri);
-    k_next<<<gridN(NR), kRed, 0, st>>>(S.V, S.x, S.w, NR, S.kdev, S.alpha, S.beta, S.m, S.tri);
-    k_bump<<<1, 1, 0, st>>>(S.kdev);
+    int nsq = (int)S.sqn;
+    if (S.sqn > kNormParts) {
+        k_sum<<<1, kRed, 0, st>>>(S.sq, S.sqn);
+        nsq = 1;
+    }
+    k_next<<<(unsigned)((S.NR + kRed * kNextRows - 1) / (kRed * kNextRows)), kRed, 0, st>>>(S.V, k < 0 ? S.x : nullptr, S.w, S.NR, kdev, k, S.sq, nsq, S.alpha, S.beta,
+                                         S.m, S.tri);
+    if (k < 0) k_bump<<<1, 1, 0, st>>>(S.kdev);
+}
+
+// Iteration k, or with k < 0 the iteration that the device counter says (graph capture).
+int enqueue_iteration(const SpmvOp &op, LzState &S, bool f32, int k, hipStream_t st) {
+    const double *x = current(S, k);
+    if (f32) {
+        k_f64_to_f32<<<1024, kRed, 0, st>>>(x, S.x32, S.NR);
+        QSD_TRY(op.matvec(1, S.x32, 1, S.w32, 1, S.cplx ? QSD_C64 : QSD_F32, st));
+        k_f32_to_f64<<<1024, kRed, 0, st>>>(S.w32, S.w, S.NR);
+    } else {
+        QSD_TRY(op.matvec(1, x, 1, S.w, 1, S.cplx ? QSD_C128 : QSD_F64, st));
+    }
+    if (S.cplx)
+        enqueue_blas<true>(S, k, st);
+    else
+        enqueue_blas<false>(S, k, st);
     QSD_CHECK_HIP(hipGetLastError());
     return QSD_OK;
 }
 
-__global__ void k_zero(double *p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0;
+// alpha, beta, the head of tri and the iteration counter at the start of a run
+__global__ void k_clear(double *__restrict__ alpha, double *__restrict__ beta, int m, double *__restrict__ tri,
+                        int *__restrict__ kdev) {
+    for (int i = threadIdx.x; i < m; i += blockDim.x) alpha[i] = beta[i] = 0.0;
+    if (threadIdx.x < 4) tri[threadIdx.x] = 0.0;
+    if (threadIdx.x == 0) *kdev = 0;
 }
-__global__ void k_zero_i(int *p) { *p = 0; }
 
 }  // namespace
 }  // namespace qsd
@@ -473,23 +509,38 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
     S.m = (int)std::min<int64_t>(o.max_iter, N);
     const bool f32 = o.spmv_dtype == QSD_F32;
     int rc = QSD_OK;
-    auto alloc_all = [&]() -> int {
-        QSD_TRY(dev_alloc(&S.V, (size_t)(S.m + 1) * NR));
-        QSD_TRY(dev_alloc(&S.x, NR));
-        QSD_TRY(dev_alloc(&S.w, NR));
-        if (f32) {
-            QSD_TRY(dev_alloc(&S.x32, NR));
-            QSD_TRY(dev_alloc(&S.w32, NR));
-        }
-        QSD_TRY(dev_alloc(&S.part, (size_t)(S.m + 1) * kDotBlocks * (cplx ? 2 : 1)));
-        QSD_TRY(dev_alloc(&S.hv, (size_t)(S.m + 1) * (cplx ? 2 : 1)));
-        QSD_TRY(dev_alloc(&S.alpha, S.m));
-        QSD_TRY(dev_alloc(&S.beta, S.m));
-        QSD_TRY(dev_alloc(&S.kdev, 1));
-        QSD_TRY(dev_alloc(&S.tri, S.m + 4));
-        return QSD_OK;
-    };
-    rc = alloc_all();
+    S.parts = (int)std::min<int64_t>(kMaxParts, std::max<int64_t>(1, (N + kPartRows - 1) / kPartRows));
+    S.sqn = (N + kRed - 1) / kRed;
+    {
+        // one allocation, carved (256-byte aligned)
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            const size_t at = off;
+            off += (bytes + 255) / 256 * 256;
+            return at;
+        };
+        const int P = cplx ? 2 : 1;
+        const size_t oV = take((size_t)(S.m + 1) * NR * 8), ox = take(NR * 8), ow = take(NR * 8);
+        const size_t ox32 = take(f32 ? NR * 4 : 0), ow32 = take(f32 ? NR * 4 : 0);
+        const size_t op_ = take((size_t)(S.m + 1) * S.parts * P * 8);
+        const size_t os = take(std::max<size_t>(S.sqn, kMaxParts) * 8), oh = take((size_t)(S.m + 1) * P * 8);
+        const size_t oa = take((size_t)S.m * 8), ob = take((size_t)S.m * 8), ok = take(8), ot = take((size_t)(S.m + 4) * 8);
+        const size_t osp = take(8);
+        rc = dev_alloc(&S.mem, off);
+        S.V = (double *)(S.mem + oV);
+        S.x = (double *)(S.mem + ox);
+        S.w = (double *)(S.mem + ow);
+        S.x32 = (float *)(S.mem + ox32);
+        S.w32 = (float *)(S.mem + ow32);
+        S.part = (double *)(S.mem + op_);
+        S.sq = (double *)(S.mem + os);
+        S.hv = (double *)(S.mem + oh);
+        S.alpha = (double *)(S.mem + oa);
+        S.beta = (double *)(S.mem + ob);
+        S.kdev = (int *)(S.mem + ok);
+        S.tri = (double *)(S.mem + ot);
+        S.spike = (int64_t *)(S.mem + osp);
+    }
     // a sparse operator is applied from the list of its elements: the operator's own, or one made
     // for this solve (its cost is that of about three SpMVs)
     qsd_hits *made = nullptr;
@@ -516,21 +567,12 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
                 break;
             }
         } else {
-            int64_t *spike = nullptr;
-            if ((rc = dev_alloc(&spike, 1)) != QSD_OK) break;
-            if (o.v0_mode == QSD_V0_MIN_DIAG) k_argmin<<<1, kRed, 0, st>>>(op.diag(), N, spike);
-            k_init_v0<<<1024, kRed, 0, st>>>(S.x, NR, o.v0_mode, o.seed, spike, cplx ? 2 : 1);
-            if (hipStreamSynchronize(st) != hipSuccess) rc = fail(QSD_ERR_HIP, "v0 failed");
-            dev_free(spike);
-            if (rc != QSD_OK) break;
+            if (o.v0_mode == QSD_V0_MIN_DIAG) k_argmin<<<1, kRed, 0, st>>>(op.diag(), N, S.spike);
+            k_init_v0<<<1024, kRed, 0, st>>>(S.x, NR, o.v0_mode, o.seed, S.spike, cplx ? 2 : 1);
         }
-        k_sq_part<<<kDotBlocks, kRed, 0, st>>>(S.x, NR, S.part);
-        k_scale<<<1024, kRed, 0, st>>>(S.x, NR, S.part, kDotBlocks);
-        k_copy_row<<<1024, kRed, 0, st>>>(S.x, S.V, NR);
-        k_zero<<<64, kRed, 0, st>>>(S.alpha, S.m);
-        k_zero<<<64, kRed, 0, st>>>(S.beta, S.m);
-        k_zero<<<1, 64, 0, st>>>(S.tri, 4);
-        k_zero_i<<<1, 1, 0, st>>>(S.kdev);
+        k_sq_part<<<kMaxParts, kRed, 0, st>>>(S.x, NR, S.sq);
+        k_scale<<<1024, kRed, 0, st>>>(S.x, NR, S.sq, kMaxParts, S.V);
+        k_clear<<<1, 256, 0, st>>>(S.alpha, S.beta, S.m, S.tri, S.kdev);
         if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
             rc = fail(QSD_ERR_HIP, "event create failed");
             break;
@@ -540,7 +582,7 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
                 rc = fail(QSD_ERR_HIP, "stream capture failed");
                 break;
             }
-            int erc = enqueue_iteration(op, S, f32, st);
+            int erc = enqueue_iteration(op, S, f32, -1, st);
             hipError_t ce = hipStreamEndCapture(st, &graph);
             if (erc != QSD_OK || ce != hipSuccess) {
                 rc = erc != QSD_OK ? erc : fail(QSD_ERR_HIP, "end capture failed");
@@ -559,7 +601,7 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
                 if (gexec) {
                     if (hipGraphLaunch(gexec, st) != hipSuccess) rc = fail(QSD_ERR_HIP, "graph launch failed");
                 } else {
-                    rc = enqueue_iteration(op, S, f32, st);
+                    rc = enqueue_iteration(op, S, f32, done + s, st);
                 }
             }
             if (rc != QSD_OK) break;
@@ -598,7 +640,7 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
         if (f32)
             rc = op.matvec(1, S.x32, 1, S.w32, 1, mv32, st);
         else
-            rc = op.matvec(1, S.x, 1, S.w, 1, mv64, st);
+            rc = op.matvec(1, gexec ? S.x : S.V, 1, S.w, 1, mv64, st);
         hipEventRecord(e1, st);
         if (rc != QSD_OK) break;
         hipEventSynchronize(e1);
@@ -606,8 +648,8 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
         if (o.want_vector) {
             double *y = (double *)d_evec;
             k_gemv_n<<<gridN(NR), kRed, 0, st>>>(S.V, S.tri + 3, iters, NR, y);
-            k_sq_part<<<kDotBlocks, kRed, 0, st>>>(y, NR, S.part);
-            k_scale<<<1024, kRed, 0, st>>>(y, NR, S.part, kDotBlocks);
+            k_sq_part<<<kMaxParts, kRed, 0, st>>>(y, NR, S.sq);
+            k_scale<<<1024, kRed, 0, st>>>(y, NR, S.sq, kMaxParts, nullptr);
             if (op.takes(mv64)) {
                 if ((rc = op.matvec(1, y, 1, S.w, 1, mv64, st)) != QSD_OK) break;
             } else {  // a stored FP32 matrix: the residual of the FP32 operator
@@ -615,9 +657,9 @@ int lanczos_impl(SpmvOp op, const qsd_lanczos_opts *opts, double *eval_out, void
                 if ((rc = op.matvec(1, S.x32, 1, S.w32, 1, mv32, st)) != QSD_OK) break;
                 k_f32_to_f64<<<1024, kRed, 0, st>>>(S.w32, S.w, NR);
             }
-            k_resid_part<<<kDotBlocks, kRed, 0, st>>>(S.w, y, theta, NR, S.part);
-            std::vector<double> parts(kDotBlocks);
-            if (hipMemcpyAsync(parts.data(), S.part, kDotBlocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            k_resid_part<<<kMaxParts, kRed, 0, st>>>(S.w, y, theta, NR, S.sq);
+            std::vector<double> parts(kMaxParts);
+            if (hipMemcpyAsync(parts.data(), S.sq, kMaxParts * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess) {
                 rc = fail(QSD_ERR_HIP, "residual failed");
                 break;
