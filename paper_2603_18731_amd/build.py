@@ -15,7 +15,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libqsd.so")
 
 SOURCES = ["ham.hip", "serve.hip", "csr.hip", "spmv_w1.hip", "spmv_w2.hip", "spmv_w4.hip", "spmv_w8.hip",
-           "spmv_w16.hip", "product.hip", "hits.hip", "subspace.hip", "lanczos.hip", "block.hip", "ramps.hip", "opcompile.cpp", "api.cpp"]
+           "spmv_w16.hip", "product.hip", "product_csr.hip", "hits.hip", "subspace.hip", "lanczos.hip", "block.hip", "ramps.hip", "opcompile.cpp", "api.cpp"]
 # bench-only microbenchmarks, a library of their own (not part of the C-ABI in include/qsd.h)
 BENCH_SOURCES = ["bench/gather_rate.hip"]
 BENCH_LIB = os.path.join(HERE, "libqsd_bench.so")

@@ -408,7 +408,9 @@ extern "C" int qsd_csr_build(const qsd_ham *h, int64_t *d_indptr, void *d_indice
     if (!fill) {
         int64_t *counts = nullptr;
         QSD_TRY(dev_alloc(&counts, h->N + 1));
-        switch (h->Wp) {
+        if (prod_csr_usable(h))
+            prod_csr_count(h, counts, st);
+        else switch (h->Wp) {
             case 1: launch_count<1>(h, counts, st); break;
             case 2: launch_count<2>(h, counts, st); break;
             case 4: launch_count<4>(h, counts, st); break;
@@ -429,9 +431,21 @@ extern "C" int qsd_csr_build(const qsd_ham *h, int64_t *d_indptr, void *d_indice
         return rc;
     }
     int64_t nnz = 0;
+    const bool f32 = dtype == QSD_F32 || dtype == QSD_C64;
+    if (prod_csr_usable(h)) {
+        const bool i32 = index_type == QSD_INDEX_I32;
+        int rc = f32 ? (i32 ? prod_csr_fill<float, int32_t>(h, d_indptr, d_indices, d_data, st)
+                            : prod_csr_fill<float, int64_t>(h, d_indptr, d_indices, d_data, st))
+                     : (i32 ? prod_csr_fill<double, int32_t>(h, d_indptr, d_indices, d_data, st)
+                            : prod_csr_fill<double, int64_t>(h, d_indptr, d_indices, d_data, st));
+        if (hipMemcpyAsync(&nnz, d_indptr + h->N, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            if (rc == QSD_OK) rc = fail(QSD_ERR_HIP, "CSR fill failed: %s", hipGetErrorString(hipGetLastError()));
+        if (nnz_out) *nnz_out = nnz;
+        return rc;
+    }
     QSD_CHECK_HIP(hipMemcpyAsync(&nnz, d_indptr + h->N, 8, hipMemcpyDeviceToHost, st));
     QSD_CHECK_HIP(hipStreamSynchronize(st));
-    const bool f32 = dtype == QSD_F32 || dtype == QSD_C64;
     int64_t *cols = nullptr;
     void *vals = nullptr;
     QSD_TRY(dev_alloc(&cols, nnz));

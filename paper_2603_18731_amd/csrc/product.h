@@ -115,4 +115,10 @@ void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t 
 template <class ET>
 void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, int V, uint32_t lds, hipStream_t st);
 
+// CSR assembly (product_csr.hip): entries per row, and the rows' entries in column order.
+bool prod_csr_usable(const qsd_ham *h);
+void prod_csr_count(const qsd_ham *h, int64_t *counts, hipStream_t st);
+template <class ET, class IT>
+int prod_csr_fill(const qsd_ham *h, const int64_t *indptr, void *indices, void *data, hipStream_t st);
+
 }  // namespace qsd

@@ -207,3 +207,33 @@ def test_batched_mix(dtype):
         assert (e1[s], it1[s], rr1[s]) == (e[slots[k]], it[slots[k]], rr[slots[k]])
         one.remove(s)
     assert e[slots[1]] == e[slots[1]] and st[slots[1]] != 0
+
+
+@pytest.mark.parametrize("na,nb", [(257, 7), (40, 40), (1, 60), (60, 1), (513, 3)])
+@pytest.mark.parametrize("index,dtype", [(qsd.INDEX_I32, torch.float64), (qsd.INDEX_I64, torch.float32)])
+def test_csr_bitwise(na, nb, index, dtype):
+    """The CSR build from the lists against the row engine's (structure and values bitwise), with
+    every pair of keys present and with pairs missing, and on a spin chain."""
+    if na > 1 and nb > 1:
+        ops, keys = c3_parts(na, nb)
+    else:
+        w = wl.c3_molecular(na, nb)
+        ops, keys = w.ops, w.keys
+    drop = np.random.default_rng(6).random(ops.n_terms) < 0.3
+    cases = [(ops, keys), (_edited(ops, lambda k, t: len(t[1]) == 2 or not drop[k]), keys)]
+    if na == nb:
+        cases.append((wl.tfim_chain(11), wl.full_space(11)))
+    for tl, ks in cases:
+        sub = qsd.Subspace(ks, tl.n_qubits)
+        assert sub.hash_info()[2]
+        H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(tl))
+        say("factored CSR", na, nb, tl.n_terms, index, dtype)
+        H.schedule = DEFAULT | qsd.SCHED_HASH_LOOKUP
+        want = H.to_csr(index, dtype)
+        H.schedule = DEFAULT
+        got = H.to_csr(index, dtype)
+        for g, w_ in zip(got, want):
+            assert torch.equal(g, w_)
+        A = qsd.CsrMatrix(H, index, dtype)
+        for g, w_ in zip(A.export(), want):
+            assert torch.equal(g, w_)
