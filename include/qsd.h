@@ -491,7 +491,7 @@ int qsd_block_lanczos(const qsd_ham *h, int32_t block, const qsd_lanczos_opts *o
  * qsd_csr_export    copies indptr [N+1] (int64), indices [nnz], data [nnz] to device buffers
  *                   (any may be NULL); async on `stream`.
  * qsd_csr_matvec    Y = A X, same layout and dtype rules as qsd_matvec except that the vector
- *                   dtype must be the stored dtype (DTYPE otherwise).  LPR lanes per row with a
+ *                   dtype must be the stored dtype (DTYPE otherwise).  Entry slots per row with a
  *                   fixed reduction tree: bitwise reproducible.  Async.
  * qsd_csr_lanczos / qsd_csr_block_lanczos
  *                   qsd_lanczos / qsd_block_lanczos on the stored matrix (opts->spmv_dtype must

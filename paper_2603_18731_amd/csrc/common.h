@@ -255,7 +255,7 @@ struct qsd_csr {
     void *indices = nullptr;    // [nnz] int32 or int64
     void *data = nullptr;       // [nnz] (x2 for complex) FP64 or FP32
     double *diag = nullptr;     // [N] real part of the diagonal (start vectors)
-    int lpr = 1;                // SpMV lanes per row
+    int lpr = 1;                // SpMV entry slots per row
 };
 
 namespace qsd {

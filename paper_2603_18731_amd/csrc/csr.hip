@@ -12,8 +12,8 @@
 // the column's row, at positions taken from per-row atomic cursors.  Each row is then sorted
 // by column, which makes the result independent of the atomic order.
 //
-// SpMV: LPR lanes per row (1, 4, 16 or 64, from the mean row length), entries strided over the
-// row's lanes and summed by a fixed shuffle tree: bitwise reproducible.
+// SpMV: 1, 4, 16 or 32 entry slots per row (from the mean row length), entries strided over the
+// row's slots and summed by a fixed shuffle tree: bitwise reproducible.
 #include <algorithm>
 #include <vector>
 
@@ -96,29 +96,10 @@ __global__ void k_fill0_u64(unsigned long long *p, int64_t n) {
         p[i] = 0ull;
 }
 
-// One stored entry's contribution to the row sums of `nvec` vectors.
-template <int NV, class ET, bool CPLX>
-__device__ __forceinline__ void csr_term(double vr, double vi, int64_t c, const ET *__restrict__ x, int64_t ldx,
-                                         int nvec, double (&are)[NV], double (&aim)[NV]) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (v < nvec) {
-            if (CPLX) {
-                const double xr = (double)x[2 * (c * ldx + v)], xi = (double)x[2 * (c * ldx + v) + 1];
-                are[v] += vr * xr - vi * xi;
-                aim[v] += vr * xi + vi * xr;
-            } else {
-                are[v] += vr * (double)x[c * ldx + v];
-            }
-        }
-    }
-}
-
-// stored entries in flight per lane: more for the long rows that get many lanes (LPR = 64 means a
-// mean row length of 96 or more), two for the short rows
+// stored entries in flight per lane
 template <int LPR>
 constexpr int csr_batch() {
-    return LPR >= 64 ? 8 : LPR >= 16 ? 4 : 2;
+    return LPR >= 16 ? 4 : 2;
 }
 
 // Index and value loads: non-temporal for long rows (streamed once, kept out of the caches that
@@ -129,96 +110,94 @@ __device__ __forceinline__ T stream_load(const T *p) {
     return *p;
 }
 
-// y[r] = sum over the row's entries of A_rc x[c] for `nvec` interleaved vectors; LPR lanes per
-// row (consecutive lanes of one wave), FP64 accumulation, fixed reduction tree.  A lane takes
-// entries a + sub, a + sub + LPR, ... in order, csr_batch<LPR>() at a time: the column indices and
-// values of long rows are streamed once (non-temporal loads, so they do not evict x from the
-// caches) and the x gathers of a batch are all in flight together.
-template <int LPR, int NV, class IT, class ET, bool CPLX>
+// y[r] = sum over the row's entries of A_rc x[c] for `nvec` <= NV interleaved vectors, FP64
+// accumulation.  S entry slots per row, NV lanes each (consecutive lanes of one wave, a vector a
+// lane), so a slot's lanes read x[c][:] as one piece and a wave instruction meets 64 / NV lines
+// instead of 64 per vector (one lane per slot for all vectors: 16 vectors on 80M entries 4.34 ms, 4
+// vectors 1.27 ms).  A slot takes entries a + slot, a + slot + S, ... in order, a batch at a time
+// with its x in flight together; the slots are added by a fixed tree.
+//
+// With one vector a row gets 32 slots at most: 64 left most lanes of the last batch idle (mean
+// rows of 110 / 225 / 770 entries: 85 / 431 / 8070 us, with 32: 51 / 344 / 7510 us).  The x gathers
+// bound it: a line of x from L2 for nearly every entry, at 75-80% of the 64 bytes a clock that a CU
+// takes from L2.
+template <int S, int NV, class IT, class ET, bool CPLX>
 __global__ __launch_bounds__(256) void k_csr_spmv(const int64_t *__restrict__ indptr, const IT *__restrict__ idx,
                                                  const ET *__restrict__ val, int64_t N, const ET *__restrict__ x,
                                                  int64_t ldx, ET *__restrict__ y, int64_t ldy, int nvec) {
-    const int sub = threadIdx.x % LPR;
-    const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
-    double are[NV], aim[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) are[v] = aim[v] = 0.0;
-    constexpr int kCsrBatch = csr_batch<LPR>();
+    constexpr int L = S * NV;  // lanes per row
+    constexpr int kB = csr_batch<S>();
+    const int slot = (threadIdx.x % L) / NV, v = threadIdx.x % NV, vc = NV == 1 || v < nvec ? v : 0;
+    const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
+    double are = 0.0, aim = 0.0;
     if (row < N) {
         const int64_t a = indptr[row], b = indptr[row + 1];
-        // batches of kCsrBatch entries per lane; past the row's end the loads repeat its last
-        // entry (always valid) and the term is skipped, so the sum takes the entries in order
-        for (int64_t e = a + sub; e < b; e += kCsrBatch * LPR) {
-            int64_t c[kCsrBatch];
-            double vr[kCsrBatch], vi[kCsrBatch];
+        // past the row's end the loads repeat its last entry (always valid) and the term is
+        // skipped, so the sum takes the entries in order
+        for (int64_t e = a + slot; e < b; e += kB * S) {
+            int64_t c[kB];
+            double vr[kB], vi[kB], xr[kB], xi[kB];
 #pragma unroll
-            for (int k = 0; k < kCsrBatch; ++k) {
-                const int64_t ek = min(e + (int64_t)k * LPR, b - 1);
-                c[k] = (int64_t)stream_load<LPR>(&idx[ek]);
-                if (CPLX) {
-                    vr[k] = (double)stream_load<LPR>(&val[2 * ek]);
-                    vi[k] = (double)stream_load<LPR>(&val[2 * ek + 1]);
-                } else {
-                    vr[k] = (double)stream_load<LPR>(&val[ek]);
-                    vi[k] = 0.0;
-                }
+            for (int k = 0; k < kB; ++k) {
+                const int64_t ek = min(e + (int64_t)k * S, b - 1);
+                c[k] = (int64_t)stream_load<S>(&idx[ek]);
+                vr[k] = (double)stream_load<S>(&val[CPLX ? 2 * ek : ek]);
+                vi[k] = CPLX ? (double)stream_load<S>(&val[2 * ek + 1]) : 0.0;
             }
-            if (NV == 1 && !CPLX) {
-                // one real vector: the batch's x gathers are issued together too
-                double xv[kCsrBatch];
 #pragma unroll
-                for (int k = 0; k < kCsrBatch; ++k) xv[k] = (double)x[c[k] * ldx];
+            for (int k = 0; k < kB; ++k) {
+                const int64_t o = c[k] * ldx + vc;
+                xr[k] = (double)x[CPLX ? 2 * o : o];
+                xi[k] = CPLX ? (double)x[2 * o + 1] : 0.0;
+            }
 #pragma unroll
-                for (int k = 0; k < kCsrBatch; ++k)
-                    if (e + (int64_t)k * LPR < b) are[0] += vr[k] * xv[k];
-            } else {
-#pragma unroll
-                for (int k = 0; k < kCsrBatch; ++k)
-                    if (e + (int64_t)k * LPR < b) csr_term<NV, ET, CPLX>(vr[k], vi[k], c[k], x, ldx, nvec, are, aim);
+            for (int k = 0; k < kB; ++k) {
+                if (e + (int64_t)k * S >= b) continue;
+                if (CPLX) {
+                    are += vr[k] * xr[k] - vi[k] * xi[k];
+                    aim += vr[k] * xi[k] + vi[k] * xr[k];
+                } else {
+                    are += vr[k] * xr[k];
+                }
             }
         }
     }
 #pragma unroll
-    for (int d = LPR / 2; d >= 1; d >>= 1) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            are[v] += __shfl_xor(are[v], d, 64);
-            if (CPLX) aim[v] += __shfl_xor(aim[v], d, 64);
-        }
+    for (int d = L / 2; d >= NV; d >>= 1) {
+        are += __shfl_xor(are, d, 64);
+        if (CPLX) aim += __shfl_xor(aim, d, 64);
     }
-    if (sub == 0 && row < N) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            if (v < nvec) {
-                if (CPLX) {
-                    y[2 * (row * ldy + v)] = (ET)are[v];
-                    y[2 * (row * ldy + v) + 1] = (ET)aim[v];
-                } else {
-                    y[row * ldy + v] = (ET)are[v];
-                }
-            }
+    if (slot == 0 && row < N && v < nvec) {
+        if (CPLX) {
+            y[2 * (row * ldy + v)] = (ET)are;
+            y[2 * (row * ldy + v) + 1] = (ET)aim;
+        } else {
+            y[row * ldy + v] = (ET)are;
         }
     }
 }
 
-template <int LPR, int NV, class IT, class ET, bool CPLX>
+template <int S, int NV, class IT, class ET, bool CPLX>
 void launch_spmv(const qsd_csr *c, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
-    const int64_t threads = c->N * LPR;
+    constexpr int kS = S * NV <= 64 ? S : 64 / NV;
+    const int64_t threads = c->N * kS * NV;
     const unsigned grid = (unsigned)((threads + 255) / 256);
-    k_csr_spmv<LPR, NV, IT, ET, CPLX><<<grid, 256, 0, st>>>(c->indptr, (const IT *)c->indices, (const ET *)c->data,
-                                                            c->N, (const ET *)x, ldx, (ET *)y, ldy, nvec);
+    k_csr_spmv<kS, NV, IT, ET, CPLX><<<grid, 256, 0, st>>>(c->indptr, (const IT *)c->indices, (const ET *)c->data,
+                                                           c->N, (const ET *)x, ldx, (ET *)y, ldy, nvec);
 }
 
-template <int LPR, class IT, class ET, bool CPLX>
+template <int S, class IT, class ET, bool CPLX>
 void spmv_nv(const qsd_csr *c, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
     if (nvec <= 1)
-        launch_spmv<LPR, 1, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
+        launch_spmv<S, 1, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
+    else if (nvec <= 2)
+        launch_spmv<S, 2, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
     else if (nvec <= 4 || CPLX)
-        launch_spmv<LPR, 4, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
+        launch_spmv<S, 4, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
     else if (nvec <= 8)
-        launch_spmv<LPR, CPLX ? 4 : 8, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
+        launch_spmv<S, CPLX ? 4 : 8, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
     else
-        launch_spmv<LPR, CPLX ? 4 : 16, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
+        launch_spmv<S, CPLX ? 4 : 16, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st);
 }
 
 template <class IT, class ET, bool CPLX>
@@ -227,7 +206,7 @@ void spmv_lpr(const qsd_csr *c, const void *x, int64_t ldx, void *y, int64_t ldy
         case 1: spmv_nv<1, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st); break;
         case 4: spmv_nv<4, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st); break;
         case 16: spmv_nv<16, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st); break;
-        default: spmv_nv<64, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st); break;
+        default: spmv_nv<32, IT, ET, CPLX>(c, x, ldx, y, ldy, nvec, st); break;
     }
 }
 
@@ -380,7 +359,7 @@ extern "C" int qsd_csr_create(const qsd_ham *h, int32_t index_type, int32_t dtyp
         return rc;
     }
     const double mean = (double)c->nnz / (double)std::max<int64_t>(1, c->N);
-    c->lpr = mean < 6.0 ? 1 : mean < 24.0 ? 4 : mean < 96.0 ? 16 : 64;
+    c->lpr = mean < 6.0 ? 1 : mean < 24.0 ? 4 : mean < 96.0 ? 16 : 32;
     *out = c;
     return QSD_OK;
 }
