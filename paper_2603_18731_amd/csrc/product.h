@@ -27,7 +27,7 @@ namespace qsd {
 template <class ET>
 struct ProdVals {
     ET *a1 = nullptr;    // [nA1][na] sums of the terms that depend on the low part alone
-    ET *a2 = nullptr;    // [nA2][na]
+    ET *a2 = nullptr;    // [nA2 / 4][na][4]
     ET *dep = nullptr;   // [high qubits][nUa] coefficients of the class A terms that want a high qubit
     ET *ctab = nullptr;  // [nW][nU] class AB coefficients (0: no such term)
     ET *wtab = nullptr;  // [nWb][na] class B sums up to the terms that want a low qubit
@@ -40,20 +40,24 @@ struct ProdVals {
 struct qsd_prod {
     int32_t split = 0;
     uint32_t na = 0, nb = 0;
+    uint32_t T = 0;         // low parts per workgroup (a tile)
     // longest list over the parts, per segment
     uint32_t nA1 = 0, nA2 = 0, nAB = 0, nB1 = 0, nB2 = 0, nBAB = 0;
     uint32_t nUa = 0, nU = 0, nW = 0, nWb = 0, tail_len = 0;
     uint32_t rmask = 0;     // high qubits (shifted to 0) that class A terms want
     uint32_t max_occ = 0;   // most of them set in one sampled high part
     bool full = false;      // every pair of class AB keys has a term
-    // lists: low parts [k][na], high parts [nb][k]
+    // lists: low parts by position (order[position] = rank, place[rank] = position; within a tile by
+    // the length of the AB list), A1 [k][na], A2 and AB four entries together (prod_at), padded with
+    // entries that add nothing; high parts [nb][k]
+    uint32_t *order = nullptr, *place = nullptr;
     uint32_t *a1_ent = nullptr;  // column rank | (2 key + sign) << 16
-    uint32_t *a2_col = nullptr;  // column rank
+    uint16_t *a2_col = nullptr;  // column rank
     uint32_t *ab_ent = nullptr;  // column rank | (2 key + sign) << 16
     uint32_t *b1_ent = nullptr;  // [nb][nB1][2] row-block rank, 2 key + sign | tail count << 24
     uint32_t *b2_col = nullptr;  // row-block rank
     uint32_t *bab_ent = nullptr; // [nb][nBAB][2] row-block rank, 2 key + sign
-    uint32_t *alen = nullptr;    // [3][na] lengths A1, A2, AB
+    uint32_t *alen = nullptr;    // [3][na] lengths A1, A2, AB, by position
     uint32_t *blen = nullptr;    // [4][nb] lengths B1, B2, AB, and the high part itself
     qsd::ProdVals<double> d;
     qsd::ProdVals<float> f;
@@ -62,13 +66,20 @@ struct qsd_prod {
 
 namespace qsd {
 
+// Place of entry k of the low part at position `at` in the A2 and AB lists.
+__host__ __device__ inline int64_t prod_at(uint32_t k, uint32_t na, uint32_t at) {
+    return ((int64_t)(k >> 2) * na + at) * 4 + (k & 3u);
+}
+
 // What the SpMV kernels read of a plan, by value (or in a request table).
 template <class ET>
 struct ProdView {
-    uint32_t na, nb, nB1, nB2, nBAB, nUa, nU, tail_len, rmask, full;
-    const uint32_t *__restrict__ a1_ent, *__restrict__ a2_col, *__restrict__ ab_ent;
+    uint32_t na, nb, T, nB1, nB2, nBAB, nUa, nU, tail_len, rmask, full;
+    const uint32_t *__restrict__ a1_ent;
+    const uint16_t *__restrict__ a2_col;
+    const uint32_t *__restrict__ ab_ent;
     const uint32_t *__restrict__ b1_ent, *__restrict__ b2_col, *__restrict__ bab_ent;
-    const uint32_t *__restrict__ alen, *__restrict__ blen;
+    const uint32_t *__restrict__ alen, *__restrict__ blen, *__restrict__ order, *__restrict__ place;
     const ET *__restrict__ a1, *__restrict__ a2, *__restrict__ dep, *__restrict__ ctab, *__restrict__ wtab,
         *__restrict__ tail, *__restrict__ b2;
     const ET *__restrict__ diag;
@@ -111,9 +122,11 @@ uint32_t prod_blocks(const qsd_ham *h, int nvec, int V);
 template <class ET>
 void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st);
 
-// The same for n requests of a device table in one launch; every row is evaluated as above.
+// The same for n requests of a device table in one launch of workgroups of T threads (the largest
+// of the requests'); every row is evaluated as above.
 template <class ET>
-void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, int V, uint32_t lds, hipStream_t st);
+void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, uint32_t T, int V, uint32_t lds,
+                         hipStream_t st);
 
 // CSR assembly (product_csr.hip): entries per row, and the rows' entries in column order.
 bool prod_csr_usable(const qsd_ham *h);

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <numeric>
 #include <type_traits>
 #include <unordered_map>
 #include <unordered_set>
@@ -17,6 +18,12 @@ namespace {
 constexpr uint32_t kLdsBytes = 64u * 1024u;  // a workgroup's x row and tables (two or more workgroups per CU)
 constexpr uint32_t kMaxKeys = 16384;         // term keys of one part: 2 key + sign fits 15 bits
 constexpr uint32_t kMaxTail = 200;           // terms after the table, counted in 8 bits
+// Threads and low parts per workgroup.  1500 x 1500 strings in FP64: 256 1054 us, 384 1167 (four
+// tiles with a short last one), 512 950, 768 979; 600 x 600: 98, 88, 88, 89.
+constexpr uint32_t kMaxThreads = 512;
+// Waves per SIMD that the registers must allow.  600 x 600: 88 us without it, 72 with 7; 8 costs
+// scalar spills (300 x 301: 24.6 -> 26.4).
+constexpr int kWaves = 7;
 constexpr uint64_t kMaxTable = 1ull << 23;   // entries of a two-sided table
 
 // What the list kernels read of the operator.
@@ -79,6 +86,7 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
     const uint32_t lowmask = (1u << v.split) - 1u;
     const uint32_t part = HIGH ? (uint32_t)(v.keys[(int64_t)i * v.na] >> v.split) : (uint32_t)v.keys[i] & lowmask;
     const uint32_t *filt = v.pfilt + (HIGH ? kPartWords / 2 : 0);
+    const uint32_t at = !HIGH && WRITE ? p.place[i] : i;  // a low part's position
     uint32_t n1 = 0, n2 = 0, n3 = 0;
     for (uint32_t g0 = 0; g0 < g.n; g0 += 64u) {
         const uint32_t q = g0 + (uint32_t)lane;
@@ -131,15 +139,18 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
                         ++at;
                     }
                 } else {
-                    const int64_t o = (int64_t)k * v.na + i;
+                    const int64_t o = (int64_t)k * v.na + at;
                     p.a1_ent[o] = col | key << 16;
                     p.d.a1[o] = val;
                     p.f.a1[o] = val32;
                 }
             } else {
                 const uint32_t k = n2 + below(b2, lane);
-                const int64_t o = HIGH ? (int64_t)i * p.nB2 + k : (int64_t)k * v.na + i;
-                (HIGH ? p.b2_col : p.a2_col)[o] = col;
+                const int64_t o = HIGH ? (int64_t)i * p.nB2 + k : prod_at(k, v.na, at);
+                if (HIGH)
+                    p.b2_col[o] = col;
+                else
+                    p.a2_col[o] = (uint16_t)col;
                 (HIGH ? p.d.b2 : p.d.a2)[o] = val;
                 (HIGH ? p.f.b2 : p.f.a2)[o] = val32;
             }
@@ -166,10 +177,27 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
                 e[0] = col;
                 e[1] = 2u * (uint32_t)key + sgn;
             } else {
-                p.ab_ent[(int64_t)k * v.na + i] = col | (2u * (uint32_t)key + sgn) << 16;
+                p.ab_ent[prod_at(k, v.na, at)] = col | (2u * (uint32_t)key + sgn) << 16;
             }
         }
         n3 += (uint32_t)__popcll(b3);
+    }
+    if (WRITE && !HIGH) {
+        // the rest of A2 and AB: entries that add 0 * 0 (the zeros after x's row and after the
+        // coefficients), so that a wave's lanes walk them without a test
+        const uint32_t zero = 2u * p.nU;
+        for (uint32_t k = n2 + lane; k < p.nA2; k += 64u) {
+            const int64_t o = prod_at(k, v.na, at);
+            p.a2_col[o] = (uint16_t)v.na;
+            p.d.a2[o] = 0.0;
+            p.f.a2[o] = 0.0f;
+        }
+        for (uint32_t k = n3 + lane; k < p.nAB; k += 64u) p.ab_ent[prod_at(k, v.na, at)] = v.na | zero << 16;
+        if (lane == 0) {
+            p.alen[at] = n1;
+            p.alen[n + at] = n2;
+            p.alen[2 * (int64_t)n + at] = n3;
+        }
     }
     if (!WRITE && lane == 0) {
         uint32_t *len = HIGH ? p.blen : p.alen;
@@ -202,91 +230,128 @@ __global__ __launch_bounds__(256) void k_prod_wtab(const uint64_t *__restrict__ 
 
 // ------------------------------------------------------------------------------- SpMV
 
-// One workgroup: 256 low parts of one high part b, V of the interleaved vectors.  Class A and AB
+// Four values of a list at once.
+template <class T>
+struct alignas(4 * sizeof(T)) Four {
+    T v[4];
+};
+
+// One workgroup: T low parts of the high part b, V of the interleaved vectors.  Class A and AB
 // columns lie in whole rows x[b'][:], which are staged in LDS (12 KB for 1500 strings in FP64), so
 // the random gathers run at the LDS rate and not at the 0.36 lanes per clock and CU that the texture
-// path gives gathers from L2; b's own list is uniform over the workgroup (scalar loads), and class
-// B reads x[b'][a] coalesced.  Bound by the LDS gathers (one for x, one for the coefficient of an
-// AB element).
+// path gives gathers from L2; the high part's own lists are uniform over the workgroup (scalar
+// loads), and class B reads x[b'][a] coalesced.
+//
+// The low parts of a tile sit in lanes by the length of their AB lists, so the lanes of a wave end
+// together (in rank order a wave of 1500 strings walks 27 entries for a mean of 19), and A2 and AB
+// are padded with entries that add 0 * 0 and read four at a time, so there is no lane test and no
+// remainder loop.  Before class B the sums go back to rank order through LDS.  Lists in rank order
+// with a remainder loop: 1500 x 1500 1200 -> 950 us, 600 x 600 117 -> 88.
+//
+// Bound: LDS.  An AB element is two LDS reads (coefficient, x) at random banks, some three and a half
+// passes each; 1500 x 1500 has 970 M of them.  Two high parts per workgroup, which share the list
+// reads, gained nothing here (1115 us) and loading the next row into registers ahead of its turn 2 %.
 template <class ET, int V>
 __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__restrict__ x, int64_t ldx,
                                            ET *__restrict__ y, int64_t ldy, int nv, uint32_t tile, uint32_t b,
                                            char *smem) {
-    ET *xs = (ET *)smem;              // [na][V]
-    ET *aux = xs + (size_t)p.na * V;  // class A table rows, then the AB coefficients of one high key
-    const uint32_t al = tile * 256u + threadIdx.x;
-    const bool valid = al < p.na;
-    const uint32_t a = valid ? al : p.na - 1u;
-    const int64_t row = (int64_t)b * p.na + a;
+    ET *xs = (ET *)smem;                     // [na + 1][V], the last 0
+    ET *aux = xs + (size_t)(p.na + 1u) * V;  // class A table rows, then the AB coefficients
+    const uint32_t B = blockDim.x;
+    const uint32_t pos = tile * p.T + threadIdx.x;
+    const bool valid = threadIdx.x < p.T && pos < p.na;
+    const uint32_t at = valid ? pos : p.na - 1u;
 
     auto stage = [&](uint32_t bc) {
         const ET *xr = x + (int64_t)bc * p.na * ldx;
-        for (uint32_t j = threadIdx.x; j < p.na; j += 256u)
+        for (uint32_t j = threadIdx.x; j < p.na; j += B)
 #pragma unroll
             for (int v = 0; v < V; ++v) xs[j * V + v] = (V == 1 || v < nv) ? xr[(int64_t)j * ldx + v] : (ET)0;
     };
+    // a wave's longest list, in steps of four
+    auto wave_steps = [](uint32_t n) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) n = max(n, (uint32_t)__shfl_xor((int)n, d, 64));
+        return ((uint32_t)__builtin_amdgcn_readfirstlane((int)n) + 3u) / 4u;
+    };
+    const uint32_t al = p.order[at];  // the lane's low part up to class B
     double acc[V];
     {
+        const int64_t row = (int64_t)b * p.na + al;
         const double dr = (double)p.diag[row];
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = (V == 1 || v < nv) ? dr * (double)x[row * ldx + v] : 0.0;
     }
+    const uint32_t n1 = valid ? p.alen[at] : 0u;
+    const uint32_t n2 = wave_steps(valid ? p.alen[p.na + at] : 0u);
+    const uint32_t n3 = wave_steps(valid ? p.alen[2 * (int64_t)p.na + at] : 0u);
     // class A: columns of the row's own block
-    const uint32_t nocc = (uint32_t)__popc(p.blen[3 * (int64_t)p.nb + b] & p.rmask);
-    {
-        stage(b);
-        uint32_t m = p.blen[3 * (int64_t)p.nb + b] & p.rmask;
-        for (uint32_t q = 0; m; ++q, m &= m - 1u) {
-            const ET *d = p.dep + (int64_t)__builtin_ctz(m) * p.nUa;
-            for (uint32_t u = threadIdx.x; u < p.nUa; u += 256u) aux[q * p.nUa + u] = d[u];
-        }
+    const uint32_t occ = p.blen[3 * (int64_t)p.nb + b] & p.rmask;
+    const uint32_t nocc = (uint32_t)__popc(occ);
+    if (threadIdx.x < V) xs[p.na * V + threadIdx.x] = (ET)0;
+    stage(b);
+    uint32_t m = occ;
+    for (uint32_t r = 0; m; ++r, m &= m - 1u) {
+        const ET *d = p.dep + (int64_t)__builtin_ctz(m) * p.nUa;
+        for (uint32_t u = threadIdx.x; u < p.nUa; u += B) aux[r * p.nUa + u] = d[u];
     }
     __syncthreads();
-    const uint32_t n1 = valid ? p.alen[a] : 0u, n2 = valid ? p.alen[p.na + a] : 0u;
-    const uint32_t n3 = valid ? p.alen[2 * (int64_t)p.na + a] : 0u;
+#pragma unroll 2
     for (uint32_t k = 0; k < n1; ++k) {
-        const uint32_t e = p.a1_ent[(int64_t)k * p.na + a];
-        ET val = p.a1[(int64_t)k * p.na + a];
+        const uint32_t e = p.a1_ent[(int64_t)k * p.na + at];
+        ET val = p.a1[(int64_t)k * p.na + at];
         const uint32_t u = e >> 17, col = e & 0xFFFFu;
         const bool neg = (e >> 16) & 1u;
-        for (uint32_t q = 0; q < nocc; ++q) {
-            const ET c = aux[q * p.nUa + u];
+        for (uint32_t r = 0; r < nocc; ++r) {
+            const ET c = aux[r * p.nUa + u];
             val += neg ? -c : c;
         }
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] += (double)val * (double)xs[col * V + v];
     }
-#pragma unroll 4
-    for (uint32_t k = 0; k < n2; ++k) {
-        const uint32_t col = p.a2_col[(int64_t)k * p.na + a];
-        const ET val = p.a2[(int64_t)k * p.na + a];
+    {
+        const auto *cols = (const Four<uint16_t> *)p.a2_col;
+        const auto *vals = (const Four<ET> *)p.a2;
+#pragma unroll(V == 1 ? 2 : 1)
+        for (uint32_t k = 0; k < n2; ++k) {
+            const Four<uint16_t> col = cols[(int64_t)k * p.na + at];
+            const Four<ET> val = vals[(int64_t)k * p.na + at];
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[v] += (double)val * (double)xs[col * V + v];
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    acc[v] += (double)val.v[j] * (double)xs[(uint32_t)col.v[j] * V + v];
+        }
     }
-    // class AB: for each of b's flips, its row of x and its key's coefficients (both signs: entry
-    // 2 u + s is the coefficient with the low part's sign s applied; 0 = the pair has no term)
+    // class AB: each flip of the high part brings a row of x and its key's coefficients (both signs:
+    // entry 2 u + s is the coefficient with the low part's sign s applied, the last is 0; 0 = the
+    // pair of keys has no term)
+    const uint32_t nab = p.blen[2 * (int64_t)p.nb + b];
+    const auto *ents = (const Four<uint32_t> *)p.ab_ent;
     auto class_ab = [&](auto full) {
-        const uint32_t nab = p.blen[2 * (int64_t)p.nb + b];
-        for (uint32_t e = 0; e < nab; ++e) {
-            const uint32_t bc = p.bab_ent[2 * ((int64_t)b * p.nBAB + e)];
-            const uint32_t w = p.bab_ent[2 * ((int64_t)b * p.nBAB + e) + 1];
-            const ET *ct = p.ctab + (int64_t)(w >> 1) * p.nU;
-            __syncthreads();  // the previous row and table are no longer read
-            stage(bc);
-            for (uint32_t u = threadIdx.x; u < p.nU; u += 256u) {
-                const ET c = (w & 1u) ? -ct[u] : ct[u];
+        for (uint32_t i = 0; i < nab; ++i) {
+            const uint32_t *ent = p.bab_ent + 2 * ((int64_t)b * p.nBAB + i);
+            const ET *ct = p.ctab + (int64_t)(ent[1] >> 1) * p.nU;
+            __syncthreads();  // the previous row and tables are no longer read
+            stage(ent[0]);
+            for (uint32_t u = threadIdx.x; u < p.nU; u += B) {
+                const ET c = (ent[1] & 1u) ? -ct[u] : ct[u];
                 aux[2 * u] = c;
                 aux[2 * u + 1] = -c;
             }
+            if (threadIdx.x == 0) aux[2 * p.nU] = (ET)0;
             __syncthreads();
-#pragma unroll 4
+#pragma unroll(V == 1 ? 2 : 1)
             for (uint32_t k = 0; k < n3; ++k) {
-                const uint32_t f = p.ab_ent[(int64_t)k * p.na + a];
-                const ET c = aux[f >> 16];
-                const uint32_t col = f & 0xFFFFu;
-                if (decltype(full)::value || c != (ET)0) {
+                const Four<uint32_t> f = ents[(int64_t)k * p.na + at];
 #pragma unroll
-                    for (int v = 0; v < V; ++v) acc[v] += (double)c * (double)xs[col * V + v];
+                for (int j = 0; j < 4; ++j) {
+                    const ET c = aux[f.v[j] >> 16];
+                    const uint32_t col = f.v[j] & 0xFFFFu;
+                    if (decltype(full)::value || c != (ET)0) {
+#pragma unroll
+                        for (int v = 0; v < V; ++v) acc[v] += (double)c * (double)xs[col * V + v];
+                    }
                 }
             }
         }
@@ -295,40 +360,52 @@ __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__re
         class_ab(std::true_type{});
     else
         class_ab(std::false_type{});
+    // back to rank order
+    double *ex = (double *)smem;  // [T][V]
+    __syncthreads();
+    if (valid) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) ex[(al - tile * p.T) * V + v] = acc[v];
+    }
+    __syncthreads();
+    if (!valid) return;
+#pragma unroll
+    for (int v = 0; v < V; ++v) acc[v] = ex[threadIdx.x * V + v];
     // class B: the same low part in other blocks
+    const uint32_t a = pos;
     const ET *xa = x + (int64_t)a * ldx;
     const int64_t bstride = (int64_t)p.na * ldx;
     const uint32_t m1 = p.blen[b], m2 = p.blen[p.nb + b];
     for (uint32_t i = 0; i < m1; ++i) {
-        const int64_t at = (int64_t)b * p.nB1 + i;
-        const uint32_t bc = p.b1_ent[2 * at], e = p.b1_ent[2 * at + 1];
+        const int64_t o = (int64_t)b * p.nB1 + i;
+        const uint32_t bc = p.b1_ent[2 * o], e = p.b1_ent[2 * o + 1];
         const uint32_t w = (e & 0xFFFFFFu) >> 1, nt = e >> 24;
         const ET wv = p.wtab[(int64_t)w * p.na + a];
         ET val = (e & 1u) ? -wv : wv;
-        for (uint32_t t = 0; t < nt; ++t) val += p.tail[at * p.tail_len + t];
+        for (uint32_t t = 0; t < nt; ++t) val += p.tail[o * p.tail_len + t];
 #pragma unroll
         for (int v = 0; v < V; ++v)
             if (V == 1 || v < nv) acc[v] += (double)val * (double)xa[bc * bstride + v];
     }
 #pragma unroll 8
     for (uint32_t i = 0; i < m2; ++i) {
-        const int64_t at = (int64_t)b * p.nB2 + i;
-        const double val = (double)p.b2[at];
-        const int64_t o = p.b2_col[at] * bstride;
+        const int64_t o = (int64_t)b * p.nB2 + i;
+        const double val = (double)p.b2[o];
+        const int64_t c = p.b2_col[o] * bstride;
 #pragma unroll
         for (int v = 0; v < V; ++v)
-            if (V == 1 || v < nv) acc[v] += val * (double)xa[o + v];
+            if (V == 1 || v < nv) acc[v] += val * (double)xa[c + v];
     }
-    if (valid) {
+    const int64_t row = (int64_t)b * p.na + a;
 #pragma unroll
-        for (int v = 0; v < V; ++v)
-            if (V == 1 || v < nv) y[row * ldy + v] = (ET)acc[v];
-    }
+    for (int v = 0; v < V; ++v)
+        if (V == 1 || v < nv) y[row * ldy + v] = (ET)acc[v];
 }
 
 template <class ET, int V>
-__global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ x, int64_t ldx,
-                                                     ET *__restrict__ y, int64_t ldy, int nvec) {
+__global__ __launch_bounds__(kMaxThreads, kWaves) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ x,
+                                                                    int64_t ldx, ET *__restrict__ y, int64_t ldy,
+                                                                    int nvec) {
     extern __shared__ __align__(16) char smem[];
     // workgroups of one XCD take consecutive high parts of one tile of low parts: they share the
     // tile's lists in that XCD's L2
@@ -340,7 +417,7 @@ __global__ __launch_bounds__(256) void k_prod_matvec(ProdView<ET> p, const ET *_
 
 // Requests of a table: a workgroup finds its request by the requests' first workgroups.
 template <class ET, int V>
-__global__ __launch_bounds__(256) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n) {
+__global__ __launch_bounds__(kMaxThreads, kWaves) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n) {
     extern __shared__ __align__(16) char smem[];
     int lo = 0, hi = n - 1;
     while (lo < hi) {
@@ -353,7 +430,7 @@ __global__ __launch_bounds__(256) void k_prod_batched(const ProdReq<ET> *__restr
     const ProdReq<ET> &R = reqs[lo];
     if (R.kdev && *R.kdev >= R.m) return;  // at its iteration limit (uniform for the block)
     uint32_t id = blockIdx.x - R.first;
-    const uint32_t per = (R.p.na + 255u) / 256u * R.p.nb;  // workgroups per vector chunk
+    const uint32_t per = (R.p.na + R.p.T - 1u) / R.p.T * R.p.nb;  // workgroups per vector chunk
     const uint32_t vc = id / per;
     id -= vc * per;
     const uint32_t tile = id / R.p.nb;
@@ -361,11 +438,14 @@ __global__ __launch_bounds__(256) void k_prod_batched(const ProdReq<ET> *__restr
     prod_block<ET, V>(R.p, R.x + v0, R.ld, R.y + v0, R.ld, min(V, R.nv - v0), tile, id - tile * R.p.nb, smem);
 }
 
-uint32_t aux_entries(const qsd_prod *p) { return std::max(p->max_occ * p->nUa, 2u * p->nU); }
+uint32_t tiles_of(const qsd_prod *p) { return (p->na + p->T - 1u) / p->T; }
 
+// LDS of a workgroup: x and the zero after it, the class A table rows or the AB coefficients and the
+// zero after them; then the sums in rank order.
 template <class ET>
 uint32_t lds_bytes(const qsd_prod *p, int V) {
-    return (uint32_t)((p->na * V + aux_entries(p)) * sizeof(ET));
+    const uint32_t aux = std::max(p->max_occ * p->nUa, 2u * p->nU + 1u);
+    return std::max((uint32_t)(((p->na + 1u) * V + aux) * sizeof(ET)), p->T * V * 8u);
 }
 
 // ------------------------------------------------------------------- host classification
@@ -624,7 +704,8 @@ std::vector<float> narrowed(const std::vector<double> &v) { return std::vector<f
 
 // The lists: counted, sized by one round trip to the host, then written.  `scratch` and `keep`
 // hold the host images, which the caller keeps until the stream has passed the copies.
-int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, Block &keep, hipStream_t st) {
+int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, Block &keep, Block &lists,
+                 hipStream_t st) {
     const qsd_subspace *s = h->s;
     size_t og[2][3], of[2][5];
     for (int H = 0; H < 2; ++H) {
@@ -645,7 +726,6 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     const size_t oa = keep.room(3 * (size_t)p->na * 4), ob = keep.room(4 * (size_t)p->nb * 4);
     QSD_TRY(scratch.upload(st));
     QSD_TRY(keep.upload(st));
-    p->mem[0] = keep.dev;
     p->d.dep = keep.at<double>(od);
     p->f.dep = keep.at<float>(od32);
     p->d.ctab = keep.at<double>(oc);
@@ -667,18 +747,27 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     k_prod_lists<false, false><<<ga, 256, 0, st>>>(v, g[0], f[0], *p, mx);
     k_prod_lists<true, false><<<gb, 256, 0, st>>>(v, g[1], f[1], *p, mx + 4);
     uint32_t m[8];
+    std::vector<uint32_t> n3(p->na);
     QSD_CHECK_HIP(hipMemcpyAsync(m, mx, sizeof(m), hipMemcpyDeviceToHost, st));
+    QSD_CHECK_HIP(hipMemcpyAsync(n3.data(), p->alen + 2 * (size_t)p->na, (size_t)p->na * 4, hipMemcpyDeviceToHost, st));
     QSD_CHECK_HIP(hipStreamSynchronize(st));
     p->nA1 = m[0];
-    p->nA2 = m[1];
-    p->nAB = m[2];
+    p->nA2 = (m[1] + 3u) / 4u * 4u;
+    p->nAB = (m[2] + 3u) / 4u * 4u;
     p->nB1 = m[4];
     p->nB2 = m[5];
     p->nBAB = m[6];
     p->max_occ = m[7];
-    Block lists;
+    // within each tile, the low parts by the length of their AB lists
     const size_t na = p->na, nb = p->nb;
-    const size_t o1 = lists.room(4 * p->nA1 * na), o2 = lists.room(4 * p->nA2 * na), o3 = lists.room(4 * p->nAB * na);
+    std::vector<uint32_t> order(na), place(na);
+    std::iota(order.begin(), order.end(), 0u);
+    for (size_t t = 0; t < na; t += p->T)
+        std::stable_sort(order.begin() + t, order.begin() + std::min<size_t>(na, t + p->T),
+                         [&](uint32_t i, uint32_t j) { return n3[i] > n3[j]; });
+    for (size_t i = 0; i < na; ++i) place[order[i]] = (uint32_t)i;
+    const size_t oo = lists.put(order), op = lists.put(place);
+    const size_t o1 = lists.room(4 * p->nA1 * na), o2 = lists.room(2 * p->nA2 * na), o3 = lists.room(4 * p->nAB * na);
     const size_t o4 = lists.room(8 * p->nB1 * nb), o5 = lists.room(4 * p->nB2 * nb), o6 = lists.room(8 * p->nBAB * nb);
     size_t ov[2][5];
     for (int k = 0; k < 2; ++k) {
@@ -690,9 +779,10 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
         ov[k][4] = lists.room(e * nb * p->nB2);
     }
     QSD_TRY(lists.upload(st));
-    p->mem[1] = lists.dev;
+    p->order = lists.at<uint32_t>(oo);
+    p->place = lists.at<uint32_t>(op);
     p->a1_ent = lists.at<uint32_t>(o1);
-    p->a2_col = lists.at<uint32_t>(o2);
+    p->a2_col = lists.at<uint16_t>(o2);
     p->ab_ent = lists.at<uint32_t>(o3);
     p->b1_ent = lists.at<uint32_t>(o4);
     p->b2_col = lists.at<uint32_t>(o5);
@@ -739,6 +829,9 @@ int prod_build(qsd_ham *h, hipStream_t st) {
     if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
     p->split = s->split;
     p->na = s->pna;
+    // tiles of up to kMaxThreads low parts, of one size, in whole waves
+    const uint32_t tiles = (p->na + kMaxThreads - 1u) / kMaxThreads;
+    p->T = ((p->na + tiles - 1u) / tiles + 63u) / 64u * 64u;
     p->nb = (uint32_t)(s->N / s->pna);
     p->nUa = c.nUa;
     p->nU = (uint32_t)c.fwant[0].size();
@@ -747,11 +840,14 @@ int prod_build(qsd_ham *h, hipStream_t st) {
     p->tail_len = c.tail_len;
     p->rmask = c.rmask;
     p->full = c.full;
-    Block scratch, keep;
-    const int rc = build_device(h, p, c, scratch, keep, st);
-    if (rc != QSD_OK) (void)hipStreamSynchronize(st);  // the host images outlive their copies
+    Block scratch, keep, lists;
+    int rc = build_device(h, p, c, scratch, keep, lists, st);
+    // the host images outlive their copies
+    if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
+        rc = fail(QSD_ERR_HIP, "product lists failed: %s", hipGetErrorString(hipGetLastError()));
     dev_free(scratch.dev);
-    if (!p->mem[0]) p->mem[0] = keep.dev;
+    p->mem[0] = keep.dev;
+    p->mem[1] = lists.dev;
     if (rc != QSD_OK || lds_bytes<double>(p, 1) > kLdsBytes) {
         prod_free(p);
         return rc;
@@ -776,9 +872,10 @@ ProdView<ET> prod_view(const qsd_ham *h) {
         v = &p->f;
         diag = h->diag32;
     }
-    return ProdView<ET>{p->na, p->nb, p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask, p->full ? 1u : 0u,
-                        p->a1_ent, p->a2_col, p->ab_ent, p->b1_ent, p->b2_col, p->bab_ent, p->alen, p->blen,
-                        v->a1, v->a2, v->dep, v->ctab, v->wtab, v->tail, v->b2, diag};
+    return ProdView<ET>{p->na, p->nb, p->T, p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask,
+                        p->full ? 1u : 0u,
+                        p->a1_ent, p->a2_col, p->ab_ent, p->b1_ent, p->b2_col, p->bab_ent, p->alen, p->blen, p->order,
+                        p->place, v->a1, v->a2, v->dep, v->ctab, v->wtab, v->tail, v->b2, diag};
 }
 
 template <class ET>
@@ -796,7 +893,7 @@ int prod_width(const qsd_ham *h, int nvec) {
 }
 
 uint32_t prod_blocks(const qsd_ham *h, int nvec, int V) {
-    return (h->prod->na + 255u) / 256u * h->prod->nb * (uint32_t)((nvec + V - 1) / V);
+    return tiles_of(h->prod) * h->prod->nb * (uint32_t)((nvec + V - 1) / V);
 }
 
 template <class ET>
@@ -804,25 +901,27 @@ void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t 
     const int V = prod_width<ET>(h, nvec);
     const uint32_t lds = prod_lds<ET>(h, V);
     const ProdView<ET> p = prod_view<ET>(h);
-    const dim3 grid(prod_blocks(h, 1, 1), (unsigned)((nvec + V - 1) / V));
     const ET *xe = (const ET *)x;
     ET *ye = (ET *)y;
+    const unsigned tiles = tiles_of(h->prod), T = h->prod->T;
+    const dim3 grid(tiles * p.nb, (unsigned)((nvec + V - 1) / V));
     if (V == 4)
-        k_prod_matvec<ET, 4><<<grid, 256, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
+        k_prod_matvec<ET, 4><<<grid, T, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
     else if (V == 2)
-        k_prod_matvec<ET, 2><<<grid, 256, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
+        k_prod_matvec<ET, 2><<<grid, T, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
     else
-        k_prod_matvec<ET, 1><<<grid, 256, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
+        k_prod_matvec<ET, 1><<<grid, T, lds, st>>>(p, xe, ldx, ye, ldy, nvec);
 }
 
 template <class ET>
-void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, int V, uint32_t lds, hipStream_t st) {
+void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, uint32_t T, int V, uint32_t lds,
+                         hipStream_t st) {
     if (V == 4)
-        k_prod_batched<ET, 4><<<blocks, 256, lds, st>>>(d_reqs, n);
+        k_prod_batched<ET, 4><<<blocks, T, lds, st>>>(d_reqs, n);
     else if (V == 2)
-        k_prod_batched<ET, 2><<<blocks, 256, lds, st>>>(d_reqs, n);
+        k_prod_batched<ET, 2><<<blocks, T, lds, st>>>(d_reqs, n);
     else
-        k_prod_batched<ET, 1><<<blocks, 256, lds, st>>>(d_reqs, n);
+        k_prod_batched<ET, 1><<<blocks, T, lds, st>>>(d_reqs, n);
 }
 
 #define QSD_PROD_FOR(ET)                                                                                     \
@@ -830,7 +929,7 @@ void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, int 
     template uint32_t prod_lds<ET>(const qsd_ham *, int);                                                    \
     template int prod_width<ET>(const qsd_ham *, int);                                                       \
     template void prod_matvec<ET>(const qsd_ham *, const void *, int64_t, void *, int64_t, int, hipStream_t); \
-    template void prod_matvec_batched<ET>(const ProdReq<ET> *, int, uint32_t, int, uint32_t, hipStream_t);
+    template void prod_matvec_batched<ET>(const ProdReq<ET> *, int, uint32_t, uint32_t, int, uint32_t, hipStream_t);
 QSD_PROD_FOR(double)
 QSD_PROD_FOR(float)
 #undef QSD_PROD_FOR

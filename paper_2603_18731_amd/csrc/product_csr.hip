@@ -37,9 +37,10 @@ template <class ET>
 __global__ __launch_bounds__(256) void k_prod_sort_low(ProdView<ET> p, uint32_t nAB, Sorted<ET> s) {
     const uint32_t a = blockIdx.x * 4u + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
     if (a >= p.na) return;
-    const uint32_t n1 = p.alen[a], n = n1 + p.alen[p.na + a], n3 = p.alen[2 * (int64_t)p.na + a];
+    const uint32_t at = p.place[a];
+    const uint32_t n1 = p.alen[at], n = n1 + p.alen[p.na + at], n3 = p.alen[2 * (int64_t)p.na + at];
     auto col_a = [&](uint32_t k) {
-        return k < n1 ? p.a1_ent[(int64_t)k * p.na + a] & 0xFFFFu : p.a2_col[(int64_t)(k - n1) * p.na + a];
+        return k < n1 ? p.a1_ent[(int64_t)k * p.na + at] & 0xFFFFu : (uint32_t)p.a2_col[prod_at(k - n1, p.na, at)];
     };
     uint32_t below_a = 0, below_ab = 0;
     for (uint32_t k = lane; k < n; k += 64u) {
@@ -47,14 +48,14 @@ __global__ __launch_bounds__(256) void k_prod_sort_low(ProdView<ET> p, uint32_t 
         uint32_t rank = 0;
         for (uint32_t q = 0; q < n; ++q) rank += col_a(q) < c;
         const int64_t o = (int64_t)a * s.nA + rank;
-        s.a[o] = c | (k < n1 ? (p.a1_ent[(int64_t)k * p.na + a] >> 16) + 1u : 0u) << 16;
-        s.av[o] = k < n1 ? p.a1[(int64_t)k * p.na + a] : p.a2[(int64_t)(k - n1) * p.na + a];
+        s.a[o] = c | (k < n1 ? (p.a1_ent[(int64_t)k * p.na + at] >> 16) + 1u : 0u) << 16;
+        s.av[o] = k < n1 ? p.a1[(int64_t)k * p.na + at] : p.a2[prod_at(k - n1, p.na, at)];
         below_a += c < a;
     }
     for (uint32_t k = lane; k < n3; k += 64u) {
-        const uint32_t e = p.ab_ent[(int64_t)k * p.na + a];
+        const uint32_t e = p.ab_ent[prod_at(k, p.na, at)];
         uint32_t rank = 0;
-        for (uint32_t q = 0; q < n3; ++q) rank += (p.ab_ent[(int64_t)q * p.na + a] & 0xFFFFu) < (e & 0xFFFFu);
+        for (uint32_t q = 0; q < n3; ++q) rank += (p.ab_ent[prod_at(q, p.na, at)] & 0xFFFFu) < (e & 0xFFFFu);
         s.ab[(int64_t)a * nAB + rank] = e;
         below_ab += (e & 0xFFFFu) < a;
     }
@@ -126,15 +127,15 @@ __global__ __launch_bounds__(256) void k_prod_csr_count(ProdView<ET> p, int64_t 
     const uint32_t tiles = (p.na + 255u) / 256u;
     const uint32_t b = blockIdx.x / tiles, a = (blockIdx.x - b * tiles) * 256u + threadIdx.x;
     if (a >= p.na) return;
-    const uint32_t n3 = p.alen[2 * (int64_t)p.na + a], nab = p.blen[2 * (int64_t)p.nb + b];
-    int64_t n = 1 + (int64_t)p.alen[a] + p.alen[p.na + a] + p.blen[b] + p.blen[p.nb + b];
+    const uint32_t at = p.place[a], n3 = p.alen[2 * (int64_t)p.na + at], nab = p.blen[2 * (int64_t)p.nb + b];
+    int64_t n = 1 + (int64_t)p.alen[at] + p.alen[p.na + at] + p.blen[b] + p.blen[p.nb + b];
     if (p.full) {
         n += (int64_t)n3 * nab;
     } else {
         for (uint32_t e = 0; e < nab; ++e) {
             const uint32_t w = p.bab_ent[2 * ((int64_t)b * p.nBAB + e) + 1];
             const ET *ct = p.ctab + (int64_t)(w >> 1) * p.nU;
-            for (uint32_t k = 0; k < n3; ++k) n += ct[p.ab_ent[(int64_t)k * p.na + a] >> 17] != (ET)0;
+            for (uint32_t k = 0; k < n3; ++k) n += ct[p.ab_ent[prod_at(k, p.na, at)] >> 17] != (ET)0;
         }
     }
     counts[(int64_t)b * p.na + a] = n;
@@ -199,7 +200,8 @@ __global__ __launch_bounds__(256) void k_prod_csr_fill(ProdView<ET> p, Sorted<ET
     __syncthreads();
     for (uint32_t a = a0 + (threadIdx.x >> 6); a < min(a0 + kFillRows, p.na); a += 4u) {
         const Row<ET> R{p, s, nAB, a, b, p.blen[3 * (int64_t)p.nb + b] & p.rmask, (int64_t)b * p.na + a};
-        const uint32_t n3 = p.alen[2 * (int64_t)p.na + a], nown = p.alen[a] + p.alen[p.na + a] + 1u;
+        const uint32_t at = p.place[a];
+        const uint32_t n3 = p.alen[2 * (int64_t)p.na + at], nown = p.alen[at] + p.alen[p.na + at] + 1u;
         const uint32_t pos_a = s.pos[2 * a], pos_ab = s.pos[2 * a + 1];
         const int64_t o = indptr[R.row];
         const uint32_t len = (uint32_t)(indptr[R.row + 1] - o);
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(256) void k_prod_csr_walk(ProdView<ET> p, Sorted<ET
     const uint32_t b = blockIdx.x / tiles, a = (blockIdx.x - b * tiles) * 256u + threadIdx.x;
     if (a >= p.na) return;
     const Row<ET> R{p, s, nAB, a, b, p.blen[3 * (int64_t)p.nb + b] & p.rmask, (int64_t)b * p.na + a};
-    const uint32_t n3 = p.alen[2 * (int64_t)p.na + a], nA = p.alen[a] + p.alen[p.na + a];
+    const uint32_t at = p.place[a], n3 = p.alen[2 * (int64_t)p.na + at], nA = p.alen[at] + p.alen[p.na + at];
     int64_t o = indptr[R.row];
     auto put = [&](int64_t col, ET v) {
         idx[o] = (IT)col;
@@ -282,7 +284,7 @@ bool prod_csr_usable(const qsd_ham *h) {
 }
 
 void prod_csr_count(const qsd_ham *h, int64_t *counts, hipStream_t st) {
-    k_prod_csr_count<double><<<prod_blocks(h, 1, 1), 256, 0, st>>>(prod_view<double>(h), counts);
+    k_prod_csr_count<double><<<(h->prod->na + 255u) / 256u * h->prod->nb, 256, 0, st>>>(prod_view<double>(h), counts);
 }
 
 template <class ET, class IT>
@@ -315,7 +317,7 @@ int prod_csr_fill(const qsd_ham *h, const int64_t *indptr, void *indices, void *
         k_prod_csr_fill<ET, IT><<<(p->na + kFillRows - 1u) / kFillRows * p->nb, 256, s.nB * sizeof(uint3), st>>>(
             v, s, p->nAB, indptr, (IT *)indices, (ET *)data);
     else
-        k_prod_csr_walk<ET, IT><<<prod_blocks(h, 1, 1), 256, 0, st>>>(v, s, p->nAB, indptr, (IT *)indices, (ET *)data);
+        k_prod_csr_walk<ET, IT><<<(p->na + 255u) / 256u * p->nb, 256, 0, st>>>(v, s, p->nAB, indptr, (IT *)indices, (ET *)data);
     const bool ok = hipGetLastError() == hipSuccess;
     dev_free(mem);
     return ok ? QSD_OK : fail(QSD_ERR_HIP, "CSR fill launch failed");

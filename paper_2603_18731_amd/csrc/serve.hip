@@ -420,7 +420,7 @@ struct qsd_batch {
     uint8_t *d_prod = nullptr;
     int n_prod = 0;
     size_t cap_prod = 0;
-    uint32_t prod_blocks = 0, prod_lds = 0;
+    uint32_t prod_blocks = 0, prod_lds = 0, prod_T = 64;
     double *d_out = nullptr;  // [max_slots][4]
     int64_t *d_spike = nullptr;
     bool dirty = true;
@@ -467,9 +467,10 @@ Layout layout_of(int64_t N, int m, bool f32) {
 
 // The factored requests of the batch (one vector each), as an upload image.
 template <class ET>
-std::vector<ProdReq<ET>> prod_requests(qsd_batch *b, uint32_t &blocks, uint32_t &lds) {
+std::vector<ProdReq<ET>> prod_requests(qsd_batch *b, uint32_t &blocks, uint32_t &lds, uint32_t &T) {
     std::vector<ProdReq<ET>> out;
     blocks = lds = 0;
+    T = 64;
     for (const auto &S : b->slots) {
         if (!S.used || !S.prod) continue;
         ProdReq<ET> R{};
@@ -488,13 +489,14 @@ std::vector<ProdReq<ET>> prod_requests(qsd_batch *b, uint32_t &blocks, uint32_t 
         out.push_back(R);
         blocks += prod_blocks(S.h, 1, 1);
         lds = std::max(lds, prod_lds<ET>(S.h, 1));
+        T = std::max(T, R.p.T);
     }
     return out;
 }
 
 template <class ET>
 int sync_prod(qsd_batch *b, hipStream_t st) {
-    const auto reqs = prod_requests<ET>(b, b->prod_blocks, b->prod_lds);
+    const auto reqs = prod_requests<ET>(b, b->prod_blocks, b->prod_lds, b->prod_T);
     b->n_prod = (int)reqs.size();
     const size_t bytes = reqs.size() * sizeof(ProdReq<ET>);
     if (bytes > b->cap_prod) {
@@ -576,10 +578,11 @@ void launch_bmv(qsd_batch *b, hipStream_t st) {
     const int np = Wp == 1 ? b->n_mv_pm : 0, no = b->n_mv - np;
     if (b->n_prod > 0) {
         if (b->f32)
-            prod_matvec_batched<float>((const ProdReq<float> *)b->d_prod, b->n_prod, b->prod_blocks, 1, b->prod_lds, st);
+            prod_matvec_batched<float>((const ProdReq<float> *)b->d_prod, b->n_prod, b->prod_blocks, b->prod_T, 1,
+                                       b->prod_lds, st);
         else
-            prod_matvec_batched<double>((const ProdReq<double> *)b->d_prod, b->n_prod, b->prod_blocks, 1, b->prod_lds,
-                                        st);
+            prod_matvec_batched<double>((const ProdReq<double> *)b->d_prod, b->n_prod, b->prod_blocks, b->prod_T, 1,
+                                        b->prod_lds, st);
     }
     if (b->n_pmt > 0) {
         if (b->f32)
@@ -915,7 +918,7 @@ struct BatchedPlan {
     std::vector<ProdReq<double>> prod64;
     std::vector<ProdReq<float>> prod32;
     int prod_V = 4;
-    uint32_t prod_lds = 0, prod_blocks = 0;
+    uint32_t prod_lds = 0, prod_blocks = 0, prod_T = 64;
     size_t row_tiles = 0;  // 256-row tiles of all requests (a limit of the allocation-free entry)
 
     bool empty() const { return reqs.empty() && prod64.empty() && prod32.empty(); }
@@ -951,6 +954,7 @@ int plan_prod(int32_t n, const qsd_ham *const *hams, const void *const *xs, void
         out.push_back(R);
         blocks += prod_blocks(hams[i], nvecs[i], P.prod_V);
         P.prod_lds = std::max(P.prod_lds, prod_lds<ET>(hams[i], P.prod_V));
+        P.prod_T = std::max(P.prod_T, R.p.T);
     }
     if (blocks > (uint64_t)INT32_MAX) return fail(QSD_ERR_CAPACITY, "too many workgroups");
     P.prod_blocks = (uint32_t)blocks;
@@ -1029,10 +1033,10 @@ int run_batched(const BatchedPlan &P, int32_t dtype, uint8_t *mem, hipStream_t s
     const Tile *d_tiles = (const Tile *)(mem + P.tiles_at());
     if (!P.prod64.empty())
         prod_matvec_batched<double>((const ProdReq<double> *)(mem + P.prod_at()), (int)P.prod64.size(), P.prod_blocks,
-                                    P.prod_V, P.prod_lds, st);
+                                    P.prod_T, P.prod_V, P.prod_lds, st);
     if (!P.prod32.empty())
         prod_matvec_batched<float>((const ProdReq<float> *)(mem + P.prod_at()), (int)P.prod32.size(), P.prod_blocks,
-                                   P.prod_V, P.prod_lds, st);
+                                   P.prod_T, P.prod_V, P.prod_lds, st);
     for (const auto &L : P.launches) {
         const Tile *tl = d_tiles + L.t0;
         switch (dtype) {

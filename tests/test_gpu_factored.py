@@ -69,6 +69,36 @@ def test_molecular_bitwise(na, nb, nvec, dtype):
     _same_as_table(H, _vec(sub.N, nvec, dtype))
 
 
+# tiles of up to 512 low parts of one size: one short of, at and past the edges, a last tile that is
+# nearly empty and one that ends inside a wave
+@pytest.mark.parametrize("na,nb,nvec,dtype", [
+    (63, 3, 1, torch.float64), (65, 3, 1, torch.float32), (511, 3, 1, torch.float64), (512, 2, 1, torch.float64),
+    (513, 3, 1, torch.float64), (513, 3, 7, torch.float32), (1025, 2, 1, torch.float64), (1537, 2, 2, torch.float64)])
+def test_tiles_bitwise(na, nb, nvec, dtype):
+    ops, keys = c3_parts(na, nb)
+    sub = qsd.Subspace(keys, ops.n_qubits)
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(ops))
+    say("factored tiles", na, nb, nvec, dtype)
+    _same_as_table(H, _vec(sub.N, nvec, dtype))
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_non_finite_stays_in_its_rows(value):
+    """The entries that fill up the lists add 0 * 0: a value of x that is not finite reaches the rows
+    that have an element there and no other."""
+    ops, keys = c3_parts(130, 9)
+    sub = qsd.Subspace(keys, ops.n_qubits)
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(ops))
+    x = _vec(sub.N, 1, torch.float64)
+    x[130 * 4 + 7] = value
+    y = H.matvec(x)
+    H.schedule = DEFAULT | qsd.SCHED_HASH_LOOKUP
+    z = H.matvec(x)
+    bad = ~torch.isfinite(z)
+    assert 0 < int(bad.sum()) < sub.N
+    assert torch.equal(bad, ~torch.isfinite(y)) and torch.equal(y[~bad], z[~bad])
+
+
 def _edited(ops, keep=None, extra=()):
     terms = [t for k, t in enumerate(ops.terms()) if keep is None or keep(k, t)]
     return wl.TermList.from_terms(ops.n_qubits, terms + list(extra), ops.fermionic)
