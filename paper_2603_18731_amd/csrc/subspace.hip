@@ -67,6 +67,27 @@ __global__ __launch_bounds__(kBlock) void k_scan_add(int64_t *__restrict__ out, 
         if (base + k < n) out[base + k] += add;
 }
 
+// Elements of scratch that the tile sums of a scan of n elements need, over all levels.
+int64_t scan_scratch(int64_t n) {
+    int64_t total = 0;
+    while (n > kScanTile) {
+        n = (n + kScanTile - 1) / kScanTile;
+        total += n;
+    }
+    return total;
+}
+
+void scan_enqueue(const int64_t *in, int64_t *out, int64_t n, int64_t *scratch, hipStream_t st) {
+    const int64_t tiles = (n + kScanTile - 1) / kScanTile;
+    if (tiles <= 1) {
+        if (n > 0) k_scan_tiles<<<1, kBlock, 0, st>>>(in, out, n, nullptr);
+        return;
+    }
+    k_scan_tiles<<<(unsigned)tiles, kBlock, 0, st>>>(in, out, n, scratch);
+    scan_enqueue(scratch, scratch, tiles, scratch + tiles, st);
+    k_scan_add<<<(unsigned)tiles, kBlock, 0, st>>>(out, n, scratch);
+}
+
 // ------------------------------------------------------------------------ ingest
 
 // Row-major [n][W] -> word planes [Wp][n] (padding words zero) and per-word OR / AND.
@@ -99,8 +120,13 @@ __global__ __launch_bounds__(kBlock) void k_ingest(const uint64_t *__restrict__ 
     }
     __syncthreads();
     if (threadIdx.x < Wp) {
-        atomicOr(&or_and[threadIdx.x], s_or[threadIdx.x]);
-        atomicAnd(&or_and[kMaxWords + threadIdx.x], s_and[threadIdx.x]);
+        // the words only gain (lose) bits, so an old value that has them all needs no atomic: most
+        // workgroups end without one
+        unsigned long long *o = &or_and[threadIdx.x], *a = &or_and[kMaxWords + threadIdx.x];
+        if (s_or[threadIdx.x] & ~__hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicOr(o, s_or[threadIdx.x]);
+        if (~s_and[threadIdx.x] & __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicAnd(a, s_and[threadIdx.x]);
     }
 }
 
@@ -180,6 +206,203 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint64_t *__restric
             for (int w = 0; w < Wp; ++w) dst[(int64_t)w * n + o] = src[(int64_t)w * n + i];
         }
     }
+}
+
+// ------------------------------------------------------------------------ merge sort
+//
+// Tiles of 32 KB of keys (four workgroups per CU) sorted in LDS, then passes that merge pairs of
+// runs.  Only 16-bit indices move in LDS; the keys stay where they were loaded and are written out
+// once per pass.  Bound by the chain of LDS reads of the merging threads.
+template <int Wp>
+struct MergeTile {
+    static constexpr int kKeys = 4096 / Wp, kItems = kKeys / kBlock;  // 16, 8, 4, 2, 1 per thread
+    uint64_t key[kKeys * Wp];
+    uint16_t idx[2][kKeys];
+};
+
+template <int Wp>
+__device__ __forceinline__ bool key_after(const uint64_t (&a)[Wp], const uint64_t (&b)[Wp]) {  // a > b
+    bool gt = false, eq = true;
+#pragma unroll
+    for (int w = Wp - 1; w >= 0; --w) {
+        gt |= eq && a[w] > b[w];
+        eq &= a[w] == b[w];
+    }
+    return gt;
+}
+
+// Outputs [o, o + n) of the merge of the runs `a` (la keys) and `b` (lb keys) of indices into key[].
+template <int Wp>
+__device__ __forceinline__ void merge_lds(const uint64_t *key, const uint16_t *a, int la, const uint16_t *b, int lb, int o,
+                                          int n, uint16_t *out) {
+    auto load = [&](int i, uint64_t(&k)[Wp]) {
+#pragma unroll
+        for (int w = 0; w < Wp; ++w) k[w] = key[i * Wp + w];
+    };
+    uint64_t ka[Wp], kb[Wp];
+    // how many of the first o outputs come from a
+    int lo = max(0, o - lb), hi = min(o, la);
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        load(a[mid], ka);
+        load(b[o - 1 - mid], kb);
+        if (key_after<Wp>(ka, kb))
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    int i = lo, j = o - lo;
+    uint16_t ia = i < la ? a[i] : (uint16_t)0, ib = j < lb ? b[j] : (uint16_t)0;
+    load(ia, ka);
+    load(ib, kb);
+    for (int k = 0; k < n; ++k) {
+        const bool from_b = i >= la || (j < lb && key_after<Wp>(ka, kb));
+        out[o + k] = from_b ? ib : ia;
+        if (from_b) {
+            ++j;
+            if (j < lb) load(ib = b[j], kb);
+        } else {
+            ++i;
+            if (i < la) load(ia = a[i], ka);
+        }
+    }
+}
+
+template <int Wp>
+__global__ __launch_bounds__(kBlock) void k_sort_tiles(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
+                                                       int64_t n) {
+    using Tile = MergeTile<Wp>;
+    __shared__ Tile t;
+    const int64_t base = (int64_t)blockIdx.x * Tile::kKeys;
+    const int m = (int)min((int64_t)Tile::kKeys, n - base);
+    for (int w = 0; w < Wp; ++w)
+        for (int k = threadIdx.x; k < m; k += kBlock) t.key[k * Wp + w] = src[(int64_t)w * n + base + k];
+    for (int k = threadIdx.x; k < m; k += kBlock) t.idx[0][k] = (uint16_t)k;
+    __syncthreads();
+    int cur = 0;
+    for (int run = 1; run < m; run <<= 1) {
+        // a thread writes kItems outputs, which lie in one pair of runs or hold whole pairs
+        const int first = threadIdx.x * Tile::kItems;
+        for (int o = first; o < min(first + Tile::kItems, m);) {
+            const int pair = o / (2 * run) * (2 * run);
+            const int la = min(run, m - pair), lb = min(run, m - pair - la);
+            const int cnt = min(min(Tile::kItems, 2 * run), la + lb - (o - pair));
+            merge_lds<Wp>(t.key, &t.idx[cur][pair], la, &t.idx[cur][pair + la], lb, o - pair, cnt, &t.idx[cur ^ 1][pair]);
+            o += cnt;
+        }
+        cur ^= 1;
+        __syncthreads();
+    }
+    for (int w = 0; w < Wp; ++w)
+        for (int k = threadIdx.x; k < m; k += kBlock) dst[(int64_t)w * n + base + k] = t.key[t.idx[cur][k] * Wp + w];
+}
+
+// One pass: pairs of runs of `run` keys (a multiple of the tile) merged, a tile of outputs per
+// workgroup.  Two waves find the ends of its part of the first run, 64 positions at a time (a
+// bisection by one lane is 20 dependent reads of memory).
+template <int Wp>
+__global__ __launch_bounds__(kBlock) void k_merge_runs(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
+                                                       int64_t n, int64_t run) {
+    using Tile = MergeTile<Wp>;
+    __shared__ Tile t;
+    __shared__ int64_t split[2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t o0 = (int64_t)blockIdx.x * Tile::kKeys;
+    const int64_t pair = o0 / (2 * run) * (2 * run);
+    const int64_t la = min(run, n - pair), lb = min(run, n - pair - la);
+    const uint64_t *a = src + pair, *b = a + la;
+    const int64_t d0 = o0 - pair, d1 = min(d0 + Tile::kKeys, la + lb);
+    if (wave < 2) {
+        const int64_t d = wave == 0 ? d0 : d1;
+        int64_t lo = max((int64_t)0, d - lb), hi = min(d, la);
+        while (lo < hi) {
+            const int64_t len = hi - lo, step = (len + 63) / 64, i = lo + lane * step;
+            bool before = false;  // a[i] is among the first d
+            if (i < hi) {
+                uint64_t ka[Wp], kb[Wp];
+#pragma unroll
+                for (int w = 0; w < Wp; ++w) {
+                    ka[w] = a[(int64_t)w * n + i];
+                    kb[w] = b[(int64_t)w * n + d - 1 - i];
+                }
+                before = !key_after<Wp>(ka, kb);
+            }
+            const int c = __popcll(__ballot(before));  // lanes 0 .. c - 1
+            if (step == 1) {
+                lo += c;
+                break;
+            }
+            if (c == 0) {
+                hi = lo;
+            } else {
+                hi = min(hi, lo + (int64_t)c * step);
+                lo += (int64_t)(c - 1) * step + 1;
+            }
+        }
+        if (lane == 0) split[wave] = lo;
+    }
+    __syncthreads();
+    const int64_t i0 = split[0], j0 = d0 - i0;
+    const int na = (int)(split[1] - i0), m = (int)(d1 - d0);
+    for (int w = 0; w < Wp; ++w)
+        for (int k = threadIdx.x; k < m; k += kBlock)
+            t.key[k * Wp + w] = k < na ? a[(int64_t)w * n + i0 + k] : b[(int64_t)w * n + j0 + (k - na)];
+    for (int k = threadIdx.x; k < m; k += kBlock) t.idx[0][k] = (uint16_t)k;
+    __syncthreads();
+    const int o = threadIdx.x * Tile::kItems;
+    if (o < m) merge_lds<Wp>(t.key, &t.idx[0][0], na, &t.idx[0][na], m - na, o, min(Tile::kItems, m - o), t.idx[1]);
+    __syncthreads();
+    for (int w = 0; w < Wp; ++w)
+        for (int k = threadIdx.x; k < m; k += kBlock) dst[(int64_t)w * n + o0 + k] = t.key[t.idx[1][k] * Wp + w];
+}
+
+// Sorts the keys src[Wp][n] with the scratch tmp[Wp][n]; the result is in *out (one of the two).
+// `varies` = the bits that differ between keys.
+//
+// A radix pass (histogram, three scan launches, scatter: 40 us for 1M keys of 200 bits, 25 of them)
+// and a merge pass (20 us, ten of them and the tile sort) both read and write all keys, so the
+// number of passes decides; the tile sort counts as two.  Whole builds, radix / merge, in us: 36 bits
+// x 30 000 (5 digits, 3 merges) 332 / 341, 36 bits x 10M (5, 12) 2864 / 3363, 64 bits x 1M (8, 8)
+// 593 / 575, 100 bits x 100 000 (13, 6) 535 / 376, 200 bits x 1M (25, 10) 1948 / 986, 1000 bits x
+// 50 000 (125, 8) 6794 / 641.
+template <int Wp>
+int sort_keys(uint64_t *src, uint64_t *tmp, int64_t n, const uint64_t *varies, int W, uint64_t **out, hipStream_t st) {
+    int digits = 0, merges = 0;
+    for (int w = 0; w < W; ++w)
+        for (int d = 0; d < 8; ++d) digits += ((varies[w] >> (8 * d)) & 255u) != 0;
+    *out = src;
+    if (digits == 0) return QSD_OK;
+    using Tile = MergeTile<Wp>;
+    for (int64_t run = Tile::kKeys; run < n; run <<= 1) ++merges;
+    if (merges + 2 < digits) {
+        const unsigned tiles = (unsigned)((n + Tile::kKeys - 1) / Tile::kKeys);
+        k_sort_tiles<Wp><<<tiles, kBlock, 0, st>>>(src, tmp, n);
+        std::swap(src, tmp);
+        for (int64_t run = Tile::kKeys; run < n; run <<= 1) {
+            k_merge_runs<Wp><<<tiles, kBlock, 0, st>>>(src, tmp, n, run);
+            std::swap(src, tmp);
+        }
+        *out = src;
+        return QSD_OK;
+    }
+    const int64_t nblocks = (n + kRsTile - 1) / kRsTile;
+    int64_t *hist = nullptr;
+    QSD_TRY(dev_alloc(&hist, (size_t)(256 * nblocks + scan_scratch(256 * nblocks))));
+    for (int w = 0; w < W; ++w) {
+        for (int d = 0; d < 8; ++d) {
+            if (!((varies[w] >> (8 * d)) & 255u)) continue;  // digit equal in every key
+            k_rs_hist<<<(unsigned)nblocks, kBlock, 0, st>>>(src + (int64_t)w * n, n, 8 * d, hist, nblocks);
+            scan_enqueue(hist, hist, 256 * nblocks, hist + 256 * nblocks, st);
+            k_rs_scatter<Wp><<<(unsigned)nblocks, kBlock, 0, st>>>(src, tmp, n, w, 8 * d, hist, nblocks);
+            std::swap(src, tmp);
+        }
+    }
+    *out = src;
+    // the histogram must outlive the passes
+    int rc = QSD_OK;
+    if (hipStreamSynchronize(st) != hipSuccess) rc = fail(QSD_ERR_HIP, "sort failed: %s", hipGetErrorString(hipGetLastError()));
+    dev_free(hist);
+    return rc;
 }
 
 // ------------------------------------------------------------------------ unique
@@ -431,23 +654,11 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             break;
         }
         if ((rc = dev_alloc(&tmp, (size_t)Wp * n_in)) != QSD_OK) break;
-        uint64_t *src = planes, *dst = tmp;
+        uint64_t *src = planes;
         if (!(flags & QSD_SUB_ASSUME_SORTED_UNIQUE)) {
-            const int64_t nblocks = (n_in + kRsTile - 1) / kRsTile;
-            int64_t *hist = nullptr;
-            if ((rc = dev_alloc(&hist, (size_t)256 * nblocks)) != QSD_OK) break;
-            for (int w = 0; w < W && rc == QSD_OK; ++w) {
-                const uint64_t varies = oa[w] ^ oa[kMaxWords + w];
-                for (int d = 0; d < 8; ++d) {
-                    if (!((varies >> (8 * d)) & 255u)) continue;  // digit equal in every key
-                    k_rs_hist<<<(unsigned)nblocks, kBlock, 0, st>>>(src + (int64_t)w * n_in, n_in, 8 * d, hist, nblocks);
-                    if ((rc = exclusive_scan_i64(hist, hist, 256 * nblocks, st)) != QSD_OK) break;
-                    k_rs_scatter<Wp><<<(unsigned)nblocks, kBlock, 0, st>>>(src, dst, n_in, w, 8 * d, hist, nblocks);
-                    std::swap(src, dst);
-                }
-            }
-            dev_free(hist);
-            if (rc != QSD_OK) break;
+            uint64_t varies[kMaxWords];
+            for (int w = 0; w < W; ++w) varies[w] = oa[w] ^ oa[kMaxWords + w];
+            if ((rc = sort_keys<Wp>(planes, tmp, n_in, varies, W, &src, st)) != QSD_OK) break;
         }
         // deduplicate
         int64_t *fl = nullptr, *pos = nullptr;
@@ -532,18 +743,12 @@ SubView view_of(const qsd_subspace *s) {
 
 int exclusive_scan_i64(const int64_t *d_in, int64_t *d_out, int64_t n, hipStream_t st) {
     if (n <= 0) return QSD_OK;
-    const int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles == 1) {
-        k_scan_tiles<<<1, kBlock, 0, st>>>(d_in, d_out, n, nullptr);
-        return hipGetLastError() == hipSuccess ? QSD_OK : fail(QSD_ERR_HIP, "scan launch failed");
-    }
     int64_t *sums = nullptr;
-    QSD_TRY(dev_alloc(&sums, tiles));
-    k_scan_tiles<<<(unsigned)tiles, kBlock, 0, st>>>(d_in, d_out, n, sums);
-    int rc = exclusive_scan_i64(sums, sums, tiles, st);
-    if (rc == QSD_OK) k_scan_add<<<(unsigned)tiles, kBlock, 0, st>>>(d_out, n, sums);
+    if (n > kScanTile) QSD_TRY(dev_alloc(&sums, scan_scratch(n)));
+    scan_enqueue(d_in, d_out, n, sums, st);
+    int rc = hipGetLastError() == hipSuccess ? QSD_OK : fail(QSD_ERR_HIP, "scan launch failed");
     // the scratch must outlive the kernels that use it
-    if (hipStreamSynchronize(st) != hipSuccess) rc = fail(QSD_ERR_HIP, "scan failed");
+    if (sums && hipStreamSynchronize(st) != hipSuccess) rc = fail(QSD_ERR_HIP, "scan failed");
     dev_free(sums);
     return rc;
 }
