@@ -1,10 +1,13 @@
-"""GPU parity of the canonical order of a subspace: sorted, deduplicated keys, exactly.
+"""GPU parity of what a new subspace and operator are set up with: sorted, deduplicated keys and the
+diagonal, exactly.
 
 The keys are sorted by digits or by merging sorted tiles (4096 words of keys), whichever takes fewer
 passes; the order of distinct keys is unique, so numpy's is the oracle.
 """
 import numpy as np
 import pytest
+
+import workloads as wl
 
 from _util import say
 
@@ -66,3 +69,46 @@ def test_sort_patterns(order):
         b[:, :-1] = b[0, :-1]
     say("sort", order)
     _check(np.ascontiguousarray(b), n_qubits)
+
+
+# the diagonal's runs: masks in one or two 32-bit words of the key, in the same words for any number of
+# terms, in more words, with projectors, and of a complex operator
+@pytest.mark.parametrize("n_qubits,kinds,seed", [
+    (12, "zz", 0), (40, "zz", 1), (40, "n", 2), (64, "zzzz", 3), (100, "zz n zzzz identity", 4), (200, "zz", 5),
+    (200, "zz n zzzz", 6), (500, "zz n", 7), (100, "zz n complex", 8)])
+def test_diagonal_exact(n_qubits, kinds, seed):
+    rng = np.random.default_rng(seed)
+    terms = []
+    for k in kinds.split():
+        for j in range(37):
+            c = float(rng.integers(-64, 65)) / 16 or 0.25
+            if k == "zz":  # neighbours: many terms in the same words
+                q = int(rng.integers(0, n_qubits - 1))
+                terms.append((c, [(q, wl.Z), (q + 1, wl.Z)][: 1 + j % 2]))
+            elif k == "zzzz":
+                terms.append((c, [(int(q), wl.Z) for q in sorted(rng.choice(n_qubits, 4, replace=False))]))
+            elif k == "n":
+                qs = sorted(rng.choice(n_qubits, 1 + j % 3, replace=False))
+                terms.append((c, [(int(q), (wl.P1, wl.P0, wl.Z)[(i + j) % 3]) for i, q in enumerate(qs)]))
+            elif k == "identity":
+                terms.append((c, []))
+                break
+            else:
+                terms.append((1j * c, [(j, wl.RAISE), (j + 1, wl.LOWER)]))
+    ops = wl.TermList.from_terms(n_qubits, terms, False)
+    b = np.unique(_bits(3000, n_qubits, seed)[:, ::-1], axis=0)[:, ::-1]
+    H = qsd.SubspaceHamiltonian(qsd.Subspace(torch.from_numpy(b.copy().view(np.int64)).cuda(), n_qubits),
+                                qsd.operator_from_termlist(ops))
+    got = H.diagonal().cpu().numpy()
+    want = np.zeros(len(b))
+    for c, word in terms:
+        if isinstance(c, complex):
+            continue
+        v = np.full(len(b), c)
+        for q, code in word:
+            bit = (b[:, q // 64] >> np.uint64(q % 64)) & np.uint64(1)
+            v *= {wl.Z: 1 - 2 * bit.astype(np.int64), wl.P1: bit.astype(np.int64),
+                  wl.P0: 1 - bit.astype(np.int64)}[code]
+        want += v
+    say("diagonal", n_qubits, kinds)
+    assert np.array_equal(got, want)
