@@ -212,11 +212,15 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint64_t *__restric
 //
 // Tiles of 32 KB of keys (four workgroups per CU) sorted in LDS, then passes that merge pairs of
 // runs.  Only 16-bit indices move in LDS; the keys stay where they were loaded and are written out
-// once per pass.  Bound by the chain of LDS reads of the merging threads.
+// once per pass.  Bound by the chain of LDS reads in which a thread finds its part of the two runs,
+// so threads are many and their outputs few: 1.1M keys of 200 bits, builds in us, with 4 outputs per
+// thread 1312 for keys as rows, 1137 as word planes (a row stride of 32 bytes uses 8 of the 64
+// banks), 1105 with comparisons that end at the first different word; with 2 outputs 1045, with 1
+// 1078, with 8 1293.
 template <int Wp>
 struct MergeTile {
-    static constexpr int kKeys = 4096 / Wp, kItems = kKeys / kBlock;  // 16, 8, 4, 2, 1 per thread
-    uint64_t key[kKeys * Wp];
+    static constexpr int kKeys = 4096 / Wp, kItems = Wp == 1 ? 4 : 2, kThreads = kKeys / kItems;
+    uint64_t key[Wp][kKeys];
     uint16_t idx[2][kKeys];
 };
 
@@ -231,33 +235,43 @@ __device__ __forceinline__ bool key_after(const uint64_t (&a)[Wp], const uint64_
     return gt;
 }
 
-// Outputs [o, o + n) of the merge of the runs `a` (la keys) and `b` (lb keys) of indices into key[].
-template <int Wp>
-__device__ __forceinline__ void merge_lds(const uint64_t *key, const uint16_t *a, int la, const uint16_t *b, int lb, int o,
-                                          int n, uint16_t *out) {
+struct Iota {  // the run of keys first, first + 1, ..
+    int first;
+    __device__ int operator[](int i) const { return first + i; }
+};
+
+// Outputs [o, o + n) of the merge of the runs `a` (la keys) and `b` (lb keys) of indices into key[][].
+template <int Wp, class Run>
+__device__ __forceinline__ void merge_lds(const uint64_t (&key)[Wp][MergeTile<Wp>::kKeys], Run a, int la, Run b,
+                                          int lb, int o, int n, uint16_t *out) {
     auto load = [&](int i, uint64_t(&k)[Wp]) {
 #pragma unroll
-        for (int w = 0; w < Wp; ++w) k[w] = key[i * Wp + w];
+        for (int w = 0; w < Wp; ++w) k[w] = key[w][i];
     };
     uint64_t ka[Wp], kb[Wp];
     // how many of the first o outputs come from a
     int lo = max(0, o - lb), hi = min(o, la);
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        load(a[mid], ka);
-        load(b[o - 1 - mid], kb);
-        if (key_after<Wp>(ka, kb))
+        const int x = a[mid], y = b[o - 1 - mid];
+        bool gt = false;
+        for (int w = Wp - 1; w >= 0; --w) {
+            const uint64_t p = key[w][x], q = key[w][y];
+            gt = p > q;
+            if (p != q) break;
+        }
+        if (gt)
             hi = mid;
         else
             lo = mid + 1;
     }
     int i = lo, j = o - lo;
-    uint16_t ia = i < la ? a[i] : (uint16_t)0, ib = j < lb ? b[j] : (uint16_t)0;
+    int ia = i < la ? a[i] : 0, ib = j < lb ? b[j] : 0;
     load(ia, ka);
     load(ib, kb);
     for (int k = 0; k < n; ++k) {
         const bool from_b = i >= la || (j < lb && key_after<Wp>(ka, kb));
-        out[o + k] = from_b ? ib : ia;
+        out[o + k] = (uint16_t)(from_b ? ib : ia);
         if (from_b) {
             ++j;
             if (j < lb) load(ib = b[j], kb);
@@ -269,15 +283,15 @@ __device__ __forceinline__ void merge_lds(const uint64_t *key, const uint16_t *a
 }
 
 template <int Wp>
-__global__ __launch_bounds__(kBlock) void k_sort_tiles(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
-                                                       int64_t n) {
+__global__ __launch_bounds__(MergeTile<Wp>::kThreads) void k_sort_tiles(const uint64_t *__restrict__ src,
+                                                                        uint64_t *__restrict__ dst, int64_t n) {
     using Tile = MergeTile<Wp>;
     __shared__ Tile t;
     const int64_t base = (int64_t)blockIdx.x * Tile::kKeys;
     const int m = (int)min((int64_t)Tile::kKeys, n - base);
     for (int w = 0; w < Wp; ++w)
-        for (int k = threadIdx.x; k < m; k += kBlock) t.key[k * Wp + w] = src[(int64_t)w * n + base + k];
-    for (int k = threadIdx.x; k < m; k += kBlock) t.idx[0][k] = (uint16_t)k;
+        for (int k = threadIdx.x; k < m; k += Tile::kThreads) t.key[w][k] = src[(int64_t)w * n + base + k];
+    for (int k = threadIdx.x; k < m; k += Tile::kThreads) t.idx[0][k] = (uint16_t)k;
     __syncthreads();
     int cur = 0;
     for (int run = 1; run < m; run <<= 1) {
@@ -287,22 +301,24 @@ __global__ __launch_bounds__(kBlock) void k_sort_tiles(const uint64_t *__restric
             const int pair = o / (2 * run) * (2 * run);
             const int la = min(run, m - pair), lb = min(run, m - pair - la);
             const int cnt = min(min(Tile::kItems, 2 * run), la + lb - (o - pair));
-            merge_lds<Wp>(t.key, &t.idx[cur][pair], la, &t.idx[cur][pair + la], lb, o - pair, cnt, &t.idx[cur ^ 1][pair]);
+            const uint16_t *a = &t.idx[cur][pair], *b = a + la;
+            merge_lds<Wp>(t.key, a, la, b, lb, o - pair, cnt, &t.idx[cur ^ 1][pair]);
             o += cnt;
         }
         cur ^= 1;
         __syncthreads();
     }
     for (int w = 0; w < Wp; ++w)
-        for (int k = threadIdx.x; k < m; k += kBlock) dst[(int64_t)w * n + base + k] = t.key[t.idx[cur][k] * Wp + w];
+        for (int k = threadIdx.x; k < m; k += Tile::kThreads) dst[(int64_t)w * n + base + k] = t.key[w][t.idx[cur][k]];
 }
 
 // One pass: pairs of runs of `run` keys (a multiple of the tile) merged, a tile of outputs per
 // workgroup.  Two waves find the ends of its part of the first run, 64 positions at a time (a
 // bisection by one lane is 20 dependent reads of memory).
 template <int Wp>
-__global__ __launch_bounds__(kBlock) void k_merge_runs(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
-                                                       int64_t n, int64_t run) {
+__global__ __launch_bounds__(MergeTile<Wp>::kThreads) void k_merge_runs(const uint64_t *__restrict__ src,
+                                                                        uint64_t *__restrict__ dst, int64_t n,
+                                                                        int64_t run) {
     using Tile = MergeTile<Wp>;
     __shared__ Tile t;
     __shared__ int64_t split[2];
@@ -312,8 +328,8 @@ __global__ __launch_bounds__(kBlock) void k_merge_runs(const uint64_t *__restric
     const int64_t la = min(run, n - pair), lb = min(run, n - pair - la);
     const uint64_t *a = src + pair, *b = a + la;
     const int64_t d0 = o0 - pair, d1 = min(d0 + Tile::kKeys, la + lb);
-    if (wave < 2) {
-        const int64_t d = wave == 0 ? d0 : d1;
+    for (int e = wave; e < 2; e += Tile::kThreads / 64) {
+        const int64_t d = e == 0 ? d0 : d1;
         int64_t lo = max((int64_t)0, d - lb), hi = min(d, la);
         while (lo < hi) {
             const int64_t len = hi - lo, step = (len + 63) / 64, i = lo + lane * step;
@@ -339,32 +355,31 @@ __global__ __launch_bounds__(kBlock) void k_merge_runs(const uint64_t *__restric
                 lo += (int64_t)(c - 1) * step + 1;
             }
         }
-        if (lane == 0) split[wave] = lo;
+        if (lane == 0) split[e] = lo;
     }
     __syncthreads();
     const int64_t i0 = split[0], j0 = d0 - i0;
     const int na = (int)(split[1] - i0), m = (int)(d1 - d0);
     for (int w = 0; w < Wp; ++w)
-        for (int k = threadIdx.x; k < m; k += kBlock)
-            t.key[k * Wp + w] = k < na ? a[(int64_t)w * n + i0 + k] : b[(int64_t)w * n + j0 + (k - na)];
-    for (int k = threadIdx.x; k < m; k += kBlock) t.idx[0][k] = (uint16_t)k;
+        for (int k = threadIdx.x; k < m; k += Tile::kThreads)
+            t.key[w][k] = k < na ? a[(int64_t)w * n + i0 + k] : b[(int64_t)w * n + j0 + (k - na)];
     __syncthreads();
     const int o = threadIdx.x * Tile::kItems;
-    if (o < m) merge_lds<Wp>(t.key, &t.idx[0][0], na, &t.idx[0][na], m - na, o, min(Tile::kItems, m - o), t.idx[1]);
+    if (o < m) merge_lds<Wp>(t.key, Iota{0}, na, Iota{na}, m - na, o, min(Tile::kItems, m - o), t.idx[0]);
     __syncthreads();
     for (int w = 0; w < Wp; ++w)
-        for (int k = threadIdx.x; k < m; k += kBlock) dst[(int64_t)w * n + o0 + k] = t.key[t.idx[1][k] * Wp + w];
+        for (int k = threadIdx.x; k < m; k += Tile::kThreads) dst[(int64_t)w * n + o0 + k] = t.key[w][t.idx[0][k]];
 }
 
 // Sorts the keys src[Wp][n] with the scratch tmp[Wp][n]; the result is in *out (one of the two).
 // `varies` = the bits that differ between keys.
 //
 // A radix pass (histogram, three scan launches, scatter: 40 us for 1M keys of 200 bits, 25 of them)
-// and a merge pass (20 us, ten of them and the tile sort) both read and write all keys, so the
+// and a merge pass (30 us, ten of them and the tile sort) both read and write all keys, so the
 // number of passes decides; the tile sort counts as two.  Whole builds, radix / merge, in us: 36 bits
 // x 30 000 (5 digits, 3 merges) 332 / 341, 36 bits x 10M (5, 12) 2864 / 3363, 64 bits x 1M (8, 8)
-// 593 / 575, 100 bits x 100 000 (13, 6) 535 / 376, 200 bits x 1M (25, 10) 1948 / 986, 1000 bits x
-// 50 000 (125, 8) 6794 / 641.
+// 593 / 575, 100 bits x 100 000 (13, 6) 535 / 376, 200 bits x 1M (25, 10) 1948 / 856, 1000 bits x
+// 50 000 (125, 8) 6794 / 560.
 template <int Wp>
 int sort_keys(uint64_t *src, uint64_t *tmp, int64_t n, const uint64_t *varies, int W, uint64_t **out, hipStream_t st) {
     int digits = 0, merges = 0;
@@ -376,10 +391,10 @@ int sort_keys(uint64_t *src, uint64_t *tmp, int64_t n, const uint64_t *varies, i
     for (int64_t run = Tile::kKeys; run < n; run <<= 1) ++merges;
     if (merges + 2 < digits) {
         const unsigned tiles = (unsigned)((n + Tile::kKeys - 1) / Tile::kKeys);
-        k_sort_tiles<Wp><<<tiles, kBlock, 0, st>>>(src, tmp, n);
+        k_sort_tiles<Wp><<<tiles, Tile::kThreads, 0, st>>>(src, tmp, n);
         std::swap(src, tmp);
         for (int64_t run = Tile::kKeys; run < n; run <<= 1) {
-            k_merge_runs<Wp><<<tiles, kBlock, 0, st>>>(src, tmp, n, run);
+            k_merge_runs<Wp><<<tiles, Tile::kThreads, 0, st>>>(src, tmp, n, run);
             std::swap(src, tmp);
         }
         *out = src;
@@ -444,16 +459,46 @@ __device__ __forceinline__ uint64_t tab_hash(const uint64_t (&k)[Wp], const uint
     return h;
 }
 
+// The same for a pass over all rows.  The tables are linear, so a byte's word is that of its low
+// half and of its high half: 16 + 16 entries per byte (2 KB per key word instead of 16) staged in LDS,
+// where the 16 entries of a nibble lie in different banks.
+template <int Wp>
+struct NibbleTab {
+    uint64_t v[Wp * 16][16];
+    __device__ void load(const uint64_t *__restrict__ tab) {
+        for (int k = threadIdx.x; k < Wp * 256; k += blockDim.x) {
+            const int nib = k >> 4, e = k & 15;
+            v[nib][e] = tab[(nib >> 1) * 256 + ((nib & 1) ? e << 4 : e)];
+        }
+        __syncthreads();
+    }
+    __device__ uint64_t operator()(const uint64_t (&k)[Wp]) const {
+        uint64_t h = 0;
+#pragma unroll
+        for (int w = 0; w < Wp; ++w)
+#pragma unroll
+            for (int c = 0; c < 16; ++c) h ^= v[w * 16 + c][(k[w] >> (4 * c)) & 15u];
+        return h;
+    }
+};
+
+// `rows` (NULL: not wanted) = the keys as rows [N][Wp].
 template <int Wp>
 __global__ __launch_bounds__(kBlock) void k_hash_insert(SubView s, uint64_t *__restrict__ slots,
-                                                        uint32_t *__restrict__ bitmap, uint64_t *__restrict__ hkey,
-                                                        const uint64_t *__restrict__ ztab) {
+                                                        uint64_t *__restrict__ hkey, const uint64_t *__restrict__ ztab,
+                                                        uint64_t *__restrict__ rows) {
+    __shared__ NibbleTab<Wp> tab;
+    tab.load(ztab);
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= s.N) return;
     uint64_t k[Wp];
 #pragma unroll
     for (int w = 0; w < Wp; ++w) k[w] = s.keys[(int64_t)w * s.N + i];
-    const uint64_t h = tab_hash<Wp>(k, ztab);
+    if (rows) {
+#pragma unroll
+        for (int w = 0; w < Wp; ++w) rows[i * Wp + w] = k[w];
+    }
+    const uint64_t h = tab(k);
     hkey[i] = h;
     const unsigned long long base = ((unsigned long long)(h >> 32) << 32) | (unsigned long long)(uint32_t)i;
     uint32_t pos = (uint32_t)h & s.cmask;
@@ -461,12 +506,19 @@ __global__ __launch_bounds__(kBlock) void k_hash_insert(SubView s, uint64_t *__r
         const unsigned long long val =
             s.exact ? (base | ((unsigned long long)(step < 63u ? step : 63u) << kExactIdxBits)) : base;
         unsigned long long prev = atomicCAS((unsigned long long *)&slots[pos], ~0ull, val);
-        if (prev == ~0ull) {
-            atomicOr(&bitmap[pos >> 5], 1u << (pos & 31));
-            return;
-        }
+        if (prev == ~0ull) return;
         pos = (pos + 1) & s.cmask;
     }
+}
+
+// Occupancy of the filled table (C slots, whole waves): a pass over 64 MB for 1M strings takes 14 us,
+// an atomic per string during the insertion 30.
+__global__ __launch_bounds__(kBlock) void k_bitmap(const uint64_t *__restrict__ slots, int64_t C,
+                                                   uint32_t *__restrict__ bitmap) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= C) return;
+    const uint64_t m = __ballot(slots[i] != ~0ull);
+    if ((threadIdx.x & 31) == 0) bitmap[i >> 5] = (uint32_t)(m >> (threadIdx.x & 32));
 }
 
 template <int Wp>
@@ -546,7 +598,8 @@ __global__ __launch_bounds__(kBlock) void k_slot_order(const uint32_t *__restric
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_gather_rows(const uint64_t *__restrict__ keys,
+// (`keys` as word planes, or as rows where `rows`: one piece of memory per row instead of Wp)
+__global__ __launch_bounds__(kBlock) void k_gather_rows(const uint64_t *__restrict__ keys, bool rows,
                                                         const uint64_t *__restrict__ hkey,
                                                         const uint32_t *__restrict__ pkey,
                                                         const uint32_t *__restrict__ order, int64_t N, int Wp,
@@ -555,7 +608,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const uint64_t *__restri
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= N) return;
     const int64_t r = order[k];
-    for (int w = 0; w < Wp; ++w) okeys[(int64_t)w * N + k] = keys[(int64_t)w * N + r];
+    for (int w = 0; w < Wp; ++w) okeys[(int64_t)w * N + k] = rows ? keys[r * Wp + w] : keys[(int64_t)w * N + r];
     ohkey[k] = hkey[r];
     if (pkey) opkey[k] = pkey[r];
 }
@@ -584,24 +637,23 @@ __global__ __launch_bounds__(kBlock) void k_part_keys(const uint64_t *__restrict
 // their keys and hashes in that order.  A run of consecutive entries holds rows whose home slots
 // share a stretch of the table, so for any group their columns b ^ M_g, whose hashes are
 // h(b) ^ h(M_g), share a stretch too.
+// `krows` = the keys as rows, if the caller has them.
 int build_order(const qsd_subspace *sub, const uint64_t *hkey, const uint32_t *pkey, int64_t C, bool exact,
-                const uint64_t *slots, const uint32_t *bitmap, SlotRows *out, hipStream_t st) {
+                const uint64_t *slots, const uint32_t *bitmap, const uint64_t *krows, SlotRows *out, hipStream_t st) {
     const int64_t N = sub->N, nw = C / 32;
     int64_t *base = nullptr;
     SlotRows o;
-    QSD_TRY(dev_alloc(&base, nw));
+    QSD_TRY(dev_alloc(&base, nw + scan_scratch(nw)));
     int rc = dev_alloc(&o.order, N);
     if (rc == QSD_OK) rc = dev_alloc(&o.keys, (size_t)sub->Wp * N);
     if (rc == QSD_OK) rc = dev_alloc(&o.hkey, N);
     if (rc == QSD_OK && pkey) rc = dev_alloc(&o.pkey, N);
     if (rc == QSD_OK) {
         k_word_counts<<<grid_for(nw, kBlock), kBlock, 0, st>>>(bitmap, nw, base);
-        rc = exclusive_scan_i64(base, base, nw, st);
-    }
-    if (rc == QSD_OK) {
+        scan_enqueue(base, base, nw, base + nw, st);
         k_slot_order<<<grid_for(nw, kBlock), kBlock, 0, st>>>(bitmap, slots, nw, base, exact ? 1u : 0u, o.order);
-        k_gather_rows<<<grid_for(N, kBlock), kBlock, 0, st>>>(sub->keys, hkey, pkey, o.order, N, sub->Wp, o.keys,
-                                                              o.hkey, o.pkey);
+        k_gather_rows<<<grid_for(N, kBlock), kBlock, 0, st>>>(krows ? krows : sub->keys, krows != nullptr, hkey, pkey,
+                                                              o.order, N, sub->Wp, o.keys, o.hkey, o.pkey);
         if (hipStreamSynchronize(st) != hipSuccess)
             rc = fail(QSD_ERR_HIP, "slot order failed: %s", hipGetErrorString(hipGetLastError()));
     }
@@ -619,27 +671,23 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
                hipStream_t st) {
     const int W = sub->W;
     uint64_t *planes = nullptr, *tmp = nullptr;
+    int64_t *fl = nullptr, *pos = nullptr;
     unsigned long long *or_and = nullptr;
     QSD_TRY(dev_alloc(&planes, (size_t)Wp * n_in));
     int rc = QSD_OK;
+    std::vector<uint64_t> tab;
     auto cleanup = [&]() {
+        (void)hipStreamSynchronize(st);  // what is enqueued reads them
+        dev_free(fl);
+        dev_free(pos);
         dev_free(planes);
         dev_free(tmp);
         dev_free(or_and);
     };
     do {
         if ((rc = dev_alloc(&or_and, 2 * kMaxWords)) != QSD_OK) break;
-        {
-            std::vector<unsigned long long> init(2 * kMaxWords);
-            for (int w = 0; w < kMaxWords; ++w) {
-                init[w] = 0ull;
-                init[kMaxWords + w] = ~0ull;
-            }
-            if (hipMemcpyAsync(or_and, init.data(), init.size() * 8, hipMemcpyHostToDevice, st) != hipSuccess) {
-                rc = fail(QSD_ERR_HIP, "copy failed");
-                break;
-            }
-        }
+        k_fill_u64<<<1, kBlock, 0, st>>>((uint64_t *)or_and, kMaxWords, 0ull);
+        k_fill_u64<<<1, kBlock, 0, st>>>((uint64_t *)or_and + kMaxWords, kMaxWords, ~0ull);
         k_ingest<<<grid_for(n_in, kBlock), kBlock, 0, st>>>(d_bits, n_in, W, Wp, planes, or_and);
         std::vector<unsigned long long> oa(2 * kMaxWords);
         if (hipMemcpyAsync(oa.data(), or_and, oa.size() * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -661,28 +709,21 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             if ((rc = sort_keys<Wp>(planes, tmp, n_in, varies, W, &src, st)) != QSD_OK) break;
         }
         // deduplicate
-        int64_t *fl = nullptr, *pos = nullptr;
-        if ((rc = dev_alloc(&fl, n_in)) != QSD_OK) break;
-        if ((rc = dev_alloc(&pos, n_in)) != QSD_OK) {
-            dev_free(fl);
-            break;
-        }
+        const int64_t n1 = n_in + 1;  // pos[n_in] = N (the flag there moves nothing)
+        if ((rc = dev_alloc(&fl, n1)) != QSD_OK) break;
+        if ((rc = dev_alloc(&pos, n1 + scan_scratch(n1))) != QSD_OK) break;
         k_unique_flags<Wp><<<grid_for(n_in, kBlock), kBlock, 0, st>>>(src, n_in, fl);
-        rc = exclusive_scan_i64(fl, pos, n_in, st);
-        int64_t last[2] = {0, 0};
-        if (rc == QSD_OK) {
-            if (hipMemcpyAsync(&last[0], pos + n_in - 1, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                hipMemcpyAsync(&last[1], fl + n_in - 1, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                hipStreamSynchronize(st) != hipSuccess)
-                rc = fail(QSD_ERR_HIP, "sort failed: %s", hipGetErrorString(hipGetLastError()));
-        }
-        const int64_t N = last[0] + last[1];
+        scan_enqueue(fl, pos, n1, pos + n1, st);
+        // the hash words and tables while the device sorts
+        hash_words(sub->n_qubits, sub->z);
+        hash_byte_tables(Wp, sub->z, tab);
+        int64_t N = 0;
+        if (hipMemcpyAsync(&N, pos + n_in, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            rc = fail(QSD_ERR_HIP, "sort failed: %s", hipGetErrorString(hipGetLastError()));
         if (rc == QSD_OK && N >= 0xFFFFFFFFll) rc = fail(QSD_ERR_CAPACITY, "%lld unique strings exceed 2^32-2", (long long)N);
         if (rc == QSD_OK) rc = dev_alloc(&sub->keys, (size_t)Wp * N);
         if (rc == QSD_OK) k_compact<Wp><<<grid_for(n_in, kBlock), kBlock, 0, st>>>(src, n_in, fl, pos, sub->keys, N);
-        if (rc == QSD_OK && hipStreamSynchronize(st) != hipSuccess) rc = fail(QSD_ERR_HIP, "compact failed");
-        dev_free(fl);
-        dev_free(pos);
         if (rc != QSD_OK) break;
         sub->N = N;
         // hash table
@@ -693,10 +734,7 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             break;
         }
         sub->C = C;
-        hash_words(sub->n_qubits, sub->z);
         sub->exact = exact_tags_ok(sub->z, sub->W, N, C);
-        std::vector<uint64_t> tab;
-        hash_byte_tables(Wp, sub->z, tab);
         if ((rc = dev_alloc(&sub->ztab, tab.size())) != QSD_OK) break;
         if ((rc = dev_alloc(&sub->slots, C)) != QSD_OK) break;
         if ((rc = dev_alloc(&sub->bitmap, C / 32)) != QSD_OK) break;
@@ -706,14 +744,12 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             break;
         }
         k_fill_u64<<<1024, kBlock, 0, st>>>(sub->slots, C, ~0ull);
-        k_fill_u32<<<256, kBlock, 0, st>>>(sub->bitmap, C / 32, 0u);
         SubView v{sub->keys, sub->hkey, sub->slots, sub->bitmap, N, (uint32_t)(C - 1), sub->exact ? 1u : 0u};
-        k_hash_insert<Wp><<<grid_for(N, kBlock), kBlock, 0, st>>>(v, sub->slots, sub->bitmap, sub->hkey, sub->ztab);
-        if (hipStreamSynchronize(st) != hipSuccess) {
-            rc = fail(QSD_ERR_HIP, "hash build failed: %s", hipGetErrorString(hipGetLastError()));
-            break;
-        }
-        rc = build_order(sub, sub->hkey, nullptr, C, sub->exact, sub->slots, sub->bitmap, &sub->rows, st);
+        // the sort's memory takes the keys as rows for the slot order
+        uint64_t *rows = Wp > 1 ? tmp : nullptr;
+        k_hash_insert<Wp><<<grid_for(N, kBlock), kBlock, 0, st>>>(v, sub->slots, sub->hkey, sub->ztab, rows);
+        k_bitmap<<<grid_for(C, kBlock), kBlock, 0, st>>>(sub->slots, C, sub->bitmap);
+        rc = build_order(sub, sub->hkey, nullptr, C, sub->exact, sub->slots, sub->bitmap, rows, &sub->rows, st);
     } while (0);
     cleanup();
     return rc;
@@ -843,10 +879,10 @@ int rehash_impl(qsd_subspace *sub, int64_t C, int split, hipStream_t st) {
         if (rc == QSD_OK) rc = dev_alloc(&bitmap, C / 32);
         if (rc == QSD_OK) {
             k_fill_u64<<<1024, kBlock, 0, st>>>(slots, C, ~0ull);
-            k_fill_u32<<<256, kBlock, 0, st>>>(bitmap, C / 32, 0u);
             // writes the row hashes (the same values when the words did not change)
             SubView v{sub->keys, hkey, slots, bitmap, sub->N, (uint32_t)(C - 1), exact ? 1u : 0u};
-            k_hash_insert<Wp><<<grid_for(sub->N, kBlock), kBlock, 0, st>>>(v, slots, bitmap, hkey, ztab);
+            k_hash_insert<Wp><<<grid_for(sub->N, kBlock), kBlock, 0, st>>>(v, slots, hkey, ztab, nullptr);
+            k_bitmap<<<grid_for(C, kBlock), kBlock, 0, st>>>(slots, C, bitmap);
         }
     }
     if (rc == QSD_OK && split > 0) {
@@ -897,7 +933,7 @@ int rehash_impl(qsd_subspace *sub, int64_t C, int split, hipStream_t st) {
     if (rc == QSD_OK && hipStreamSynchronize(st) != hipSuccess)
         rc = fail(QSD_ERR_HIP, "hash rebuild failed: %s", hipGetErrorString(hipGetLastError()));
     SlotRows rows;
-    if (rc == QSD_OK) rc = build_order(sub, hkey, pkey, C, exact, slots, bitmap, &rows, st);
+    if (rc == QSD_OK) rc = build_order(sub, hkey, pkey, C, exact, slots, bitmap, nullptr, &rows, st);
     // the bound operators' group hashes (new words) and part indices (part filters)
     const size_t nb = sub->bound.size();
     std::vector<uint64_t *> ghash(nb, nullptr);
