@@ -6,6 +6,7 @@
 #include <array>
 #include <complex>
 #include <cstdint>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -92,6 +93,39 @@ void dev_free(T *&p) {
     raw_free((void *)p);
     p = nullptr;
 }
+
+// Arrays laid out in one block of device memory (256-byte aligned); those that are put come first and
+// are copied from their host image, which lives as long as this.
+struct Block {
+    std::vector<uint8_t> image;
+    size_t size = 0;
+    uint8_t *dev = nullptr;
+    template <class T>
+    size_t put(const std::vector<T> &v) {
+        const size_t at = room(v.size() * sizeof(T));
+        image.resize(size);
+        if (!v.empty()) std::memcpy(image.data() + at, v.data(), v.size() * sizeof(T));
+        return at;
+    }
+    size_t room(size_t bytes) {
+        const size_t at = size;
+        size += (bytes + 255) / 256 * 256;
+        return at;
+    }
+    template <class T>
+    T *at(size_t off) const {
+        return (T *)(dev + off);
+    }
+    int copy(hipStream_t st) {
+        if (!image.empty())
+            QSD_CHECK_HIP(hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, st));
+        return QSD_OK;
+    }
+    int upload(hipStream_t st) {
+        QSD_TRY(dev_alloc(&dev, size));
+        return copy(st);
+    }
+};
 
 // Hash of every off-diagonal group's flip mask under the subspace's hash words, and its packed
 // part indices under the subspace's part words.
@@ -221,6 +255,7 @@ struct qsd_ham {
     uint32_t schedule = QSD_SCHED_XCD_REMAP | QSD_SCHED_FILTER_FIRST;
     double *diag = nullptr;       // [N] real part (FP64)
     double *diag_im = nullptr;    // [N] imaginary part (complex operators only)
+    uint8_t *tables = nullptr;    // the operator's tables below, but for g_hash and g_part, in one block
     uint64_t *g_mask = nullptr;
     uint64_t *g_hash = nullptr;
     uint32_t *g_part = nullptr;   // [G] packed part indices (subspaces with part filters)

@@ -295,19 +295,9 @@ void free_ham(qsd_ham *h) {
     }
     dev_free(h->diag);
     dev_free(h->diag_im);
-    dev_free(h->g_mask);
+    dev_free(h->tables);
     dev_free(h->g_hash);
     dev_free(h->g_part);
-    dev_free(h->g_pos);
-    dev_free(h->g_scan);
-    dev_free(h->g_info);
-    dev_free(h->g_term0);
-    dev_free(h->g_nterm);
-    dev_free(h->g_iptr);
-    dev_free(h->t_cws);
-    dev_free(h->t_coef);
-    dev_free(h->t_cw32);
-    dev_free(h->t_coef32);
     dev_free(h->diag32);
     dev_free(h->diag32_im);
     dev_free(h->rowbits);
@@ -326,21 +316,13 @@ void launch_diag(const qsd_ham *h, const DiagRun *runs, size_t nruns, const Diag
 
 int create_impl(qsd_ham *h, hipStream_t st) {
     const qsd_op *op = h->op;
-    QSD_TRY(upload(&h->g_mask, op->g_mask, st));
-    const std::vector<uint64_t> gh = group_hashes(op, h->s->z);  // alive until the synchronize below
+    const std::vector<uint64_t> gh = group_hashes(op, h->s->z);  // alive until the synchronize below, as all images
     QSD_TRY(upload(&h->g_hash, gh, st));
     std::vector<uint32_t> gp;
     if (h->s->split > 0) {
         gp = group_parts(op, h->s->pz);
         QSD_TRY(upload(&h->g_part, gp, st));
     }
-    QSD_TRY(upload(&h->g_pos, op->g_pos, st));
-    QSD_TRY(upload(&h->g_scan, op->g_scan, st));
-    QSD_TRY(upload(&h->g_info, op->g_info, st));
-    QSD_TRY(upload(&h->g_term0, op->g_term0, st));
-    QSD_TRY(upload(&h->g_nterm, op->g_nterm, st));
-    QSD_TRY(upload(&h->g_iptr, op->g_iptr, st));
-    QSD_TRY(upload(&h->t_cws, op->t_cws, st));
     std::vector<uint32_t> cw32;
     if (op->n_qubits <= 32) {
         // one-word keys of at most 32 qubits: the term masks fit 32 bits
@@ -350,48 +332,59 @@ int create_impl(qsd_ham *h, hipStream_t st) {
             for (int k = 0; k < 3; ++k) cw32[t * 4 + k] = (uint32_t)op->t_cws[t * 3 + k];
             cw32[t * 4 + 3] = op->t_tail[t];
         }
-        QSD_TRY(upload(&h->t_cw32, cw32, st));
     }
-    QSD_TRY(upload(&h->t_coef, op->t_coef, st));
     std::vector<float> c32(op->t_coef.size());
     for (size_t k = 0; k < c32.size(); ++k) c32[k] = (float)op->t_coef[k];
-    QSD_TRY(upload(&h->t_coef32, c32, st));
+    // one copy each for the tables that stay and for the diagonal's (a copy costs the host 16 us)
+    Block tables, dtables;
+    const size_t o_mask = tables.put(op->g_mask), o_pos = tables.put(op->g_pos), o_scan = tables.put(op->g_scan),
+                 o_info = tables.put(op->g_info), o_term0 = tables.put(op->g_term0), o_nterm = tables.put(op->g_nterm),
+                 o_iptr = tables.put(op->g_iptr), o_cws = tables.put(op->t_cws), o_cw32 = tables.put(cw32),
+                 o_coef = tables.put(op->t_coef), o_coef32 = tables.put(c32);
+    QSD_TRY(dev_alloc(&tables.dev, tables.size));
+    h->tables = tables.dev;
+    QSD_TRY(tables.copy(st));
+    h->g_mask = tables.at<uint64_t>(o_mask);
+    h->g_pos = tables.at<uint64_t>(o_pos);
+    h->g_scan = tables.at<uint64_t>(o_scan);
+    h->g_info = tables.at<uint32_t>(o_info);
+    h->g_term0 = tables.at<uint32_t>(o_term0);
+    h->g_nterm = tables.at<uint32_t>(o_nterm);
+    h->g_iptr = tables.at<uint16_t>(o_iptr);
+    h->t_cws = tables.at<uint64_t>(o_cws);
+    if (op->n_qubits <= 32) h->t_cw32 = tables.at<uint32_t>(o_cw32);
+    h->t_coef = tables.at<double>(o_coef);
+    h->t_coef32 = tables.at<float>(o_coef32);
     QSD_TRY(dev_alloc(&h->diag, h->N));
     QSD_TRY(dev_alloc(&h->diag32, h->N));
     if (h->is_complex) {
         QSD_TRY(dev_alloc(&h->diag_im, h->N));
         QSD_TRY(dev_alloc(&h->diag32_im, h->N));
     }
-    uint64_t *dcws = nullptr;
-    double *dcoef = nullptr;
-    DiagRun *druns = nullptr;
-    DiagTerm *dterms = nullptr;
-    DiagWant *dwants = nullptr;
-    const DiagPlan plan = diag_plan(op);  // alive until the synchronize below
-    int rc = upload(&druns, plan.runs, st);
-    if (rc == QSD_OK) rc = upload(&dterms, plan.terms, st);
-    if (rc == QSD_OK) rc = upload(&dwants, plan.wants, st);
+    const DiagPlan plan = diag_plan(op);
     const bool any = std::any_of(plan.runs.begin(), plan.runs.end(), [](const DiagRun &r) { return r.n >> 30 == kDiagAny; });
-    if (rc == QSD_OK && any) rc = upload(&dcws, op->diag_cws, st);
-    if (rc == QSD_OK && any) rc = upload(&dcoef, op->diag_coef, st);
+    const size_t o_runs = dtables.put(plan.runs), o_terms = dtables.put(plan.terms), o_wants = dtables.put(plan.wants);
+    const size_t o_dcws = any ? dtables.put(op->diag_cws) : 0, o_dcoef = any ? dtables.put(op->diag_coef) : 0;
+    int rc = dev_alloc(&dtables.dev, dtables.size);
+    if (rc == QSD_OK) rc = dtables.copy(st);
     if (rc == QSD_OK) {
-        const size_t n = plan.runs.size();
+        auto diag = [&](auto wp) {
+            launch_diag<decltype(wp)::value>(h, dtables.at<DiagRun>(o_runs), plan.runs.size(), dtables.at<DiagTerm>(o_terms),
+                                             dtables.at<DiagWant>(o_wants), dtables.at<uint64_t>(o_dcws),
+                                             dtables.at<double>(o_dcoef), st);
+        };
         switch (h->Wp) {
-            case 1: launch_diag<1>(h, druns, n, dterms, dwants, dcws, dcoef, st); break;
-            case 2: launch_diag<2>(h, druns, n, dterms, dwants, dcws, dcoef, st); break;
-            case 4: launch_diag<4>(h, druns, n, dterms, dwants, dcws, dcoef, st); break;
-            case 8: launch_diag<8>(h, druns, n, dterms, dwants, dcws, dcoef, st); break;
-            case 16: launch_diag<16>(h, druns, n, dterms, dwants, dcws, dcoef, st); break;
+            case 1: diag(std::integral_constant<int, 1>{}); break;
+            case 2: diag(std::integral_constant<int, 2>{}); break;
+            case 4: diag(std::integral_constant<int, 4>{}); break;
+            case 8: diag(std::integral_constant<int, 8>{}); break;
+            case 16: diag(std::integral_constant<int, 16>{}); break;
         }
         rc = prod_build(h, st);
         if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
             rc = fail(QSD_ERR_HIP, "diagonal kernel failed: %s", hipGetErrorString(hipGetLastError()));
     }
-    dev_free(dcws);
-    dev_free(dcoef);
-    dev_free(druns);
-    dev_free(dterms);
-    dev_free(dwants);
+    dev_free(dtables.dev);
     return rc;
 }
 

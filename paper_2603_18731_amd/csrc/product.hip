@@ -670,36 +670,6 @@ Classified classify(const qsd_op *op, int split) {
     return c;
 }
 
-// Arrays laid out in one block of device memory (256-byte aligned), the first `bytes` of which
-// are copied from the host image.
-struct Block {
-    std::vector<uint8_t> image;
-    size_t size = 0;
-    uint8_t *dev = nullptr;
-    template <class T>
-    size_t put(const std::vector<T> &v) {
-        const size_t at = room(v.size() * sizeof(T));
-        image.resize(size);
-        if (!v.empty()) std::memcpy(image.data() + at, v.data(), v.size() * sizeof(T));
-        return at;
-    }
-    size_t room(size_t bytes) {
-        const size_t at = size;
-        size += (bytes + 255) / 256 * 256;
-        return at;
-    }
-    template <class T>
-    T *at(size_t off) const {
-        return (T *)(dev + off);
-    }
-    int upload(hipStream_t st) {
-        QSD_TRY(dev_alloc(&dev, size));
-        if (!image.empty())
-            QSD_CHECK_HIP(hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, st));
-        return QSD_OK;
-    }
-};
-
 std::vector<float> narrowed(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
 
 // The lists: counted, sized by one round trip to the host, then written.  `scratch` and `keep`
