@@ -307,7 +307,9 @@ int qsd_ham_diag_splitting(const qsd_ham *h, double *lowest, double *splitting, 
  *                         index from the map and the table is not read.  Not swept by the
  *                         autotuner (the map needs no memory access).
  * A new operator starts with XCD_REMAP | FILTER_FIRST (faster than the plain schedule on every
- * workload measured; slot order pays off when most probes miss, which qsd_ham_autotune finds).
+ * workload measured).  Slot order pays off when most probes miss: an operator whose schedule was
+ * never set also takes its rows in slot order (without the bits and the list above) where a sample
+ * of its rows has at most one present column per row; qsd_ham_autotune finds the rest.
  * The batched entries (qsd_batch_*, qsd_matvec_batched) use each operator's schedule too.
  * qsd_ham_set_schedule sets the bits (INVALID_ARG for unknown bits). */
 #define QSD_SCHED_XCD_REMAP 1u

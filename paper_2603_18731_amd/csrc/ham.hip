@@ -181,6 +181,28 @@ __global__ __launch_bounds__(kBlock) void k_diag(SubView s, const DiagRun *__res
     }
 }
 
+// Columns present in the subspace of kSampleRows rows spread over it (a wave per row, a lane per group).
+constexpr int kSampleRows = 64;
+constexpr int64_t kSampleGroups = 4096;  // operators with more are not sampled
+
+template <int Wp>
+__global__ __launch_bounds__(kBlock) void k_sample_columns(SubView s, const uint64_t *__restrict__ g_mask,
+                                                           const uint64_t *__restrict__ g_hash, int64_t G,
+                                                           uint32_t *__restrict__ count) {
+    const int lane = threadIdx.x & 63;
+    const int64_t r = (int64_t)(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * s.N / kSampleRows;
+    const uint64_t hrow = s.hkey[r];
+    uint32_t n = 0;
+    for (int64_t g = lane; g < G; g += 64) {
+        uint64_t col[Wp];
+#pragma unroll
+        for (int w = 0; w < Wp; ++w) col[w] = s.keys[(int64_t)w * s.N + r] ^ g_mask[g * Wp + w];
+        n += probe<Wp>(s, hrow ^ g_hash[g], col) >= 0;
+    }
+    for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+    if (lane == 0) atomicAdd(count, n);
+}
+
 // ------------------------------------------------------------------------------- matvec
 
 // Bit r of `bits` = row r has an off-diagonal element (a probe whose column is present and
@@ -365,6 +387,9 @@ int create_impl(qsd_ham *h, hipStream_t st) {
     const bool any = std::any_of(plan.runs.begin(), plan.runs.end(), [](const DiagRun &r) { return r.n >> 30 == kDiagAny; });
     const size_t o_runs = dtables.put(plan.runs), o_terms = dtables.put(plan.terms), o_wants = dtables.put(plan.wants);
     const size_t o_dcws = any ? dtables.put(op->diag_cws) : 0, o_dcoef = any ? dtables.put(op->diag_coef) : 0;
+    const size_t o_count = dtables.put(std::vector<uint32_t>(1, 0u));
+    const bool sampled = !h->s->prank && !h->s->pfilt && h->G <= kSampleGroups;
+    uint32_t columns = kSampleRows + 1;
     int rc = dev_alloc(&dtables.dev, dtables.size);
     if (rc == QSD_OK) rc = dtables.copy(st);
     if (rc == QSD_OK) {
@@ -372,6 +397,9 @@ int create_impl(qsd_ham *h, hipStream_t st) {
             launch_diag<decltype(wp)::value>(h, dtables.at<DiagRun>(o_runs), plan.runs.size(), dtables.at<DiagTerm>(o_terms),
                                              dtables.at<DiagWant>(o_wants), dtables.at<uint64_t>(o_dcws),
                                              dtables.at<double>(o_dcoef), st);
+            if (sampled)
+                k_sample_columns<decltype(wp)::value><<<kSampleRows / (kBlock / 64), kBlock, 0, st>>>(
+                    sview(h->s), h->g_mask, h->g_hash, h->G, dtables.at<uint32_t>(o_count));
         };
         switch (h->Wp) {
             case 1: diag(std::integral_constant<int, 1>{}); break;
@@ -380,9 +408,12 @@ int create_impl(qsd_ham *h, hipStream_t st) {
             case 8: diag(std::integral_constant<int, 8>{}); break;
             case 16: diag(std::integral_constant<int, 16>{}); break;
         }
-        rc = prod_build(h, st);
+        if (sampled && hipMemcpyAsync(&columns, dtables.at<uint32_t>(o_count), 4, hipMemcpyDeviceToHost, st) != hipSuccess)
+            rc = fail(QSD_ERR_HIP, "copy failed");
+        if (rc == QSD_OK) rc = prod_build(h, st);
         if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
             rc = fail(QSD_ERR_HIP, "diagonal kernel failed: %s", hipGetErrorString(hipGetLastError()));
+        h->slot_default = columns <= kSampleRows;
     }
     dev_free(dtables.dev);
     return rc;
@@ -735,6 +766,7 @@ extern "C" int qsd_ham_set_schedule(qsd_ham *h, uint32_t schedule) {
         QSD_TRY(ensure_rowbits(h, nullptr));
     }
     h->schedule = schedule;
+    h->slot_default = false;
     return QSD_OK;
 }
 
@@ -777,6 +809,7 @@ extern "C" int qsd_ham_autotune(qsd_ham *h, int32_t nvec, int32_t dtype, int32_t
     };
     if (rc == QSD_OK && (flags & QSD_TUNE_SCHEDULE)) rc = ensure_rowbits(h, st);
     const uint32_t sched0 = h->schedule;
+    const bool slot0 = h->slot_default;
     const int64_t C0 = sub->C;
     const int32_t split0 = sub->split;
     const double load0 = (double)sub->N / (double)sub->C;
@@ -799,6 +832,7 @@ extern "C" int qsd_ham_autotune(qsd_ham *h, int32_t nvec, int32_t dtype, int32_t
     // every schedule on the current table, then the three fastest on every other table
     std::vector<std::pair<float, uint32_t>> ranked;
     if (flags & QSD_TUNE_SCHEDULE) {
+        h->slot_default = false;  // what is timed is what the bits say
         for (uint32_t sc = 0; sc <= kSchedAll && rc == QSD_OK; ++sc) {
             float ms = 0.0f;
             rc = consider(sc, load0, ms);
@@ -840,6 +874,7 @@ extern "C" int qsd_ham_autotune(qsd_ham *h, int32_t nvec, int32_t dtype, int32_t
         h->schedule = best_sched;
     } else {
         h->schedule = sched0;
+        h->slot_default = slot0;
     }
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);

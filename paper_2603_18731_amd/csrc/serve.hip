@@ -685,7 +685,7 @@ int add_impl(qsd_batch *b, const qsd_ham *h, const qsd_csr *c, int32_t v0_mode, 
         d.h = ham_view(h, b->f32);
         d.diag = h->diag;
         d.diag32 = h->diag32;
-        d.sched = h->schedule;
+        d.sched = h->launch_schedule();
         S.prod = prod_usable(h);
     } else {
         d.diag = c->diag;
@@ -998,7 +998,7 @@ int plan_batched(int32_t n, const qsd_ham *const *hams, const void *const *xs, v
                 R.y = (char *)ys[i] + c0 * esz;
                 R.ld = nvecs[i];
                 R.nv = std::min(chunk, nvecs[i] - c0);
-                R.sched = h->schedule;
+                R.sched = h->launch_schedule();
                 L.nv_max = std::max(L.nv_max, R.nv);
                 const int slot = (int)P.reqs.size();
                 P.reqs.push_back(R);

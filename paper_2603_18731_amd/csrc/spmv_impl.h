@@ -81,11 +81,11 @@ void launch_mv(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ld
     if (h->s->pfilt)
         k_matvec<Wp, NV, ET, CPLX, 1><<<nd + tiles, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), dre, dim,
                                                                     (const ET *)x, ldx, (ET *)y, ldy, nvec,
-                                                                    h->schedule, h->rowbits, nd);
+                                                                    h->launch_schedule(), h->rowbits, nd);
     else
         k_matvec<Wp, NV, ET, CPLX, 0><<<nd + tiles, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), dre, dim,
                                                                     (const ET *)x, ldx, (ET *)y, ldy, nvec,
-                                                                    h->schedule, h->rowbits, nd);
+                                                                    h->launch_schedule(), h->rowbits, nd);
 }
 
 template <int Wp, class ET, bool CPLX>

@@ -134,3 +134,32 @@ def test_solve_bitwise(graph):
             out.append((e, info["iterations"], v))
         say("solve", H.N, out[0][:2])
         assert out[0][:2] == out[1][:2] and torch.equal(out[0][2], out[1][2])
+
+
+# an operator whose schedule was never set takes its rows in slot order where at most one column per
+# sampled row is present (fewer rows than the sample, a tile's edge, several tiles), and in canonical
+# order otherwise; a set schedule is what it says
+@pytest.mark.parametrize("nvec,dtype", [(1, torch.float64), (3, torch.float32), (16, torch.float64)])
+@pytest.mark.parametrize("name,n", [("few", 2), ("few", 64), ("few", 257), ("few", 20_001), ("dense", 300),
+                                    ("dense", 6000), ("complex", 700)])
+def test_unset_schedule_bitwise(name, n, nvec, dtype):
+    if name == "dense":
+        keys, ops = np.arange(n, dtype=np.uint64).reshape(-1, 1), wl.tfim_chain(40)
+    else:
+        keys, ops = _chain_keys(n, n // 8), wl.xxz_terms(40, [(0, 1), (7, 31)], 1.0, 0.5)
+        if name == "complex":
+            ops = wl.TermList.from_terms(40, list(ops.terms()) + [(0.5j, [(3, wl.RAISE), (9, wl.LOWER)]),
+                                                                  (-0.5j, [(3, wl.LOWER), (9, wl.RAISE)])], False)
+            dtype = {torch.float64: torch.complex128, torch.float32: torch.complex64}[dtype]
+    sub = qsd.Subspace(keys, 40)
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(ops))
+    assert H.is_complex == (name == "complex")
+    default = qsd.SCHED_XCD_REMAP | qsd.SCHED_FILTER_FIRST
+    x = torch.randn((sub.N, nvec) if nvec > 1 else sub.N, dtype=dtype, device="cuda")
+    say("unset schedule", name, n, nvec, dtype)
+    assert H.schedule == default
+    y = H.matvec(x, out=torch.full_like(x, float("nan")))
+    b = qsd.matvec_batched([H, H], [x, x])
+    H.schedule = default
+    z = H.matvec(x, out=torch.full_like(x, float("nan")))
+    assert torch.equal(y, z) and torch.equal(b[0], z) and torch.equal(b[1], z)
