@@ -141,13 +141,16 @@ __global__ __launch_bounds__(256) void k_prod_csr_count(ProdView<ET> p, int64_t 
     counts[(int64_t)b * p.na + a] = n;
 }
 
-// What a row's entries are made of.
-template <class ET>
+// What a row's entries are made of.  `dep` and `tail` are the class A table (a row per high qubit) and
+// the block's class B tails; staged, their copies in LDS, the table's rows only those that the high
+// part has set.
+template <class ET, bool STAGED>
 struct Row {
     const ProdView<ET> &p;
     const Sorted<ET> &s;
     uint32_t nAB, a, b, occ;
     int64_t row;
+    const ET *dep, *tail;
 
     __device__ __forceinline__ ET class_a(uint32_t k, uint32_t &col) const {
         const int64_t o = (int64_t)a * s.nA + k;
@@ -156,8 +159,9 @@ struct Row {
         col = e & 0xFFFFu;
         if (e >> 16) {
             const uint32_t f = (e >> 16) - 1u;
-            for (uint32_t m = occ; m; m &= m - 1u) {
-                const ET c = p.dep[(int64_t)__builtin_ctz(m) * p.nUa + (f >> 1)];
+            uint32_t r = 0;
+            for (uint32_t m = occ; m; m &= m - 1u, ++r) {
+                const ET c = dep[(STAGED ? r : (uint32_t)__builtin_ctz(m)) * p.nUa + (f >> 1)];
                 v += (f & 1u) ? -c : c;
             }
         }
@@ -170,7 +174,7 @@ struct Row {
         const uint32_t e = p.b1_ent[2 * at + 1];
         const ET w = p.wtab[(int64_t)((e & 0xFFFFFFu) >> 1) * p.na + a];
         ET v = (e & 1u) ? -w : w;
-        for (uint32_t t = 0; t < e >> 24; ++t) v += p.tail[at * p.tail_len + t];
+        for (uint32_t t = 0; t < e >> 24; ++t) v += tail[k * p.tail_len + t];
         return v;
     }
     __device__ __forceinline__ ET class_ab(uint32_t ab, uint32_t k, uint32_t &col) const {
@@ -186,27 +190,48 @@ struct Row {
 // writes a row's entries 64 at a time, each lane finding its entry's block by bisection of the
 // block list (in LDS, uniform over the workgroup's rows).  A lane per row instead, walking its
 // entries, wrote 64 lines an instruction: 315 us for 8.9M entries (301 x 301) and 2250 us for 80M.
-constexpr uint32_t kFillRows = 32;  // rows per workgroup
+// A wave has entries of every class in nearly every instruction, and the sums over the high part's
+// set qubits and over the tails are chains of reads: from LDS, not from L2 (whole builds of 301 x 301
+// 250 -> 202 us, of 600 x 600 892 -> 735).  Rows per workgroup, which share the tables: 8 204 and
+// 800 us, 16 202 and 734, 32 211 and 745, 64 213 and 785.
+constexpr uint32_t kFillRows = 16;
+
+template <class ET>
+size_t fill_lds(const qsd_prod *p, uint32_t nB) {
+    return (nB * sizeof(uint3) + 15u) / 16u * 16u + ((size_t)p->max_occ * p->nUa + (size_t)p->nB1 * p->tail_len) * sizeof(ET);
+}
 
 template <class ET, class IT>
 __global__ __launch_bounds__(256) void k_prod_csr_fill(ProdView<ET> p, Sorted<ET> s, uint32_t nAB,
                                                        const int64_t *__restrict__ indptr, IT *__restrict__ idx,
                                                        ET *__restrict__ val) {
-    extern __shared__ uint3 blk[];
+    extern __shared__ __align__(16) char fill_smem[];
+    uint32_t *bz = (uint32_t *)fill_smem, *bx = bz + s.nB, *by = bx + s.nB;  // the block list, by component
+    ET *tail = (ET *)(fill_smem + (s.nB * sizeof(uint3) + 15u) / 16u * 16u), *dep = tail + p.nB1 * p.tail_len;
     const uint32_t tiles = (p.na + kFillRows - 1u) / kFillRows;
     const uint32_t b = blockIdx.x / tiles, a0 = (blockIdx.x - b * tiles) * kFillRows, lane = threadIdx.x & 63u;
     const uint32_t nblk = s.nblk[b];
-    for (uint32_t k = threadIdx.x; k < nblk; k += 256u) blk[k] = s.b[(int64_t)b * s.nB + k];
+    for (uint32_t k = threadIdx.x; k < nblk; k += 256u) {
+        const uint3 w = s.b[(int64_t)b * s.nB + k];
+        bx[k] = w.x;
+        by[k] = w.y;
+        bz[k] = w.z;
+    }
+    const uint32_t ntail = p.blen[b] * p.tail_len, occ = p.blen[3 * (int64_t)p.nb + b] & p.rmask;
+    for (uint32_t k = threadIdx.x; k < ntail; k += 256u) tail[k] = p.tail[(int64_t)b * p.nB1 * p.tail_len + k];
+    uint32_t q = 0;
+    for (uint32_t m = occ; m; m &= m - 1u, ++q)
+        for (uint32_t u = threadIdx.x; u < p.nUa; u += 256u) dep[q * p.nUa + u] = p.dep[__builtin_ctz(m) * p.nUa + u];
     __syncthreads();
     for (uint32_t a = a0 + (threadIdx.x >> 6); a < min(a0 + kFillRows, p.na); a += 4u) {
-        const Row<ET> R{p, s, nAB, a, b, p.blen[3 * (int64_t)p.nb + b] & p.rmask, (int64_t)b * p.na + a};
+        const Row<ET, true> R{p, s, nAB, a, b, occ, (int64_t)b * p.na + a, dep, tail};
         const uint32_t at = p.place[a];
         const uint32_t n3 = p.alen[2 * (int64_t)p.na + at], nown = p.alen[at] + p.alen[p.na + at] + 1u;
         const uint32_t pos_a = s.pos[2 * a], pos_ab = s.pos[2 * a + 1];
         const int64_t o = indptr[R.row];
         const uint32_t len = (uint32_t)(indptr[R.row + 1] - o);
         auto first = [&](uint32_t i) {  // entries before block i
-            const uint32_t z = blk[i].z;
+            const uint32_t z = bz[i];
             return (z & kBPos) * n3 + ((z >> 14) & kBPos) + ((z >> 31) ? nown : 0u);
         };
         for (uint32_t e = lane; e < len; e += 64u) {
@@ -219,7 +244,7 @@ __global__ __launch_bounds__(256) void k_prod_csr_fill(ProdView<ET> p, Sorted<ET
                     hi = mid - 1u;
             }
             uint32_t m = e - first(lo), col = a;
-            const uint3 w = blk[lo];
+            const uint2 w = {bx[lo], by[lo]};
             ET v;
             if (w.y == kBOwn) {
                 if (m == pos_a)
@@ -237,7 +262,8 @@ __global__ __launch_bounds__(256) void k_prod_csr_fill(ProdView<ET> p, Sorted<ET
     }
 }
 
-// Operators with pairs of keys that have no term: a lane per row walks its blocks.
+// Operators with pairs of keys that have no term (or with tables that LDS cannot hold): a lane per row
+// walks its blocks.
 template <class ET, class IT>
 __global__ __launch_bounds__(256) void k_prod_csr_walk(ProdView<ET> p, Sorted<ET> s, uint32_t nAB,
                                                        const int64_t *__restrict__ indptr, IT *__restrict__ idx,
@@ -245,7 +271,8 @@ __global__ __launch_bounds__(256) void k_prod_csr_walk(ProdView<ET> p, Sorted<ET
     const uint32_t tiles = (p.na + 255u) / 256u;
     const uint32_t b = blockIdx.x / tiles, a = (blockIdx.x - b * tiles) * 256u + threadIdx.x;
     if (a >= p.na) return;
-    const Row<ET> R{p, s, nAB, a, b, p.blen[3 * (int64_t)p.nb + b] & p.rmask, (int64_t)b * p.na + a};
+    const Row<ET, false> R{p, s, nAB, a, b, p.blen[3 * (int64_t)p.nb + b] & p.rmask, (int64_t)b * p.na + a, p.dep,
+                           p.tail + (int64_t)b * p.nB1 * p.tail_len};
     const uint32_t at = p.place[a], n3 = p.alen[2 * (int64_t)p.na + at], nA = p.alen[at] + p.alen[p.na + at];
     int64_t o = indptr[R.row];
     auto put = [&](int64_t col, ET v) {
@@ -313,8 +340,9 @@ int prod_csr_fill(const qsd_ham *h, const int64_t *indptr, void *indices, void *
     const ProdView<ET> v = prod_view<ET>(h);
     k_prod_sort_low<ET><<<(p->na + 3u) / 4u, 256, 0, st>>>(v, p->nAB, s);
     k_prod_sort_high<ET><<<p->nb, 256, s.nB * 4u, st>>>(v, s);
-    if (p->full)
-        k_prod_csr_fill<ET, IT><<<(p->na + kFillRows - 1u) / kFillRows * p->nb, 256, s.nB * sizeof(uint3), st>>>(
+    const size_t lds = fill_lds<ET>(p, s.nB);
+    if (p->full && lds <= 64u * 1024u)
+        k_prod_csr_fill<ET, IT><<<(p->na + kFillRows - 1u) / kFillRows * p->nb, 256, lds, st>>>(
             v, s, p->nAB, indptr, (IT *)indices, (ET *)data);
     else
         k_prod_csr_walk<ET, IT><<<(p->na + 255u) / 256u * p->nb, 256, 0, st>>>(v, s, p->nAB, indptr, (IT *)indices, (ET *)data);
