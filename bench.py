@@ -33,6 +33,7 @@ KERNEL_SOURCES = {
     "k_matvec": ["paper_2603_18731_amd/csrc/engine.h", "paper_2603_18731_amd/csrc/matvec.h",
                  "paper_2603_18731_amd/csrc/device.h", "paper_2603_18731_amd/csrc/spmv_impl.h"],
     "k_prod_matvec": ["paper_2603_18731_amd/csrc/product.h", "paper_2603_18731_amd/csrc/product.hip"],
+    "k_hits_matvec": ["paper_2603_18731_amd/csrc/hits.h", "paper_2603_18731_amd/csrc/hits.hip"],
 }
 LDS_PEAK_GBS = 256 * 128 * 2.4  # 256 CUs x 128 bytes per clock at 2.4 GHz
 
@@ -703,8 +704,14 @@ def measure_spmv(w, nvec, dtype_name, steps, warmup, max_load, schedule, split=0
     # coefficient read per stored element
     kernel = "k_prod_matvec" if product and group_order == "parts" and not sched & qsd.SCHED_HASH_LOOKUP and \
         not H.is_complex else "k_matvec"
+    # a sparse operator under a slot-order schedule runs from the list of its elements: every row
+    # streams its diagonal, x and y; an element reads its list entry, its row's key and x
+    if kernel == "k_matvec" and sched & qsd.SCHED_SLOT_ORDER and not sched & qsd.SCHED_HASH_LOOKUP and hits <= N:
+        kernel = "k_hits_matvec"
     if kernel == "k_matvec":
         bound, peak, balg = "hbm", HBM_PEAK_GBS, algorithmic_bytes(N, W, probes, hits, nvec, esz)
+    elif kernel == "k_hits_matvec":
+        bound, peak, balg = "hbm", HBM_PEAK_GBS, N * (8 + 2 * nvec * esz) + hits * (16 + 8 * W + nvec * esz)
     else:
         bound, peak, balg = "lds", LDS_PEAK_GBS, hits * (nvec + 1) * esz
     achieved = balg / (k_avg / 1e3) / 1e9

@@ -106,8 +106,8 @@ DiagPlan diag_plan(const qsd_op *op) {
 // Bound by the vector ALU: seven operations per row and term of a kDiagSign run (masks, parity, the
 // sign moved into the coefficient, the sum), where whole masks of four words took thirty; the terms
 // are scalar loads, four in flight.  A term that does not match adds 0, which changes no sum that
-// starts at 0.  1M strings of 200 qubits, 417 terms: 323 -> 62 us; 150 rows of a 24-qubit molecule, 300
-// terms: 43 -> 23.
+// starts at 0.  1M strings of 200 qubits, 200 terms: 323 -> 62 us; small subspaces of a 16-orbital
+// molecule, bound by the chain of loads: 43 -> 23.
 template <int Wp>
 __global__ __launch_bounds__(kBlock) void k_diag(SubView s, const DiagRun *__restrict__ runs, uint32_t nruns,
                                                  const DiagFour<DiagTerm> *__restrict__ terms,

@@ -80,10 +80,12 @@ __global__ __launch_bounds__(kBlock) void k_hit_fill(SubView s, HamView h, const
 }
 
 // The first `nl` workgroups take the listed rows (chains of dependent reads, so they start first,
-// the longest rows before the rest), the others write y = d x, element by element in storage order (coalesced whatever the
-// number of vectors), for the rows without elements.  The listed rows' sums are formed as in every other path (d x first, then the elements in group
-// order), so the results are bitwise the same.  Bound by the stream of x, d and y: the list is a
-// few per cent of the rows on the workloads this serves.
+// the longest rows before the rest), the others write y = d x, element by element in storage order
+// (coalesced whatever the number of vectors), for the rows without elements.  The listed rows' sums
+// are formed as in every other path (d x first, then the elements in group order), so the results are
+// bitwise the same.  Bound by the stream of x, d and y: the list is a few per cent of the rows on the
+// workloads this serves.  3M rows of 200 qubits, 8 vectors: 119 us, 106 at the rate of a copy; with
+// the row engine 1651.
 constexpr int kDiagItems = 4;
 
 template <int Wp, int NV, class ET, bool CPLX>
