@@ -74,7 +74,7 @@ __host__ __device__ inline int64_t prod_at(uint32_t k, uint32_t na, uint32_t at)
 // What the SpMV kernels read of a plan, by value (or in a request table).
 template <class ET>
 struct ProdView {
-    uint32_t na, nb, T, nB1, nB2, nBAB, nUa, nU, tail_len, rmask, full;
+    uint32_t na, nb, T, aux, nB1, nB2, nBAB, nUa, nU, tail_len, rmask, full;
     const uint32_t *__restrict__ a1_ent;
     const uint16_t *__restrict__ a2_col;
     const uint32_t *__restrict__ ab_ent;

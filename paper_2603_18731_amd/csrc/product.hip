@@ -22,8 +22,8 @@ constexpr uint32_t kMaxTail = 200;           // terms after the table, counted i
 // tiles with a short last one), 512 950, 768 979; 600 x 600: 98, 88, 88, 89.
 constexpr uint32_t kMaxThreads = 512;
 // Waves per SIMD that the registers must allow.  600 x 600: 88 us without it, 72 with 7; 8 costs
-// scalar spills (300 x 301: 24.6 -> 26.4).
-constexpr int kWaves = 7;
+// scalar spills (300 x 301: 24.6 -> 26.4).  Four vectors spill at 7 (400 x 400 in FP32 46 us, at 5 44).
+constexpr int waves_for(int V) { return V >= 4 ? 5 : 7; }
 constexpr uint64_t kMaxTable = 1ull << 23;   // entries of a two-sided table
 
 // What the list kernels read of the operator.
@@ -236,6 +236,28 @@ struct alignas(4 * sizeof(T)) Four {
     T v[4];
 };
 
+// Where the class B tails lie in a workgroup's LDS: after x with its zero and `aux` table entries, and
+// after the sums in rank order.
+template <class ET>
+__host__ __device__ inline uint32_t tail_at(uint32_t na, uint32_t T, uint32_t aux, int V) {
+    const uint32_t a = ((na + 1u) * V + aux) * (uint32_t)sizeof(ET), b = T * V * 8u;
+    return ((a > b ? a : b) + 31u) / 32u * 32u;
+}
+
+// V values of the interleaved vectors, read or written at once.
+template <class ET, int V>
+struct alignas(V * sizeof(ET) < 16 ? V * sizeof(ET) : 16) Pack {
+    ET v[V];
+};
+
+// Whether a workgroup's V vectors can be: all of them are there, and aligned.
+template <class ET, int V>
+__device__ __forceinline__ bool wide(const ET *x, int64_t ldx, const ET *y, int64_t ldy, int nv) {
+    return V > 1 && nv == V &&
+           (((uintptr_t)x | (uintptr_t)y | (uintptr_t)(ldx * sizeof(ET)) | (uintptr_t)(ldy * sizeof(ET))) &
+            (alignof(Pack<ET, V>) - 1u)) == 0u;
+}
+
 // One workgroup: T low parts of the high part b, V of the interleaved vectors.  Class A and AB
 // columns lie in whole rows x[b'][:], which are staged in LDS (12 KB for 1500 strings in FP64), so
 // the random gathers run at the LDS rate and not at the 0.36 lanes per clock and CU that the texture
@@ -246,12 +268,17 @@ struct alignas(4 * sizeof(T)) Four {
 // together (in rank order a wave of 1500 strings walks 27 entries for a mean of 19), and A2 and AB
 // are padded with entries that add 0 * 0 and read four at a time, so there is no lane test and no
 // remainder loop.  Before class B the sums go back to rank order through LDS.  Lists in rank order
-// with a remainder loop: 1500 x 1500 1200 -> 950 us, 600 x 600 117 -> 88.
+// with a remainder loop: 1500 x 1500 1200 -> 950 us, 600 x 600 117 -> 88.  With the class B tails in
+// LDS 920 and (88 -> 72 by the registers' bound) 69.
 //
 // Bound: LDS.  An AB element is two LDS reads (coefficient, x) at random banks, some three and a half
 // passes each; 1500 x 1500 has 970 M of them.  Two high parts per workgroup, which share the list
 // reads, gained nothing here (1115 us) and loading the next row into registers ahead of its turn 2 %.
-template <class ET, int V>
+//
+// With several vectors a lane's values lie ldx apart from the next lane's, so an instruction that
+// reads one of them meets 64 lines: WIDE reads all V at once (300 x 300, 8 vectors in FP64 102 -> 68 us,
+// 400 x 400, 4 in FP32 80 -> 44; eight vectors per workgroup spill: 80 and 16 vectors 184 for 228).
+template <class ET, int V, bool WIDE>
 __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__restrict__ x, int64_t ldx,
                                            ET *__restrict__ y, int64_t ldy, int nv, uint32_t tile, uint32_t b,
                                            char *smem) {
@@ -262,11 +289,20 @@ __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__re
     const bool valid = threadIdx.x < p.T && pos < p.na;
     const uint32_t at = valid ? pos : p.na - 1u;
 
+    using Vec = Pack<ET, V>;
+    auto get = [&](const ET *at) {
+        Vec t;
+        if constexpr (WIDE) {
+            t = *(const Vec *)at;
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) t.v[v] = (V == 1 || v < nv) ? at[v] : (ET)0;
+        }
+        return t;
+    };
     auto stage = [&](uint32_t bc) {
         const ET *xr = x + (int64_t)bc * p.na * ldx;
-        for (uint32_t j = threadIdx.x; j < p.na; j += B)
-#pragma unroll
-            for (int v = 0; v < V; ++v) xs[j * V + v] = (V == 1 || v < nv) ? xr[(int64_t)j * ldx + v] : (ET)0;
+        for (uint32_t j = threadIdx.x; j < p.na; j += B) *(Vec *)(xs + j * V) = get(xr + (int64_t)j * ldx);
     };
     // a wave's longest list, in steps of four
     auto wave_steps = [](uint32_t n) {
@@ -279,8 +315,9 @@ __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__re
     {
         const int64_t row = (int64_t)b * p.na + al;
         const double dr = (double)p.diag[row];
+        const Vec t = get(x + row * ldx);
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[v] = (V == 1 || v < nv) ? dr * (double)x[row * ldx + v] : 0.0;
+        for (int v = 0; v < V; ++v) acc[v] = dr * (double)t.v[v];
     }
     const uint32_t n1 = valid ? p.alen[at] : 0u;
     const uint32_t n2 = wave_steps(valid ? p.alen[p.na + at] : 0u);
@@ -289,6 +326,15 @@ __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__re
     const uint32_t occ = p.blen[3 * (int64_t)p.nb + b] & p.rmask;
     const uint32_t nocc = (uint32_t)__popc(occ);
     if (threadIdx.x < V) xs[p.na * V + threadIdx.x] = (ET)0;
+    // class B terms after the table, in fours (0 past the last), where the sums at the end leave them
+    const uint32_t m1 = p.blen[b], m2 = p.blen[p.nb + b], tl = (p.tail_len + 3u) / 4u * 4u;
+    ET *tails = (ET *)(smem + tail_at<ET>(p.na, p.T, p.aux, V));
+    for (uint32_t k = threadIdx.x; k < m1 * tl; k += B) {
+        const uint32_t i = k / tl, t = k - i * tl;
+        const int64_t o = (int64_t)b * p.nB1 + i;
+        // (read from L2 one by one they were a chain of scalar loads: 1500 x 1500 950 us, 337 x 411 29)
+        tails[k] = t < p.b1_ent[2 * o + 1] >> 24 ? p.tail[o * p.tail_len + t] : (ET)0;
+    }
     stage(b);
     uint32_t m = occ;
     for (uint32_t r = 0; m; ++r, m &= m - 1u) {
@@ -375,50 +421,65 @@ __device__ __forceinline__ void prod_block(const ProdView<ET> &p, const ET *__re
     const uint32_t a = pos;
     const ET *xa = x + (int64_t)a * ldx;
     const int64_t bstride = (int64_t)p.na * ldx;
-    const uint32_t m1 = p.blen[b], m2 = p.blen[p.nb + b];
     for (uint32_t i = 0; i < m1; ++i) {
         const int64_t o = (int64_t)b * p.nB1 + i;
         const uint32_t bc = p.b1_ent[2 * o], e = p.b1_ent[2 * o + 1];
         const uint32_t w = (e & 0xFFFFFFu) >> 1, nt = e >> 24;
         const ET wv = p.wtab[(int64_t)w * p.na + a];
+        const Vec t = get(xa + bc * bstride);
         ET val = (e & 1u) ? -wv : wv;
-        for (uint32_t t = 0; t < nt; ++t) val += p.tail[o * p.tail_len + t];
+        for (uint32_t q = 0; q < nt; q += 4u) {
+            const Four<ET> c = *(const Four<ET> *)(tails + i * tl + q);
 #pragma unroll
-        for (int v = 0; v < V; ++v)
-            if (V == 1 || v < nv) acc[v] += (double)val * (double)xa[bc * bstride + v];
+            for (int j = 0; j < 4; ++j) val += c.v[j];
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] += (double)val * (double)t.v[v];
     }
 #pragma unroll 8
     for (uint32_t i = 0; i < m2; ++i) {
         const int64_t o = (int64_t)b * p.nB2 + i;
         const double val = (double)p.b2[o];
-        const int64_t c = p.b2_col[o] * bstride;
+        const Vec t = get(xa + p.b2_col[o] * bstride);
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] += val * (double)t.v[v];
+    }
+    ET *yr = y + ((int64_t)b * p.na + a) * ldy;
+    if constexpr (WIDE) {
+        Vec t;
+#pragma unroll
+        for (int v = 0; v < V; ++v) t.v[v] = (ET)acc[v];
+        *(Vec *)yr = t;
+    } else {
 #pragma unroll
         for (int v = 0; v < V; ++v)
-            if (V == 1 || v < nv) acc[v] += val * (double)xa[c + v];
+            if (V == 1 || v < nv) yr[v] = (ET)acc[v];
     }
-    const int64_t row = (int64_t)b * p.na + a;
-#pragma unroll
-    for (int v = 0; v < V; ++v)
-        if (V == 1 || v < nv) y[row * ldy + v] = (ET)acc[v];
 }
 
 template <class ET, int V>
-__global__ __launch_bounds__(kMaxThreads, kWaves) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ x,
+__global__ __launch_bounds__(kMaxThreads, waves_for(V)) void k_prod_matvec(ProdView<ET> p, const ET *__restrict__ x,
                                                                     int64_t ldx, ET *__restrict__ y, int64_t ldy,
                                                                     int nvec) {
-    extern __shared__ __align__(16) char smem[];
+    extern __shared__ __align__(32) char smem[];
     // workgroups of one XCD take consecutive high parts of one tile of low parts: they share the
     // tile's lists in that XCD's L2
     const uint32_t id = (uint32_t)tile_index(blockIdx.x, gridDim.x, true);
     const uint32_t tile = id / p.nb;
     const int v0 = blockIdx.y * V;
-    prod_block<ET, V>(p, x + v0, ldx, y + v0, ldy, min(V, nvec - v0), tile, id - tile * p.nb, smem);
+    const int nv = min(V, nvec - v0);
+    x += v0;
+    y += v0;
+    if (wide<ET, V>(x, ldx, y, ldy, nv))
+        prod_block<ET, V, (V > 1)>(p, x, ldx, y, ldy, nv, tile, id - tile * p.nb, smem);
+    else
+        prod_block<ET, V, false>(p, x, ldx, y, ldy, nv, tile, id - tile * p.nb, smem);
 }
 
 // Requests of a table: a workgroup finds its request by the requests' first workgroups.
 template <class ET, int V>
-__global__ __launch_bounds__(kMaxThreads, kWaves) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n) {
-    extern __shared__ __align__(16) char smem[];
+__global__ __launch_bounds__(kMaxThreads, waves_for(V)) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n) {
+    extern __shared__ __align__(32) char smem[];
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -435,17 +496,22 @@ __global__ __launch_bounds__(kMaxThreads, kWaves) void k_prod_batched(const Prod
     id -= vc * per;
     const uint32_t tile = id / R.p.nb;
     const int v0 = (int)vc * V;
-    prod_block<ET, V>(R.p, R.x + v0, R.ld, R.y + v0, R.ld, min(V, R.nv - v0), tile, id - tile * R.p.nb, smem);
+    const int nv = min(V, R.nv - v0);
+    if (wide<ET, V>(R.x + v0, R.ld, R.y + v0, R.ld, nv))
+        prod_block<ET, V, (V > 1)>(R.p, R.x + v0, R.ld, R.y + v0, R.ld, nv, tile, id - tile * R.p.nb, smem);
+    else
+        prod_block<ET, V, false>(R.p, R.x + v0, R.ld, R.y + v0, R.ld, nv, tile, id - tile * R.p.nb, smem);
 }
 
 uint32_t tiles_of(const qsd_prod *p) { return (p->na + p->T - 1u) / p->T; }
 
 // LDS of a workgroup: x and the zero after it, the class A table rows or the AB coefficients and the
-// zero after them; then the sums in rank order.
+// zero after them (then the sums in rank order), and the class B tails.
+uint32_t aux_entries(const qsd_prod *p) { return std::max(p->max_occ * p->nUa, 2u * p->nU + 1u); }
+
 template <class ET>
 uint32_t lds_bytes(const qsd_prod *p, int V) {
-    const uint32_t aux = std::max(p->max_occ * p->nUa, 2u * p->nU + 1u);
-    return std::max((uint32_t)(((p->na + 1u) * V + aux) * sizeof(ET)), p->T * V * 8u);
+    return tail_at<ET>(p->na, p->T, aux_entries(p), V) + p->nB1 * ((p->tail_len + 3u) / 4u * 4u) * (uint32_t)sizeof(ET);
 }
 
 // ------------------------------------------------------------------- host classification
@@ -842,7 +908,7 @@ ProdView<ET> prod_view(const qsd_ham *h) {
         v = &p->f;
         diag = h->diag32;
     }
-    return ProdView<ET>{p->na, p->nb, p->T, p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask,
+    return ProdView<ET>{p->na, p->nb, p->T, aux_entries(p), p->nB1, p->nB2, p->nBAB, p->nUa, p->nU, p->tail_len, p->rmask,
                         p->full ? 1u : 0u,
                         p->a1_ent, p->a2_col, p->ab_ent, p->b1_ent, p->b2_col, p->bab_ent, p->alen, p->blen, p->order,
                         p->place, v->a1, v->a2, v->dep, v->ctab, v->wtab, v->tail, v->b2, diag};

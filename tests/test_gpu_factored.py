@@ -82,6 +82,27 @@ def test_tiles_bitwise(na, nb, nvec, dtype):
     _same_as_table(H, _vec(sub.N, nvec, dtype))
 
 
+# whole groups of vectors are read at once where x, y and their row stride are aligned: aligned, one
+# element off in x, in y or in both, a stride that is no multiple of 16 bytes, and a short last group
+@pytest.mark.parametrize("nvec,dtype", [(2, torch.float64), (4, torch.float64), (6, torch.float64), (8, torch.float64),
+                                        (2, torch.float32), (4, torch.float32), (6, torch.float32)])
+def test_alignment_bitwise(nvec, dtype):
+    ops, keys = c3_parts(130, 9)
+    sub = qsd.Subspace(keys, ops.n_qubits)
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(ops))
+    x = _vec(sub.N, nvec, dtype)
+    say("factored alignment", nvec, dtype)
+    want = _same_as_table(H, x)
+    n = x.numel()
+    for ox, oy in ((1, 0), (0, 1), (1, 1), (2, 2)):
+        xs = torch.zeros(n + 4, dtype=dtype, device="cuda")[ox:ox + n].view_as(x).copy_(x)
+        ys = torch.full((n + 4,), float("nan"), dtype=dtype, device="cuda")
+        y = ys[oy:oy + n].view_as(x)
+        H.matvec(xs, out=y)
+        assert torch.equal(y, want)
+        assert int(torch.isnan(ys).sum()) == 4  # nothing beside y
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_non_finite_stays_in_its_rows(value):
     """The entries that fill up the lists add 0 * 0: a value of x that is not finite reaches the rows
