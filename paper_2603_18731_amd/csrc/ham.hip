@@ -183,6 +183,9 @@ __global__ __launch_bounds__(kBlock) void k_diag(SubView s, const DiagRun *__res
 
 // Columns present in the subspace of kSampleRows rows spread over it (a wave per row, a lane per group).
 constexpr int kSampleRows = 64;
+// What one row counts at most: a sample around a reference string has a few rows with hundreds (5M
+// strings of 200 qubits, 0.09 on average, hit one and kept the slower order).
+constexpr uint32_t kSampleMost = 4;
 constexpr int64_t kSampleGroups = 4096;  // operators with more are not sampled
 
 template <int Wp>
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_columns(SubView s, const uint
         n += probe<Wp>(s, hrow ^ g_hash[g], col) >= 0;
     }
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
-    if (lane == 0) atomicAdd(count, n);
+    if (lane == 0) atomicAdd(count, min(n, kSampleMost));
 }
 
 // ------------------------------------------------------------------------------- matvec
