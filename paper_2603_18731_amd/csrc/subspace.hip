@@ -512,13 +512,16 @@ __global__ __launch_bounds__(kBlock) void k_hash_insert(SubView s, uint64_t *__r
 }
 
 // Occupancy of the filled table (C slots, whole waves): a pass over 64 MB for 1M strings takes 14 us,
-// an atomic per string during the insertion 30.
+// an atomic per string during the insertion 30.  C may be 2^32, more threads than a launch can have,
+// so the workgroups stride over the table.
+constexpr int64_t kBitmapBlocks = 1 << 20;
+
 __global__ __launch_bounds__(kBlock) void k_bitmap(const uint64_t *__restrict__ slots, int64_t C,
                                                    uint32_t *__restrict__ bitmap) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= C) return;
-    const uint64_t m = __ballot(slots[i] != ~0ull);
-    if ((threadIdx.x & 31) == 0) bitmap[i >> 5] = (uint32_t)(m >> (threadIdx.x & 32));
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < C; i += (int64_t)gridDim.x * kBlock) {
+        const uint64_t m = __ballot(slots[i] != ~0ull);
+        if ((threadIdx.x & 31) == 0) bitmap[i >> 5] = (uint32_t)(m >> (threadIdx.x & 32));
+    }
 }
 
 template <int Wp>
@@ -571,6 +574,13 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
 }
 
 inline unsigned grid_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
+inline unsigned bitmap_grid(int64_t C) { return (unsigned)std::min(kBitmapBlocks, (C + kBlock - 1) / kBlock); }
+
+// Whether the launches since the call began were accepted (a synchronize does not say so).
+int launched(const char *what) {
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? QSD_OK : fail(QSD_ERR_HIP, "%s: launch failed: %s", what, hipGetErrorString(e));
+}
 
 // ------------------------------------------------------------------- slot order of the rows
 
@@ -654,7 +664,8 @@ int build_order(const qsd_subspace *sub, const uint64_t *hkey, const uint32_t *p
         k_slot_order<<<grid_for(nw, kBlock), kBlock, 0, st>>>(bitmap, slots, nw, base, exact ? 1u : 0u, o.order);
         k_gather_rows<<<grid_for(N, kBlock), kBlock, 0, st>>>(krows ? krows : sub->keys, krows != nullptr, hkey, pkey,
                                                               o.order, N, sub->Wp, o.keys, o.hkey, o.pkey);
-        if (hipStreamSynchronize(st) != hipSuccess)
+        rc = launched("slot order");
+        if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
             rc = fail(QSD_ERR_HIP, "slot order failed: %s", hipGetErrorString(hipGetLastError()));
     }
     dev_free(base);
@@ -718,6 +729,7 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
         hash_words(sub->n_qubits, sub->z);
         hash_byte_tables(Wp, sub->z, tab);
         int64_t N = 0;
+        if ((rc = launched("sort")) != QSD_OK) break;
         if (hipMemcpyAsync(&N, pos + n_in, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             rc = fail(QSD_ERR_HIP, "sort failed: %s", hipGetErrorString(hipGetLastError()));
@@ -748,7 +760,8 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
         // the sort's memory takes the keys as rows for the slot order
         uint64_t *rows = Wp > 1 ? tmp : nullptr;
         k_hash_insert<Wp><<<grid_for(N, kBlock), kBlock, 0, st>>>(v, sub->slots, sub->hkey, sub->ztab, rows);
-        k_bitmap<<<grid_for(C, kBlock), kBlock, 0, st>>>(sub->slots, C, sub->bitmap);
+        k_bitmap<<<bitmap_grid(C), kBlock, 0, st>>>(sub->slots, C, sub->bitmap);
+        if ((rc = launched("hash build")) != QSD_OK) break;
         rc = build_order(sub, sub->hkey, nullptr, C, sub->exact, sub->slots, sub->bitmap, rows, &sub->rows, st);
     } while (0);
     cleanup();
@@ -816,6 +829,7 @@ extern "C" int qsd_subspace_build(const uint64_t *d_bits, int64_t n_in, int32_t 
     sub->W = (n_qubits + 63) / 64;
     sub->Wp = padded_words(n_qubits);
     hipStream_t st = (hipStream_t)stream;
+    (void)hipGetLastError();  // what an earlier call left is not this one's
     int rc;
     switch (sub->Wp) {
         case 1: rc = build_impl<1>(sub, d_bits, n_in, flags, max_load, st); break;
@@ -882,7 +896,8 @@ int rehash_impl(qsd_subspace *sub, int64_t C, int split, hipStream_t st) {
             // writes the row hashes (the same values when the words did not change)
             SubView v{sub->keys, hkey, slots, bitmap, sub->N, (uint32_t)(C - 1), exact ? 1u : 0u};
             k_hash_insert<Wp><<<grid_for(sub->N, kBlock), kBlock, 0, st>>>(v, slots, hkey, ztab, nullptr);
-            k_bitmap<<<grid_for(C, kBlock), kBlock, 0, st>>>(slots, C, bitmap);
+            k_bitmap<<<bitmap_grid(C), kBlock, 0, st>>>(slots, C, bitmap);
+            rc = launched("hash rebuild");
         }
     }
     if (rc == QSD_OK && split > 0) {
@@ -901,6 +916,7 @@ int rehash_impl(qsd_subspace *sub, int64_t C, int split, hipStream_t st) {
         if (rc == QSD_OK) {
             k_fill_u32<<<16, kBlock, 0, st>>>(pfilt, kPartWords, 0u);
             k_part_keys<Wp><<<grid_for(sub->N, kBlock), kBlock, 0, st>>>(sub->keys, sub->N, ptab_d, pkey, pfilt);
+            rc = launched("part filters");
         }
         // the host tables must outlive their copies
         if (rc == QSD_OK && hipStreamSynchronize(st) != hipSuccess)
@@ -1042,6 +1058,7 @@ extern "C" int qsd_subspace_rehash(qsd_subspace *s, double max_load, int32_t spl
     if (C > (1ll << 32)) return fail(QSD_ERR_CAPACITY, "hash table would exceed 2^32 slots");
     if (C == s->C && split == s->split) return QSD_OK;
     hipStream_t st = (hipStream_t)stream;
+    (void)hipGetLastError();
     switch (s->Wp) {
         case 1: return rehash_impl<1>(s, C, split, st);
         case 2: return rehash_impl<2>(s, C, split, st);
