@@ -701,13 +701,10 @@ def measure_spmv(w, nvec, dtype_name, steps, warmup, max_load, schedule, split=0
     ms_per_step = wall * 1e3 / steps
     # an operator that factors over an alpha x beta product runs from per-part lists: no table and
     # no row keys are read, and its bound is the LDS, with at least one value of x and one
-    # coefficient read per stored element
-    kernel = "k_prod_matvec" if product and group_order == "parts" and not sched & qsd.SCHED_HASH_LOOKUP and \
-        not H.is_complex else "k_matvec"
-    # a sparse operator under a slot-order schedule runs from the list of its elements: every row
-    # streams its diagonal, x and y; an element reads its list entry, its row's key and x
-    if kernel == "k_matvec" and sched & qsd.SCHED_SLOT_ORDER and not sched & qsd.SCHED_HASH_LOOKUP and hits <= N:
-        kernel = "k_hits_matvec"
+    # coefficient read per stored element; a sparse operator under a slot-order schedule runs from
+    # the list of its elements: every row streams its diagonal, x and y; an element reads its list
+    # entry, its row's key and x
+    kernel = {qsd.PATH_FACTORED: "k_prod_matvec", qsd.PATH_ELEMENTS: "k_hits_matvec"}.get(H.spmv_path, "k_matvec")
     if kernel == "k_matvec":
         bound, peak, balg = "hbm", HBM_PEAK_GBS, algorithmic_bytes(N, W, probes, hits, nvec, esz)
     elif kernel == "k_hits_matvec":

@@ -320,6 +320,24 @@ int qsd_ham_diag_splitting(const qsd_ham *h, double *lowest, double *splitting, 
 int qsd_ham_set_schedule(qsd_ham *h, uint32_t schedule);
 int qsd_ham_get_schedule(const qsd_ham *h, uint32_t *schedule);
 
+/* The kernels that qsd_matvec takes for this operator as it stands (its schedule, its subspace's
+ * split and what was built beside it decide; the results do not depend on it).
+ *   QSD_PATH_ROWS         every group of every row, rows in canonical order
+ *   QSD_PATH_SLOTS        the same in slot order
+ *   QSD_PATH_SLOTS_SPLIT  slot order, the rows without off-diagonal elements written apart
+ *   QSD_PATH_PRODUCT_MAP  every group of every row, columns from the product map
+ *   QSD_PATH_ELEMENTS     the list of the off-diagonal elements (see QSD_SCHED_SLOT_ORDER)
+ *   QSD_PATH_FACTORED     lists per low and per high part of a product subspace (real operators
+ *                         bound to it whose groups' elements combine from what each part knows;
+ *                         qsd_csr_build and the batched entries use them too) */
+#define QSD_PATH_ROWS 0
+#define QSD_PATH_SLOTS 1
+#define QSD_PATH_SLOTS_SPLIT 2
+#define QSD_PATH_PRODUCT_MAP 3
+#define QSD_PATH_ELEMENTS 4
+#define QSD_PATH_FACTORED 5
+int qsd_ham_spmv_path(const qsd_ham *h, int32_t *path);
+
 /* Autotuner (not in the paper).  Times `reps` SpMVs (nvec vectors of `dtype`, internal buffers)
  * with HIP events for every candidate and keeps the fastest:
  *   QSD_TUNE_SCHEDULE  every schedule above (on the current table);

@@ -31,6 +31,8 @@ V0_UNIFORM, V0_MIN_DIAG, V0_RANDOM, V0_USER = 0, 1, 2, 3
 SCHED_XCD_REMAP, SCHED_SLOT_ORDER, SCHED_LOCKSTEP, SCHED_FILTER_FIRST = 1, 2, 4, 8
 SCHED_ALL = 15
 SCHED_HASH_LOOKUP = 16  # look columns up in the hash table even with a product map
+# what a SpMV runs (``SubspaceHamiltonian.spmv_path``)
+PATH_ROWS, PATH_SLOTS, PATH_SLOTS_SPLIT, PATH_PRODUCT_MAP, PATH_ELEMENTS, PATH_FACTORED = range(6)
 TUNE_SCHEDULE, TUNE_LOAD, TUNE_SPLIT = 1, 2, 4
 CSR_LOWER_MIRROR = 1
 NOALLOC_MAX_REQUESTS, NOALLOC_MAX_TILES = 256, 65536  # limits of qsd_matvec_batched_noalloc
@@ -49,6 +51,7 @@ EXPORTED = [
     "qsd_csr_create", "qsd_csr_info", "qsd_csr_export", "qsd_csr_matvec", "qsd_csr_lanczos", "qsd_csr_block_lanczos",
     "qsd_csr_destroy", "qsd_subspace_select", "qsd_ramps",
     "qsd_ham_diag_splitting", "qsd_batch_add_csr", "qsd_batch_footprint_rows", "qsd_subspace_hash_info",
+    "qsd_ham_spmv_path",
 ]
 
 
@@ -189,6 +192,7 @@ def lib():
         "qsd_ham_set_schedule": ([P, U32], ctypes.c_int),
         "qsd_ham_get_schedule": ([P, P], ctypes.c_int),
         "qsd_ham_autotune": ([P, I32, I32, I32, U32, P, P], ctypes.c_int),
+        "qsd_ham_spmv_path": ([P, P], ctypes.c_int),
         "qsd_subspace_rehash": ([P, D, I32, P], ctypes.c_int),
         "qsd_subspace_hash_info": ([P, P, P, P], ctypes.c_int),
         "qsd_csr_create": ([P, I32, I32, U32, P, P, PP], ctypes.c_int),
@@ -471,6 +475,13 @@ class SubspaceHamiltonian:
     @schedule.setter
     def schedule(self, value: int):
         _check(lib().qsd_ham_set_schedule(self._h, int(value)))
+
+    @property
+    def spmv_path(self) -> int:
+        """What ``matvec`` runs for this operator as it stands: one of ``PATH_*``."""
+        v = ctypes.c_int32()
+        _check(lib().qsd_ham_spmv_path(self._h, ctypes.byref(v)))
+        return v.value
 
     def autotune(self, nvec: int = 1, dtype=None, reps: int = 3, schedule: bool = True, load: bool = True,
                  split: bool = False, stream=None) -> dict:

@@ -467,9 +467,26 @@ int check_dtype(const qsd_ham *h, int32_t dtype) {
 }
 
 }  // namespace
+
+int32_t spmv_path(const qsd_ham *h) {
+    const bool table = (h->schedule & QSD_SCHED_HASH_LOOKUP) != 0;
+    if (prod_usable(h)) return QSD_PATH_FACTORED;
+    if (h->hits && !table && (h->schedule & QSD_SCHED_SLOT_ORDER)) return QSD_PATH_ELEMENTS;
+    if (h->Wp == 1 && h->s->prank && !table) return QSD_PATH_PRODUCT_MAP;
+    if ((h->schedule & QSD_SCHED_SLOT_ORDER) && h->rowbits) return QSD_PATH_SLOTS_SPLIT;
+    return h->launch_schedule() & QSD_SCHED_SLOT_ORDER ? QSD_PATH_SLOTS : QSD_PATH_ROWS;
+}
+
 }  // namespace qsd
 
 using namespace qsd;
+
+extern "C" int qsd_ham_spmv_path(const qsd_ham *h, int32_t *path) {
+    clear_error();
+    if (!h || !path) return fail(QSD_ERR_INVALID_ARG, "NULL argument");
+    *path = spmv_path(h);
+    return QSD_OK;
+}
 
 extern "C" int qsd_ham_create(const qsd_subspace *s, const qsd_op *op, uint32_t flags, const qsd_allocator *alloc,
                               void *stream, qsd_ham **out) {
@@ -534,7 +551,8 @@ extern "C" int qsd_matvec(const qsd_ham *h, int32_t nvec, const void *d_x, int64
     if (ldx > INT32_MAX || ldy > INT32_MAX) return fail(QSD_ERR_INVALID_ARG, "leading dimension of 2^31 or more");
     QSD_TRY(check_dtype(h, dtype));
     hipStream_t st = (hipStream_t)stream;
-    if (prod_usable(h)) {  // real operators only
+    const int32_t path = spmv_path(h);
+    if (path == QSD_PATH_FACTORED) {  // real operators only
         if (dtype == QSD_F64)
             prod_matvec<double>(h, d_x, ldx, d_y, ldy, nvec, st);
         else
@@ -542,7 +560,7 @@ extern "C" int qsd_matvec(const qsd_ham *h, int32_t nvec, const void *d_x, int64
         QSD_CHECK_HIP(hipGetLastError());
         return QSD_OK;
     }
-    if (h->hits && (h->schedule & QSD_SCHED_SLOT_ORDER) && !(h->schedule & QSD_SCHED_HASH_LOOKUP))
+    if (path == QSD_PATH_ELEMENTS)
         return hits_matvec(h, h->hits, nvec, d_x, ldx, d_y, ldy, dtype, st);
     const int chunk = (dtype == QSD_C128 || dtype == QSD_C64) ? 4 : 16;
     const size_t esz = dtype == QSD_F64 ? 8 : dtype == QSD_F32 ? 4 : dtype == QSD_C128 ? 16 : 8;

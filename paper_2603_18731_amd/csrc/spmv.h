@@ -5,6 +5,9 @@
 #include "common.h"
 
 namespace qsd {
+// QSD_PATH_*: what qsd_matvec runs for `h` as it stands.
+int32_t spmv_path(const qsd_ham *h);
+
 // Launches Y = H X for nvec (1..16; 1..4 complex) interleaved vectors of element type ET on
 // an operator whose keys have Wp padded words.
 template <int Wp, class ET, bool CPLX>

@@ -59,13 +59,13 @@ void launch_mv(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ld
     const ET *dre = f32 ? (const ET *)h->diag32 : (const ET *)h->diag;
     const ET *dim = CPLX ? (f32 ? (const ET *)h->diag32_im : (const ET *)h->diag_im) : nullptr;
     const unsigned tiles = grid_for(h->N, kBlock);
-    const bool split = (h->schedule & QSD_SCHED_SLOT_ORDER) && h->rowbits;
-    const unsigned nd = split ? (tiles + 7u) & ~7u : 0u;
+    const int32_t path = spmv_path(h);
+    const unsigned nd = path == QSD_PATH_SLOTS_SPLIT ? (tiles + 7u) & ~7u : 0u;
     // the part-filter variant only for subspaces that have filters (the other one carries no
     // filter code, so it keeps its registers), the product-map variant for one-word product
     // subspaces
     if constexpr (Wp == 1) {
-        if (h->s->prank && !(h->schedule & QSD_SCHED_HASH_LOOKUP)) {
+        if (path == QSD_PATH_PRODUCT_MAP) {
             // tiles within the product's blocks of rows when a block spans at least two tiles
             // (rows in canonical order: each high part's |A| rows are consecutive)
             const uint32_t pna = h->s->pna;
