@@ -473,7 +473,7 @@ int32_t spmv_path(const qsd_ham *h) {
     if (prod_usable(h)) return QSD_PATH_FACTORED;
     if (h->hits && !table && (h->schedule & QSD_SCHED_SLOT_ORDER)) return QSD_PATH_ELEMENTS;
     if (h->Wp == 1 && h->s->prank && !table) return QSD_PATH_PRODUCT_MAP;
-    if ((h->schedule & QSD_SCHED_SLOT_ORDER) && h->rowbits) return QSD_PATH_SLOTS_SPLIT;
+    if ((h->schedule & QSD_SCHED_SLOT_ORDER) && (h->rowbits || h->hits)) return QSD_PATH_SLOTS_SPLIT;
     return h->launch_schedule() & QSD_SCHED_SLOT_ORDER ? QSD_PATH_SLOTS : QSD_PATH_ROWS;
 }
 

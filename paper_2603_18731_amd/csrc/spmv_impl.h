@@ -5,6 +5,7 @@
 #include "common.h"
 #include "device.h"
 #include "engine.h"
+#include "hits.h"
 #include "matvec.h"
 #include "spmv.h"
 
@@ -60,6 +61,7 @@ void launch_mv(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ld
     const ET *dim = CPLX ? (f32 ? (const ET *)h->diag32_im : (const ET *)h->diag_im) : nullptr;
     const unsigned tiles = grid_for(h->N, kBlock);
     const int32_t path = spmv_path(h);
+    const uint64_t *bits = h->hits ? h->hits->rowbits : h->rowbits;  // (one of them at most)
     const unsigned nd = path == QSD_PATH_SLOTS_SPLIT ? (tiles + 7u) & ~7u : 0u;
     // the part-filter variant only for subspaces that have filters (the other one carries no
     // filter code, so it keeps its registers), the product-map variant for one-word product
@@ -81,11 +83,11 @@ void launch_mv(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t ld
     if (h->s->pfilt)
         k_matvec<Wp, NV, ET, CPLX, 1><<<nd + tiles, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), dre, dim,
                                                                     (const ET *)x, ldx, (ET *)y, ldy, nvec,
-                                                                    h->launch_schedule(), h->rowbits, nd);
+                                                                    h->launch_schedule(), bits, nd);
     else
         k_matvec<Wp, NV, ET, CPLX, 0><<<nd + tiles, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), dre, dim,
                                                                     (const ET *)x, ldx, (ET *)y, ldy, nvec,
-                                                                    h->launch_schedule(), h->rowbits, nd);
+                                                                    h->launch_schedule(), bits, nd);
 }
 
 template <int Wp, class ET, bool CPLX>

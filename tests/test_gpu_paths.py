@@ -110,3 +110,18 @@ def test_unset_schedule_samples():
     assert H.spmv_path == qsd.PATH_ROWS
     H = _ham(np.arange(6000, dtype=np.uint64).reshape(-1, 1), wl.tfim_chain(40))
     assert H.spmv_path == qsd.PATH_ROWS
+
+
+@pytest.mark.parametrize("name", ["few", "sampled", "wide"])
+def test_slot_order_through_the_table_is_split(name):
+    """A sparse operator under SLOT_ORDER | HASH_LOOKUP, which the element list does not serve: the
+    rows without elements are still written apart (the list holds the bits that say which)."""
+    keys, tl = CASES[name]()
+    H = _ham(keys, tl)
+    x = torch.randn((H.N, 3), dtype=torch.float64, device="cuda")
+    H.schedule = DEFAULT | qsd.SCHED_HASH_LOOKUP
+    want = H.matvec(x)
+    for extra in (0, qsd.SCHED_XCD_REMAP, qsd.SCHED_LOCKSTEP, qsd.SCHED_FILTER_FIRST):
+        H.schedule = qsd.SCHED_SLOT_ORDER | qsd.SCHED_HASH_LOOKUP | extra
+        assert H.spmv_path == qsd.PATH_SLOTS_SPLIT
+        assert torch.equal(H.matvec(x, out=torch.full_like(x, float("nan"))), want)
