@@ -512,7 +512,8 @@ int qsd_block_lanczos(const qsd_ham *h, int32_t block, const qsd_lanczos_opts *o
  *                   (any may be NULL); async on `stream`.
  * qsd_csr_matvec    Y = A X, same layout and dtype rules as qsd_matvec except that the vector
  *                   dtype must be the stored dtype (DTYPE otherwise).  Entry slots per row with a
- *                   fixed reduction tree: bitwise reproducible.  Async.
+ *                   fixed reduction tree: bitwise reproducible, and a vector's result does not
+ *                   depend on how many are multiplied with it.  Async.
  * qsd_csr_lanczos / qsd_csr_block_lanczos
  *                   qsd_lanczos / qsd_block_lanczos on the stored matrix (opts->spmv_dtype must
  *                   be the stored dtype).

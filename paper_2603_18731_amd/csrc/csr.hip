@@ -13,7 +13,7 @@
 // by column, which makes the result independent of the atomic order.
 //
 // SpMV: 1, 4, 16 or 32 entry slots per row (from the mean row length), entries strided over the
-// row's slots and summed by a fixed shuffle tree: bitwise reproducible.
+// row's slots and summed by a fixed tree: bitwise reproducible, a vector alone or among others.
 #include <algorithm>
 #include <vector>
 
@@ -96,10 +96,10 @@ __global__ void k_fill0_u64(unsigned long long *p, int64_t n) {
         p[i] = 0ull;
 }
 
-// stored entries in flight per lane
-template <int LPR>
-constexpr int csr_batch() {
-    return LPR >= 16 ? 4 : 2;
+// rounds of a row's slots in flight
+template <int S>
+constexpr int csr_rounds() {
+    return S >= 16 ? 4 : 2;
 }
 
 // Index and value loads: non-temporal for long rows (streamed once, kept out of the caches that
@@ -111,11 +111,14 @@ __device__ __forceinline__ T stream_load(const T *p) {
 }
 
 // y[r] = sum over the row's entries of A_rc x[c] for `nvec` <= NV interleaved vectors, FP64
-// accumulation.  S entry slots per row, NV lanes each (consecutive lanes of one wave, a vector a
-// lane), so a slot's lanes read x[c][:] as one piece and a wave instruction meets 64 / NV lines
-// instead of 64 per vector (one lane per slot for all vectors: 16 vectors on 80M entries 4.34 ms, 4
-// vectors 1.27 ms).  A slot takes entries a + slot, a + slot + S, ... in order, a batch at a time
-// with its x in flight together; the slots are added by a fixed tree.
+// accumulation.  S entry slots per row, P * NV consecutive lanes of one wave, a vector a lane: the
+// lanes of a slot read x[c][:] as one piece and a wave instruction meets 64 / NV lines instead of
+// 64 per vector (one lane per slot for all vectors: 16 vectors on 80M entries 4.34 ms, 4 vectors
+// 1.27 ms).  A slot takes entries a + slot, a + slot + S, ... in order, several rounds with their x in
+// flight together; the slots are added by a fixed tree.  Where a wave has no room for S slots of NV
+// lanes a lane has U of them, P apart, with a sum each, so that a vector's result does not depend on
+// how many are multiplied with it (80M entries, fewer slots / U sums a lane, 8 and 16 vectors in FP64
+// 852 / 863 and 1540 / 1587 us, in FP32 649 / 499 and 1146 / 879).
 //
 // With one vector a row gets 32 slots at most: 64 left most lanes of the last batch idle (mean
 // rows of 110 / 225 / 770 entries: 85 / 431 / 8070 us, with 32: 51 / 344 / 7510 us).  The x gathers
@@ -125,24 +128,28 @@ template <int S, int NV, class IT, class ET, bool CPLX>
 __global__ __launch_bounds__(256) void k_csr_spmv(const int64_t *__restrict__ indptr, const IT *__restrict__ idx,
                                                  const ET *__restrict__ val, int64_t N, const ET *__restrict__ x,
                                                  int64_t ldx, ET *__restrict__ y, int64_t ldy, int nvec) {
-    constexpr int L = S * NV;  // lanes per row
-    constexpr int kB = csr_batch<S>();
+    constexpr int P = S * NV <= 64 ? S : 64 / NV;
+    constexpr int U = S / P;
+    constexpr int L = P * NV;  // lanes per row
+    constexpr int kR = (csr_rounds<S>() + U - 1) / U, kB = kR * U;
     const int slot = (threadIdx.x % L) / NV, v = threadIdx.x % NV, vc = NV == 1 || v < nvec ? v : 0;
     const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
-    double are = 0.0, aim = 0.0;
+    double are[U], aim[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) are[u] = aim[u] = 0.0;
     if (row < N) {
         const int64_t a = indptr[row], b = indptr[row + 1];
         // past the row's end the loads repeat its last entry (always valid) and the term is
         // skipped, so the sum takes the entries in order
-        for (int64_t e = a + slot; e < b; e += kB * S) {
+        for (int64_t e = a + slot; e < b; e += kR * S) {
             int64_t c[kB];
             double vr[kB], vi[kB], xr[kB], xi[kB];
 #pragma unroll
             for (int k = 0; k < kB; ++k) {
-                const int64_t ek = min(e + (int64_t)k * S, b - 1);
-                c[k] = (int64_t)stream_load<S>(&idx[ek]);
-                vr[k] = (double)stream_load<S>(&val[CPLX ? 2 * ek : ek]);
-                vi[k] = CPLX ? (double)stream_load<S>(&val[2 * ek + 1]) : 0.0;
+                const int64_t ek = min(e + (int64_t)k * P, b - 1);
+                c[k] = (int64_t)stream_load<P>(&idx[ek]);
+                vr[k] = (double)stream_load<P>(&val[CPLX ? 2 * ek : ek]);
+                vi[k] = CPLX ? (double)stream_load<P>(&val[2 * ek + 1]) : 0.0;
             }
 #pragma unroll
             for (int k = 0; k < kB; ++k) {
@@ -152,38 +159,45 @@ __global__ __launch_bounds__(256) void k_csr_spmv(const int64_t *__restrict__ in
             }
 #pragma unroll
             for (int k = 0; k < kB; ++k) {
-                if (e + (int64_t)k * S >= b) continue;
+                if (e + (int64_t)k * P >= b) continue;
                 if (CPLX) {
-                    are += vr[k] * xr[k] - vi[k] * xi[k];
-                    aim += vr[k] * xi[k] + vi[k] * xr[k];
+                    are[k % U] += vr[k] * xr[k] - vi[k] * xi[k];
+                    aim[k % U] += vr[k] * xi[k] + vi[k] * xr[k];
                 } else {
-                    are += vr[k] * xr[k];
+                    are[k % U] += vr[k] * xr[k];
                 }
             }
         }
     }
+    // the slots of a lane, then those of the row's lanes
+#pragma unroll
+    for (int d = U / 2; d >= 1; d >>= 1)
+#pragma unroll
+        for (int u = 0; u < d; ++u) {
+            are[u] += are[u + d];
+            aim[u] += aim[u + d];
+        }
 #pragma unroll
     for (int d = L / 2; d >= NV; d >>= 1) {
-        are += __shfl_xor(are, d, 64);
-        if (CPLX) aim += __shfl_xor(aim, d, 64);
+        are[0] += __shfl_xor(are[0], d, 64);
+        if (CPLX) aim[0] += __shfl_xor(aim[0], d, 64);
     }
     if (slot == 0 && row < N && v < nvec) {
         if (CPLX) {
-            y[2 * (row * ldy + v)] = (ET)are;
-            y[2 * (row * ldy + v) + 1] = (ET)aim;
+            y[2 * (row * ldy + v)] = (ET)are[0];
+            y[2 * (row * ldy + v) + 1] = (ET)aim[0];
         } else {
-            y[row * ldy + v] = (ET)are;
+            y[row * ldy + v] = (ET)are[0];
         }
     }
 }
 
 template <int S, int NV, class IT, class ET, bool CPLX>
 void launch_spmv(const qsd_csr *c, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
-    constexpr int kS = S * NV <= 64 ? S : 64 / NV;
-    const int64_t threads = c->N * kS * NV;
+    const int64_t threads = c->N * (S * NV <= 64 ? S * NV : 64);
     const unsigned grid = (unsigned)((threads + 255) / 256);
-    k_csr_spmv<kS, NV, IT, ET, CPLX><<<grid, 256, 0, st>>>(c->indptr, (const IT *)c->indices, (const ET *)c->data,
-                                                           c->N, (const ET *)x, ldx, (ET *)y, ldy, nvec);
+    k_csr_spmv<S, NV, IT, ET, CPLX><<<grid, 256, 0, st>>>(c->indptr, (const IT *)c->indices, (const ET *)c->data,
+                                                          c->N, (const ET *)x, ldx, (ET *)y, ldy, nvec);
 }
 
 template <int S, class IT, class ET, bool CPLX>
