@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void k_csr_spmv(const int64_t *__restrict__ in
     constexpr int L = P * NV;  // lanes per row
     constexpr int kR = (csr_rounds<S>() + U - 1) / U, kB = kR * U;
     const int slot = (threadIdx.x % L) / NV, v = threadIdx.x % NV, vc = NV == 1 || v < nvec ? v : 0;
-    const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
+    const int64_t row = (((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x) / L;
     double are[U], aim[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) are[u] = aim[u] = 0.0;
@@ -195,7 +195,9 @@ __global__ __launch_bounds__(256) void k_csr_spmv(const int64_t *__restrict__ in
 template <int S, int NV, class IT, class ET, bool CPLX>
 void launch_spmv(const qsd_csr *c, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
     const int64_t threads = c->N * (S * NV <= 64 ? S * NV : 64);
-    const unsigned grid = (unsigned)((threads + 255) / 256);
+    // (one dimension of a launch holds fewer than 2^32 threads)
+    const int64_t blocks = (threads + 255) / 256, x_blocks = std::min<int64_t>(blocks, 1 << 23);
+    const dim3 grid((unsigned)x_blocks, (unsigned)((blocks + x_blocks - 1) / x_blocks));
     k_csr_spmv<S, NV, IT, ET, CPLX><<<grid, 256, 0, st>>>(c->indptr, (const IT *)c->indices, (const ET *)c->data,
                                                           c->N, (const ET *)x, ldx, (ET *)y, ldy, nvec);
 }

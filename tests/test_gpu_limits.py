@@ -42,3 +42,30 @@ def test_table_of_2_to_32_slots():
             assert torch.equal(H.matvec(x), want)
         del H, sub
         torch.cuda.empty_cache()
+
+
+def _flips(nlo, nhi, split, qubits):
+    """Rows (a, b), a < nlo and b < nhi, of strings of 2 * split qubits, ascending, on the GPU, and the
+    sum of X on ``qubits`` with a field."""
+    b = torch.arange(nhi, dtype=torch.int64, device="cuda") << split
+    keys = (b[:, None] + torch.arange(nlo, dtype=torch.int64, device="cuda")[None, :]).reshape(-1, 1)
+    terms = [(0.25 + 0.125 * k, [(q, wl.X)]) for k, q in enumerate(qubits)]
+    terms += [(0.5 + 0.0625 * q, [(q, wl.Z)]) for q in range(2 * split)]
+    return keys, wl.TermList.from_terms(2 * split, terms)
+
+
+def test_csr_spmm_of_2_to_26_rows():
+    """Rows times lanes of a row reach 2^32: 16 vectors on a matrix of nine entries per row."""
+    keys, tl = _flips(4096, 16384, 14, (0, 1, 5, 11, 14, 15, 20, 27))
+    sub = qsd.Subspace(keys, 28, assume_sorted_unique=True)
+    del keys
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(tl))
+    m = qsd.CsrMatrix(H, dtype=torch.float32)
+    assert m.N == 1 << 26 and m.nnz == 9 * m.N
+    say("csr", m.N, m.nnz)
+    X = torch.randn((m.N, 16), dtype=torch.float32, device="cuda")
+    Y = m.matvec(X, out=torch.full_like(X, float("nan")))
+    for v in (0, 7, 15):
+        assert torch.equal(m.matvec(X[:, v].contiguous()), Y[:, v])
+    del X, Y, m, H, sub
+    torch.cuda.empty_cache()
