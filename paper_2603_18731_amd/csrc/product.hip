@@ -25,6 +25,10 @@ constexpr uint32_t kMaxThreads = 512;
 // scalar spills (300 x 301: 24.6 -> 26.4).  Four vectors spill at 7 (400 x 400 in FP32 46 us, at 5 44).
 constexpr int waves_for(int V) { return V >= 4 ? 5 : 7; }
 constexpr uint64_t kMaxTable = 1ull << 23;   // entries of a two-sided table
+// Bytes of the lists: 14 KB per low and 25 per high part of a 16-orbital molecule, 35 MB for 1500 x 1500
+// strings.  Few low parts with many high ones of long class B tails can ask for gigabytes, in which case
+// the plan may be at most as large as the subspace's own keys, hashes and table (128 bytes a row).
+constexpr uint64_t kMaxLists = 1ull << 30, kMaxListsPerRow = 128;
 
 // What the list kernels read of the operator.
 struct GroupList {
@@ -738,6 +742,8 @@ Classified classify(const qsd_op *op, int split) {
 
 std::vector<float> narrowed(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
 
+constexpr int kNoPlan = 1;  // the lists do not fit: no error, and no plan
+
 // The lists: counted, sized by one round trip to the host, then written.  `scratch` and `keep`
 // hold the host images, which the caller keeps until the stream has passed the copies.
 int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, Block &keep, Block &lists,
@@ -794,6 +800,7 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     p->nB2 = m[5];
     p->nBAB = m[6];
     p->max_occ = m[7];
+    if (lds_bytes<double>(p, 1) > kLdsBytes) return kNoPlan;
     // within each tile, the low parts by the length of their AB lists
     const size_t na = p->na, nb = p->nb;
     std::vector<uint32_t> order(na), place(na);
@@ -814,6 +821,7 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
         ov[k][3] = lists.room(e * nb * p->nB1 * p->tail_len);
         ov[k][4] = lists.room(e * nb * p->nB2);
     }
+    if (lists.size > std::max(kMaxLists, kMaxListsPerRow * (uint64_t)s->N)) return kNoPlan;
     QSD_TRY(lists.upload(st));
     p->order = lists.at<uint32_t>(oo);
     p->place = lists.at<uint32_t>(op);
@@ -884,9 +892,9 @@ int prod_build(qsd_ham *h, hipStream_t st) {
     dev_free(scratch.dev);
     p->mem[0] = keep.dev;
     p->mem[1] = lists.dev;
-    if (rc != QSD_OK || lds_bytes<double>(p, 1) > kLdsBytes) {
+    if (rc != QSD_OK) {
         prod_free(p);
-        return rc;
+        return rc == kNoPlan ? QSD_OK : rc;
     }
     h->prod = p;
     return QSD_OK;

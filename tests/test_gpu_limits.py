@@ -69,3 +69,56 @@ def test_csr_spmm_of_2_to_26_rows():
         assert torch.equal(m.matvec(X[:, v].contiguous()), Y[:, v])
     del X, Y, m, H, sub
     torch.cuda.empty_cache()
+
+
+class _Peak:
+    """Allocator over PyTorch's that follows the bytes in use and refuses blocks for which
+    ``refuse(nbytes)`` holds."""
+
+    def __init__(self, refuse=None):
+        self.live, self.now, self.peak, self.sizes = {}, 0, 0, []
+
+        def alloc(ctx, nbytes, stream):
+            if refuse and refuse(int(nbytes)):
+                return None
+            p = torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
+            self.live[int(p)] = int(nbytes)
+            self.sizes.append(int(nbytes))
+            self.now += int(nbytes)
+            self.peak = max(self.peak, self.now)
+            return p
+
+        def free(ctx, ptr, stream):
+            self.now -= self.live.pop(int(ptr))
+            torch.cuda.caching_allocator_delete(int(ptr))
+
+        self.struct = qsd.Allocator(None, qsd.ALLOC_FN(alloc), qsd.FREE_FN(free))
+
+
+def _long_tails(words):
+    """Three low parts, every high part of 16 qubits; every high qubit's flip has a term that wants a
+    low qubit and ``words`` more on the high qubits, which a plan lists per high part."""
+    terms = []
+    for q in range(16, 32):
+        terms += [(0.5 + 0.01 * q, [(q, wl.X)]), (0.25, [(0, wl.P1), (q, wl.X)])]
+        others = [r for r in range(16, 32) if r != q]
+        pairs = [(a, b, c) for a in others for b in others if a < b for c in others if b < c][:words]
+        terms += [(0.125 + 0.001 * k, [(r, wl.Z) for r in w] + [(q, wl.X)]) for k, w in enumerate(pairs)]
+    keys = (np.arange(1 << 16, dtype=np.uint64)[:, None] << np.uint64(16)) + np.array([1, 2, 5], dtype=np.uint64)
+    return keys.reshape(-1, 1), wl.TermList.from_terms(32, terms)
+
+
+@pytest.mark.parametrize("words,path", [(8, qsd.PATH_FACTORED), (200, qsd.PATH_PRODUCT_MAP)])
+def test_plan_is_bounded(words, path):
+    """Lists of 2.5 GB for a subspace of 196 608 strings are not made, and not asked for."""
+    keys, tl = _long_tails(words)
+    sub = qsd.Subspace(keys, 32)
+    a = _Peak()
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(tl), allocator=a.struct)
+    say("lists", words, H.spmv_path, max(a.sizes))
+    assert H.spmv_path == path and a.peak < 1 << 30
+    x = torch.randn(sub.N, dtype=torch.float64, device="cuda")
+    y = H.matvec(x)
+    H.schedule = DEFAULT | qsd.SCHED_HASH_LOOKUP
+    assert torch.equal(H.matvec(x), y)
+    del H
