@@ -121,10 +121,6 @@ struct Block {
             QSD_CHECK_HIP(hipMemcpyAsync(dev, image.data(), image.size(), hipMemcpyHostToDevice, st));
         return QSD_OK;
     }
-    int upload(hipStream_t st) {
-        QSD_TRY(dev_alloc(&dev, size));
-        return copy(st);
-    }
 };
 
 // Hash of every off-diagonal group's flip mask under the subspace's hash words, and its packed

@@ -413,7 +413,7 @@ int create_impl(qsd_ham *h, hipStream_t st) {
         }
         if (sampled && hipMemcpyAsync(&columns, dtables.at<uint32_t>(o_count), 4, hipMemcpyDeviceToHost, st) != hipSuccess)
             rc = fail(QSD_ERR_HIP, "copy failed");
-        if (rc == QSD_OK) rc = prod_build(h, st);
+        if (rc == QSD_OK) rc = prod_build(h, tables.size, st);
         if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
             rc = fail(QSD_ERR_HIP, "diagonal kernel failed: %s", hipGetErrorString(hipGetLastError()));
         h->slot_default = columns <= kSampleRows;

@@ -100,8 +100,8 @@ struct ProdReq {
 
 // Builds h->prod when the subspace has a product map and the operator factors as above (the group
 // order keeps the classes apart); leaves it NULL otherwise.  The operator's tables must have been
-// uploaded.  Waits once for the list lengths; the lists themselves are enqueued.
-int prod_build(qsd_ham *h, hipStream_t st);
+// uploaded (`tables` bytes).  Waits once for the list lengths; the lists themselves are enqueued.
+int prod_build(qsd_ham *h, size_t tables, hipStream_t st);
 void prod_free(qsd_prod *&p);
 
 // Whether the SpMV of `h` runs from the plan.

@@ -747,8 +747,17 @@ constexpr int kNoPlan = 1;  // the lists do not fit: no error, and no plan
 // The lists: counted, sized by one round trip to the host, then written.  `scratch` and `keep`
 // hold the host images, which the caller keeps until the stream has passed the copies.
 int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, Block &keep, Block &lists,
-                 hipStream_t st) {
+                 size_t tables, hipStream_t st) {
     const qsd_subspace *s = h->s;
+    // The product map needs none of this memory, so a block that is refused means no plan; only one
+    // that is no larger than the operator's tables counts as one of them (where that does not fit,
+    // neither do the vectors).
+    auto alloc = [&](Block &b) -> int {
+        const int rc = dev_alloc(&b.dev, b.size);
+        if (rc != QSD_ERR_OUT_OF_MEMORY || b.size <= tables) return rc;
+        clear_error();
+        return kNoPlan;
+    };
     size_t og[2][3], of[2][5];
     for (int H = 0; H < 2; ++H) {
         og[H][0] = scratch.put(c.gflip[H]);
@@ -766,8 +775,10 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     const size_t od = keep.put(c.dep), od32 = keep.put(narrowed(c.dep));
     const size_t oc = keep.put(c.ctab), oc32 = keep.put(narrowed(c.ctab));
     const size_t oa = keep.room(3 * (size_t)p->na * 4), ob = keep.room(4 * (size_t)p->nb * 4);
-    QSD_TRY(scratch.upload(st));
-    QSD_TRY(keep.upload(st));
+    QSD_TRY(alloc(scratch));
+    QSD_TRY(scratch.copy(st));
+    QSD_TRY(alloc(keep));
+    QSD_TRY(keep.copy(st));
     p->d.dep = keep.at<double>(od);
     p->f.dep = keep.at<float>(od32);
     p->d.ctab = keep.at<double>(oc);
@@ -822,7 +833,8 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
         ov[k][4] = lists.room(e * nb * p->nB2);
     }
     if (lists.size > std::max(kMaxLists, kMaxListsPerRow * (uint64_t)s->N)) return kNoPlan;
-    QSD_TRY(lists.upload(st));
+    QSD_TRY(alloc(lists));
+    QSD_TRY(lists.copy(st));
     p->order = lists.at<uint32_t>(oo);
     p->place = lists.at<uint32_t>(op);
     p->a1_ent = lists.at<uint32_t>(o1);
@@ -862,7 +874,7 @@ void prod_free(qsd_prod *&p) {
     p = nullptr;
 }
 
-int prod_build(qsd_ham *h, hipStream_t st) {
+int prod_build(qsd_ham *h, size_t tables, hipStream_t st) {
     const qsd_subspace *s = h->s;
     if (!s->prank || h->is_complex || h->G == 0) return QSD_OK;
     // the x row of one block and the tables have to fit a workgroup's LDS
@@ -885,7 +897,7 @@ int prod_build(qsd_ham *h, hipStream_t st) {
     p->rmask = c.rmask;
     p->full = c.full;
     Block scratch, keep, lists;
-    int rc = build_device(h, p, c, scratch, keep, lists, st);
+    int rc = build_device(h, p, c, scratch, keep, lists, tables, st);
     // the host images outlive their copies
     if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
         rc = fail(QSD_ERR_HIP, "product lists failed: %s", hipGetErrorString(hipGetLastError()));

@@ -122,3 +122,24 @@ def test_plan_is_bounded(words, path):
     H.schedule = DEFAULT | qsd.SCHED_HASH_LOOKUP
     assert torch.equal(H.matvec(x), y)
     del H
+
+
+def test_plan_that_does_not_fit():
+    """Every block of a plan that is larger than the operator's tables can be refused: the operator is
+    bound all the same and runs from the product map."""
+    w = wl.c3_molecular(1500, 60)
+    sub = qsd.Subspace(w.keys, 32)
+    op = qsd.operator_from_termlist(w.ops)
+    a = _Peak()
+    H = qsd.SubspaceHamiltonian(sub, op, allocator=a.struct)
+    assert H.spmv_path == qsd.PATH_FACTORED
+    x = torch.randn(sub.N, dtype=torch.float64, device="cuda")
+    want = H.matvec(x)
+    lists = max(a.sizes)
+    say("blocks", a.sizes)
+    b = _Peak(refuse=lambda n: n == lists)
+    G = qsd.SubspaceHamiltonian(sub, op, allocator=b.struct)
+    assert G.spmv_path == qsd.PATH_PRODUCT_MAP and max(b.sizes) < lists
+    assert torch.equal(G.matvec(x), want)
+    del G, H
+    assert not a.live and not b.live
