@@ -24,8 +24,8 @@ struct qsd_hits {
 namespace qsd {
 
 // Builds the list when the operator has at most N off-diagonal elements (a sample of the rows is
-// counted first); *out stays NULL otherwise.  Device memory from the current allocator scope.
-// Synchronizes.
+// counted first) and the list fits the memory; *out stays NULL otherwise.  Device memory from the
+// current allocator scope.  Synchronizes.
 int hits_build(const qsd_ham *h, qsd_hits **out, hipStream_t st);
 void hits_free(qsd_hits *&p);
 

@@ -336,8 +336,13 @@ int hits_build(const qsd_ham *h, qsd_hits **out, hipStream_t st) {
     auto *p = new (std::nothrow) qsd_hits();
     if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
     int64_t *scratch = nullptr;
-    const int rc = build(h, p, scratch, st);
+    int rc = build(h, p, scratch, st);
     dev_free(scratch);
+    if (rc == QSD_ERR_OUT_OF_MEMORY) {  // every caller has a path without the list
+        clear_error();
+        hits_free(p);
+        return QSD_OK;
+    }
     if (rc != QSD_OK || !p->mem)
         hits_free(p);
     else

@@ -6,6 +6,7 @@ import pytest
 import workloads as wl
 
 from _util import c2_keys, say
+from test_gpu_hits import CASES
 
 torch = pytest.importorskip("torch")
 qsd = pytest.importorskip("paper_2603_18731_amd")
@@ -143,3 +144,35 @@ def test_plan_that_does_not_fit():
     assert torch.equal(G.matvec(x), want)
     del G, H
     assert not a.live and not b.live
+
+
+def test_element_list_that_does_not_fit():
+    """The element list's memory is refused, the counts that come before it or the list itself: the
+    slot-order schedules go by row bits, and a solve by the table."""
+    keys, tl = CASES["sampled"]()
+    sub = qsd.Subspace(keys, tl.n_qubits)
+    op = qsd.operator_from_termlist(tl)
+    H = qsd.SubspaceHamiltonian(sub, op)
+    x = torch.randn(sub.N, dtype=torch.float64, device="cuda")
+    want = H.matvec(x)
+    solve = dict(tol=1e-9, max_iter=60, want_vector=True, raise_on_nonconv=False)
+    energy = H.lanczos(**solve)
+    log = _Peak()
+    G = qsd.SubspaceHamiltonian(sub, op, allocator=log.struct)
+    bound = len(log.sizes)
+    G.schedule = qsd.SCHED_ALL
+    assert G.spmv_path == qsd.PATH_ELEMENTS
+    counts, bits, sums, records = log.sizes[bound:]  # (sums: the scan's scratch)
+    assert counts >= 8 * sub.N and bits >= sub.N / 8
+    for size in (counts, sums, records):
+        off = [False]
+        a = _Peak(refuse=lambda n: n == size and off[0])
+        G = qsd.SubspaceHamiltonian(sub, op, allocator=a.struct)
+        off[0] = True
+        e = G.lanczos(**solve)
+        assert e[0] == energy[0] and torch.equal(e[1], energy[1])
+        G.schedule = qsd.SCHED_ALL
+        assert G.spmv_path == qsd.PATH_SLOTS_SPLIT
+        assert torch.equal(G.matvec(x, out=torch.full_like(x, float("nan"))), want)
+        del G
+        assert not a.live
