@@ -93,8 +93,9 @@ __global__ __launch_bounds__(kBlock) void k_hits_matvec(SubView s, HamView h, qs
                                                         const ET *__restrict__ dim, const ET *__restrict__ x,
                                                         int64_t ldx, ET *__restrict__ y, int64_t ldy, int nvec,
                                                         unsigned nl) {
-    if (blockIdx.x >= nl) {
-        const int64_t n = s.N * nvec, e0 = (int64_t)(blockIdx.x - nl) * (kBlock * kDiagItems) + threadIdx.x;
+    const unsigned block = blockIdx.y * gridDim.x + blockIdx.x;
+    if (block >= nl) {
+        const int64_t n = s.N * nvec, e0 = (int64_t)(block - nl) * (kBlock * kDiagItems) + threadIdx.x;
 #pragma unroll
         for (int k = 0; k < kDiagItems; ++k) {
             const int64_t e = e0 + k * kBlock;
@@ -128,14 +129,14 @@ __global__ __launch_bounds__(kBlock) void k_hits_matvec(SubView s, HamView h, qs
     // a row with many elements has a wave of its own, another NV lanes, a vector each (x and y are
     // read and written in whole lines)
     const unsigned nw = (unsigned)((p.L + kBlock / 64 - 1) / (kBlock / 64));
-    const bool own = blockIdx.x < nw;
+    const bool own = block < nw;
     int64_t i, ic;  // position in the list, and one that is always valid
     if (own) {
-        i = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+        i = (int64_t)block * (kBlock / 64) + (threadIdx.x >> 6);
         if (i >= p.L) return;  // whole waves
         i = ic = p.lng[i];
     } else {
-        i = ((int64_t)(blockIdx.x - nw) * kBlock + threadIdx.x) / NV;
+        i = ((int64_t)(block - nw) * kBlock + threadIdx.x) / NV;
         ic = i < p.M ? i : p.M - 1;
     }
     const int v = lane % NV, vc = v < nvec ? v : 0;
@@ -289,7 +290,10 @@ void launch(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, voi
     const ET *dim = CPLX ? (f32 ? (const ET *)h->diag32_im : (const ET *)h->diag_im) : nullptr;
     const unsigned nd = (unsigned)((h->N * nvec + kBlock * kDiagItems - 1) / (kBlock * kDiagItems));
     const unsigned nl = (unsigned)((p->L + kBlock / 64 - 1) / (kBlock / 64)) + tiles_of(p->M * NV);
-    k_hits_matvec<Wp, NV, ET, CPLX><<<nl + nd, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), *p, dre, dim,
+    // (one dimension of a launch holds fewer than 2^32 threads; a larger one is cut short without an error)
+    const unsigned blocks = nl + nd, x_blocks = std::min(blocks, 1u << 23);
+    const dim3 grid(x_blocks, (blocks + x_blocks - 1u) / x_blocks);
+    k_hits_matvec<Wp, NV, ET, CPLX><<<grid, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), *p, dre, dim,
                                                                (const ET *)x, ldx, (ET *)y, ldy, nvec, nl);
 }
 

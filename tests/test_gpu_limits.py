@@ -176,3 +176,21 @@ def test_element_list_that_does_not_fit():
         assert torch.equal(G.matvec(x, out=torch.full_like(x, float("nan"))), want)
         del G
         assert not a.live
+
+
+def test_element_list_of_2_to_28_rows():
+    """An element in each of 2^28 rows and 16 vectors: rows times vectors are 2^32 lanes."""
+    n = 1 << 28
+    keys = torch.arange(n, dtype=torch.int64, device="cuda").reshape(-1, 1)
+    sub = qsd.Subspace(keys, 40, max_load=0.5, assume_sorted_unique=True)
+    del keys
+    tl = wl.TermList.from_terms(40, [(0.75, [(0, wl.X)]), (0.5, [(3, wl.Z)])])
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(tl))
+    H.schedule = qsd.SCHED_ALL
+    assert H.spmv_path == qsd.PATH_ELEMENTS
+    X = torch.randn((n, 16), dtype=torch.float32, device="cuda")
+    Y = H.matvec(X, out=torch.full_like(X, float("nan")))
+    for v in (0, 9, 15):
+        assert torch.equal(H.matvec(X[:, v].contiguous()), Y[:, v])
+    del X, Y, H, sub
+    torch.cuda.empty_cache()
