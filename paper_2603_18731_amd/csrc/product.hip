@@ -482,19 +482,22 @@ __global__ __launch_bounds__(kMaxThreads, waves_for(V)) void k_prod_matvec(ProdV
 
 // Requests of a table: a workgroup finds its request by the requests' first workgroups.
 template <class ET, int V>
-__global__ __launch_bounds__(kMaxThreads, waves_for(V)) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n) {
+__global__ __launch_bounds__(kMaxThreads, waves_for(V)) void k_prod_batched(const ProdReq<ET> *__restrict__ reqs, int n,
+                                                                           uint32_t blocks) {
     extern __shared__ __align__(32) char smem[];
+    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
+    if (block >= blocks) return;
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (reqs[mid].first <= blockIdx.x)
+        if (reqs[mid].first <= block)
             lo = mid;
         else
             hi = mid - 1;
     }
     const ProdReq<ET> &R = reqs[lo];
     if (R.kdev && *R.kdev >= R.m) return;  // at its iteration limit (uniform for the block)
-    uint32_t id = blockIdx.x - R.first;
+    uint32_t id = block - R.first;
     const uint32_t per = (R.p.na + R.p.T - 1u) / R.p.T * R.p.nb;  // workgroups per vector chunk
     const uint32_t vc = id / per;
     id -= vc * per;
@@ -972,12 +975,15 @@ void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t 
 template <class ET>
 void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, uint32_t T, int V, uint32_t lds,
                          hipStream_t st) {
+    // (one dimension of a launch holds fewer than 2^32 threads; a larger one is cut short without an error)
+    const uint32_t x_blocks = std::min(blocks, 1u << 22);
+    const dim3 grid(x_blocks, (blocks + x_blocks - 1u) / x_blocks);
     if (V == 4)
-        k_prod_batched<ET, 4><<<blocks, T, lds, st>>>(d_reqs, n);
+        k_prod_batched<ET, 4><<<grid, T, lds, st>>>(d_reqs, n, blocks);
     else if (V == 2)
-        k_prod_batched<ET, 2><<<blocks, T, lds, st>>>(d_reqs, n);
+        k_prod_batched<ET, 2><<<grid, T, lds, st>>>(d_reqs, n, blocks);
     else
-        k_prod_batched<ET, 1><<<blocks, T, lds, st>>>(d_reqs, n);
+        k_prod_batched<ET, 1><<<grid, T, lds, st>>>(d_reqs, n, blocks);
 }
 
 #define QSD_PROD_FOR(ET)                                                                                     \

@@ -956,7 +956,7 @@ int plan_prod(int32_t n, const qsd_ham *const *hams, const void *const *xs, void
         P.prod_lds = std::max(P.prod_lds, prod_lds<ET>(hams[i], P.prod_V));
         P.prod_T = std::max(P.prod_T, R.p.T);
     }
-    if (blocks > (uint64_t)INT32_MAX) return fail(QSD_ERR_CAPACITY, "too many workgroups");
+    if (blocks > (uint64_t)UINT32_MAX) return fail(QSD_ERR_CAPACITY, "too many workgroups");
     P.prod_blocks = (uint32_t)blocks;
     return QSD_OK;
 }

@@ -194,3 +194,23 @@ def test_element_list_of_2_to_28_rows():
         assert torch.equal(H.matvec(X[:, v].contiguous()), Y[:, v])
     del X, Y, H, sub
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("entry", ["matvec_batched", "matvec_batched_noalloc"])
+def test_batched_factored_workgroups(entry):
+    """Requests of two low and 65 536 high parts beside one of 512 low parts, whose workgroups are the
+    launch's: 2^23 workgroups of 512 threads and more."""
+    terms = [(0.5, [(q, wl.X)]) for q in (0, 16, 24, 31)] + [(0.25 + 0.01 * q, [(q, wl.Z)]) for q in range(32)]
+    tl = wl.TermList.from_terms(32, terms)
+    op = qsd.operator_from_termlist(tl)
+    hams = []
+    for nlo, nhi in ((2, 1 << 16), (512, 2)):
+        keys = (np.arange(nhi, dtype=np.uint64)[:, None] << np.uint64(16)) + np.arange(nlo, dtype=np.uint64)
+        hams.append(qsd.SubspaceHamiltonian(qsd.Subspace(keys.reshape(-1, 1), 32), op))
+        assert hams[-1].spmv_path == qsd.PATH_FACTORED
+    hams = [hams[0]] * 32 + [hams[1]]
+    xs = [torch.randn((h.N, 16), dtype=torch.float64, device="cuda") for h in hams]
+    say("batched", entry)
+    ys = getattr(qsd, entry)(hams, xs, [torch.full_like(x, float("nan")) for x in xs])
+    for h, x, y in zip(hams, xs, ys):
+        assert torch.equal(y, h.matvec(x))
