@@ -9,7 +9,16 @@
 namespace qsd {
 namespace {
 
-constexpr int kSampleTiles = 256;
+// Whether a list pays is asked of a sample first where the count of all rows, which takes as long as an
+// SpMV by the row engine, is dear: many rows, or many groups, which a lane walks one after the other
+// however few rows there are (10 000 rows of a molecular product, 18 280 groups: 2.2 ms, 1.5% of a solve
+// of 30 iterations, which lost that much; the sample takes 67 us).
+constexpr int kSampleRows = 256, kSampleThreads = 512;
+constexpr int64_t kSampleTiles = 512, kSampleGroups = 1024;
+// What one row counts at most (a sample around a reference string has a few rows with hundreds), and the
+// elements per row beyond which the rest is not counted: one is the limit, and some room for chance.
+constexpr uint32_t kSampleMost = 8;
+constexpr double kSampleMean = 1.5;
 // Elements from which a row gets a wave of its own.  A lane walks its elements in a chain of
 // dependent reads, about a microsecond each: 156 rows of 18 to 39 elements (700 000 heavy-hex
 // strings) kept the launch going for 34 us, and 150 rows of 48 to 117 (3M strings, 8 vectors) for
@@ -18,31 +27,61 @@ constexpr uint32_t kLongRow = 8;
 
 inline unsigned tiles_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// Off-diagonal elements of the rows of tile blockIdx.x * stride: their number per row (1 << 32 |
-// count for a row that has some; NULL: not kept), the row bits, and the total.
+// Off-diagonal elements of kSampleRows rows spread over the subspace: a workgroup per row, a thread per
+// group (a term with the row's ladder and projector bits in a group whose column is present).
 template <int Wp>
-__global__ __launch_bounds__(kBlock) void k_hit_count(SubView s, HamView h, int64_t stride,
-                                                      int64_t *__restrict__ cnt, uint64_t *__restrict__ bits,
+__global__ __launch_bounds__(kSampleThreads) void k_hit_sample(SubView s, HamView h,
+                                                               unsigned long long *__restrict__ total) {
+    __shared__ uint32_t sum;
+    if (threadIdx.x == 0) sum = 0u;
+    __syncthreads();
+    const int64_t r = (int64_t)blockIdx.x * s.N / kSampleRows;
+    uint64_t key[Wp];
+#pragma unroll
+    for (int w = 0; w < Wp; ++w) key[w] = s.keys[(int64_t)w * s.N + r];
+    const uint64_t hrow = s.hkey[r];
+    uint32_t n = 0;
+    for (int64_t g = threadIdx.x; g < h.G; g += kSampleThreads) {
+        uint64_t col[Wp];
+#pragma unroll
+        for (int w = 0; w < Wp; ++w) col[w] = key[w] ^ h.g_mask[g * Wp + w];
+        if (probe<Wp>(s, hrow ^ h.g_hash[g], col) < 0) continue;
+        const uint32_t t0 = h.g_term0[g], t1 = t0 + h.g_nterm[g];
+        bool any = false;
+        for (uint32_t t = t0; t < t1 && !any; ++t) any = term_pass<Wp>(key, h.t_cws + (int64_t)t * 3 * Wp);
+        n += any;
+    }
+    for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+    if ((threadIdx.x & 63) == 0 && n) atomicAdd(&sum, n);
+    __syncthreads();
+    if (threadIdx.x == 0 && sum) atomicAdd(total, (unsigned long long)min(sum, kSampleMost));
+}
+
+// Off-diagonal elements of all rows: their number per row (1 << 32 | count for a row that has some),
+// the row bits, the total, and the rows with many.
+template <int Wp>
+__global__ __launch_bounds__(kBlock) void k_hit_count(SubView s, HamView h, int64_t *__restrict__ cnt,
+                                                      uint64_t *__restrict__ bits,
                                                       unsigned long long *__restrict__ total) {
     __shared__ ChunkLds<Wp> lds;
     uint64_t key[Wp], hrow;
     uint32_t prow;
     bool valid;
-    const int64_t row0 = (int64_t)blockIdx.x * stride * kBlock;
+    const int64_t row0 = (int64_t)blockIdx.x * kBlock;
     const int64_t r = load_row<Wp>(s, row0, key, hrow, prow, valid);
     uint32_t n = 0;
     row_engine<Wp>(s, h, key, hrow, prow, valid, lds, sink<double>([&](int64_t, double, double, int) { ++n; }), nullptr,
                    false, true);
     if (!valid) n = 0;
-    if (valid && cnt) cnt[r] = n ? (int64_t)((1ull << 32) | n) : 0;
+    if (valid) cnt[r] = n ? (int64_t)((1ull << 32) | n) : 0;
     const uint64_t w = __ballot(n != 0u);
     const int64_t word = (row0 >> 6) + (threadIdx.x >> 6);
-    if (bits && (threadIdx.x & 63) == 0 && word * 64 < s.N) bits[word] = w;
+    if ((threadIdx.x & 63) == 0 && word * 64 < s.N) bits[word] = w;
     unsigned long long t = n;
     for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
     const uint64_t lng = __ballot(n > kLongRow);
     if ((threadIdx.x & 63) == 0 && t) atomicAdd(total, t);
-    if (cnt && (threadIdx.x & 63) == 0 && lng) atomicAdd(total + 2, (unsigned long long)__popcll(lng));
+    if ((threadIdx.x & 63) == 0 && lng) atomicAdd(total + 1, (unsigned long long)__popcll(lng));
 }
 
 // rows[i], ptr[i] of the rows with elements, from the scanned counts (rows << 32 | elements).
@@ -212,46 +251,42 @@ __global__ void k_hit_zero(unsigned long long *p, int n) {
     if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
 }
 
-template <int Wp>
-void count_launch(const qsd_ham *h, unsigned grid, int64_t stride, int64_t *cnt, uint64_t *bits,
-                  unsigned long long *total, hipStream_t st) {
-    k_hit_count<Wp><<<grid, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, false), stride, cnt, bits, total);
-}
-
-void count(const qsd_ham *h, unsigned grid, int64_t stride, int64_t *cnt, uint64_t *bits, unsigned long long *total,
-           hipStream_t st) {
+// f(integral_constant of the operator's key width)
+template <class F>
+void with_width(const qsd_ham *h, F f) {
+    using std::integral_constant;
     switch (h->Wp) {
-        case 1: count_launch<1>(h, grid, stride, cnt, bits, total, st); break;
-        case 2: count_launch<2>(h, grid, stride, cnt, bits, total, st); break;
-        case 4: count_launch<4>(h, grid, stride, cnt, bits, total, st); break;
-        case 8: count_launch<8>(h, grid, stride, cnt, bits, total, st); break;
-        case 16: count_launch<16>(h, grid, stride, cnt, bits, total, st); break;
+        case 1: f(integral_constant<int, 1>{}); break;
+        case 2: f(integral_constant<int, 2>{}); break;
+        case 4: f(integral_constant<int, 4>{}); break;
+        case 8: f(integral_constant<int, 8>{}); break;
+        case 16: f(integral_constant<int, 16>{}); break;
     }
 }
 
-template <int Wp>
-void fill_launch(const qsd_ham *h, const qsd_hits *p, hipStream_t st) {
-    k_hit_fill<Wp><<<tiles_of(p->M), kBlock, 0, st>>>(sub_view(h->s), ham_view(h, false), p->rows, p->M, p->ptr, p->rec);
-}
-
-int build(const qsd_ham *h, qsd_hits *p, int64_t *&scratch, hipStream_t st) {
+// `small` takes three totals (elements, rows with many, those listed so far), `scratch` the rows' counts.
+int build(const qsd_ham *h, qsd_hits *p, int64_t *&small, int64_t *&scratch, hipStream_t st) {
     const int64_t N = h->N, tiles = tiles_of(N);
-    unsigned long long t[3] = {0, 0, 0};
-    // totals, then the rows' counts
-    QSD_TRY(dev_alloc(&scratch, 4 + N + 1));
-    auto *total = (unsigned long long *)scratch;
-    int64_t *cnt = scratch + 4;
-    // a sample first: operators with more elements than rows are left after a small part of a pass
+    unsigned long long t[2] = {0, 0};
+    QSD_TRY(dev_alloc(&small, 4));
+    auto *total = (unsigned long long *)small;
+    const SubView s = sub_view(h->s);
+    const HamView v = ham_view(h, false);
     k_hit_zero<<<1, 64, 0, st>>>(total, 4);
-    if (tiles > 2 * kSampleTiles) {
-        const int64_t stride = tiles / kSampleTiles;
-        count(h, kSampleTiles, stride, nullptr, nullptr, total + 1, st);
-        QSD_CHECK_HIP(hipMemcpyAsync(t, total, sizeof(t), hipMemcpyDeviceToHost, st));
+    if (tiles > kSampleTiles || h->G > kSampleGroups) {
+        with_width(h, [&](auto wp) {
+            k_hit_sample<decltype(wp)::value><<<kSampleRows, kSampleThreads, 0, st>>>(s, v, total + 3);
+        });
+        QSD_CHECK_HIP(hipMemcpyAsync(t, total + 3, 8, hipMemcpyDeviceToHost, st));
         QSD_CHECK_HIP(hipStreamSynchronize(st));
-        if (t[1] > (unsigned long long)kSampleTiles * kBlock) return QSD_OK;
+        if ((double)t[0] > kSampleMean * kSampleRows) return QSD_OK;
     }
+    QSD_TRY(dev_alloc(&scratch, N + 1));
+    int64_t *cnt = scratch;
     QSD_TRY(dev_alloc(&p->rowbits, (size_t)((N + 63) / 64)));
-    count(h, (unsigned)tiles, 1, cnt, p->rowbits, total, st);
+    with_width(h, [&](auto wp) {
+        k_hit_count<decltype(wp)::value><<<(unsigned)tiles, kBlock, 0, st>>>(s, v, cnt, p->rowbits, total);
+    });
     int64_t sum = 0;
     QSD_TRY(exclusive_scan_i64(cnt, cnt, N + 1, st));  // (cnt[N] is read, and moves nothing)
     QSD_CHECK_HIP(hipMemcpyAsync(t, total, sizeof(t), hipMemcpyDeviceToHost, st));
@@ -260,7 +295,7 @@ int build(const qsd_ham *h, qsd_hits *p, int64_t *&scratch, hipStream_t st) {
     if (t[0] > (unsigned long long)N) return QSD_OK;
     p->H = (int64_t)t[0];
     p->M = sum >> 32;
-    p->L = (int64_t)t[2];
+    p->L = (int64_t)t[1];
     auto up = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
     const size_t at1 = up(p->H * sizeof(qsd_hit)), at2 = at1 + up(p->M * 4), at3 = at2 + up((p->M + 1) * 4);
     QSD_TRY(dev_alloc(&p->mem, at3 + p->L * 4));
@@ -268,16 +303,11 @@ int build(const qsd_ham *h, qsd_hits *p, int64_t *&scratch, hipStream_t st) {
     p->rows = (uint32_t *)(p->mem + at1);
     p->ptr = (uint32_t *)(p->mem + at2);
     p->lng = (uint32_t *)(p->mem + at3);
-    k_hit_rows<<<tiles_of(N + 1), kBlock, 0, st>>>(cnt, N, p->rows, p->ptr, p->lng, total + 3);
-    if (p->M > 0) {
-        switch (h->Wp) {
-            case 1: fill_launch<1>(h, p, st); break;
-            case 2: fill_launch<2>(h, p, st); break;
-            case 4: fill_launch<4>(h, p, st); break;
-            case 8: fill_launch<8>(h, p, st); break;
-            case 16: fill_launch<16>(h, p, st); break;
-        }
-    }
+    k_hit_rows<<<tiles_of(N + 1), kBlock, 0, st>>>(cnt, N, p->rows, p->ptr, p->lng, total + 2);
+    if (p->M > 0)
+        with_width(h, [&](auto wp) {
+            k_hit_fill<decltype(wp)::value><<<tiles_of(p->M), kBlock, 0, st>>>(s, v, p->rows, p->M, p->ptr, p->rec);
+        });
     QSD_CHECK_HIP(hipGetLastError());
     return QSD_OK;
 }
@@ -315,13 +345,7 @@ void by_width(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, v
 template <class ET, bool CPLX>
 void by_key(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec,
             hipStream_t st) {
-    switch (h->Wp) {
-        case 1: by_width<1, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
-        case 2: by_width<2, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
-        case 4: by_width<4, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
-        case 8: by_width<8, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
-        case 16: by_width<16, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); break;
-    }
+    with_width(h, [&](auto wp) { by_width<decltype(wp)::value, ET, CPLX>(h, p, x, ldx, y, ldy, nvec, st); });
 }
 
 }  // namespace
@@ -339,8 +363,9 @@ int hits_build(const qsd_ham *h, qsd_hits **out, hipStream_t st) {
     if (h->N == 0 || h->G == 0) return QSD_OK;
     auto *p = new (std::nothrow) qsd_hits();
     if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
-    int64_t *scratch = nullptr;
-    int rc = build(h, p, scratch, st);
+    int64_t *small = nullptr, *scratch = nullptr;
+    int rc = build(h, p, small, scratch, st);
+    dev_free(small);
     dev_free(scratch);
     if (rc == QSD_ERR_OUT_OF_MEMORY) {  // every caller has a path without the list
         clear_error();

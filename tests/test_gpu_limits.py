@@ -162,7 +162,7 @@ def test_element_list_that_does_not_fit():
     bound = len(log.sizes)
     G.schedule = qsd.SCHED_ALL
     assert G.spmv_path == qsd.PATH_ELEMENTS
-    counts, bits, sums, records = log.sizes[bound:]  # (sums: the scan's scratch)
+    *_, counts, bits, sums, records = log.sizes[bound:]  # (sums: the scan's scratch)
     assert counts >= 8 * sub.N and bits >= sub.N / 8
     for size in (counts, sums, records):
         off = [False]

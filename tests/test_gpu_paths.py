@@ -125,3 +125,24 @@ def test_slot_order_through_the_table_is_split(name):
         H.schedule = qsd.SCHED_SLOT_ORDER | qsd.SCHED_HASH_LOOKUP | extra
         assert H.spmv_path == qsd.PATH_SLOTS_SPLIT
         assert torch.equal(H.matvec(x, out=torch.full_like(x, float("nan"))), want)
+
+
+def test_dense_solve_makes_no_count():
+    """A solve asks a sample whether a list pays before it counts the elements of all rows, which takes
+    as long as an SpMV: a dense operator of many groups takes no more memory than its basis."""
+    ops, keys = c3_parts(60, 60)
+    sizes = []
+
+    def alloc(ctx, nbytes, stream):
+        sizes.append(int(nbytes))
+        return torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
+
+    a = qsd.Allocator(None, qsd.ALLOC_FN(alloc), qsd.FREE_FN(lambda c, p, s: torch.cuda.caching_allocator_delete(int(p))))
+    H = qsd.SubspaceHamiltonian(qsd.Subspace(keys, 32), qsd.operator_from_termlist(ops, order_by_parts=False),
+                                allocator=a)
+    assert H.spmv_path == qsd.PATH_PRODUCT_MAP
+    del sizes[:]
+    H.lanczos(tol=1e-9, max_iter=60, raise_on_nonconv=False)
+    say("solve", H.N, sizes)
+    assert max(sizes) >= 60 * 8 * H.N and all(n < 8 * H.N for n in sizes if n != max(sizes))
+    del H
