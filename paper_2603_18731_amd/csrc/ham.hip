@@ -360,13 +360,13 @@ int create_impl(qsd_ham *h, hipStream_t st) {
     }
     std::vector<float> c32(op->t_coef.size());
     for (size_t k = 0; k < c32.size(); ++k) c32[k] = (float)op->t_coef[k];
-    // one copy each for the tables that stay and for the diagonal's (a copy costs the host 16 us)
+    // one block each for the tables that stay and for the diagonal's
     Block tables, dtables;
     const size_t o_mask = tables.put(op->g_mask), o_pos = tables.put(op->g_pos), o_scan = tables.put(op->g_scan),
                  o_info = tables.put(op->g_info), o_term0 = tables.put(op->g_term0), o_nterm = tables.put(op->g_nterm),
                  o_iptr = tables.put(op->g_iptr), o_cws = tables.put(op->t_cws), o_cw32 = tables.put(cw32),
                  o_coef = tables.put(op->t_coef), o_coef32 = tables.put(c32);
-    QSD_TRY(dev_alloc(&tables.dev, tables.size));
+    QSD_TRY(dev_alloc(&tables.dev, tables.size()));
     h->tables = tables.dev;
     QSD_TRY(tables.copy(st));
     h->g_mask = tables.at<uint64_t>(o_mask);
@@ -393,7 +393,7 @@ int create_impl(qsd_ham *h, hipStream_t st) {
     const size_t o_count = dtables.put(std::vector<uint32_t>(1, 0u));
     const bool sampled = !h->s->prank && !h->s->pfilt && h->G <= kSampleGroups;
     uint32_t columns = kSampleRows + 1;
-    int rc = dev_alloc(&dtables.dev, dtables.size);
+    int rc = dev_alloc(&dtables.dev, dtables.size());
     if (rc == QSD_OK) rc = dtables.copy(st);
     if (rc == QSD_OK) {
         auto diag = [&](auto wp) {
@@ -413,7 +413,7 @@ int create_impl(qsd_ham *h, hipStream_t st) {
         }
         if (sampled && hipMemcpyAsync(&columns, dtables.at<uint32_t>(o_count), 4, hipMemcpyDeviceToHost, st) != hipSuccess)
             rc = fail(QSD_ERR_HIP, "copy failed");
-        if (rc == QSD_OK) rc = prod_build(h, tables.size, st);
+        if (rc == QSD_OK) rc = prod_build(h, tables.size(), st);
         if (hipStreamSynchronize(st) != hipSuccess && rc == QSD_OK)
             rc = fail(QSD_ERR_HIP, "diagonal kernel failed: %s", hipGetErrorString(hipGetLastError()));
         h->slot_default = columns <= kSampleRows;

@@ -756,8 +756,8 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     // that is no larger than the operator's tables counts as one of them (where that does not fit,
     // neither do the vectors).
     auto alloc = [&](Block &b) -> int {
-        const int rc = dev_alloc(&b.dev, b.size);
-        if (rc != QSD_ERR_OUT_OF_MEMORY || b.size <= tables) return rc;
+        const int rc = dev_alloc(&b.dev, b.size());
+        if (rc != QSD_ERR_OUT_OF_MEMORY || b.size() <= tables) return rc;
         clear_error();
         return kNoPlan;
     };
@@ -823,7 +823,7 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
         std::stable_sort(order.begin() + t, order.begin() + std::min<size_t>(na, t + p->T),
                          [&](uint32_t i, uint32_t j) { return n3[i] > n3[j]; });
     for (size_t i = 0; i < na; ++i) place[order[i]] = (uint32_t)i;
-    const size_t oo = lists.put(order), op = lists.put(place);
+    const size_t oo = lists.put(std::move(order)), op = lists.put(std::move(place));
     const size_t o1 = lists.room(4 * p->nA1 * na), o2 = lists.room(2 * p->nA2 * na), o3 = lists.room(4 * p->nAB * na);
     const size_t o4 = lists.room(8 * p->nB1 * nb), o5 = lists.room(4 * p->nB2 * nb), o6 = lists.room(8 * p->nBAB * nb);
     size_t ov[2][5];
@@ -835,7 +835,7 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
         ov[k][3] = lists.room(e * nb * p->nB1 * p->tail_len);
         ov[k][4] = lists.room(e * nb * p->nB2);
     }
-    if (lists.size > std::max(kMaxLists, kMaxListsPerRow * (uint64_t)s->N)) return kNoPlan;
+    if (lists.size() > std::max(kMaxLists, kMaxListsPerRow * (uint64_t)s->N)) return kNoPlan;
     QSD_TRY(alloc(lists));
     QSD_TRY(lists.copy(st));
     p->order = lists.at<uint32_t>(oo);
