@@ -7,6 +7,7 @@
 #include <complex>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -227,6 +228,10 @@ struct CompiledTerm {
     std::complex<double> c;    // coefficient of the word
 };
 
+namespace qsd {
+struct Classified;  // factor.h
+}
+
 struct qsd_op {
     int32_t n_qubits = 0;
     int32_t Wp = 0;
@@ -253,6 +258,8 @@ struct qsd_op {
     // its one qubit beyond the flip mask set); 0 elsewhere
     std::vector<uint32_t> t_tail;         // [To]
     int64_t max_group_terms = 0;
+    // real operators of 2 to 32 qubits: whether and how it factors over the halves of the strings
+    std::shared_ptr<const qsd::Classified> parts;
 };
 
 constexpr int kIptr = 18;  // 2^4 + 1 pointers, padded to an even count

@@ -13,6 +13,7 @@
 #include <string>
 
 #include "common.h"
+#include "factor.h"
 
 namespace qsd {
 
@@ -560,6 +561,14 @@ extern "C" int qsd_op_compile(int32_t n_qubits, int64_t n_terms, const int64_t *
     // the device reads scan records 8 at a time
     while (op->g_scan.size() % 8 != 0 || op->g_scan.size() < op->g_info.size() + 8) op->g_scan.push_back(0);
     op->is_complex = cplx_mat;
+    if (n_qubits >= 2 && n_qubits <= 32 && !cplx_mat) {
+        Classified c = classify(op, n_qubits / 2);
+        if (!c.ok) {  // only the verdict is kept
+            c = Classified();
+            c.split = n_qubits / 2;
+        }
+        op->parts = std::make_shared<const Classified>(std::move(c));
+    }
     *out = op;
     return QSD_OK;
 }

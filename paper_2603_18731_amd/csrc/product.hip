@@ -1,30 +1,26 @@
-// Factored SpMV on alpha x beta product subspaces: the plan (host classification of the groups,
-// lists built on the device) and the kernel.  See product.h for the form.
+// Factored SpMV on alpha x beta product subspaces: the plan (lists built on the device from the
+// operator's classification, factor.h) and the kernel.  See product.h for the form.
 #include "product.h"
 
 #include <algorithm>
 #include <cstring>
 #include <numeric>
 #include <type_traits>
-#include <unordered_map>
-#include <unordered_set>
 
 #include "device.h"
+#include "factor.h"
 #include "matvec.h"
 
 namespace qsd {
 namespace {
 
 constexpr uint32_t kLdsBytes = 64u * 1024u;  // a workgroup's x row and tables (two or more workgroups per CU)
-constexpr uint32_t kMaxKeys = 16384;         // term keys of one part: 2 key + sign fits 15 bits
-constexpr uint32_t kMaxTail = 200;           // terms after the table, counted in 8 bits
 // Threads and low parts per workgroup.  1500 x 1500 strings in FP64: 256 1054 us, 384 1167 (four
 // tiles with a short last one), 512 950, 768 979; 600 x 600: 98, 88, 88, 89.
 constexpr uint32_t kMaxThreads = 512;
 // Waves per SIMD that the registers must allow.  600 x 600: 88 us without it, 72 with 7; 8 costs
 // scalar spills (300 x 301: 24.6 -> 26.4).  Four vectors spill at 7 (400 x 400 in FP32 46 us, at 5 44).
 constexpr int waves_for(int V) { return V >= 4 ? 5 : 7; }
-constexpr uint64_t kMaxTable = 1ull << 23;   // entries of a two-sided table
 // Bytes of the lists: 14 KB per low and 25 per high part of a 16-orbital molecule, 35 MB for 1500 x 1500
 // strings.  Few low parts with many high ones of long class B tails can ask for gigabytes, in which case
 // the plan may be at most as large as the subspace's own keys, hashes and table (128 bytes a row).
@@ -56,11 +52,6 @@ struct BuildView {
     uint32_t na, nb;
     int split;
 };
-
-// Term kinds within a group's part-only segment.
-constexpr uint32_t kOwn = 0;    // depends on the group's own part alone
-constexpr uint32_t kOther = 1;  // wants one qubit of the other part (class A: its key's table row)
-constexpr uint32_t kFirst = 2;  // class B: the own term that heads its key's table row
 
 __device__ __forceinline__ uint32_t below(uint64_t m, int lane) {
     return (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
@@ -521,227 +512,7 @@ uint32_t lds_bytes(const qsd_prod *p, int V) {
     return tail_at<ET>(p->na, p->T, aux_entries(p), V) + p->nB1 * ((p->tail_len + 3u) / 4u * 4u) * (uint32_t)sizeof(ET);
 }
 
-// ------------------------------------------------------------------- host classification
-
-struct HostTerm {
-    uint32_t care, want, sign;
-};
-
-// Everything the device lists need of the operator, or `ok` = false.
-struct Classified {
-    bool ok = false;
-    std::vector<uint32_t> tinfo;                    // [T]
-    std::vector<uint32_t> gflip[2], gt0[2], gnt[2]; // part-only groups (A, B)
-    uint32_t n1[2] = {0, 0};
-    std::vector<uint32_t> fflip[2], fcare[2], fkey0[2], fwant[2], fsign[2];
-    std::vector<double> ctab, dep, whead, wdep;     // dep [high][nUa], wdep [nWb][low]
-    uint32_t nUa = 0, nWb = 0, tail_len = 0, rmask = 0;
-    bool full = true;
-};
-
-Classified classify(const qsd_op *op, int split) {
-    Classified c;
-    const int nhi = op->n_qubits - split;
-    if (op->Wp != 1 || op->is_complex || split < 1 || split > 16 || nhi < 1 || nhi > 16) return c;
-    const uint32_t lm = (1u << split) - 1u;
-    const size_t G = op->g_info.size(), T = op->t_coef.size() / 2;
-    c.tinfo.assign(T, 0u);
-    auto term = [&](size_t t) {
-        return HostTerm{(uint32_t)op->t_cws[3 * t], (uint32_t)op->t_cws[3 * t + 1], (uint32_t)op->t_cws[3 * t + 2]};
-    };
-    auto half = [&](uint32_t m, int high) { return high ? m >> split : m & lm; };
-    // the classes in order: low part only, both, high part only
-    int stage = 0;
-    size_t ab0 = G, ab1 = 0;
-    for (size_t g = 0; g < G; ++g) {
-        const uint32_t m = (uint32_t)op->g_mask[g];
-        const int cls = half(m, 0) ? (half(m, 1) ? 1 : 0) : 2;
-        if (cls < stage) return c;
-        stage = cls;
-        if (cls == 1) {
-            ab0 = std::min(ab0, g);
-            ab1 = g + 1;
-        }
-    }
-    if (ab0 == G) ab1 = G;
-    // classes A and B: within the terms that one ladder pattern selects, own terms and terms
-    // that want one qubit of the other part
-    uint32_t seg_tail = 0;
-    std::vector<std::pair<uint64_t, double>> dep;  // (key << 8 | qubit, coefficient)
-    for (size_t g = 0; g < G; ++g) {
-        if (g >= ab0 && g < ab1 && ab0 < G) continue;
-        const uint32_t m = (uint32_t)op->g_mask[g];
-        const int H = half(m, 0) ? 0 : 1;
-        const size_t a = op->g_term0[g], e = a + op->g_nterm[g];
-        bool byflip = true;
-        for (size_t t = a; t < e; ++t) byflip &= (term(t).care & m) == m;
-        bool anydep = false;
-        uint32_t tails = 0;
-        // patterns: at most 2^4 with a ladder group, found in stored order
-        std::vector<uint32_t> pats;
-        for (size_t t = a; t < e; ++t) {
-            const uint32_t p = byflip ? term(t).want & m : 0u;
-            if (std::find(pats.begin(), pats.end(), p) == pats.end()) {
-                pats.push_back(p);
-                if (pats.size() > 16) return c;
-            }
-        }
-        for (const uint32_t p : pats) {
-            uint32_t own_before = 0, own_after = 0, deps = 0, last_q = 0;
-            HostTerm key{};
-            size_t head_t = 0;  // the last own term before the others
-            for (size_t t = a; t < e; ++t) {
-                const HostTerm x = term(t);
-                if (byflip && (x.want & m) != p) continue;
-                const uint32_t oc = half(x.care, !H), ow = half(x.want, !H), os = half(x.sign, !H);
-                const HostTerm k{half(x.care, H), half(x.want, H), half(x.sign, H)};
-                if (!oc && !os) {
-                    if (deps) {
-                        if (H == 0) return c;  // class A: own terms come first
-                        ++own_after;
-                    } else {
-                        ++own_before;
-                        head_t = t;
-                    }
-                    continue;
-                }
-                if (os || oc != ow || (oc & (oc - 1u))) return c;
-                const uint32_t q = (uint32_t)__builtin_ctz(oc);
-                if (deps && q <= last_q) return c;
-                last_q = q;
-                if (!deps) {
-                    // the terms' own part: one key for all of them; an own term with the key's
-                    // projector bits makes the element exist whenever one of them matches (class
-                    // B: that term alone comes before them, with the key's sign mask)
-                    if (!own_before || (H == 1 && own_before != 1)) return c;
-                    bool same = false;
-                    for (size_t u = a; u < t; ++u) {
-                        const HostTerm y = term(u);
-                        if (byflip && (y.want & m) != p) continue;
-                        same |= half(y.care, H) == k.care && half(y.want, H) == k.want &&
-                                (H == 0 || half(y.sign, H) == k.sign);
-                    }
-                    if (!same) return c;
-                    key = k;
-                    const uint32_t id = H == 0 ? c.nUa++ : c.nWb++;
-                    if (id + 1 >= kMaxKeys) return c;
-                    if (H == 1) {
-                        c.tinfo[head_t] = kFirst | id << 8;
-                        c.whead.push_back(op->t_coef[2 * head_t]);
-                    }
-                } else if (key.care != k.care || key.want != k.want || key.sign != k.sign) {
-                    return c;
-                }
-                ++deps;
-                const uint32_t id = (H == 0 ? c.nUa : c.nWb) - 1u;
-                c.tinfo[t] = kOther | id << 8;
-                if (H == 0) {
-                    dep.push_back({(uint64_t)id << 8 | q, op->t_coef[2 * t]});
-                    c.rmask |= 1u << q;
-                } else {
-                    c.wdep.resize((size_t)c.nWb * split, 0.0);
-                    c.wdep[(size_t)id * split + q] = op->t_coef[2 * t];
-                }
-            }
-            anydep |= deps != 0;
-            if (H == 1) tails = std::max(tails, deps ? own_after : own_before);
-        }
-        // (terms that follow the table in segment 1, which ends with the last group that has one)
-        if (H == 1) {
-            seg_tail = std::max(seg_tail, tails);
-            if (anydep) c.tail_len = seg_tail;
-        }
-        c.gflip[H].push_back(half(m, H));
-        c.gt0[H].push_back((uint32_t)a);
-        c.gnt[H].push_back((uint32_t)(e - a));
-        if (anydep) c.n1[H] = (uint32_t)c.gflip[H].size();
-    }
-    // (groups of segment 1 without such terms use a table row of zeros, the last one)
-    ++c.nUa;
-    ++c.nWb;
-    c.whead.push_back(0.0);
-    c.wdep.resize((size_t)c.nWb * split, 0.0);
-    c.dep.assign((size_t)nhi * c.nUa, 0.0);
-    for (auto &d : dep) c.dep[(size_t)(d.first & 255u) * c.nUa + (size_t)(d.first >> 8)] = d.second;
-    if (c.tail_len > kMaxTail) return c;
-    // class AB: per part, the flips and their keys
-    struct Flip {
-        uint32_t care;
-        std::vector<std::pair<uint32_t, uint32_t>> keys;  // want, sign
-    };
-    std::unordered_map<uint32_t, Flip> flips[2];
-    std::vector<uint32_t> order[2];
-    std::unordered_set<uint32_t> runs;
-    uint32_t cur = 0, prev = 0;
-    auto before = [](uint32_t x, uint32_t z) {
-        const int px = __builtin_popcount(x), pz = __builtin_popcount(z);
-        return px != pz ? px < pz : x < z;
-    };
-    for (size_t g = ab0; g < ab1; ++g) {
-        const uint32_t m = (uint32_t)op->g_mask[g], ml = half(m, 0), mh = half(m, 1);
-        if (g == ab0 || mh != cur) {
-            if (!runs.insert(mh).second) return c;  // the groups of one high flip are not together
-            cur = mh;
-            order[1].push_back(mh);
-        } else if (!before(prev, ml)) {
-            return c;
-        }
-        prev = ml;
-        for (size_t t = op->g_term0[g], e = t + op->g_nterm[g]; t < e; ++t) {
-            const HostTerm x = term(t);
-            if (op->t_coef[2 * t] == 0.0 || (float)op->t_coef[2 * t] == 0.0f) return c;  // 0 marks an absent pair
-            for (int H = 0; H < 2; ++H) {
-                auto it = flips[H].find(half(m, H));
-                if (it == flips[H].end()) {
-                    it = flips[H].emplace(half(m, H), Flip{half(x.care, H), {}}).first;
-                    if (H == 0) order[0].push_back(ml);
-                }
-                if (it->second.care != half(x.care, H)) return c;
-                bool have = false;
-                for (auto &k : it->second.keys)
-                    if (k.first == half(x.want, H)) {
-                        if (k.second != half(x.sign, H)) return c;
-                        have = true;
-                    }
-                if (!have) it->second.keys.push_back({half(x.want, H), half(x.sign, H)});
-                if (it->second.keys.size() > 16) return c;
-            }
-        }
-    }
-    std::sort(order[0].begin(), order[0].end(), before);
-    std::unordered_map<uint64_t, uint32_t> id[2];  // flip << 16 | want -> key
-    for (int H = 0; H < 2; ++H) {
-        for (const uint32_t m : order[H]) {
-            c.fflip[H].push_back(m);
-            c.fcare[H].push_back(flips[H][m].care);
-            c.fkey0[H].push_back((uint32_t)c.fwant[H].size());
-            for (auto &k : flips[H][m].keys) {
-                id[H][(uint64_t)m << 16 | k.first] = (uint32_t)c.fwant[H].size();
-                c.fwant[H].push_back(k.first);
-                c.fsign[H].push_back(k.second);
-            }
-        }
-        c.fkey0[H].push_back((uint32_t)c.fwant[H].size());
-        if (c.fwant[H].size() >= kMaxKeys) return c;
-    }
-    const size_t nU = c.fwant[0].size(), nW = c.fwant[1].size();
-    if ((uint64_t)nU * nW > kMaxTable) return c;
-    c.ctab.assign(nU * nW, 0.0);
-    for (size_t g = ab0; g < ab1; ++g) {
-        const uint32_t m = (uint32_t)op->g_mask[g];
-        for (size_t t = op->g_term0[g], e = t + op->g_nterm[g]; t < e; ++t) {
-            const HostTerm x = term(t);
-            const uint32_t u = id[0][(uint64_t)half(m, 0) << 16 | half(x.want, 0)];
-            const uint32_t w = id[1][(uint64_t)half(m, 1) << 16 | half(x.want, 1)];
-            double &v = c.ctab[(size_t)w * nU + u];
-            if (v != 0.0) return c;  // two terms for one pair of keys
-            v = op->t_coef[2 * t];
-        }
-    }
-    for (double v : c.ctab) c.full &= v != 0.0;
-    c.ok = true;
-    return c;
-}
+// ------------------------------------------------------------------------------- plan
 
 std::vector<float> narrowed(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
 
@@ -882,7 +653,9 @@ int prod_build(qsd_ham *h, size_t tables, hipStream_t st) {
     if (!s->prank || h->is_complex || h->G == 0) return QSD_OK;
     // the x row of one block and the tables have to fit a workgroup's LDS
     if ((uint64_t)s->pna * sizeof(double) > kLdsBytes) return QSD_OK;
-    const Classified c = classify(h->op, s->split);
+    const bool kept = h->op->parts && h->op->parts->split == s->split;
+    const Classified other = kept ? Classified() : classify(h->op, s->split);
+    const Classified &c = kept ? *h->op->parts : other;
     if (!c.ok || (uint64_t)c.nWb * s->pna > kMaxTable) return QSD_OK;
     auto *p = new (std::nothrow) qsd_prod();
     if (!p) return fail(QSD_ERR_OUT_OF_MEMORY, "host allocation failed");
