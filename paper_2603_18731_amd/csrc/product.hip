@@ -69,22 +69,34 @@ __device__ __forceinline__ int flip_key(const FlipList &f, uint32_t i, uint32_t 
     return -1;
 }
 
-// The lists of one part, one wave per part: 64 groups (flips) at a time, the entries that exist
-// keep their order through a ballot.  WRITE = false only counts (lengths and their maxima).
-// (One pass over some thousand groups per part, once per operator: latency-bound.)
+// The lists of one part, one workgroup per part: 64 groups (flips) at a time, the entries that exist
+// keep their order through a ballot; each wave takes a run of the groups and of the flips.  WRITE = false
+// only counts: entries per wave (which tell a wave where to write), lengths and their maxima.
+// Latency-bound (a chain of reads per 64 groups): 300 x 300 strings of a 16-orbital molecule, 1940
+// groups and 120 flips a part: 372 us with a wave per part and a launch each for low and high ones, 117 so.
+constexpr uint32_t kListWaves = 8;
+
 template <bool HIGH, bool WRITE>
-__global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, FlipList f, qsd_prod p,
-                                                    uint32_t *__restrict__ mx) {
-    const int lane = threadIdx.x & 63;
-    const uint32_t i = blockIdx.x * 4u + (threadIdx.x >> 6), n = HIGH ? v.nb : v.na;
-    if (i >= n) return;  // whole waves
+__device__ __forceinline__ void prod_lists(const BuildView &v, const GroupList &g, const FlipList &f, const qsd_prod &p,
+                                           uint32_t i, uint32_t *__restrict__ cnt, uint32_t *__restrict__ mx,
+                                           uint32_t (*__restrict__ sums)[3]) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, n = HIGH ? v.nb : v.na;
     const uint32_t lowmask = (1u << v.split) - 1u;
     const uint32_t part = HIGH ? (uint32_t)(v.keys[(int64_t)i * v.na] >> v.split) : (uint32_t)v.keys[i] & lowmask;
     const uint32_t *filt = v.pfilt + (HIGH ? kPartWords / 2 : 0);
     const uint32_t at = !HIGH && WRITE ? p.place[i] : i;  // a low part's position
+    cnt += (HIGH ? (int64_t)v.na + i : (int64_t)i) * kListWaves * 3;
     uint32_t n1 = 0, n2 = 0, n3 = 0;
-    for (uint32_t g0 = 0; g0 < g.n; g0 += 64u) {
-        const uint32_t q = g0 + (uint32_t)lane;
+    if (WRITE)
+        for (uint32_t w = 0; w < wave; ++w) {
+            n1 += cnt[3 * w];
+            n2 += cnt[3 * w + 1];
+            n3 += cnt[3 * w + 2];
+        }
+    auto run = [&](uint32_t len) { return ((len + 63u) / 64u + kListWaves - 1u) / kListWaves * 64u; };
+    const uint32_t gr = run(g.n), fr = run(f.n);
+    for (uint32_t g0 = wave * gr; g0 < min(wave * gr + gr, g.n); g0 += 64u) {
+        const uint32_t q = g0 + lane;
         bool on = false;
         uint32_t col = 0, key = 0, sgn = 0, nt = 0;
         double val = 0.0;
@@ -118,7 +130,7 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
         const uint64_t b1 = __ballot(on && q < g.n1), b2 = __ballot(on && q >= g.n1);
         if (WRITE && on) {
             if (q < g.n1) {
-                const uint32_t k = n1 + below(b1, lane);
+                const uint32_t k = n1 + below(b1, (int)lane);
                 if (HIGH) {
                     uint32_t *e = p.b1_ent + 2 * ((int64_t)i * p.nB1 + k);
                     e[0] = col;
@@ -140,7 +152,7 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
                     p.f.a1[o] = val32;
                 }
             } else {
-                const uint32_t k = n2 + below(b2, lane);
+                const uint32_t k = n2 + below(b2, (int)lane);
                 const int64_t o = HIGH ? (int64_t)i * p.nB2 + k : prod_at(k, v.na, at);
                 if (HIGH)
                     p.b2_col[o] = col;
@@ -153,8 +165,8 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
         n1 += (uint32_t)__popcll(b1);
         n2 += (uint32_t)__popcll(b2);
     }
-    for (uint32_t f0 = 0; f0 < f.n; f0 += 64u) {
-        const uint32_t q = f0 + (uint32_t)lane;
+    for (uint32_t f0 = wave * fr; f0 < min(wave * fr + fr, f.n); f0 += 64u) {
+        const uint32_t q = f0 + lane;
         uint32_t col = 0, sgn = 0;
         int key = -1;
         if (q < f.n) {
@@ -166,7 +178,7 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
         }
         const uint64_t b3 = __ballot(key >= 0);
         if (WRITE && key >= 0) {
-            const uint32_t k = n3 + below(b3, lane);
+            const uint32_t k = n3 + below(b3, (int)lane);
             if (HIGH) {
                 uint32_t *e = p.bab_ent + 2 * ((int64_t)i * p.nBAB + k);
                 e[0] = col;
@@ -177,34 +189,51 @@ __global__ __launch_bounds__(256) void k_prod_lists(BuildView v, GroupList g, Fl
         }
         n3 += (uint32_t)__popcll(b3);
     }
-    if (WRITE && !HIGH) {
-        // the rest of A2 and AB: entries that add 0 * 0 (the zeros after x's row and after the
-        // coefficients), so that a wave's lanes walk them without a test
+    if (!WRITE) {
+        if (lane == 0) {
+            cnt[3 * wave] = sums[wave][0] = n1;
+            cnt[3 * wave + 1] = sums[wave][1] = n2;
+            cnt[3 * wave + 2] = sums[wave][2] = n3;
+        }
+        __syncthreads();
+        if (threadIdx.x < 3u) {
+            uint32_t t = 0;
+            for (uint32_t w = 0; w < kListWaves; ++w) t += sums[w][threadIdx.x];
+            (HIGH ? p.blen : p.alen)[threadIdx.x * (int64_t)n + i] = t;
+            atomicMax(&mx[(HIGH ? 4u : 0u) + threadIdx.x], t);
+        }
+        if (HIGH && threadIdx.x == 0) {
+            p.blen[3 * (int64_t)n + i] = part;
+            atomicMax(&mx[7], (uint32_t)__popc(part & p.rmask));
+        }
+    } else if (!HIGH) {
+        // the lengths by position, and the rest of A2 and AB: entries that add 0 * 0 (the zeros after x's
+        // row and after the coefficients), so that a wave's lanes walk them without a test
+        uint32_t t[3] = {0u, 0u, 0u};
+        for (uint32_t w = 0; w < kListWaves; ++w)
+            for (int k = 0; k < 3; ++k) t[k] += cnt[3 * w + k];
         const uint32_t zero = 2u * p.nU;
-        for (uint32_t k = n2 + lane; k < p.nA2; k += 64u) {
+        for (uint32_t k = t[1] + threadIdx.x; k < p.nA2; k += 64u * kListWaves) {
             const int64_t o = prod_at(k, v.na, at);
             p.a2_col[o] = (uint16_t)v.na;
             p.d.a2[o] = 0.0;
             p.f.a2[o] = 0.0f;
         }
-        for (uint32_t k = n3 + lane; k < p.nAB; k += 64u) p.ab_ent[prod_at(k, v.na, at)] = v.na | zero << 16;
-        if (lane == 0) {
-            p.alen[at] = n1;
-            p.alen[n + at] = n2;
-            p.alen[2 * (int64_t)n + at] = n3;
-        }
+        for (uint32_t k = t[2] + threadIdx.x; k < p.nAB; k += 64u * kListWaves)
+            p.ab_ent[prod_at(k, v.na, at)] = v.na | zero << 16;
+        if (threadIdx.x < 3u) p.alen[threadIdx.x * (int64_t)n + at] = t[threadIdx.x];
     }
-    if (!WRITE && lane == 0) {
-        uint32_t *len = HIGH ? p.blen : p.alen;
-        len[i] = n1;
-        len[n + i] = n2;
-        len[2 * (int64_t)n + i] = n3;
-        if (HIGH) len[3 * (int64_t)n + i] = part;
-        atomicMax(&mx[0], n1);
-        atomicMax(&mx[1], n2);
-        atomicMax(&mx[2], n3);
-        if (HIGH) atomicMax(&mx[3], (uint32_t)__popc(part & p.rmask));
-    }
+}
+
+template <bool WRITE>
+__global__ __launch_bounds__(64 * kListWaves) void k_prod_lists(BuildView v, GroupList ga, FlipList fa, GroupList gb,
+                                                                FlipList fb, qsd_prod p, uint32_t *__restrict__ cnt,
+                                                                uint32_t *__restrict__ mx) {
+    __shared__ uint32_t sums[kListWaves][3];
+    if (blockIdx.x < v.na)
+        prod_lists<false, WRITE>(v, ga, fa, p, blockIdx.x, cnt, mx, sums);
+    else
+        prod_lists<true, WRITE>(v, gb, fb, p, blockIdx.x - v.na, cnt, mx, sums);
 }
 
 // wtab[w][a] = the key's first term plus its terms that want a low qubit the part has set, in
@@ -546,6 +575,7 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     const size_t oi = scratch.put(c.tinfo), om = scratch.put(std::vector<uint32_t>(8, 0u));
     const size_t owh = scratch.put(c.whead), owd = scratch.put(c.wdep);
     const size_t owh32 = scratch.put(narrowed(c.whead)), owd32 = scratch.put(narrowed(c.wdep));
+    const size_t on = scratch.room(((size_t)p->na + p->nb) * kListWaves * 3 * 4);
     const size_t od = keep.put(c.dep), od32 = keep.put(narrowed(c.dep));
     const size_t oc = keep.put(c.ctab), oc32 = keep.put(narrowed(c.ctab));
     const size_t oa = keep.room(3 * (size_t)p->na * 4), ob = keep.room(4 * (size_t)p->nb * 4);
@@ -570,9 +600,8 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
                         scratch.at<uint32_t>(of[H][3]), scratch.at<uint32_t>(of[H][4]), (uint32_t)c.fflip[H].size()};
     }
     uint32_t *mx = scratch.at<uint32_t>(om);
-    const unsigned ga = (p->na + 3u) / 4u, gb = (p->nb + 3u) / 4u;
-    k_prod_lists<false, false><<<ga, 256, 0, st>>>(v, g[0], f[0], *p, mx);
-    k_prod_lists<true, false><<<gb, 256, 0, st>>>(v, g[1], f[1], *p, mx + 4);
+    uint32_t *cnt = scratch.at<uint32_t>(on);
+    k_prod_lists<false><<<p->na + p->nb, 64 * kListWaves, 0, st>>>(v, g[0], f[0], g[1], f[1], *p, cnt, mx);
     uint32_t m[8];
     std::vector<uint32_t> n3(p->na);
     QSD_CHECK_HIP(hipMemcpyAsync(m, mx, sizeof(m), hipMemcpyDeviceToHost, st));
@@ -627,8 +656,7 @@ int build_device(qsd_ham *h, qsd_prod *p, const Classified &c, Block &scratch, B
     };
     values(p->d, ov[0]);
     values(p->f, ov[1]);
-    k_prod_lists<false, true><<<ga, 256, 0, st>>>(v, g[0], f[0], *p, nullptr);
-    k_prod_lists<true, true><<<gb, 256, 0, st>>>(v, g[1], f[1], *p, nullptr);
+    k_prod_lists<true><<<p->na + p->nb, 64 * kListWaves, 0, st>>>(v, g[0], f[0], g[1], f[1], *p, cnt, nullptr);
     const dim3 gw((p->na + 255u) / 256u, p->nWb);
     k_prod_wtab<double><<<gw, 256, 0, st>>>(s->keys, p->na, p->split, scratch.at<double>(owh), scratch.at<double>(owd),
                                            p->d.wtab);
