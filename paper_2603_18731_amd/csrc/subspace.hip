@@ -437,14 +437,17 @@ __global__ __launch_bounds__(kBlock) void k_unique_flags(const uint64_t *__restr
     flags[i] = f;
 }
 
+// (`pos` = the scanned flags, n + 1 of them: a key that stays has a place of its own)
 template <int Wp>
 __global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__ keys, int64_t n,
-                                                    const int64_t *__restrict__ flags, const int64_t *__restrict__ pos,
-                                                    uint64_t *__restrict__ out, int64_t N) {
+                                                    const int64_t *__restrict__ pos, uint64_t *__restrict__ out,
+                                                    int64_t N) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n || !flags[i]) return;
+    if (i >= n) return;
+    const int64_t o = pos[i];
+    if (pos[i + 1] == o) return;
 #pragma unroll
-    for (int w = 0; w < Wp; ++w) out[(int64_t)w * N + pos[i]] = keys[(int64_t)w * n + i];
+    for (int w = 0; w < Wp; ++w) out[(int64_t)w * N + o] = keys[(int64_t)w * n + i];
 }
 
 // -------------------------------------------------------------------------- hash
@@ -682,15 +685,15 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
                hipStream_t st) {
     const int W = sub->W;
     uint64_t *planes = nullptr, *tmp = nullptr;
-    int64_t *fl = nullptr, *pos = nullptr;
     unsigned long long *or_and = nullptr;
-    QSD_TRY(dev_alloc(&planes, (size_t)Wp * n_in));
+    // two buffers for the sort; the one that the keys have left takes the places of the distinct ones
+    // (n_in + 1 of them and the scan's sums), so that the table's memory is all that comes on top
+    const int64_t n1 = n_in + 1, room = std::max((int64_t)Wp * n_in, n1 + scan_scratch(n1));
+    QSD_TRY(dev_alloc(&planes, (size_t)room));
     int rc = QSD_OK;
     std::vector<uint64_t> tab;
     auto cleanup = [&]() {
         (void)hipStreamSynchronize(st);  // what is enqueued reads them
-        dev_free(fl);
-        dev_free(pos);
         dev_free(planes);
         dev_free(tmp);
         dev_free(or_and);
@@ -712,7 +715,7 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             rc = fail(QSD_ERR_INVALID_ARG, "a bit-string has a bit set at a position >= n_qubits (%d)", sub->n_qubits);
             break;
         }
-        if ((rc = dev_alloc(&tmp, (size_t)Wp * n_in)) != QSD_OK) break;
+        if ((rc = dev_alloc(&tmp, (size_t)room)) != QSD_OK) break;
         uint64_t *src = planes;
         if (!(flags & QSD_SUB_ASSUME_SORTED_UNIQUE)) {
             uint64_t varies[kMaxWords];
@@ -720,11 +723,9 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             if ((rc = sort_keys<Wp>(planes, tmp, n_in, varies, W, &src, st)) != QSD_OK) break;
         }
         // deduplicate
-        const int64_t n1 = n_in + 1;  // pos[n_in] = N (the flag there moves nothing)
-        if ((rc = dev_alloc(&fl, n1)) != QSD_OK) break;
-        if ((rc = dev_alloc(&pos, n1 + scan_scratch(n1))) != QSD_OK) break;
-        k_unique_flags<Wp><<<grid_for(n_in, kBlock), kBlock, 0, st>>>(src, n_in, fl);
-        scan_enqueue(fl, pos, n1, pos + n1, st);
+        int64_t *pos = (int64_t *)(src == planes ? tmp : planes);
+        k_unique_flags<Wp><<<grid_for(n_in, kBlock), kBlock, 0, st>>>(src, n_in, pos);
+        scan_enqueue(pos, pos, n1, pos + n1, st);  // pos[n_in] = N (the flag there moves nothing)
         // the hash words and tables while the device sorts
         hash_words(sub->n_qubits, sub->z);
         hash_byte_tables(Wp, sub->z, tab);
@@ -735,7 +736,7 @@ int build_impl(qsd_subspace *sub, const uint64_t *d_bits, int64_t n_in, uint32_t
             rc = fail(QSD_ERR_HIP, "sort failed: %s", hipGetErrorString(hipGetLastError()));
         if (rc == QSD_OK && N >= 0xFFFFFFFFll) rc = fail(QSD_ERR_CAPACITY, "%lld unique strings exceed 2^32-2", (long long)N);
         if (rc == QSD_OK) rc = dev_alloc(&sub->keys, (size_t)Wp * N);
-        if (rc == QSD_OK) k_compact<Wp><<<grid_for(n_in, kBlock), kBlock, 0, st>>>(src, n_in, fl, pos, sub->keys, N);
+        if (rc == QSD_OK) k_compact<Wp><<<grid_for(n_in, kBlock), kBlock, 0, st>>>(src, n_in, pos, sub->keys, N);
         if (rc != QSD_OK) break;
         sub->N = N;
         // hash table

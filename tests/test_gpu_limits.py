@@ -214,3 +214,25 @@ def test_batched_factored_workgroups(entry):
     ys = getattr(qsd, entry)(hams, xs, [torch.full_like(x, float("nan")) for x in xs])
     for h, x, y in zip(hams, xs, ys):
         assert torch.equal(y, h.matvec(x))
+
+
+@pytest.mark.parametrize("qubits,words", [(36, 1), (100, 2), (200, 4)])
+def test_subspace_build_memory(qubits, words):
+    """What a build holds at its peak: two buffers for the sort, and the subspace itself with the counts
+    of its slot order."""
+    n = 200_003
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    bits = torch.randint(0, 1 << 62, (n, words), dtype=torch.int64, device="cuda", generator=g)
+    bits[:, -1] &= (1 << (qubits - 64 * (words - 1))) - 1
+    bits[n // 2:] = bits[: n - n // 2].clone()  # duplicates
+    a = _Peak()
+    sub = qsd.Subspace(bits, qubits, allocator=a.struct)
+    say("peak", sub.N, a.peak)
+    assert sub.N <= n // 2 + 1
+    own = sub.N * (8 * words + 8 + 4 + 8 * words + 8) + sub.capacity * 8 + sub.capacity // 8
+    assert a.peak <= 2 * 8 * words * n + own + sub.capacity // 32 * 8 + (1 << 18)
+    assert torch.equal(sub.lookup(sub.keys()), torch.arange(sub.N, device="cuda"))
+    assert bool((sub.lookup(bits) >= 0).all())
+    del sub
+    assert not a.live
