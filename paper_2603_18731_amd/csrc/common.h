@@ -95,6 +95,14 @@ void dev_free(T *&p) {
     p = nullptr;
 }
 
+// The grid of a launch of many workgroups.  One dimension of a launch holds fewer than 2^32 threads, and
+// a larger one is cut short without an error: workgroups past 2^31 threads go to the second dimension.
+// A kernel's workgroup is then blockIdx.y * gridDim.x + blockIdx.x, and those past the last one leave.
+inline dim3 folded_grid(int64_t blocks, int threads) {
+    const int64_t most = (1ll << 31) / threads, x = blocks < 1 ? 1 : blocks < most ? blocks : most;
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+
 // Arrays laid out in one block of device memory (256-byte aligned).  Small ones are gathered in a host
 // image and copied with it (a copy costs the host 16 us); those of 64 KB or more are copied from where
 // they are (gathering the 7 MB of a molecular operator's tables touched fresh pages for 0.6 ms).

@@ -77,11 +77,12 @@ __global__ __launch_bounds__(kBlock) void k_fill_lower(SubView s, HamView h, con
 
 // Sort each row's entries by column (one workgroup per row; see sort_row_entries).
 template <class ET, class IT, bool CPLX>
-__global__ __launch_bounds__(kBlock) void k_sort_rows(const int64_t *__restrict__ indptr, int64_t *__restrict__ cols,
+__global__ __launch_bounds__(kBlock) void k_sort_rows(const int64_t *__restrict__ indptr, int64_t N, int64_t *__restrict__ cols,
                                                       const typename C2<ET>::T *__restrict__ vals, IT *__restrict__ out_idx,
                                                       ET *__restrict__ out_val) {
     __shared__ int64_t sc[kSortLds];
-    const int64_t row = blockIdx.x;
+    const int64_t row = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (row >= N) return;
     const int64_t a = indptr[row], b = indptr[row + 1];
     sort_row_entries<ET, IT, CPLX>(a, b - a, cols, vals, out_idx, out_val, sc);
 }
@@ -195,9 +196,7 @@ __global__ __launch_bounds__(256) void k_csr_spmv(const int64_t *__restrict__ in
 template <int S, int NV, class IT, class ET, bool CPLX>
 void launch_spmv(const qsd_csr *c, const void *x, int64_t ldx, void *y, int64_t ldy, int nvec, hipStream_t st) {
     const int64_t threads = c->N * (S * NV <= 64 ? S * NV : 64);
-    // (one dimension of a launch holds fewer than 2^32 threads)
-    const int64_t blocks = (threads + 255) / 256, x_blocks = std::min<int64_t>(blocks, 1 << 23);
-    const dim3 grid((unsigned)x_blocks, (unsigned)((blocks + x_blocks - 1) / x_blocks));
+    const dim3 grid = folded_grid((threads + 255) / 256, 256);
     k_csr_spmv<S, NV, IT, ET, CPLX><<<grid, 256, 0, st>>>(c->indptr, (const IT *)c->indices, (const ET *)c->data,
                                                           c->N, (const ET *)x, ldx, (ET *)y, ldy, nvec);
 }
@@ -247,18 +246,18 @@ void free_csr(qsd_csr *c) {
 
 template <class ET>
 void sort_into(qsd_csr *c, int64_t *cols, const void *vals, hipStream_t st) {
-    const unsigned grid = (unsigned)c->N;
+    const dim3 grid = folded_grid(c->N, kBlock);
     const auto *v = (const typename C2<ET>::T *)vals;
     if (c->index_type == QSD_INDEX_I32) {
         if (c->cplx)
-            k_sort_rows<ET, int32_t, true><<<grid, kBlock, 0, st>>>(c->indptr, cols, v, (int32_t *)c->indices, (ET *)c->data);
+            k_sort_rows<ET, int32_t, true><<<grid, kBlock, 0, st>>>(c->indptr, c->N, cols, v, (int32_t *)c->indices, (ET *)c->data);
         else
-            k_sort_rows<ET, int32_t, false><<<grid, kBlock, 0, st>>>(c->indptr, cols, v, (int32_t *)c->indices, (ET *)c->data);
+            k_sort_rows<ET, int32_t, false><<<grid, kBlock, 0, st>>>(c->indptr, c->N, cols, v, (int32_t *)c->indices, (ET *)c->data);
     } else {
         if (c->cplx)
-            k_sort_rows<ET, int64_t, true><<<grid, kBlock, 0, st>>>(c->indptr, cols, v, (int64_t *)c->indices, (ET *)c->data);
+            k_sort_rows<ET, int64_t, true><<<grid, kBlock, 0, st>>>(c->indptr, c->N, cols, v, (int64_t *)c->indices, (ET *)c->data);
         else
-            k_sort_rows<ET, int64_t, false><<<grid, kBlock, 0, st>>>(c->indptr, cols, v, (int64_t *)c->indices, (ET *)c->data);
+            k_sort_rows<ET, int64_t, false><<<grid, kBlock, 0, st>>>(c->indptr, c->N, cols, v, (int64_t *)c->indices, (ET *)c->data);
     }
 }
 

@@ -291,11 +291,12 @@ __global__ __launch_bounds__(kBlock) void k_csr_fill(SubView s, HamView h, const
 
 // Sort each row's entries by column (one workgroup per row; see sort_row_entries).
 template <class ET, class IT, bool CPLX>
-__global__ __launch_bounds__(kBlock) void k_csr_sort(const int64_t *__restrict__ indptr, int64_t *__restrict__ cols,
+__global__ __launch_bounds__(kBlock) void k_csr_sort(const int64_t *__restrict__ indptr, int64_t N, int64_t *__restrict__ cols,
                                                      const typename C2<ET>::T *__restrict__ vals, IT *__restrict__ out_idx,
                                                      ET *__restrict__ out_val) {
     __shared__ int64_t sc[kSortLds];
-    const int64_t row = blockIdx.x;
+    const int64_t row = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (row >= N) return;
     const int64_t a = indptr[row], b = indptr[row + 1];
     sort_row_entries<ET, IT, CPLX>(a, b - a, cols, vals, out_idx, out_val, sc);
 }
@@ -643,23 +644,23 @@ extern "C" int qsd_csr_build(const qsd_ham *h, int64_t *d_indptr, void *d_indice
             fill_w<float>(h, d_indptr, cols, vals, st);
         else
             fill_w<double>(h, d_indptr, cols, vals, st);
-        const unsigned grid = (unsigned)h->N;
+        const dim3 grid = folded_grid(h->N, kBlock);
         const bool cx = h->is_complex;
         if (index_type == QSD_INDEX_I32) {
             if (f32) {
-                if (cx) k_csr_sort<float, int32_t, true><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const float2 *)vals, (int32_t *)d_indices, (float *)d_data);
-                else k_csr_sort<float, int32_t, false><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const float2 *)vals, (int32_t *)d_indices, (float *)d_data);
+                if (cx) k_csr_sort<float, int32_t, true><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const float2 *)vals, (int32_t *)d_indices, (float *)d_data);
+                else k_csr_sort<float, int32_t, false><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const float2 *)vals, (int32_t *)d_indices, (float *)d_data);
             } else {
-                if (cx) k_csr_sort<double, int32_t, true><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const double2 *)vals, (int32_t *)d_indices, (double *)d_data);
-                else k_csr_sort<double, int32_t, false><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const double2 *)vals, (int32_t *)d_indices, (double *)d_data);
+                if (cx) k_csr_sort<double, int32_t, true><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const double2 *)vals, (int32_t *)d_indices, (double *)d_data);
+                else k_csr_sort<double, int32_t, false><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const double2 *)vals, (int32_t *)d_indices, (double *)d_data);
             }
         } else {
             if (f32) {
-                if (cx) k_csr_sort<float, int64_t, true><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const float2 *)vals, (int64_t *)d_indices, (float *)d_data);
-                else k_csr_sort<float, int64_t, false><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const float2 *)vals, (int64_t *)d_indices, (float *)d_data);
+                if (cx) k_csr_sort<float, int64_t, true><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const float2 *)vals, (int64_t *)d_indices, (float *)d_data);
+                else k_csr_sort<float, int64_t, false><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const float2 *)vals, (int64_t *)d_indices, (float *)d_data);
             } else {
-                if (cx) k_csr_sort<double, int64_t, true><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const double2 *)vals, (int64_t *)d_indices, (double *)d_data);
-                else k_csr_sort<double, int64_t, false><<<grid, kBlock, 0, st>>>(d_indptr, cols, (const double2 *)vals, (int64_t *)d_indices, (double *)d_data);
+                if (cx) k_csr_sort<double, int64_t, true><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const double2 *)vals, (int64_t *)d_indices, (double *)d_data);
+                else k_csr_sort<double, int64_t, false><<<grid, kBlock, 0, st>>>(d_indptr, h->N, cols, (const double2 *)vals, (int64_t *)d_indices, (double *)d_data);
             }
         }
         if (hipStreamSynchronize(st) != hipSuccess)

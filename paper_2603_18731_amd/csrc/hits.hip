@@ -320,9 +320,7 @@ void launch(const qsd_ham *h, const qsd_hits *p, const void *x, int64_t ldx, voi
     const ET *dim = CPLX ? (f32 ? (const ET *)h->diag32_im : (const ET *)h->diag_im) : nullptr;
     const unsigned nd = (unsigned)((h->N * nvec + kBlock * kDiagItems - 1) / (kBlock * kDiagItems));
     const unsigned nl = (unsigned)((p->L + kBlock / 64 - 1) / (kBlock / 64)) + tiles_of(p->M * NV);
-    // (one dimension of a launch holds fewer than 2^32 threads; a larger one is cut short without an error)
-    const unsigned blocks = nl + nd, x_blocks = std::min(blocks, 1u << 23);
-    const dim3 grid(x_blocks, (blocks + x_blocks - 1u) / x_blocks);
+    const dim3 grid = folded_grid((int64_t)nl + nd, kBlock);
     k_hits_matvec<Wp, NV, ET, CPLX><<<grid, kBlock, 0, st>>>(sub_view(h->s), ham_view(h, f32), *p, dre, dim,
                                                                (const ET *)x, ldx, (ET *)y, ldy, nvec, nl);
 }

@@ -776,9 +776,7 @@ void prod_matvec(const qsd_ham *h, const void *x, int64_t ldx, void *y, int64_t 
 template <class ET>
 void prod_matvec_batched(const ProdReq<ET> *d_reqs, int n, uint32_t blocks, uint32_t T, int V, uint32_t lds,
                          hipStream_t st) {
-    // (one dimension of a launch holds fewer than 2^32 threads; a larger one is cut short without an error)
-    const uint32_t x_blocks = std::min(blocks, 1u << 22);
-    const dim3 grid(x_blocks, (blocks + x_blocks - 1u) / x_blocks);
+    const dim3 grid = folded_grid(blocks, (int)T);
     if (V == 4)
         k_prod_batched<ET, 4><<<grid, T, lds, st>>>(d_reqs, n, blocks);
     else if (V == 2)

@@ -209,7 +209,9 @@ __global__ __launch_bounds__(256) void k_prod_csr_fill(ProdView<ET> p, Sorted<ET
     uint32_t *bz = (uint32_t *)fill_smem, *bx = bz + s.nB, *by = bx + s.nB;  // the block list, by component
     ET *tail = (ET *)(fill_smem + (s.nB * sizeof(uint3) + 15u) / 16u * 16u), *dep = tail + p.nB1 * p.tail_len;
     const uint32_t tiles = (p.na + kFillRows - 1u) / kFillRows;
-    const uint32_t b = blockIdx.x / tiles, a0 = (blockIdx.x - b * tiles) * kFillRows, lane = threadIdx.x & 63u;
+    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint32_t b = block / tiles, a0 = (block - b * tiles) * kFillRows, lane = threadIdx.x & 63u;
+    if (b >= p.nb) return;
     const uint32_t nblk = s.nblk[b];
     for (uint32_t k = threadIdx.x; k < nblk; k += 256u) {
         const uint3 w = s.b[(int64_t)b * s.nB + k];
@@ -342,7 +344,7 @@ int prod_csr_fill(const qsd_ham *h, const int64_t *indptr, void *indices, void *
     k_prod_sort_high<ET><<<p->nb, 256, s.nB * 4u, st>>>(v, s);
     const size_t lds = fill_lds<ET>(p, s.nB);
     if (p->full && lds <= 64u * 1024u)
-        k_prod_csr_fill<ET, IT><<<(p->na + kFillRows - 1u) / kFillRows * p->nb, 256, lds, st>>>(
+        k_prod_csr_fill<ET, IT><<<folded_grid((int64_t)((p->na + kFillRows - 1u) / kFillRows) * p->nb, 256), 256, lds, st>>>(
             v, s, p->nAB, indptr, (IT *)indices, (ET *)data);
     else
         k_prod_csr_walk<ET, IT><<<(p->na + 255u) / 256u * p->nb, 256, 0, st>>>(v, s, p->nAB, indptr, (IT *)indices, (ET *)data);

@@ -236,3 +236,25 @@ def test_subspace_build_memory(qubits, words):
     assert bool((sub.lookup(bits) >= 0).all())
     del sub
     assert not a.live
+
+
+@pytest.mark.parametrize("build", ["to_csr", "lower_mirror"])
+def test_csr_build_of_more_than_2_to_24_rows(build):
+    """A workgroup per row sorts its entries: 2^24 rows of 256 threads are 2^32."""
+    n = (1 << 24) + 300
+    keys = torch.arange(n, dtype=torch.int64, device="cuda").reshape(-1, 1) * 2
+    sub = qsd.Subspace(keys, 40, assume_sorted_unique=True)
+    tl = wl.TermList.from_terms(40, [(0.75, [(1, wl.X)]), (0.25, [(2, wl.X)]), (0.5, [(3, wl.Z)])])
+    H = qsd.SubspaceHamiltonian(sub, qsd.operator_from_termlist(tl))
+    if build == "to_csr":
+        indptr, indices, data = H.to_csr()
+    else:
+        indptr, indices, data = qsd.CsrMatrix(H, qsd.INDEX_I64, lower_mirror=True).export()
+    rows = torch.repeat_interleave(torch.arange(n, device="cuda"), indptr[1:] - indptr[:-1])
+    bits = (keys[indices, 0] ^ keys[rows, 0])
+    assert torch.equal(torch.unique(bits), torch.tensor([0, 2, 4], device="cuda"))
+    want = torch.where(bits == 2, 0.75, torch.where(bits == 4, 0.25, 0.5 - (keys[rows, 0] >> 3 & 1).double()))
+    assert torch.equal(data, want)
+    later = rows[1:] == rows[:-1]
+    assert bool((indices[1:][later] > indices[:-1][later]).all())
+    torch.cuda.empty_cache()
