@@ -456,8 +456,8 @@ typedef struct {
 void qsd_lanczos_default_opts(qsd_lanczos_opts *opts);
 
 /* Lowest eigenvalue of H (Hermitian) by Lanczos with full reorthogonalization (classical
- * Gram-Schmidt applied twice), FP64 basis and recurrence, tridiagonal eigenproblem by Sturm
- * bisection plus inverse iteration on the device.
+ * Gram-Schmidt applied twice), FP64 basis and recurrence, tridiagonal eigenproblem on
+ * the device (multisection on the leading minors, eigenvector by a twisted factorization).
  *   eval_out  host, receives theta.
  *   d_evec    device [N] (FP64, or complex FP64 for a complex H): Ritz vector if want_vector,
  *             start vector if v0_mode == QSD_V0_USER; may be NULL otherwise.

@@ -7,8 +7,8 @@
 //   w = H x                       (SpMV, FP64 or FP32 elements with FP64 accumulation)
 //   h = V^T w; w -= V h  (twice)  (classical Gram-Schmidt applied twice against v_0..v_k)
 //   alpha_k = sum of the two h_k; beta_k = ||w||; v_{k+1} = x = w / beta_k
-// The tridiagonal eigenproblem is solved on the device every few iterations (Sturm
-// multisection for the lowest eigenvalue, inverse iteration for its vector); only theta and
+// The tridiagonal eigenproblem is solved on the device every few iterations (multisection on the
+// leading minors for the lowest eigenvalue, a twisted factorization for its vector); only theta and
 // the Ritz residual estimate beta_k |s_k| are copied to the host.
 #include <chrono>
 #include <cmath>
