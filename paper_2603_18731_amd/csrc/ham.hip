@@ -877,8 +877,22 @@ extern "C" int qsd_ham_autotune(qsd_ham *h, int32_t nvec, int32_t dtype, int32_t
         else if (k > 0)
             tables.push_back({load0, splits[k]});
     }
+    // an SpMV from the element list reads no table: another one changes its time by chance alone
+    auto reads_table = [&](uint32_t sc) {
+        h->schedule = sc;
+        return spmv_path(h) != QSD_PATH_ELEMENTS;
+    };
+    ranked.erase(std::remove_if(ranked.begin(), ranked.end(), [&](auto &p) { return !reads_table(p.second); }),
+                 ranked.end());
+    if (ranked.empty() && best_ms == INFINITY) best_ms = ms_before;  // nothing is left to be timed
     for (auto &tb : tables) {
         if (rc != QSD_OK) break;
+        if (ranked.empty()) {
+            int64_t C = 64;
+            while ((double)sub->N / (double)C > tb.first) C <<= 1;
+            if (C == C0 && tb.second == split0) best_load = tb.first;  // (the name of the table that stays)
+            continue;
+        }
         if ((rc = qsd_subspace_rehash(sub, tb.first, tb.second, stream)) != QSD_OK) break;
         if (sub->C == C0 && sub->split == split0 && (flags & QSD_TUNE_SCHEDULE)) {
             // the starting table, already timed under every schedule

@@ -146,3 +146,16 @@ def test_dense_solve_makes_no_count():
     say("solve", H.N, sizes)
     assert max(sizes) >= 60 * 8 * H.N and all(n < 8 * H.N for n in sizes if n != max(sizes))
     del H
+
+
+@pytest.mark.parametrize("schedule", [True, False])
+def test_autotune_keeps_the_table_of_a_list(schedule):
+    """An SpMV from the element list reads no table, so the autotuner does not choose one by chance."""
+    keys, tl = CASES["sampled"]()
+    H = _ham(keys, tl)
+    H.schedule = qsd.SCHED_ALL
+    before = H.subspace.capacity
+    r = H.autotune(reps=1, schedule=schedule, load=True, split=True)
+    say("tuned", r)
+    assert H.spmv_path == qsd.PATH_ELEMENTS and np.isfinite(r["ms"]) and r["ms"] > 0
+    assert H.subspace.capacity == before == r["capacity"] and r["split"] == 0 and r["max_load"] == 0.125
