@@ -252,6 +252,10 @@ int qsd_op_destroy(qsd_op *op);
  *   an operator with the same n_qubits, uploads the group and term tables and computes the
  *   diagonal d_i = H_ii once (projector letters tested before any sign is formed).  The
  *   handle references `s` and `op`; they must outlive it.  flags: reserved, pass 0.
+ *   On a product subspace (qsd_subspace_hash_info) a real operator that factors over its parts also
+ *   gets the lists of QSD_PATH_FACTORED: some 40 KB per pair of a low and a high part for a 16-orbital
+ *   molecule, 1 GiB or 128 bytes a row at most.  They are left out where `alloc` refuses a block of
+ *   them that is larger than the operator's tables.
  *   alloc: device memory of the handle and the scratch of later calls on it (NULL: hipMalloc).
  *   Enqueued on `stream`.
  */
@@ -294,7 +298,8 @@ int qsd_ham_diag_splitting(const qsd_ham *h, double *lowest, double *splitting, 
  *                         bytes, by the first qsd_ham_set_schedule or qsd_ham_autotune call that
  *                         needs them; that call synchronizes).  For an operator with at most N
  *                         off-diagonal elements that call also lists each element's column and
- *                         term range (16 bytes an element), and qsd_matvec runs from the list.
+ *                         term range (16 bytes an element, 8 a row while it is made), and qsd_matvec
+ *                         runs from the list; where that memory is refused the bits alone are made.
  *   QSD_SCHED_LOCKSTEP    the 64 lanes of a wave probe the same group in the same instruction
  *                         (lanes whose row does not have it live sit idle) instead of each lane
  *                         walking its own live groups; with SLOT_ORDER the wave's occupancy-bit
