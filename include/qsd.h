@@ -253,9 +253,9 @@ int qsd_op_destroy(qsd_op *op);
  *   diagonal d_i = H_ii once (projector letters tested before any sign is formed).  The
  *   handle references `s` and `op`; they must outlive it.  flags: reserved, pass 0.
  *   On a product subspace (qsd_subspace_hash_info) a real operator that factors over its parts also
- *   gets the lists of QSD_PATH_FACTORED: some 40 KB per pair of a low and a high part for a 16-orbital
- *   molecule, 1 GiB or 128 bytes a row at most.  They are left out where `alloc` refuses a block of
- *   them that is larger than the operator's tables.
+ *   gets the lists of QSD_PATH_FACTORED: 24 MB for 1500 x 1500 strings of a 16-orbital molecule, 134 MB
+ *   for all of them, 1 GiB or 128 bytes a row at most.  They are left out where `alloc` refuses a block
+ *   of them that is larger than the operator's tables.
  *   alloc: device memory of the handle and the scratch of later calls on it (NULL: hipMalloc).
  *   Enqueued on `stream`.
  */

@@ -21,9 +21,9 @@ constexpr uint32_t kMaxThreads = 512;
 // Waves per SIMD that the registers must allow.  600 x 600: 88 us without it, 72 with 7; 8 costs
 // scalar spills (300 x 301: 24.6 -> 26.4).  Four vectors spill at 7 (400 x 400 in FP32 46 us, at 5 44).
 constexpr int waves_for(int V) { return V >= 4 ? 5 : 7; }
-// Bytes of the lists: 14 KB per low and 25 per high part of a 16-orbital molecule, 35 MB for 1500 x 1500
-// strings.  Few low parts with many high ones of long class B tails can ask for gigabytes, in which case
-// the plan may be at most as large as the subspace's own keys, hashes and table (128 bytes a row).
+// Bytes of the lists: 24 MB for 1500 x 1500 strings of a 16-orbital molecule, 134 for all 4368 x 4368.
+// Few low parts with many high ones of long class B tails can ask for gigabytes, in which case the plan
+// may be at most as large as the subspace's own keys, hashes and table (128 bytes a row).
 constexpr uint64_t kMaxLists = 1ull << 30, kMaxListsPerRow = 128;
 
 // What the list kernels read of the operator.
