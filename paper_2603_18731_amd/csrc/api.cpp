@@ -37,12 +37,13 @@ bool custom_allocator() { return g_alloc != nullptr; }
 
 void *raw_alloc(size_t bytes) {
     if (bytes == 0) bytes = 1;
-    if (g_alloc) return g_alloc->alloc(g_alloc->ctx, bytes, g_alloc_stream);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
+    if (g_alloc)
+        p = g_alloc->alloc(g_alloc->ctx, bytes, g_alloc_stream);
+    else if (hipMalloc(&p, bytes) != hipSuccess)
+        p = nullptr;
+    // what a refused allocation leaves in the runtime is no error of the launches that follow
+    if (!p) (void)hipGetLastError();
     return p;
 }
 

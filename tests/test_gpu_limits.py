@@ -258,3 +258,33 @@ def test_csr_build_of_more_than_2_to_24_rows(build):
     later = rows[1:] == rows[:-1]
     assert bool((indices[1:][later] > indices[:-1][later]).all())
     torch.cuda.empty_cache()
+
+
+def test_refused_block_leaves_no_error():
+    """An allocator that asks the runtime, and leaves the runtime's error behind: what is done without
+    the block does not report it."""
+    import ctypes
+
+    runtime = ctypes.CDLL(qsd.LIB_PATH)  # (its hipMalloc is the one the library is bound to)
+    w = wl.c3_molecular(1500, 60)
+    sub = qsd.Subspace(w.keys, 32)
+    op = qsd.operator_from_termlist(w.ops)
+    a = _Peak()
+    H = qsd.SubspaceHamiltonian(sub, op, allocator=a.struct)
+    lists = max(a.sizes)
+
+    def refuse(n):
+        if n != lists:
+            return False
+        p = ctypes.c_void_p()
+        assert runtime.hipMalloc(ctypes.byref(p), ctypes.c_size_t(1 << 55)) != 0
+        return True
+
+    b = _Peak(refuse=refuse)
+    G = qsd.SubspaceHamiltonian(sub, op, allocator=b.struct)
+    assert G.spmv_path == qsd.PATH_PRODUCT_MAP
+    x = torch.randn(sub.N, dtype=torch.float64, device="cuda")
+    y = torch.empty_like(x)
+    G.matvec(x, out=y)
+    assert torch.equal(H.matvec(x), y)
+    del G, H
