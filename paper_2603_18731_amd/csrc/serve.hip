@@ -1016,6 +1016,35 @@ int plan_batched(int32_t n, const qsd_ham *const *hams, const void *const *xs, v
     return QSD_OK;
 }
 
+// A piece of a table in a launch's arguments, which a captured graph keeps.
+struct Piece {
+    static constexpr int kWords = 384;
+    uint64_t w[kWords];
+};
+__global__ __launch_bounds__(Piece::kWords) void k_put_piece(Piece p, uint64_t *__restrict__ dst, int n) {
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = p.w[threadIdx.x];
+}
+
+// Copies a host image that ends with the call to the device.  A captured copy would read it again at every
+// replay, so under capture it goes by the arguments of launches, 3 KB each.
+int upload_image(const std::vector<uint8_t> &image, uint8_t *mem, hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+    if (status != hipStreamCaptureStatusActive) {
+        // a pageable source: the copy returns once the host data is staged
+        if (hipMemcpyAsync(mem, image.data(), image.size(), hipMemcpyHostToDevice, st) != hipSuccess)
+            return fail(QSD_ERR_HIP, "table upload failed");
+        return QSD_OK;
+    }
+    for (size_t at = 0; at < image.size(); at += sizeof(Piece)) {
+        const size_t n = std::min(sizeof(Piece), image.size() - at);
+        Piece p{};
+        std::memcpy(p.w, image.data() + at, n);
+        k_put_piece<<<1, Piece::kWords, 0, st>>>(p, (uint64_t *)(mem + at), (int)(n / 8));
+    }
+    return QSD_OK;
+}
+
 // Uploads the plan's tables to `mem` (P.bytes() long) and enqueues its launches on st.
 int run_batched(const BatchedPlan &P, int32_t dtype, uint8_t *mem, hipStream_t st) {
     std::vector<uint8_t> image(P.bytes());
@@ -1026,9 +1055,7 @@ int run_batched(const BatchedPlan &P, int32_t dtype, uint8_t *mem, hipStream_t s
     put(P.prod_at(), P.prod64.data(), P.prod64.size() * sizeof(ProdReq<double>));
     put(P.prod_at(), P.prod32.data(), P.prod32.size() * sizeof(ProdReq<float>));  // (one of the two is empty)
     put(P.tiles_at(), P.tiles.data(), P.tiles.size() * sizeof(Tile));
-    // a pageable source: the copy returns once the host data is staged
-    if (hipMemcpyAsync(mem, image.data(), image.size(), hipMemcpyHostToDevice, st) != hipSuccess)
-        return fail(QSD_ERR_HIP, "table upload failed");
+    QSD_TRY(upload_image(image, mem, st));
     const MvReq *d_reqs = (const MvReq *)mem;
     const Tile *d_tiles = (const Tile *)(mem + P.tiles_at());
     if (!P.prod64.empty())
@@ -1058,6 +1085,7 @@ constexpr size_t kScratchTiles = QSD_NOALLOC_MAX_TILES;
 constexpr size_t kReqBytes = std::max(sizeof(MvReq), sizeof(ProdReq<double>));
 constexpr size_t kScratchBytes = kScratchReqs * kReqBytes + 512 + kScratchTiles * sizeof(Tile);
 static_assert(kScratchBytes <= (size_t(1) << 20), "the fixed scratch stays under 1 MiB");
+static_assert(sizeof(MvReq) % 8 == 0 && sizeof(ProdReq<double>) % 8 == 0 && sizeof(Tile) % 8 == 0, "copied in words");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
